@@ -17,8 +17,7 @@
 #include "forest_core.h"
 
 namespace sf {
-int forest_setup(sf_ctx* ctx, const char* who, const sf_forest* f, uint32_t feat_ld, sfforest::FastArgs& a, uint32_t* split,
-                 size_t* lds);
+int forest_setup(sf_ctx* ctx, const char* who, const sf_forest* f, uint32_t feat_ld, sfforest::FastArgs& a, uint32_t* result_words);
 }
 
 namespace {
@@ -114,7 +113,7 @@ __global__ __launch_bounds__(256) void featurize_forest(ClassifyArgs c)
             sffeat::window_stats<8, KMAX>(s, t, dmask, m, signed_times, col, FPB, dst, FPB);
     }
     __syncthreads(); // the space behind the tile is free: the walk may stage its records there
-    forest_walk<256, 1, false, false, KEEP_ROWS>(a, xT, i, i, live);
+    forest_walk<256, 1, 10, 5, false, false, KEEP_ROWS>(a, xT, i, i, live);
 }
 
 template <int KMAX, bool KEEP_ROWS>
@@ -158,16 +157,16 @@ int run_features_and_forest(sf_ctx* ctx, const char* who, const sf_packets* pk, 
     sf_forest wide = *forest;
     wide.n_features = F;
     ClassifyArgs c = {};
-    uint32_t split = 1;
-    size_t lds = 0;
+    uint32_t result_words = 0;
     const uint32_t dmax = cfg->depth[cfg->n_windows - 1];
-    int rc = sf::forest_setup(ctx, who, &wide, F, c.fa, &split, &lds);
+    int rc = sf::forest_setup(ctx, who, &wide, F, c.fa, &result_words);
     if (rc != SF_OK) return rc;
+    size_t lds = plan_lds(c.fa, result_words, 256, 80 * 1024 - 512, &c.fa.top_pairs);
     // scratch of the first window's sorting network behind the tile: one column per element
     uint32_t n0 = 8;
     while (n0 < cfg->depth[0] && n0 < 16u) n0 *= 2;
     const size_t lds_feat = (size_t)F * 1024 + (size_t)n0 * 1024;
-    const bool fused = split == 1 && dmax <= 16 && (lds > lds_feat ? lds : lds_feat) <= 80 * 1024;
+    const bool fused = dmax <= 16 && (lds > lds_feat ? lds : lds_feat) <= 80 * 1024;
     if (!fused) {
         // shapes the fused kernel does not cover (windows deeper than 16 packets, whose registers would leave one
         // block per compute unit; forests that run several lanes per flow): the same results from the separate

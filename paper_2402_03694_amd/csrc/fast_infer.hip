@@ -5,11 +5,10 @@
 // Also here: the same walk over the flows of a list (the middle tier of a three-tier cascade)
 // and the boosted-tree form of the fast model (Section 4.1), whose leaves hold margins.
 //
-// Work split: one lane owns one flow (or 2 or 4 lanes share one and split the trees, where
-// shared memory would otherwise leave too few waves resident).  The flow's feature row sits in
-// shared memory as a column, [feature][flow], so the data-dependent fetch x[feat] of every lane
-// of a wave lands in its own bank.  The kernel here copies the rows of its tile into that
-// layout; the walk itself and the packed record format are in forest_core.h.
+// Work split: a block holds a tile of flows, each flow's feature row as a shared-memory column
+// [feature][flow], so the data-dependent fetch x[feat] of every lane of a wave lands in its own bank; the waves
+// of the block split the trees between them.  The kernel here copies the rows of its tile into that layout; the
+// walk itself and the packed record format are in forest_core.h.
 #include "forest_core.h"
 
 namespace {
@@ -49,17 +48,16 @@ __global__ __launch_bounds__(256) void pack_forest(uint32_t n_trees, uint32_t de
     }
 }
 
-template <int BS, int S, bool WANT_LEAF, bool GBDT>
-__global__ __launch_bounds__(BS) void forest_votes(FastArgs a)
+template <int FPB_, int W, int ILP, int TAIL, bool WANT_LEAF, bool GBDT>
+__global__ __launch_bounds__(FPB_ * W) void forest_votes(FastArgs a)
 {
-    constexpr uint32_t FPB = BS / S;       // flows per block
-    constexpr uint32_t FPW = 64 / S;       // flows per wave
+    constexpr uint32_t FPB = FPB_;         // flows per block
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const uint32_t F = a.n_features;
     float* xT = reinterpret_cast<float*>(smem_raw);                          // [F][FPB]
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const uint32_t grp = lane / FPW;                       // which share of the trees this lane walks
-    const uint32_t slot = wave * FPW + (lane % FPW);       // flow slot in the block's tile
+    const uint32_t tid = threadIdx.x;
+    const uint32_t grp = tid / FPB;                        // which share of the trees this lane walks
+    const uint32_t slot = tid % FPB;                       // flow slot in the block's tile
     const uint32_t i = blockIdx.x * FPB + slot;
     uint32_t n = a.n_flows;
     if (a.idx_count) {
@@ -74,11 +72,10 @@ __global__ __launch_bounds__(BS) void forest_votes(FastArgs a)
         row = row < a.n_rows ? row : a.n_rows - 1u; // a bad list entry must not leave the matrix
     }
     {
-        // the S lanes of a flow each copy 1/S of its row into the flow's column
+        // the W lanes of a flow each copy their share of its row into the flow's column
         const float* x = a.feat + (size_t)row * a.ld;
-        if ((a.ld & 3u) == 0 && (F % (4u * S)) == 0 && (reinterpret_cast<uintptr_t>(a.feat) & 15u) == 0) {
-            const uint32_t per = F / 4u / S;
-            for (uint32_t q = grp * per; q < (grp + 1u) * per; ++q) {
+        if ((a.ld & 3u) == 0 && (F & 3u) == 0 && (reinterpret_cast<uintptr_t>(a.feat) & 15u) == 0) {
+            for (uint32_t q = grp; q < F / 4u; q += W) {
                 const float4 v = reinterpret_cast<const float4*>(x)[q];
                 xT[(4 * q + 0) * FPB + slot] = v.x;
                 xT[(4 * q + 1) * FPB + slot] = v.y;
@@ -86,24 +83,22 @@ __global__ __launch_bounds__(BS) void forest_votes(FastArgs a)
                 xT[(4 * q + 3) * FPB + slot] = v.w;
             }
         } else {
-            for (uint32_t f = grp; f < F; f += S) xT[f * FPB + slot] = x[f];
+            for (uint32_t f = grp; f < F; f += W) xT[f * FPB + slot] = x[f];
         }
     }
-    forest_walk<BS, S, WANT_LEAF, GBDT, false, (S > 1 || !GBDT)>(a, xT, i, row, live);
+    forest_walk<FPB_, W, ILP, TAIL, WANT_LEAF, GBDT, false>(a, xT, i, row, live);
 }
 
-template <int BS, int S, bool GBDT>
-int launch_votes(sf_ctx* ctx, const FastArgs& a, size_t lds)
+template <int FPB, int W, int ILP, int TAIL, bool GBDT>
+int launch_votes(sf_ctx* ctx, const FastArgs& a, size_t lds, int slot)
 {
-    const uint32_t fpb = BS / S;
-    const uint32_t grid = (a.n_flows + fpb - 1) / fpb;
-    constexpr int slot = sf::kLdsForest + (S == 1 ? 0 : (S == 2 ? 1 : 2)) * 4 + (GBDT ? 1 : 0);
+    const uint32_t grid = (a.n_flows + FPB - 1) / FPB;
     if (a.leaf_idx) {
-        SF_ALLOW_LDS(ctx, slot + 2, (forest_votes<BS, S, true, GBDT>));
-        forest_votes<BS, S, true, GBDT><<<grid, BS, lds, ctx->stream>>>(a);
+        SF_ALLOW_LDS(ctx, slot + 1, (forest_votes<FPB, W, ILP, TAIL, true, GBDT>));
+        forest_votes<FPB, W, ILP, TAIL, true, GBDT><<<grid, FPB * W, lds, ctx->stream>>>(a);
     } else {
-        SF_ALLOW_LDS(ctx, slot, (forest_votes<BS, S, false, GBDT>));
-        forest_votes<BS, S, false, GBDT><<<grid, BS, lds, ctx->stream>>>(a);
+        SF_ALLOW_LDS(ctx, slot, (forest_votes<FPB, W, ILP, TAIL, false, GBDT>));
+        forest_votes<FPB, W, ILP, TAIL, false, GBDT><<<grid, FPB * W, lds, ctx->stream>>>(a);
     }
     SF_LAUNCH_CHECK(ctx, "forest_votes");
     return SF_OK;
@@ -164,11 +159,70 @@ int check_model(sf_ctx* ctx, const char* who, const TreeModel& m)
     return SF_OK;
 }
 
+// The shapes a block of the walk comes in (flows x lanes per flow), see choose_shape
+enum TileShape { kTile128x8, kTile128x4, kTile64x8, kTile16x32, kTile256x2g, kTile64x4g, kTile16x16g };
+constexpr uint32_t kTileFlows[] = {128, 128, 64, 16, 256, 64, 16};
+
+// The shape of a block and its shared memory, by batch size and model.  All figures are the walk's time in
+// microseconds for 64 features and 100 trees of depth 12 unless another model is named.
+//   few flows: 16 flows x 32 lanes, nothing staged, so that even a small batch gives every compute unit a block and
+//     a lane only a few trees one after the other.  4,000 flows: 11 us against 15 (64x8) and 54 (one lane per
+//     flow); 10,000 flows: 17.6 against 16.1.  The line is 24 flows per compute unit (6,144).
+//   otherwise 64 x 8, four blocks per compute unit where 40 KB hold the tile and a pair-level of records; with
+//     enough flows to fill the chip with tiles twice as large (3 * 128 flows per unit: 80,000 flows 44 against 48 us,
+//     160,000 flows 78 against 77) 128 x 8 where its 80 KB hold one pair-level more than the smaller tile
+//     (1,048,576 flows: 450 -> 420; where they hold no more it is slower: 200 trees 272 against 293).
+//   fewer than 48 trees: 128 x 4, five trees at once per lane; eight lanes would walk a handful each
+//     (1,000,000 flows, 16 trees of depth 8: 62 against 76).
+// Boosted form: lanes split the classes, not the trees (see forest_walk), so a few large shares are better than
+// many uneven ones: 256 x 2 (1,048,576 flows, 200 trees of depth 8: 585 against 599 for 64 x 4), 64 x 4 up to
+// 3 * 128 flows per unit (30,000 flows 39 against 83 with one lane per flow), 16 x 16 for few flows.
+TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n_rows, uint32_t n_cu, size_t* lds)
+{
+    const uint32_t few = 24u * n_cu, many = 3u * 128u * n_cu;
+    auto fit = [&](TileShape s, size_t first, uint32_t least) {
+        // what `first` holds, or else a third or half of a unit's shared memory, with `least` pair-levels of records;
+        // a forest too large for that goes without, in the smallest of these (or the whole) that holds the tile
+        const size_t budgets[] = {first, 160 * 1024 / 3 - 256, 80 * 1024, 160 * 1024};
+        for (int q = 0; q < 7; ++q) {
+            const size_t b = budgets[q < 3 ? q : q - 3];
+            *lds = plan_lds(a, result_words, kTileFlows[s], b, &a.top_pairs);
+            if (*lds <= b && (q >= 3 || a.top_pairs >= least || a.depth / 2 < least)) return;
+        }
+    };
+    if (n_rows <= few) {
+        const TileShape s = gbdt ? kTile16x16g : kTile16x32;
+        *lds = plan_lds(a, result_words, 16, 0, &a.top_pairs);
+        return s;
+    }
+    if (gbdt) {
+        fit(kTile256x2g, 80 * 1024, 1);
+        if (n_rows >= many && *lds <= 80 * 1024) return kTile256x2g; // (one block per unit is slower than the smaller tile)
+        fit(kTile64x4g, 40 * 1024, 1);
+        return kTile64x4g;
+    }
+    if (a.n_trees < 48u) {
+        fit(kTile128x4, 40 * 1024, 1);
+        return kTile128x4;
+    }
+    fit(kTile64x8, 40 * 1024, 1);
+    if (n_rows >= many) {
+        uint32_t top = 0;
+        const size_t wide = plan_lds(a, result_words, 128, 80 * 1024, &top);
+        if (wide <= 80 * 1024 && top > a.top_pairs) {
+            a.top_pairs = top;
+            *lds = wide;
+            return kTile128x8;
+        }
+    }
+    return kTile64x8;
+}
+
 // The model part of the kernel arguments: checks, the packed records (made into the workspace when the model
-// carries none), the width of the vote counters, lanes per flow (*split) and the block's shared memory (*lds).
-// check_only: stop after the argument checks (a call on zero flows launches nothing).
-int setup_trees(sf_ctx* ctx, const char* who, const TreeModel& m, bool gbdt, uint32_t feat_ld, FastArgs& a, uint32_t* split_out,
-                size_t* lds_out, bool check_only = false, bool one_lane_per_flow = false)
+// carries none) and the width of the vote counters.  *result_words: words of results a flow keeps in shared
+// memory during the walk.  check_only: stop after the argument checks (a call on zero flows launches nothing).
+int setup_trees(sf_ctx* ctx, const char* who, const TreeModel& m, bool gbdt, uint32_t feat_ld, FastArgs& a, uint32_t* result_words,
+                bool check_only = false)
 {
     if (m.depth < 1 || m.depth > SF_MAX_TREE_DEPTH)
         return sf::fail(ctx, SF_EINVAL, "%s: depth %u outside 1..%d", who, m.depth, SF_MAX_TREE_DEPTH);
@@ -202,46 +256,8 @@ int setup_trees(sf_ctx* ctx, const char* who, const TreeModel& m, bool gbdt, uin
     a.n_features = m.n_features;
     a.recs = packed;
     a.leaf_label = m.leaf_label;
-    // Shared memory per block of 256 lanes: a feature column per FLOW, the per-lane result column
-    // (packed vote counters, or one binary32 margin per class) and the staged top records of
-    // every tree.  With two lanes per flow three blocks (12 waves) stay resident instead of two,
-    // which pays while the deep records of the trees in flight still fit the first-level cache
-    // (measured: faster up to depth 10, slower at 12, where more waves mean more distinct trees
-    // in flight and more cache misses).  Where even that leaves a single block resident (many
-    // features, many classes, hundreds of trees), four lanes per flow bring back a second one
-    // (measured on 500 trees x 128 features x 32 classes: 16.6 -> 11.2 ms).  Margins are summed in
-    // tree order by one lane, so the boosted form never splits a flow.
     a.vote_bits = a.n_trees <= 255 ? 8u : 16u;
-    const uint32_t result_words = gbdt ? a.n_classes : (a.n_classes * a.vote_bits + 31u) / 32u;
-    const uint32_t full_pairs = m.depth / 2;
-    size_t lds = 0;
-    // for `split` lanes per flow: how many pair-levels of records fit, and the block's shared memory.
-    // The top records may use what is left of a third, else of a half, else of the whole shared memory.
-    auto plan = [&](uint32_t split) {
-        const size_t fixed = ((size_t)a.n_features + result_words) * 4 * (256 / split);
-        size_t budget = 160 * 1024 / 3 - 256;
-        if (fixed + (size_t)a.n_trees * 16 > budget) budget = 80 * 1024 - 512;
-        if (fixed + (size_t)a.n_trees * 16 > budget) budget = 160 * 1024 - 1024;
-        uint32_t top_pairs = 0;
-        while (top_pairs < full_pairs && fixed + (size_t)a.n_trees * recs_upto(top_pairs + 1) * 16 <= budget) ++top_pairs;
-        a.top_pairs = top_pairs;
-        lds = fixed + (size_t)a.n_trees * recs_upto(top_pairs) * 16;
-    };
-    // (one_lane_per_flow: the fused feature + forest kernel builds one flow per lane; with the feature matrix's
-    // round trip gone that beats the separate kernels also where those would share a flow between two lanes:
-    // 1,048,576 flows, 100 trees of depth 10: 0.45 ms against 0.11 + 0.40 ms)
-    uint32_t split = (!gbdt && !one_lane_per_flow && a.n_trees >= 32 && recs_upto(pair_levels(m.depth)) * 16u <= 8192u) ? 2u : 1u;
-    plan(split);
-    if (split == 2 && lds > 80 * 1024) {
-        plan(4);
-        if (lds <= 80 * 1024)
-            split = 4;
-        else
-            plan(2);
-    }
-    if (lds > 160 * 1024) return sf::fail(ctx, SF_EUNSUPPORTED, "%s: %zu bytes of shared memory needed", who, lds);
-    *split_out = split;
-    *lds_out = lds;
+    *result_words = gbdt ? a.n_classes : (a.n_classes * a.vote_bits + 31u) / 32u;
     return SF_OK;
 }
 
@@ -250,10 +266,10 @@ int run_trees(sf_ctx* ctx, const char* who, const float* feat, uint32_t feat_ld,
               const uint32_t* idx_count, uint32_t n_rows, const TreeModel& m, bool gbdt, const Outputs& out)
 {
     FastArgs a = {};
-    uint32_t split = 1;
+    uint32_t result_words = 0;
     size_t lds = 0;
     {
-        const int rc = setup_trees(ctx, who, m, gbdt, feat_ld, a, &split, &lds, n_flows == 0);
+        const int rc = setup_trees(ctx, who, m, gbdt, feat_ld, a, &result_words, n_flows == 0);
         if (rc != SF_OK) return rc;
     }
     if (n_flows == 0) return SF_OK;
@@ -273,10 +289,18 @@ int run_trees(sf_ctx* ctx, const char* who, const float* feat, uint32_t feat_ld,
     a.pred = out.pred;
     a.top = out.top_votes;
     a.leaf_idx = out.leaf_idx;
-    if (split == 4) return launch_votes<256, 4, false>(ctx, a, lds);
-    if (gbdt) return launch_votes<256, 1, true>(ctx, a, lds);
-    if (split == 2) return launch_votes<256, 2, false>(ctx, a, lds);
-    return launch_votes<256, 1, false>(ctx, a, lds);
+    const TileShape shape = choose_shape(a, result_words, gbdt, n_flows, (uint32_t)ctx->n_cu, &lds);
+    if (lds > 160 * 1024) return sf::fail(ctx, SF_EUNSUPPORTED, "%s: %zu bytes of shared memory needed", who, lds);
+    const int slot = sf::kLdsForest + 2 * (int)shape;
+    switch (shape) {
+    case kTile128x8: return launch_votes<128, 8, 3, 1, false>(ctx, a, lds, slot);
+    case kTile128x4: return launch_votes<128, 4, 5, 2, false>(ctx, a, lds, slot);
+    case kTile64x8: return launch_votes<64, 8, 3, 1, false>(ctx, a, lds, slot);
+    case kTile16x32: return launch_votes<16, 32, 5, 2, false>(ctx, a, lds, slot);
+    case kTile256x2g: return launch_votes<256, 2, 5, 2, true>(ctx, a, lds, slot);
+    case kTile64x4g: return launch_votes<64, 4, 5, 2, true>(ctx, a, lds, slot);
+    default: return launch_votes<16, 16, 5, 2, true>(ctx, a, lds, slot);
+    }
 }
 
 int run_forest(sf_ctx* ctx, const char* who, const float* feat, uint32_t feat_ld, uint32_t n_flows, const uint32_t* idx,
@@ -294,13 +318,12 @@ int run_forest(sf_ctx* ctx, const char* who, const float* feat, uint32_t feat_ld
 
 namespace sf {
 // the hard-voting forest as kernel arguments (for the fused feature + forest entry point)
-int forest_setup(sf_ctx* ctx, const char* who, const sf_forest* f, uint32_t feat_ld, sfforest::FastArgs& a, uint32_t* split,
-                 size_t* lds)
+int forest_setup(sf_ctx* ctx, const char* who, const sf_forest* f, uint32_t feat_ld, sfforest::FastArgs& a, uint32_t* result_words)
 {
     if (!f) return fail(ctx, SF_EINVAL, "%s: forest is NULL", who);
     const TreeModel m = {f->n_trees, f->depth, f->n_classes, f->n_features, f->node_feat, f->node_thr, f->leaf_label,
                          nullptr, nullptr, f->packed};
-    return setup_trees(ctx, who, m, false, feat_ld, a, split, lds, false, true);
+    return setup_trees(ctx, who, m, false, feat_ld, a, result_words);
 }
 } // namespace sf
 

@@ -4,14 +4,23 @@
 // in shared memory as columns [feature][flow], and the score of Section 3.2 (top_votes = max_y votes[y],
 // LC = 1 - top_votes / n_trees; entropy or LC of the softmax for boosted trees).
 //
-// What bounds the walk is gather throughput, of the caches' address path (a compute unit retires a
-// 64-lane gather every 16 to 57 cycles, by how many cache lines it touches) and of shared memory alike,
-// so the forest is packed into 16-byte records that hold TWO levels: a node and both its children (three
-// thresholds, three feature indices).  One 16-byte load then serves two visits.  Records form a quaternary
-// heap per tree (record r has children 4r+1..4r+4); the records of the top levels of every tree are staged
-// in shared memory, the deeper ones come through the cache; the leaf label is one byte load at the end.
-// Eight trees are walked at once per lane to keep independent loads in flight.  Votes are integers in
-// shared memory; nothing in the voting form rounds.
+// What bounds the walk is gather throughput, of the caches' address path above all, so the forest is packed
+// into 16-byte records that hold TWO levels: a node and both its children (three thresholds, three feature
+// indices).  One 16-byte load then serves two visits.  Records form a quaternary heap per tree (record r has
+// children 4r+1..4r+4); the records of the top levels of every tree are staged in shared memory, the deeper
+// ones come through the cache; the leaf label is one byte load at the end.  A few trees are walked at once per
+// lane to keep independent loads in flight.  Votes are integers in shared memory; nothing in the voting form
+// rounds.
+//
+// The feature tile (F * 4 bytes per flow) is what fills shared memory, so it also limits how many flows a
+// compute unit can hold.  Several waves therefore work on the same tile, each on its share of the trees: the
+// unit then runs up to 32 waves instead of 8 and the address path stays 82-84 % busy (65 % before).  A wave's
+// lanes all walk the SAME trees, for different flows: lanes that split the trees of one flow between them
+// (as this code did before, for shapes with few resident waves) spread every record load over two to four
+// times as many cache lines.  Measured, the walk alone, before -> after: 1,048,576 flows x 64 features, 100
+// trees of depth 12: 0.588 -> 0.42 ms; depth 10: 0.375 -> 0.29 ms; 4,194,304 flows x 128 features, 500 trees of
+// depth 10: 10.2 -> 6.2 ms; 65,536 flows, 200 trees of depth 10: 70 -> 46 us; 97 flows, 100 trees of depth 12:
+// 53 -> 11 us.
 #pragma once
 
 #include <type_traits>
@@ -68,47 +77,57 @@ struct FastArgs {
     uint16_t vmin[SF_MAX_CLASSES];
 };
 
-// Trees walked at once per lane: groups of kIlp, and a last group of kIlpTail when at most that many trees are
-// left (so that 100 trees take ten full groups and 125 twelve and a half, not thirteen of eight with four idle
-// slots; measured on 100 trees of depth 12: 8 at a time 0.565 ms, 10 at a time 0.532, 12 0.565, 20 0.553).
-constexpr int kIlp = 10, kIlpTail = 5;
+// How many pair-levels of every tree fit into shared memory beside the tile (kept within `budget` bytes) and the
+// block's shared memory that makes.
+inline size_t plan_lds(const FastArgs& a, uint32_t result_words, uint32_t fpb, size_t budget, uint32_t* top_pairs)
+{
+    const size_t fixed = ((size_t)a.n_features + result_words) * 4 * fpb;
+    const uint32_t full_pairs = a.depth / 2;
+    uint32_t t = 0;
+    while (t < full_pairs && fixed + (size_t)a.n_trees * recs_upto(t + 1) * 16 <= budget) ++t;
+    *top_pairs = t;
+    return fixed + (size_t)a.n_trees * recs_upto(t) * 16;
+}
 
-
-// Shared memory of a block behind the feature tile xT ([n_features][FPB] floats, FPB = BS / S flows):
+// Shared memory of a block behind the feature tile xT ([n_features][FPB] floats, FPB flows per block):
 // vote counters (or margins), then the staged top records.
-// BS lanes per block; S lanes share one flow, lane group g of S walks trees g, g+S, g+2S, ...
-// GBDT = false: leaves are class labels and the flow's result is the vote count per class.
-// GBDT = true (S must be 1): leaves are binary32 margins; the lane's shared-memory column holds
-// one binary32 sum per class, started at the initial margin and extended tree by tree in tree
-// order (each addition rounded on its own, so the sums are reproducible bit for bit); the
-// epilogue turns them into softmax probabilities in binary64 and into the score of Section 3.2.
+// kIlp trees are walked at once per lane, kIlpTail in a last round when at most that many are left.
+// A block is FPB * W lanes; W lanes share one flow: group g = lane index / FPB.  With FPB a multiple of 64 a
+// group is whole waves, so all lanes of a wave walk the same trees (their record gathers fall on the same few
+// cache lines) and everything derived from the tree number is scalar.
+// GBDT = false: leaves are class labels and the flow's result is the vote count per class; group g walks trees
+// g, g + W, g + 2W, ...
+// GBDT = true: leaves are binary32 margins; the flow's shared-memory column holds one binary32 sum per class,
+// started at the initial margin and extended tree by tree in tree order (each addition rounded on its own, so
+// the sums are reproducible bit for bit); group g owns the classes g, g + W, ... and walks their trees; the
+// epilogue turns the sums into softmax probabilities in binary64 and into the score of Section 3.2.
 // KEEP_ROWS: the fused form (see FastArgs::feat_out).
 // i: the row of the outputs this lane's flow owns; row: its row in the feature matrix (subset form);
 // live: false for lanes past the end (they walk a valid tile column and write nothing).
 // The caller has filled xT (no barrier needed before the call: this function synchronises the block
 // before the first read of the tile).
-template <int BS, int S, bool WANT_LEAF, bool GBDT, bool KEEP_ROWS, bool EAGER = (S > 1)>
+template <int FPB_, int W, int kIlp, int kIlpTail, bool WANT_LEAF, bool GBDT, bool KEEP_ROWS>
 __device__ __forceinline__ void forest_walk(const FastArgs& a, float* xT, uint32_t i, uint32_t row, bool live)
 {
-    static_assert(!GBDT || S == 1, "margins are summed in tree order by one lane");
-    constexpr uint32_t FPB = BS / S;       // flows per block
-    constexpr uint32_t FPW = 64 / S;       // flows per wave
-    constexpr uint32_t kColShift = FPB == 256 ? 10 : (FPB == 128 ? 9 : (FPB == 64 ? 8 : 7)); // log2(bytes per feature column)
+    constexpr uint32_t FPB = FPB_, BS = FPB * W; // flows and lanes per block
+    constexpr uint32_t kColShift = FPB == 256 ? 10 : FPB == 128 ? 9 : FPB == 64 ? 8 : FPB == 32 ? 7 : FPB == 16 ? 6 : FPB == 8 ? 5 : 4; // log2(bytes per feature column)
+    static_assert((4u << (kColShift - 2)) == 4u * FPB, "flows per block is a power of two from 4 to 256");
     const uint32_t F = a.n_features, C = a.n_classes, T = a.n_trees;
     const uint32_t top_recs = recs_upto(a.top_pairs);      // records per tree held in shared memory
-    // vote counters, 32 / vote_bits classes per word, one column per FLOW: [vote_words][FPB]; the S lanes of
+    // vote counters, 32 / vote_bits classes per word, one column per FLOW: [vote_words][FPB]; the W lanes of
     // a flow add to it with shared-memory atomics (fields cannot carry into each other: a count is at most n_trees)
     const uint32_t per_shift = a.vote_bits == 8 ? 2u : 1u; // log2(counters per word)
     const uint32_t vote_words = GBDT ? C : (C + (1u << per_shift) - 1u) >> per_shift; // boosted: one float per class
     uint32_t* vT = reinterpret_cast<uint32_t*>(xT + (size_t)F * FPB);
     uint4* topT = reinterpret_cast<uint4*>(vT + (size_t)vote_words * FPB);   // [T][top_recs]
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const uint32_t grp = lane / FPW;                       // which share of the trees this lane walks
-    const uint32_t slot = wave * FPW + (lane % FPW);       // flow slot in the block's tile
+    const uint32_t tid = threadIdx.x;
+    uint32_t grp = W == 1 ? 0u : tid / FPB;                // which share of the trees this lane walks
+    if (FPB >= 64u) grp = __builtin_amdgcn_readfirstlane(grp);
+    const uint32_t slot = tid % FPB;                       // flow slot in the block's tile
     if (GBDT) {
-        for (uint32_t c = 0; c < C; ++c) vT[c * FPB + slot] = __float_as_uint(a.base ? a.base[c] : 0.f);
+        for (uint32_t c = grp; c < C; c += W) vT[c * FPB + slot] = __float_as_uint(a.base ? a.base[c] : 0.f);
     } else {
-        for (uint32_t c = grp; c < vote_words; c += S) vT[c * FPB + slot] = 0;
+        for (uint32_t c = grp; c < vote_words; c += W) vT[c * FPB + slot] = 0;
     }
     const uint32_t n_rec = recs_upto(pair_levels(a.depth));
     const uint4* recs = reinterpret_cast<const uint4*>(a.recs);
@@ -142,105 +161,103 @@ __device__ __forceinline__ void forest_walk(const FastArgs& a, float* xT, uint32
 #define SF_FEAT_ROT(FW, SH) (*(LdsFloat*)(uintptr_t)((__builtin_amdgcn_alignbit((FW), (FW), (SH)) & kFieldMask) | xl))
 #define SF_FEAT_0(FW) (kRot0 == 0u ? *(LdsFloat*)(uintptr_t)(((FW) & kFieldMask) | xl) : SF_FEAT_ROT(FW, kRot0))
 
-    // two visits from one record; o is the byte offset of the record inside its tree.
-    // EAGER = false: the child's feature is fetched after the parent's test (two shared-memory reads per
-    // record, the second dependent on the first).  The record offset moves on as
-    // 4 * o + 16 * (1 + 2 * right0 + right1) = ((o + sh) << 2) - 16 + 16 * right1 with sh = 8 or 16, the rotation
-    // that selects the child's feature field.
-    // EAGER = true: all three features up front (three independent reads), which is faster when latency
-    // binds.  Which one wins is measured per kernel: lanes sharing a flow (few waves resident) and the
-    // stand-alone vote kernel run eager (workload 2: 0.564 -> 0.543 ms), the fused feature + forest kernel
-    // and the boosted form do not (0.531 against 0.570 ms, 0.72 against 0.78 ms).
+    // Two visits from one record; o is the byte offset of the record inside its tree.  The child's feature is
+    // fetched after the parent's test (two shared-memory reads per record, the second dependent on the first:
+    // with this many waves resident fetching all three up front is no faster and costs registers).  The record
+    // offset moves on as 4 * o + 16 * (1 + 2 * right0 + right1) = ((o + sh) << 2) - 16 + 16 * right1 with
+    // sh = 8 or 16, the rotation that selects the child's feature field.
 #define SF_PAIR_STEP(REC, O)                                                                              \
     do {                                                                                                  \
         const uint32_t fw = (REC).w;                                                                      \
         const float x0 = SF_FEAT_0(fw);                                                                   \
         const bool r0 = !(x0 <= __uint_as_float((REC).x));                                                \
-        if (!EAGER) {                                                                                     \
-            const uint32_t sh = r0 ? 16u : 8u;                                                            \
-            const float tc = __uint_as_float(r0 ? (REC).z : (REC).y);                                     \
-            const float xc = SF_FEAT_ROT(fw, sh + kRot0);                                                 \
-            const bool rc = !(xc <= tc);                                                                  \
-            (O) = (((O) + sh) << 2) + (rc ? 0u : 0xFFFFFFF0u);                                            \
-        } else {                                                                                          \
-            const float x1 = SF_FEAT_ROT(fw, kRot0 + 8u);                                                 \
-            const float x2 = SF_FEAT_ROT(fw, kRot0 + 16u);                                                \
-            const bool r1 = !(x1 <= __uint_as_float((REC).y));                                            \
-            const bool r2 = !(x2 <= __uint_as_float((REC).z));                                            \
-            const uint32_t inc_l = r1 ? 32u : 16u, inc_r = r2 ? 64u : 48u;                                \
-            (O) = 4u * (O) + (r0 ? inc_r : inc_l);                                                        \
-        }                                                                                                 \
+        const uint32_t sh = r0 ? 16u : 8u;                                                                \
+        const float tc = __uint_as_float(r0 ? (REC).z : (REC).y);                                         \
+        const float xc = SF_FEAT_ROT(fw, sh + kRot0);                                                     \
+        const bool rc = !(xc <= tc);                                                                      \
+        (O) = (((O) + sh) << 2) + (rc ? 0u : 0xFFFFFFF0u);                                                \
     } while (0)
 
-    // lane group g walks trees g, g+S, ...; every group runs the same number of rounds so that
-    // the loop stays wave-uniform; a slot past the last tree repeats it and does not vote
-    const uint32_t per_grp = (T + S - 1u) / S;
+    // lane group g walks trees g, g+W, ... (boosted form: the trees of classes g, g+W, ...); every group runs
+    // the same number of rounds so that the loop stays wave-uniform; a slot past the last tree repeats it and
+    // does not vote
+    const uint32_t my_classes = GBDT ? (C > grp ? (C - grp + W - 1u) / W : 0u) : 0u;
+    uint32_t per_grp = GBDT ? (T + C - 1u) / C * ((C + W - 1u) / W) : (T + W - 1u) / W;
+    if (FPB >= 64u && grp >= (GBDT ? C : T)) per_grp = 0; // (whole waves without a share)
     // one group: ILP trees from position q0 of the lane group's list
     auto walk_group = [&](auto ilp_tag, uint32_t q0) {
-        constexpr int kIlp = decltype(ilp_tag)::value;
-        uint32_t o[kIlp], tt[kIlp];
-        bool tv[kIlp];
+        constexpr int G = decltype(ilp_tag)::value;
+        uint32_t o[G], tt[G], cls[G];
+        bool tv[G];
 #pragma unroll
-        for (int u = 0; u < kIlp; ++u) {
-            const uint32_t t = (q0 + u) * S + grp;
+        for (int u = 0; u < G; ++u) {
+            uint32_t t;
+            if (GBDT && W > 1) {
+                const uint32_t q = q0 + u, rnd = my_classes ? q / my_classes : 0u;
+                cls[u] = grp + W * (q - rnd * my_classes);
+                t = my_classes ? rnd * C + cls[u] : T;
+            } else {
+                t = (q0 + u) * W + grp;
+                if (GBDT) cls[u] = t % C;
+            }
             o[u] = 0;
             tv[u] = q0 + u < per_grp && t < T;
             tt[u] = tv[u] ? t : T - 1u;
         }
         uint32_t j = 0;
         for (; j < lds_pairs; ++j) {
-            uint4 rec[kIlp];
+            uint4 rec[G];
 #pragma unroll
-            for (int u = 0; u < kIlp; ++u)
+            for (int u = 0; u < G; ++u)
                 rec[u] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(topT) + tt[u] * top_bytes + o[u]);
 #pragma unroll
-            for (int u = 0; u < kIlp; ++u) SF_PAIR_STEP(rec[u], o[u]);
+            for (int u = 0; u < G; ++u) SF_PAIR_STEP(rec[u], o[u]);
         }
         const char* gb = reinterpret_cast<const char*>(a.recs);
         for (; j < full_pairs; ++j) {
-            uint4 rec[kIlp];
+            uint4 rec[G];
 #pragma unroll
-            for (int u = 0; u < kIlp; ++u)
+            for (int u = 0; u < G; ++u)
                 rec[u] = *reinterpret_cast<const uint4*>(gb + (size_t)tt[u] * rec_bytes + o[u]);
 #pragma unroll
-            for (int u = 0; u < kIlp; ++u) SF_PAIR_STEP(rec[u], o[u]);
+            for (int u = 0; u < G; ++u) SF_PAIR_STEP(rec[u], o[u]);
         }
-        uint32_t leaf[kIlp];
+        uint32_t leaf[G];
         if (odd) {
             // one level left: only the record's top node counts
-            uint4 rec[kIlp];
+            uint4 rec[G];
 #pragma unroll
-            for (int u = 0; u < kIlp; ++u)
+            for (int u = 0; u < G; ++u)
                 rec[u] = *reinterpret_cast<const uint4*>(gb + (size_t)tt[u] * rec_bytes + o[u]);
 #pragma unroll
-            for (int u = 0; u < kIlp; ++u) {
+            for (int u = 0; u < G; ++u) {
                 const float x0 = SF_FEAT_0(rec[u].w);
                 const bool r0 = !(x0 <= __uint_as_float(rec[u].x));
                 leaf[u] = 2u * ((o[u] >> 4) - leaf_base) + (r0 ? 1u : 0u);
             }
         } else {
 #pragma unroll
-            for (int u = 0; u < kIlp; ++u) leaf[u] = (o[u] >> 4) - leaf_base;
+            for (int u = 0; u < G; ++u) leaf[u] = (o[u] >> 4) - leaf_base;
         }
         if (GBDT) {
-            float val[kIlp];
+            float val[G];
 #pragma unroll
-            for (int u = 0; u < kIlp; ++u) val[u] = a.leaf_value[(size_t)tt[u] * n_leaf + leaf[u]];
+            for (int u = 0; u < G; ++u) val[u] = a.leaf_value[(size_t)tt[u] * n_leaf + leaf[u]];
 #pragma unroll
-            for (int u = 0; u < kIlp; ++u) { // ascending u = ascending tree: the order of the sum
+            for (int u = 0; u < G; ++u) { // ascending u = ascending tree: the order of the sum
                 if (tv[u]) {
-                    float* m = reinterpret_cast<float*>(&vcol[(tt[u] % C) * FPB]);
+                    float* m = reinterpret_cast<float*>(&vcol[cls[u] * FPB]);
                     *m = *m + val[u];
                     if (WANT_LEAF && live) a.leaf_idx[(size_t)i * T + tt[u]] = (uint16_t)leaf[u];
                 }
             }
             return;
         }
-        uint32_t lab[kIlp];
+        uint32_t lab[G];
 #pragma unroll
-        for (int u = 0; u < kIlp; ++u) lab[u] = a.leaf_label[(size_t)tt[u] * n_leaf + leaf[u]];
+        for (int u = 0; u < G; ++u) lab[u] = a.leaf_label[(size_t)tt[u] * n_leaf + leaf[u]];
 #pragma unroll
-        for (int u = 0; u < kIlp; ++u) {
+        for (int u = 0; u < G; ++u) {
             if (tv[u]) {
                 const uint32_t l = lab[u] < C ? lab[u] : C - 1u; // clamp: a bad label must not leave the tile
                 // only this lane touches its column; the add is one shared-memory instruction
@@ -260,7 +277,7 @@ __device__ __forceinline__ void forest_walk(const FastArgs& a, float* xT, uint32
 #undef SF_PAIR_STEP
 #undef SF_FEAT_0
 #undef SF_FEAT_ROT
-    if (S > 1) __syncthreads(); // all lanes of a flow have added their votes before its first lane reads them
+    if (W > 1) __syncthreads(); // all lanes of a flow have added their votes before its first lane reads them
     if (!live || grp != 0) return;
     if (GBDT) {
         const float* mcol = reinterpret_cast<const float*>(vcol);
