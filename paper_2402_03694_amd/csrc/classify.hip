@@ -1,28 +1,35 @@
-// All four steps behind one entry point, with steps 1-3 in ONE kernel: a block featurizes a tile of 256
+// All four steps behind one entry point, with steps 1-3 in ONE kernel: a block featurizes a tile of
 // flows straight into the shared-memory columns the forest walk reads (Section 3.1 of the paper: the fast
 // model sees every flow, from its first k packets) and walks the forest on them; the feature row of a
 // flow leaves the chip only if the gate (Section 3.2) hands the flow on to the slow model.
 //
 // Why: the feature step is bound by vector arithmetic and by its memory pattern, the walk by gathers;
-// with two blocks per compute unit one block's feature phase runs under the other's walk, and the
+// with several blocks per compute unit one block's feature phase runs under another's walk, and the
 // feature matrix (256 bytes per flow written, then read again) is neither written nor read for the
 // flows that stay with the fast model.
 //
-// Shared memory of a block: the tile [32 * windows][256] floats, behind it what the walk needs (vote
-// counters, staged top records).  The sorting networks of the feature phase need a scratch column per
-// lane; windows are computed from the last to the first, and every window but the first uses the
-// first window's 32 columns (not written yet) as scratch, the first window the space behind the tile
-// (the walk fills that only afterwards).
+// The block has the walk's shape (several lanes per flow in different waves, see forest_core.h), so the
+// statistics are split between the waves too: a flow's 32 statistics of a window are four independent parts
+// (ordered sums and order statistics, of sizes and of times), and a wave computes one part of one window for
+// its flows.  A part needs one quantity in registers, so the kernel stays within the 64 registers at which a
+// compute unit holds 32 waves.
+//
+// Shared memory of a block: the tile [32 * windows][flows] floats; behind it, one after the other, the packets
+// of the tile's flows as columns, the scratch columns of the sorting networks, and what the walk needs (vote
+// counters, staged top records).
 #include "featurize_core.h"
 #include "forest_core.h"
 
 namespace sf {
 int forest_setup(sf_ctx* ctx, const char* who, const sf_forest* f, uint32_t feat_ld, sfforest::FastArgs& a, uint32_t* result_words);
+sfforest::TileShape forest_shape(sfforest::FastArgs& a, uint32_t result_words, uint32_t n_rows, uint32_t n_cu, size_t* lds);
 }
 
 namespace {
 
 using namespace sfforest;
+
+constexpr uint32_t kFusedWindows = 2, kFusedDepth = 16; // the most the fused kernel is built for
 
 struct ClassifyArgs {
     uint32_t n_pkts;
@@ -31,99 +38,175 @@ struct ClassifyArgs {
     const float* iat;
     const uint8_t* dir;
     uint32_t n_windows;
-    uint32_t depth[SF_MAX_WINDOWS];
-    uint32_t wide_ok; // the packet arrays start on 16-byte (size, time) and 8-byte (direction) boundaries
+    uint32_t depth[kFusedWindows];
+    uint32_t wide_ok; // the packet arrays start on 8-byte (size, time, direction) boundaries
     FastArgs fa;      // n_flows, model, outputs, gate; n_features = 32 * n_windows
 };
 
-template <int KMAX, bool KEEP_ROWS>
-__global__ __launch_bounds__(256) void featurize_forest(ClassifyArgs c)
+// Staged packets of a tile: one column per flow, rows 0..KMAX-1 the sizes, KMAX..2 KMAX-1 the times, then the
+// direction bits and the packet count.  Four words of padding per row: the lanes of a wave that write a row pair
+// each for eight flows then fall on 64 different banks.
+__host__ __device__ constexpr uint32_t stage_stride(uint32_t fpb) { return fpb + 4u; }
+__host__ __device__ constexpr uint32_t stage_words(uint32_t kmax, uint32_t fpb) { return (2u * kmax + 2u) * stage_stride(fpb); }
+// Groups of lanes that compute statistics side by side: whole waves, also where a tile has fewer than 64 flows
+__host__ __device__ constexpr uint32_t feature_units(uint32_t fpb, uint32_t w) { return fpb >= 64u ? w : fpb * w / 64u; }
+// every second unit sorts (see below) and has a scratch column of KMAX words per flow
+__host__ __device__ constexpr uint32_t scratch_words(uint32_t kmax, uint32_t fpb, uint32_t w) { return feature_units(fpb, w) / 2u * kmax * fpb; }
+
+// One part of one window's statistics for one flow per lane: kind 0 / 2: sums of sizes / times, kind 1 / 3: order
+// statistics of sizes / times.  x: the quantity; col: scratch column; dst: the window's first row of the tile.
+template <int N, int KMAX>
+__device__ __forceinline__ void window_part(uint32_t kind, const float (&x)[KMAX], uint32_t dmask, int m, uint32_t* col, uint32_t fpb,
+                                            float* dst)
 {
-    constexpr uint32_t FPB = 256;
+    const uint32_t valid = (1u << m) - 1u, m1 = dmask & valid, m0 = ~dmask & valid; // (m <= 16)
+    const int c1 = __popc(m1), c0 = m - c1;
+    if ((kind & 1u) == 0u) {
+        const float sum = sffeat::window_sums<N, KMAX>(x, valid, m0, m1, m, c0, c1, dst + (kind ? 5u : 0u) * fpb, fpb);
+        if (kind == 0u) {
+            dst[30u * fpb] = sum;
+            dst[31u * fpb] = (float)m;
+        }
+    } else if (kind == 1u) {
+        sffeat::window_order_sizes<N, KMAX>(x, valid, m1, m, c0, c1, col, fpb, dst + 2u * fpb, fpb);
+    } else {
+        // a time with its sign bit set anywhere in the wave: the order statistics take the general path
+        uint32_t sign_bits = 0;
+#pragma unroll
+        for (int j = 0; j < KMAX; ++j) sign_bits |= __float_as_uint(x[j]);
+        const bool signed_times = __any((int)(sign_bits >> 31));
+        sffeat::window_order_times<N, KMAX>(x, valid, m0, m1, m, c0, c1, signed_times, col, fpb, dst + 7u * fpb, fpb);
+    }
+}
+
+// FPB flows per block, W lanes per flow (the walk's shape).
+// One wave per 64 flows did all of this before (256 flows per block, one lane per flow).  The kernel, before -> after:
+// 1,048,576 flows x 16 packets, windows of 8 and 16, 100 trees of depth 12, a quarter of the rows kept: 572 -> 541 us;
+// windows of 5 and 10, depth 10, no rows: 468 -> 385 us; 97 ragged flows: 51 -> 11 us.  What bounds it: the walk's
+// gathers (forest_core.h) and about 80 us of vector arithmetic for the statistics; smaller tiles (64 x 8) overlap the
+// two no better and hold fewer staged records (whole pass 716 -> 773 us).
+template <int FPB_, int W, int ILP, int TAIL, int KMAX, bool KEEP_ROWS>
+__global__ __launch_bounds__(FPB_ * W, 8) void featurize_forest(ClassifyArgs c)
+{
+    constexpr uint32_t FPB = FPB_, BS = FPB * W, SS = stage_stride(FPB), UNITS = feature_units(FPB, W);
+    constexpr uint32_t P = KMAX / 2; // lanes that fetch one flow's packets, two packets each
+    static_assert((FPB * P) % 64u == 0 && (P == 4 || P == 8), "every flow's packets are fetched by lanes of one wave, whole waves take part");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const FastArgs& a = c.fa;
     float* xT = reinterpret_cast<float*>(smem_raw); // [32 * windows][FPB]
     uint32_t* behind = reinterpret_cast<uint32_t*>(xT + (size_t)a.n_features * FPB);
-    const uint32_t tid = threadIdx.x;
-    const uint32_t i = blockIdx.x * FPB + tid;
-    const bool live = i < a.n_flows;
-    // a lane past the last flow works on the last flow (its loads stay inside the arrays) and writes nothing
-    const uint32_t flow = live ? i : a.n_flows - 1u;
-    uint32_t o, n;
-    {
+    const uint32_t tid = threadIdx.x, flow0 = blockIdx.x * FPB;
+    for (uint32_t q = tid; q < FPB * P; q += BS) {
+        // consecutive lanes hold consecutive packets of a flow and the flows follow each other in memory, so the
+        // loads of a wave are one contiguous piece (flows longer than the window leave gaps)
+        const uint32_t f = q / P, p = q % P;
+        // a slot past the last flow works on the last flow (its loads stay inside the arrays)
+        const uint32_t flow = flow0 + f < a.n_flows ? flow0 + f : a.n_flows - 1u;
         uint32_t b = c.off[flow], e = c.off[flow + 1];
         b = b < c.n_pkts ? b : c.n_pkts; // clamp: malformed offsets must not leave the arrays
         e = e < c.n_pkts ? e : c.n_pkts;
         e = e < b ? b : e;
-        o = b;
-        n = e - b;
-    }
-    const uint32_t dmax = c.depth[c.n_windows - 1];
-    const int avail = (int)(n < dmax ? n : dmax);
-    float s[KMAX], t[KMAX];
-    uint64_t dmask = 0;
-    if (avail == KMAX && (o & 7u) == 0 && c.wide_ok) {
-        // whole window present and 16-byte aligned (array bases included): wide loads
+        const uint32_t n = e - b, dmax = c.depth[c.n_windows - 1u], avail = n < dmax ? n : dmax;
+        float s[2] = {0.f, 0.f}, t[2] = {0.f, 0.f};
+        uint32_t d = 0;
+        const uint32_t o = b + 2u * p;
+        if (2u * p + 1u < avail && (o & 1u) == 0 && c.wide_ok) {
+            const uint32_t sz = *reinterpret_cast<const uint32_t*>(c.size + o);
+            const float2 tm = *reinterpret_cast<const float2*>(c.iat + o);
+            const uint32_t dd = *reinterpret_cast<const uint16_t*>(c.dir + o);
+            s[0] = (float)(sz & 0xFFFFu);
+            s[1] = (float)(sz >> 16);
+            t[0] = tm.x;
+            t[1] = tm.y;
+            d = (dd & 1u) | ((dd >> 7) & 2u);
+        } else {
 #pragma unroll
-        for (int q = 0; q < KMAX / 8; ++q) {
-            const uint4 sz = *reinterpret_cast<const uint4*>(c.size + o + 8 * q);
-            const uint32_t w[4] = {sz.x, sz.y, sz.z, sz.w};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                s[8 * q + 2 * k] = (float)(w[k] & 0xFFFFu);
-                s[8 * q + 2 * k + 1] = (float)(w[k] >> 16);
-            }
-            const float4 t0 = *reinterpret_cast<const float4*>(c.iat + o + 8 * q);
-            const float4 t1 = *reinterpret_cast<const float4*>(c.iat + o + 8 * q + 4);
-            t[8 * q + 0] = t0.x; t[8 * q + 1] = t0.y; t[8 * q + 2] = t0.z; t[8 * q + 3] = t0.w;
-            t[8 * q + 4] = t1.x; t[8 * q + 5] = t1.y; t[8 * q + 6] = t1.z; t[8 * q + 7] = t1.w;
-            const uint2 dd = *reinterpret_cast<const uint2*>(c.dir + o + 8 * q);
-            const uint32_t dw[2] = {dd.x, dd.y};
-#pragma unroll
-            for (int k = 0; k < 8; ++k) dmask |= (uint64_t)((dw[k >> 2] >> (8 * (k & 3))) & 1u) << (8 * q + k);
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < KMAX; ++j) {
-            if (j < avail) {
-                s[j] = (float)c.size[o + j];
-                t[j] = c.iat[o + j];
-                dmask |= (uint64_t)(c.dir[o + j] & 1u) << j;
-            } else {
-                s[j] = 0.f;
-                t[j] = 0.f;
+            for (uint32_t k = 0; k < 2u; ++k) {
+                if (2u * p + k < avail) {
+                    s[k] = (float)c.size[o + k];
+                    t[k] = c.iat[o + k];
+                    d |= (uint32_t)(c.dir[o + k] & 1u) << k;
+                }
             }
         }
-    }
-    // a time with its sign bit set anywhere in the wave: the order statistics take the general path
-    uint32_t sign_bits = 0;
+        d <<= 2u * p;
 #pragma unroll
-    for (int j = 0; j < KMAX; ++j) sign_bits |= __float_as_uint(t[j]);
-    const bool signed_times = __any((int)(sign_bits >> 31));
-    for (int w = (int)c.n_windows - 1; w >= 0; --w) {
-        const int dw = (int)c.depth[w];
-        const int m = avail < dw ? avail : dw;
-        // every address below is the lane's own column: no two lanes (or waves) share a word
-        uint32_t* col = (w > 0 ? reinterpret_cast<uint32_t*>(xT) : behind) + tid;
-        float* dst = xT + (size_t)(32 * w) * FPB + tid;
-        // the smallest network that covers every lane's window (wave-uniform choice)
-        if (KMAX >= 16 && __any(m > 8))
-            sffeat::window_stats<(KMAX >= 16 ? 16 : KMAX), KMAX>(s, t, dmask, m, signed_times, col, FPB, dst, FPB);
-        else
-            sffeat::window_stats<8, KMAX>(s, t, dmask, m, signed_times, col, FPB, dst, FPB);
+        for (uint32_t k = 1; k < P; k *= 2) d |= (uint32_t)__shfl_xor((int)d, (int)k, 64);
+        float* st = reinterpret_cast<float*>(behind) + f;
+#pragma unroll
+        for (uint32_t k = 0; k < 2u; ++k) {
+            st[(2u * p + k) * SS] = s[k];
+            st[(KMAX + 2u * p + k) * SS] = t[k];
+        }
+        if (p == 0u) {
+            behind[2u * KMAX * SS + f] = d;
+            behind[(2u * KMAX + 1u) * SS + f] = avail;
+        }
+    }
+    __syncthreads();
+    // unit u computes the parts u, u + UNITS, ... of the list (window 0 kinds 0..3, window 1 kinds 0..3)
+    static_assert(UNITS == 4 || UNITS == 8, "a unit keeps its kind of part");
+    uint32_t unit = FPB >= 64u ? tid / FPB : tid / 64u;
+    unit = __builtin_amdgcn_readfirstlane(unit);
+    const uint32_t slot = FPB >= 64u ? tid % FPB : tid % 64u;
+    const bool has_flow = FPB >= 64u || slot < FPB;
+    const uint32_t kind = unit & 3u;
+    float x[KMAX];
+    uint32_t dmask = 0;
+    int avail = 0;
+    const bool works = has_flow && (unit >> 2) < c.n_windows;
+    if (works) {
+        const float* st = reinterpret_cast<const float*>(behind) + slot + (kind >> 1) * KMAX * SS;
+#pragma unroll
+        for (int j = 0; j < KMAX; ++j) x[j] = st[j * SS];
+        dmask = behind[2u * KMAX * SS + slot];
+        avail = (int)behind[(2u * KMAX + 1u) * SS + slot];
+    }
+    __syncthreads(); // the staged packets are in registers: their space is scratch now
+    if (works) {
+        uint32_t* col = behind + (unit >> 1) * (KMAX * FPB) + slot; // the lane's own column: no two lanes share a word
+#pragma unroll 1
+        for (uint32_t w = unit >> 2; w < c.n_windows; w += UNITS / 4u) {
+            // nothing made from the packets for one part or window is kept for another (registers)
+#pragma unroll
+            for (int j = 0; j < KMAX; ++j) asm volatile("" : "+v"(x[j]));
+            const int dw = (int)c.depth[w];
+            const int m = avail < dw ? avail : dw;
+            float* dst = xT + (size_t)(32u * w) * FPB + slot;
+            // the smallest network that covers every lane's window (wave-uniform choice)
+            if (KMAX > 8 && __any(m > 8))
+                window_part<KMAX, KMAX>(kind, x, dmask, m, col, FPB, dst);
+            else
+                window_part<8, KMAX>(kind, x, dmask, m, col, FPB, dst);
+        }
     }
     __syncthreads(); // the space behind the tile is free: the walk may stage its records there
-    forest_walk<256, 1, 10, 5, false, false, KEEP_ROWS>(a, xT, i, i, live);
+    const uint32_t i = flow0 + tid % FPB;
+    forest_walk<FPB_, W, ILP, TAIL, false, false, KEEP_ROWS>(a, xT, i, i, i < a.n_flows);
+}
+
+template <int FPB, int W, int ILP, int TAIL, int KMAX, bool KEEP_ROWS>
+int launch_fused(sf_ctx* ctx, const ClassifyArgs& c, size_t lds, int slot)
+{
+    const size_t behind = stage_words(KMAX, FPB) > scratch_words(KMAX, FPB, W) ? stage_words(KMAX, FPB) : scratch_words(KMAX, FPB, W);
+    const size_t lds_feat = ((size_t)c.fa.n_features * FPB + behind) * 4;
+    if (lds_feat > lds) lds = lds_feat;
+    auto* kernel = featurize_forest<FPB, W, ILP, TAIL, KMAX, KEEP_ROWS>;
+    SF_ALLOW_LDS(ctx, slot, kernel);
+    kernel<<<(c.fa.n_flows + FPB - 1u) / FPB, FPB * W, lds, ctx->stream>>>(c);
+    SF_LAUNCH_CHECK(ctx, "featurize_forest");
+    return SF_OK;
 }
 
 template <int KMAX, bool KEEP_ROWS>
-int launch_fused(sf_ctx* ctx, const ClassifyArgs& c, size_t lds, int slot)
+int launch_shape(sf_ctx* ctx, const ClassifyArgs& c, TileShape shape, size_t lds, int slot)
 {
-    SF_ALLOW_LDS(ctx, slot, (featurize_forest<KMAX, KEEP_ROWS>));
-    const uint32_t grid = (c.fa.n_flows + 255u) / 256u;
-    featurize_forest<KMAX, KEEP_ROWS><<<grid, 256, lds, ctx->stream>>>(c);
-    SF_LAUNCH_CHECK(ctx, "featurize_forest");
-    return SF_OK;
+    switch (shape) {
+    case kTile128x8: return launch_fused<128, 8, 3, 1, KMAX, KEEP_ROWS>(ctx, c, lds, slot);
+    case kTile128x4: return launch_fused<128, 4, 5, 2, KMAX, KEEP_ROWS>(ctx, c, lds, slot + 1);
+    case kTile64x8: return launch_fused<64, 8, 3, 1, KMAX, KEEP_ROWS>(ctx, c, lds, slot + 2);
+    default: return launch_fused<16, 32, 5, 2, KMAX, KEEP_ROWS>(ctx, c, lds, slot + 3);
+    }
 }
 
 // steps 1-3 for both entry points; keep_rows: feature rows of the flows the gate hands on are wanted
@@ -161,16 +244,12 @@ int run_features_and_forest(sf_ctx* ctx, const char* who, const sf_packets* pk, 
     const uint32_t dmax = cfg->depth[cfg->n_windows - 1];
     int rc = sf::forest_setup(ctx, who, &wide, F, c.fa, &result_words);
     if (rc != SF_OK) return rc;
-    size_t lds = plan_lds(c.fa, result_words, 256, 80 * 1024 - 512, &c.fa.top_pairs);
-    // scratch of the first window's sorting network behind the tile: one column per element
-    uint32_t n0 = 8;
-    while (n0 < cfg->depth[0] && n0 < 16u) n0 *= 2;
-    const size_t lds_feat = (size_t)F * 1024 + (size_t)n0 * 1024;
-    const bool fused = dmax <= 16 && (lds > lds_feat ? lds : lds_feat) <= 80 * 1024;
+    // Which calls are fused (and so write only the rows of the flows that are handed on) is part of the interface:
+    // windows of up to 16 packets, and features and results of a flow in at most 80 words of shared memory.
+    const bool fused = cfg->n_windows <= kFusedWindows && dmax <= kFusedDepth && F + result_words <= 80u;
     if (!fused) {
-        // shapes the fused kernel does not cover (windows deeper than 16 packets, whose registers would leave one
-        // block per compute unit; forests that run several lanes per flow): the same results from the separate
-        // kernels, with every feature row written
+        // shapes the fused kernel does not cover: the same results from the separate kernels, with every feature
+        // row written
         if (!feat || feat_ld < F) return sf::fail(ctx, SF_EINVAL, "%s: this shape needs the feature matrix", who);
         rc = sf_featurize(ctx, pk, cfg, feat, feat_ld, nullptr);
         if (rc != SF_OK) return rc;
@@ -182,8 +261,8 @@ int run_features_and_forest(sf_ctx* ctx, const char* who, const sf_packets* pk, 
     c.iat = pk->pkt_iat;
     c.dir = pk->pkt_dir;
     c.n_windows = cfg->n_windows;
-    for (int w = 0; w < SF_MAX_WINDOWS; ++w) c.depth[w] = w < (int)cfg->n_windows ? cfg->depth[w] : 0;
-    c.wide_ok = (((uintptr_t)c.size | (uintptr_t)c.iat) & 15u) == 0 && ((uintptr_t)c.dir & 7u) == 0;
+    for (uint32_t w = 0; w < kFusedWindows; ++w) c.depth[w] = w < cfg->n_windows ? cfg->depth[w] : 0;
+    c.wide_ok = (((uintptr_t)c.size | (uintptr_t)c.iat | (uintptr_t)c.dir) & 7u) == 0;
     c.fa.n_flows = n;
     c.fa.n_rows = n;
     c.fa.pred = pred;
@@ -195,10 +274,11 @@ int run_features_and_forest(sf_ctx* ctx, const char* who, const sf_packets* pk, 
     c.fa.feat_out16 = ((uintptr_t)feat & 15u) == 0 && (feat_ld & 3u) == 0;
     c.fa.n_vmin = n_vmin;
     for (uint32_t k = 0; k < SF_MAX_CLASSES; ++k) c.fa.vmin[k] = host_vmin[k < n_vmin ? k : n_vmin - 1];
-    if (lds_feat > lds) lds = lds_feat;
-    const int base = sf::kLdsClassify + (keep_rows ? 2 : 0);
-    if (dmax <= 8) return keep_rows ? launch_fused<8, true>(ctx, c, lds, base) : launch_fused<8, false>(ctx, c, lds, base);
-    return keep_rows ? launch_fused<16, true>(ctx, c, lds, base + 1) : launch_fused<16, false>(ctx, c, lds, base + 1);
+    size_t lds = 0;
+    const TileShape shape = sf::forest_shape(c.fa, result_words, n, (uint32_t)ctx->n_cu, &lds);
+    const int slot = sf::kLdsClassify + (keep_rows ? 8 : 0) + (dmax > 8 ? 4 : 0);
+    if (dmax <= 8) return keep_rows ? launch_shape<8, true>(ctx, c, shape, lds, slot) : launch_shape<8, false>(ctx, c, shape, lds, slot);
+    return keep_rows ? launch_shape<16, true>(ctx, c, shape, lds, slot) : launch_shape<16, false>(ctx, c, shape, lds, slot);
 }
 
 } // namespace

@@ -159,10 +159,6 @@ int check_model(sf_ctx* ctx, const char* who, const TreeModel& m)
     return SF_OK;
 }
 
-// The shapes a block of the walk comes in (flows x lanes per flow), see choose_shape
-enum TileShape { kTile128x8, kTile128x4, kTile64x8, kTile16x32, kTile256x2g, kTile64x4g, kTile16x16g };
-constexpr uint32_t kTileFlows[] = {128, 128, 64, 16, 256, 64, 16};
-
 // The shape of a block and its shared memory, by batch size and model.  All figures are the walk's time in
 // microseconds for 64 features and 100 trees of depth 12 unless another model is named.
 //   few flows: 16 flows x 32 lanes, nothing staged, so that even a small batch gives every compute unit a block and
@@ -317,13 +313,18 @@ int run_forest(sf_ctx* ctx, const char* who, const float* feat, uint32_t feat_ld
 } // namespace
 
 namespace sf {
-// the hard-voting forest as kernel arguments (for the fused feature + forest entry point)
+// the hard-voting forest as kernel arguments, and the block shape of its walk (for the fused feature + forest entry point)
 int forest_setup(sf_ctx* ctx, const char* who, const sf_forest* f, uint32_t feat_ld, sfforest::FastArgs& a, uint32_t* result_words)
 {
     if (!f) return fail(ctx, SF_EINVAL, "%s: forest is NULL", who);
     const TreeModel m = {f->n_trees, f->depth, f->n_classes, f->n_features, f->node_feat, f->node_thr, f->leaf_label,
                          nullptr, nullptr, f->packed};
     return setup_trees(ctx, who, m, false, feat_ld, a, result_words);
+}
+
+sfforest::TileShape forest_shape(sfforest::FastArgs& a, uint32_t result_words, uint32_t n_rows, uint32_t n_cu, size_t* lds)
+{
+    return choose_shape(a, result_words, false, n_rows, n_cu, lds);
 }
 } // namespace sf
 

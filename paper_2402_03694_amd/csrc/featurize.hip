@@ -61,7 +61,7 @@ __device__ __forceinline__ void load_wide(const FeatArgs& a, uint32_t o, RawPack
 }
 
 template <int KMAX>
-__device__ __forceinline__ void decode_wide(const RawPackets<KMAX>& r, float (&s)[KMAX], float (&t)[KMAX], uint64_t& dmask)
+__device__ __forceinline__ void decode_wide(const RawPackets<KMAX>& r, float (&s)[KMAX], float (&t)[KMAX], uint32_t& dmask)
 {
     dmask = 0;
 #pragma unroll
@@ -77,7 +77,7 @@ __device__ __forceinline__ void decode_wide(const RawPackets<KMAX>& r, float (&s
         t[8 * c + 4] = t1.x; t[8 * c + 5] = t1.y; t[8 * c + 6] = t1.z; t[8 * c + 7] = t1.w;
         const uint32_t dw[2] = {r.dr[c].x, r.dr[c].y};
 #pragma unroll
-        for (int k = 0; k < 8; ++k) dmask |= (uint64_t)((dw[k >> 2] >> (8 * (k & 3))) & 1u) << (8 * c + k);
+        for (int k = 0; k < 8; ++k) dmask |= ((dw[k >> 2] >> (8 * (k & 3))) & 1u) << (8 * c + k);
     }
 }
 
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(kWave, (KMAX <= 16 ? 3 : (LONG ? 1 : 2))) void feat
     const int avail_w = (int)(n < dmax ? n : dmax);              // packets of the deepest window
     const int avail = avail_w < KMAX ? avail_w : KMAX;           // of which the lane holds in registers
     float s[KMAX], t[KMAX];
-    uint64_t dmask = 0;
+    uint32_t dmask = 0;
     if (avail == KMAX && (o & 7u) == 0 && a.wide_ok) {
         // whole window present and 16-byte aligned (array bases included): wide loads
         RawPackets<KMAX> raw;
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(kWave, (KMAX <= 16 ? 3 : (LONG ? 1 : 2))) void feat
             if (j < avail) {
                 s[j] = (float)a.size[o + j];
                 t[j] = a.iat[o + j];
-                dmask |= (uint64_t)(a.dir[o + j] & 1u) << j;
+                dmask |= (uint32_t)(a.dir[o + j] & 1u) << j;
             } else {
                 s[j] = 0.f;
                 t[j] = 0.f;

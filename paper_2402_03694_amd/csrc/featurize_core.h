@@ -79,7 +79,17 @@ __device__ __forceinline__ void bitonic_merge(uint32_t (&a)[N])
     }
 }
 
-__device__ __forceinline__ bool bit_of(uint64_t m, int j) { return (m >> j) & 1ull; }
+__device__ __forceinline__ bool bit_of(uint32_t m, int j) { return (m >> j) & 1u; }
+
+// All ones where bit j of m is set, else zero (one signed bit-field extract).  Group membership is applied with
+// such words: compare-and-select per packet and group keeps a pair of scalar registers alive for each, more than a
+// wave has (windows of 32 packets spilled 234 of them, 48 vector registers in the fused kernel).
+__device__ __forceinline__ uint32_t bit_word(uint32_t m, int j) { return (uint32_t)__builtin_amdgcn_sbfe((int)m, (uint32_t)j, 1u); }
+// Between two parts of the statistics: the words are made again from the masks (one instruction each) instead of
+// being kept in a register per packet and group.
+__device__ __forceinline__ void forget_words(uint32_t& a, uint32_t& b, uint32_t& c) { asm volatile("" : "+v"(a), "+v"(b), "+v"(c)); }
+// x where bit j of m is set, else +0.0
+__device__ __forceinline__ float masked(float x, uint32_t m, int j) { return __uint_as_float(__float_as_uint(x) & bit_word(m, j)); }
 
 // Order statistics of one quantity for the three groups (0: direction 0, 1: direction 1, 2: all packets).
 // v[i]: the value of packet i as a non-negative integer below 2^W that orders like the value.  valid: the
@@ -87,18 +97,17 @@ __device__ __forceinline__ bool bit_of(uint64_t m, int j) { return (m >> j) & 1u
 // empty group they are meaningless (the caller writes zeros).  lo/hi: the two middle elements (equal for an
 // odd count).
 template <int N, int W>
-__device__ __forceinline__ void order_stats3(const uint32_t (&v)[N], uint64_t valid, uint64_t m1, int m, int c0, int c1,
+__device__ __forceinline__ void order_stats3(const uint32_t (&v)[N], uint32_t valid, uint32_t m1, int m, int c0, int c1,
                                              uint32_t* col, uint32_t stride, uint32_t (&mn)[3], uint32_t (&mx)[3],
                                              uint32_t (&lo)[3], uint32_t (&hi)[3])
 {
     constexpr uint32_t kMask = (1u << W) - 1u;            // W = 31: 0x7FFFFFFF
     constexpr uint32_t kPad = (1u << W) | kMask;          // the largest key; decodes to the value 0
-    uint32_t key[N];
+    uint32_t key[N], outside = ~valid;
+    forget_words(valid, outside, m1);
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const uint32_t k = bit_of(m1, i) ? ((1u << W) | (v[i] ^ kMask)) : v[i];
-        key[i] = bit_of(valid, i) ? k : kPad;
-    }
+    for (int i = 0; i < N; ++i) // direction 1: top bit set and value complemented; outside the window: kPad
+        key[i] = (v[i] ^ (bit_word(m1, i) & kPad)) | (bit_word(outside, i) & kPad);
     sort_network<N>(key);
 #pragma unroll
     for (int i = 0; i < N; ++i) col[i * stride] = key[i];
@@ -122,7 +131,7 @@ __device__ __forceinline__ void order_stats3(const uint32_t (&v)[N], uint64_t va
     hi[1] &= kMask;
     // all packets: decode (padding becomes 0, the smallest value), merge; the padding then stands first
 #pragma unroll
-    for (int i = 0; i < N; ++i) key[i] = (key[i] & kMask) ^ ((key[i] >> W) ? kMask : 0u);
+    for (int i = 0; i < N; ++i) key[i] = (key[i] ^ bit_word(key[i], W)) & kMask;
     bitonic_merge<N>(key);
 #pragma unroll
     for (int i = 0; i < N; ++i) col[i * stride] = key[i];
@@ -138,7 +147,7 @@ __device__ __forceinline__ void order_stats3(const uint32_t (&v)[N], uint64_t va
 // General path for times with the sign bit set somewhere in the wave: one full network per group on
 // order-preserving keys, padded with the largest key.
 template <int N, int KMAX>
-__device__ __forceinline__ void order_stats_signed(const float (&x)[KMAX], uint64_t gm, int cg, uint32_t* col, uint32_t stride,
+__device__ __forceinline__ void order_stats_signed(const float (&x)[KMAX], uint32_t gm, int cg, uint32_t* col, uint32_t stride,
                                                    float& mn, float& mx, float& lo, float& hi)
 {
     uint32_t key[N];
@@ -154,86 +163,71 @@ __device__ __forceinline__ void order_stats_signed(const float (&x)[KMAX], uint6
     hi = from_key(col[(cg >> 1) * stride]);
 }
 
-// The 32 statistics of one prefix window of m <= N packets -> dst[k * ds], k = 10*g + 5*q + stat, then
-// total bytes (k = 30) and packet count (k = 31).  Each result is stored as soon as it is known (the
-// sorting networks need the registers).  signed_times: wave-uniform, some lane of the wave holds a time
-// with its sign bit set.  dst and col must not overlap.
+// Mean and standard deviation of one quantity for the three groups -> dst[k * ds], k = 10 * group (+ 1 for the
+// deviation); returns the sum over all packets.  Two ordered passes: the sums, then the squared deviations.
 template <int N, int KMAX>
-__device__ __forceinline__ void window_stats(const float (&s)[KMAX], const float (&t)[KMAX], uint64_t dmask, int m,
-                                             bool signed_times, uint32_t* col, uint32_t stride, float* dst, uint32_t ds)
+__device__ __forceinline__ float window_sums(const float (&x)[KMAX], uint32_t valid, uint32_t m0, uint32_t m1, int m, int c0, int c1,
+                                             float* dst, uint32_t ds)
 {
-    static_assert(N <= KMAX, "window network larger than the register file of the flow");
-    const uint64_t valid = m >= 64 ? ~0ull : ((1ull << m) - 1ull);
-    const uint64_t m1 = dmask & valid, m0 = ~dmask & valid;
-    const int c1 = __popcll(m1), c0 = m - c1;
     const bool e0 = c0 == 0, e1 = c1 == 0, ea = m == 0;
-    {
-        // pass 1: ordered sums
-        float sS0 = 0.f, sS1 = 0.f, sSa = 0.f, sT0 = 0.f, sT1 = 0.f, sTa = 0.f;
+    forget_words(valid, m0, m1);
+    float s0 = 0.f, s1 = 0.f, sa = 0.f;
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-            const bool v = bit_of(valid, j), d0 = bit_of(m0, j), d1 = bit_of(m1, j);
-            const float a = s[j], b = t[j];
-            sSa = sSa + (v ? a : 0.f);
-            sS0 = sS0 + (d0 ? a : 0.f);
-            sS1 = sS1 + (d1 ? a : 0.f);
-            sTa = sTa + (v ? b : 0.f);
-            sT0 = sT0 + (d0 ? b : 0.f);
-            sT1 = sT1 + (d1 ? b : 0.f);
-        }
-        const float n0 = (float)(c0 > 0 ? c0 : 1), n1 = (float)(c1 > 0 ? c1 : 1), na = (float)(m > 0 ? m : 1);
-        const float mS0 = sS0 / n0, mS1 = sS1 / n1, mSa = sSa / na;
-        const float mT0 = sT0 / n0, mT1 = sT1 / n1, mTa = sTa / na;
-        // pass 2: ordered sums of squared deviations
-        float qS0 = 0.f, qS1 = 0.f, qSa = 0.f, qT0 = 0.f, qT1 = 0.f, qTa = 0.f;
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            const bool v = bit_of(valid, j), d0 = bit_of(m0, j), d1 = bit_of(m1, j);
-            const float a = s[j], b = t[j];
-            const float xa = a - mSa, xb = b - mTa;
-            const float xa2 = xa * xa, xb2 = xb * xb;
-            qSa = qSa + (v ? xa2 : 0.f);
-            qTa = qTa + (v ? xb2 : 0.f);
-            const float ga = a - (d1 ? mS1 : mS0), gb = b - (d1 ? mT1 : mT0);
-            const float ga2 = ga * ga, gb2 = gb * gb;
-            qS0 = qS0 + (d0 ? ga2 : 0.f);
-            qS1 = qS1 + (d1 ? ga2 : 0.f);
-            qT0 = qT0 + (d0 ? gb2 : 0.f);
-            qT1 = qT1 + (d1 ? gb2 : 0.f);
-        }
-        const float vS0 = qS0 / n0, vS1 = qS1 / n1, vSa = qSa / na;
-        const float vT0 = qT0 / n0, vT1 = qT1 / n1, vTa = qTa / na;
-        dst[0 * ds] = e0 ? 0.f : mS0;
-        dst[1 * ds] = e0 ? 0.f : sqrtf(vS0);
-        dst[5 * ds] = e0 ? 0.f : mT0;
-        dst[6 * ds] = e0 ? 0.f : sqrtf(vT0);
-        dst[10 * ds] = e1 ? 0.f : mS1;
-        dst[11 * ds] = e1 ? 0.f : sqrtf(vS1);
-        dst[15 * ds] = e1 ? 0.f : mT1;
-        dst[16 * ds] = e1 ? 0.f : sqrtf(vT1);
-        dst[20 * ds] = ea ? 0.f : mSa;
-        dst[21 * ds] = ea ? 0.f : sqrtf(vSa);
-        dst[25 * ds] = ea ? 0.f : mTa;
-        dst[26 * ds] = ea ? 0.f : sqrtf(vTa);
-        dst[30 * ds] = sSa; // total bytes: every partial sum is an integer below 2^24, so this is exact
-        dst[31 * ds] = (float)m;
+    for (int j = 0; j < N; ++j) {
+        sa = sa + masked(x[j], valid, j);
+        s0 = s0 + masked(x[j], m0, j);
+        s1 = s1 + masked(x[j], m1, j);
     }
-    // order statistics: sizes always as 16-bit integers (exact in binary32)
-    {
-        uint32_t v[N], a[3], b[3], c[3], d[3];
+    const float n0 = (float)(c0 > 0 ? c0 : 1), n1 = (float)(c1 > 0 ? c1 : 1), na = (float)(m > 0 ? m : 1);
+    const float u0 = s0 / n0, u1 = s1 / n1, ua = sa / na;
+    forget_words(valid, m0, m1);
+    float q0 = 0.f, q1 = 0.f, qa = 0.f;
 #pragma unroll
-        for (int i = 0; i < N; ++i) v[i] = (uint32_t)s[i];
-        order_stats3<N, 16>(v, valid, m1, m, c0, c1, col, stride, a, b, c, d);
-#pragma unroll
-        for (int g = 0; g < 3; ++g) {
-            const int cg = g == 0 ? c0 : (g == 1 ? c1 : m);
-            const float lo = (float)c[g], hi = (float)d[g];
-            const float two = lo + hi;
-            dst[(10 * g + 2) * ds] = cg == 0 ? 0.f : (float)a[g];
-            dst[(10 * g + 3) * ds] = cg == 0 ? 0.f : (float)b[g];
-            dst[(10 * g + 4) * ds] = cg == 0 ? 0.f : ((cg & 1) ? hi : two * 0.5f);
-        }
+    for (int j = 0; j < N; ++j) {
+        const uint32_t w1 = bit_word(m1, j);
+        const float ug = __uint_as_float((w1 & __float_as_uint(u1)) | (~w1 & __float_as_uint(u0)));
+        const float da = x[j] - ua, dg = x[j] - ug;
+        const float da2 = da * da, dg2 = dg * dg;
+        qa = qa + masked(da2, valid, j);
+        q0 = q0 + masked(dg2, m0, j);
+        q1 = q1 + masked(dg2, m1, j);
     }
+    const float v0 = q0 / n0, v1 = q1 / n1, va = qa / na;
+    dst[0 * ds] = e0 ? 0.f : u0;
+    dst[1 * ds] = e0 ? 0.f : sqrtf(v0);
+    dst[10 * ds] = e1 ? 0.f : u1;
+    dst[11 * ds] = e1 ? 0.f : sqrtf(v1);
+    dst[20 * ds] = ea ? 0.f : ua;
+    dst[21 * ds] = ea ? 0.f : sqrtf(va);
+    return sa;
+}
+
+// Smallest, largest and median packet size of the three groups -> dst[k * ds], k = 10 * group + 0, 1, 2: sizes as
+// 16-bit integers (exact in binary32).
+template <int N, int KMAX>
+__device__ __forceinline__ void window_order_sizes(const float (&s)[KMAX], uint32_t valid, uint32_t m1, int m, int c0, int c1,
+                                                   uint32_t* col, uint32_t stride, float* dst, uint32_t ds)
+{
+    uint32_t v[N], a[3], b[3], c[3], d[3];
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = (uint32_t)s[i];
+    order_stats3<N, 16>(v, valid, m1, m, c0, c1, col, stride, a, b, c, d);
+#pragma unroll
+    for (int g = 0; g < 3; ++g) {
+        const int cg = g == 0 ? c0 : (g == 1 ? c1 : m);
+        const float lo = (float)c[g], hi = (float)d[g];
+        const float two = lo + hi;
+        dst[(10 * g + 0) * ds] = cg == 0 ? 0.f : (float)a[g];
+        dst[(10 * g + 1) * ds] = cg == 0 ? 0.f : (float)b[g];
+        dst[(10 * g + 2) * ds] = cg == 0 ? 0.f : ((cg & 1) ? hi : two * 0.5f);
+    }
+}
+
+// The same for the times; signed_times: wave-uniform, some lane of the wave holds a time with its sign bit set.
+template <int N, int KMAX>
+__device__ __forceinline__ void window_order_times(const float (&t)[KMAX], uint32_t valid, uint32_t m0, uint32_t m1, int m, int c0,
+                                                   int c1, bool signed_times, uint32_t* col, uint32_t stride, float* dst, uint32_t ds)
+{
     if (!signed_times) {
         uint32_t v[N], a[3], b[3], c[3], d[3];
 #pragma unroll
@@ -244,23 +238,44 @@ __device__ __forceinline__ void window_stats(const float (&s)[KMAX], const float
             const int cg = g == 0 ? c0 : (g == 1 ? c1 : m);
             const float lo = __uint_as_float(c[g]), hi = __uint_as_float(d[g]);
             const float two = lo + hi;
-            dst[(10 * g + 7) * ds] = cg == 0 ? 0.f : __uint_as_float(a[g]);
-            dst[(10 * g + 8) * ds] = cg == 0 ? 0.f : __uint_as_float(b[g]);
-            dst[(10 * g + 9) * ds] = cg == 0 ? 0.f : ((cg & 1) ? hi : two * 0.5f);
+            dst[(10 * g + 0) * ds] = cg == 0 ? 0.f : __uint_as_float(a[g]);
+            dst[(10 * g + 1) * ds] = cg == 0 ? 0.f : __uint_as_float(b[g]);
+            dst[(10 * g + 2) * ds] = cg == 0 ? 0.f : ((cg & 1) ? hi : two * 0.5f);
         }
     } else {
 #pragma unroll 1
         for (int g = 0; g < 3; ++g) {
-            const uint64_t gm = g == 0 ? m0 : (g == 1 ? m1 : valid);
+            const uint32_t gm = g == 0 ? m0 : (g == 1 ? m1 : valid);
             const int cg = g == 0 ? c0 : (g == 1 ? c1 : m);
             float mn, mx, lo, hi;
             order_stats_signed<N, KMAX>(t, gm, cg, col, stride, mn, mx, lo, hi);
             const float two = lo + hi;
-            dst[(10 * g + 7) * ds] = cg == 0 ? 0.f : mn;
-            dst[(10 * g + 8) * ds] = cg == 0 ? 0.f : mx;
-            dst[(10 * g + 9) * ds] = cg == 0 ? 0.f : ((cg & 1) ? hi : two * 0.5f);
+            dst[(10 * g + 0) * ds] = cg == 0 ? 0.f : mn;
+            dst[(10 * g + 1) * ds] = cg == 0 ? 0.f : mx;
+            dst[(10 * g + 2) * ds] = cg == 0 ? 0.f : ((cg & 1) ? hi : two * 0.5f);
         }
     }
+}
+
+// The 32 statistics of one prefix window of m <= N packets -> dst[k * ds], k = 10*g + 5*q + stat, then
+// total bytes (k = 30) and packet count (k = 31).  Each result is stored as soon as it is known (the
+// sorting networks need the registers).  signed_times: wave-uniform, some lane of the wave holds a time
+// with its sign bit set.  dst and col must not overlap.
+template <int N, int KMAX>
+__device__ __forceinline__ void window_stats(const float (&s)[KMAX], const float (&t)[KMAX], uint32_t dmask, int m,
+                                             bool signed_times, uint32_t* col, uint32_t stride, float* dst, uint32_t ds)
+{
+    static_assert(N <= KMAX, "window network larger than the register file of the flow");
+    static_assert(N <= 32, "packets of a window are the bits of a word");
+    const uint32_t valid = m >= 32 ? ~0u : ((1u << m) - 1u);
+    const uint32_t m1 = dmask & valid, m0 = ~dmask & valid;
+    const int c1 = __popc(m1), c0 = m - c1;
+    const float bytes = window_sums<N, KMAX>(s, valid, m0, m1, m, c0, c1, dst, ds);
+    window_sums<N, KMAX>(t, valid, m0, m1, m, c0, c1, dst + 5 * ds, ds);
+    dst[30 * ds] = bytes; // every partial sum is an integer below 2^24, so this is exact
+    dst[31 * ds] = (float)m;
+    window_order_sizes<N, KMAX>(s, valid, m1, m, c0, c1, col, stride, dst + 2 * ds, ds);
+    window_order_times<N, KMAX>(t, valid, m0, m1, m, c0, c1, signed_times, col, stride, dst + 7 * ds, ds);
 }
 
 } // namespace sffeat

@@ -89,6 +89,10 @@ inline size_t plan_lds(const FastArgs& a, uint32_t result_words, uint32_t fpb, s
     return fixed + (size_t)a.n_trees * recs_upto(t) * 16;
 }
 
+// The shapes a block of the walk comes in (flows x lanes per flow), see choose_shape
+enum TileShape { kTile128x8, kTile128x4, kTile64x8, kTile16x32, kTile256x2g, kTile64x4g, kTile16x16g };
+constexpr uint32_t kTileFlows[] = {128, 128, 64, 16, 256, 64, 16};
+
 // Shared memory of a block behind the feature tile xT ([n_features][FPB] floats, FPB flows per block):
 // vote counters (or margins), then the staged top records.
 // kIlp trees are walked at once per lane, kIlpTail in a last round when at most that many are left.
@@ -278,8 +282,8 @@ __device__ __forceinline__ void forest_walk(const FastArgs& a, float* xT, uint32
 #undef SF_FEAT_0
 #undef SF_FEAT_ROT
     if (W > 1) __syncthreads(); // all lanes of a flow have added their votes before its first lane reads them
-    if (!live || grp != 0) return;
     if (GBDT) {
+        if (!live || grp != 0) return;
         const float* mcol = reinterpret_cast<const float*>(vcol);
         uint32_t bc = 0;
         float bm = mcol[0];
@@ -310,36 +314,45 @@ __device__ __forceinline__ void forest_walk(const FastArgs& a, float* xT, uint32
         if (a.labels) a.labels[row] = (uint16_t)bc;
         return;
     }
-    uint32_t best = 0, bestv = 0;
-    const uint32_t vmask = (1u << a.vote_bits) - 1u;
-    for (uint32_t w = 0; w < vote_words; ++w) {
-        const uint32_t word = vT[w * FPB + slot];
-        for (uint32_t k = 0; k < (1u << per_shift); ++k) {
-            const uint32_t c = (w << per_shift) + k;
-            if (c < C) {
-                const uint32_t v = (word >> (k * a.vote_bits)) & vmask;
-                if (a.votes) a.votes[(size_t)i * C + c] = (uint16_t)v;
-                if (c == 0 || v > bestv) {
-                    bestv = v;
-                    best = c;
+    bool keep = false;
+    if (live && grp == 0) {
+        uint32_t best = 0, bestv = 0;
+        const uint32_t vmask = (1u << a.vote_bits) - 1u;
+        for (uint32_t w = 0; w < vote_words; ++w) {
+            const uint32_t word = vT[w * FPB + slot];
+            for (uint32_t k = 0; k < (1u << per_shift); ++k) {
+                const uint32_t c = (w << per_shift) + k;
+                if (c < C) {
+                    const uint32_t v = (word >> (k * a.vote_bits)) & vmask;
+                    if (a.votes) a.votes[(size_t)i * C + c] = (uint16_t)v;
+                    if (c == 0 || v > bestv) {
+                        bestv = v;
+                        best = c;
+                    }
                 }
             }
         }
+        a.pred[i] = (uint16_t)best;
+        a.top[i] = (uint16_t)bestv;
+        if (a.labels) a.labels[row] = (uint16_t)best;
+        if (KEEP_ROWS) keep = bestv < a.vmin[a.n_vmin > 1u ? (best < a.n_vmin ? best : a.n_vmin - 1u) : 0u];
     }
-    a.pred[i] = (uint16_t)best;
-    a.top[i] = (uint16_t)bestv;
-    if (a.labels) a.labels[row] = (uint16_t)best;
     if (KEEP_ROWS) {
-        // the features never left the chip: the row is written out only for a flow the gate hands on
-        const uint32_t th = a.vmin[a.n_vmin > 1u ? (best < a.n_vmin ? best : a.n_vmin - 1u) : 0u];
-        if (bestv < th) {
+        // the features never left the chip: a row is written out only for a flow the gate hands on, each of the
+        // flow's W lanes its share
+        if (W > 1) {
+            if (grp == 0) vT[slot] = keep ? 1u : 0u; // (the flow's first vote word: its only reader is done with it)
+            __syncthreads();
+            keep = vT[slot] != 0u;
+        }
+        if (keep) {
             float* dst = a.feat_out + (size_t)i * a.feat_out_ld;
             if (a.feat_out16) {
-                for (uint32_t q = 0; q < F; q += 4u)
+                for (uint32_t q = 4u * grp; q < F; q += 4u * W)
                     *reinterpret_cast<float4*>(dst + q) = make_float4(xT[(q + 0u) * FPB + slot], xT[(q + 1u) * FPB + slot],
                                                                     xT[(q + 2u) * FPB + slot], xT[(q + 3u) * FPB + slot]);
             } else {
-                for (uint32_t q = 0; q < F; ++q) dst[q] = xT[q * FPB + slot];
+                for (uint32_t q = grp; q < F; q += W) dst[q] = xT[q * FPB + slot];
             }
         }
     }
