@@ -68,21 +68,33 @@ static __device__ __forceinline__ void raw_flow_range(const LayerArgs& a, uint32
     n = e0 > b0 ? e0 - b0 : 0;
 }
 
+// raw_bits a multiple of 8: the 8 features [k, k+8), k a multiple of 8, are the 8 bits of one header byte.
+// The word that holds the byte (zero past K and past the flow) ...
+static __device__ __forceinline__ uint32_t raw_word_at(const LayerArgs& a, uint32_t b0, uint32_t n, uint32_t k)
+{
+    const uint32_t j = k / a.raw_bits, b = k - j * a.raw_bits;
+    return k < a.K && j < n ? a.hdr[(size_t)(b0 + j) * a.hdr_words + (b >> 5)] : 0u;
+}
+
+// ... and its byte's bits, first bit first, as bfloat16 0.0 / 1.0
+static __device__ __forceinline__ uint4 raw_byte_bits(const LayerArgs& a, uint32_t word, uint32_t k)
+{
+    const uint32_t byte = word >> (k % a.raw_bits & 24u); // bits 0..7 (b = k mod raw_bits is a multiple of 8)
+    uint32_t v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        v[q] = ((uint32_t)__builtin_amdgcn_sbfe((int)byte, 7 - 2 * q, 1) & 0x3F80u) |
+               ((uint32_t)__builtin_amdgcn_sbfe((int)byte, 6 - 2 * q, 1) & 0x3F800000u);
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
 // 8 consecutive raw-bit features [k, k+8) of a flow whose packets start at b0 (n of them) as bfloat16 0.0 / 1.0:
 // feature k = raw_bits * packet + bit; bit b is bit 7-(b%8) of header byte b/8; zero past K and past the flow
 static __device__ __forceinline__ uint4 raw_chunk_at(const LayerArgs& a, uint32_t b0, uint32_t n, uint32_t k)
 {
     if (k >= a.K) return make_uint4(0, 0, 0, 0);
+    if ((a.raw_bits & 7u) == 0) return raw_byte_bits(a, raw_word_at(a, b0, n, k), k);
     uint16_t v[8];
-    if ((a.raw_bits & 7u) == 0 && k + 8u <= a.K) {
-        // the 8 features are the 8 bits of one header byte (k is a multiple of 8): one word load
-        const uint32_t j = k / a.raw_bits, b = k - j * a.raw_bits, byte_i = b >> 3;
-        uint32_t byte = 0;
-        if (j < n) byte = (a.hdr[(size_t)(b0 + j) * a.hdr_words + (byte_i >> 2)] >> (8u * (byte_i & 3u))) & 0xFFu;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = ((byte >> (7 - q)) & 1u) ? (uint16_t)0x3F80 : (uint16_t)0;
-        return make_uint4(pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7]));
-    }
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const uint32_t kk = k + q;

@@ -95,22 +95,33 @@ __global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const
         for (int u = 0; u < 2; ++u)
             if (row0 + cr[u] < total) raw_flow_range(a, s_flow[cr[u]], raw_b0[u], raw_n[u]); // (no packets: the row reads as zeros)
     }
-    // slab sl of the A operand as this thread's two chunks
+    // Slab sl of the A operand as this thread's two chunks.  Header bits whose bytes are whole (byte_bits) are only
+    // requested here, one word of the header per chunk, and turned into bfloat16 by unpack() when the slab is
+    // stored: made here, the wave would wait for the word, and for every weight request before it, ahead of the
+    // slab's MFMAs.
+    const bool byte_bits = AMODE == A_RAW && (a.raw_bits & 7u) == 0;
     auto fetch = [&](uint32_t sl, uint4 (&r)[2]) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            if (AMODE == A_RAW)
+            if (AMODE == A_RAW && byte_bits)
+                r[u].x = raw_word_at(a, raw_b0[u], raw_n[u], sl * WSLAB + ck);
+            else if (AMODE == A_RAW)
                 r[u] = raw_chunk_at(a, raw_b0[u], raw_n[u], sl * WSLAB + ck);
             else
                 r[u] = load_a_chunk<AMODE>(a, row0 + cr[u] < total, blockIdx.x * WBM + cr[u], AMODE != A_BF16 ? s_flow[cr[u]] : 0u,
                                            sl * WSLAB + ck);
         }
     };
+    auto store = [&](uint32_t sl, const uint4 (&r)[2]) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            *reinterpret_cast<uint4*>(slab + (sl & 1u) * (WBM * WLDS) + cr[u] * WLDS + ck) =
+                AMODE == A_RAW && byte_bits ? raw_byte_bits(a, r[u].x, sl * WSLAB + ck) : r[u];
+    };
     uint4 ra[2];
     for (uint32_t sl = 0; sl < (resident ? n_slabs : 1u); ++sl) {
         fetch(sl, ra);
-#pragma unroll
-        for (int u = 0; u < 2; ++u) *reinterpret_cast<uint4*>(slab + (sl & 1u) * (WBM * WLDS) + cr[u] * WLDS + ck) = ra[u];
+        store(sl, ra);
     }
 
     // weight operands of a column block: a 32-column block past the end repeats the last one, its results are not
@@ -189,11 +200,7 @@ __global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const
                 }
             }
             if (!resident) {
-                if (more) {
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-                        *reinterpret_cast<uint4*>(slab + ((sl + 1) & 1u) * (WBM * WLDS) + cr[u] * WLDS + ck) = ra[u];
-                }
+                if (more) store(sl + 1, ra);
                 __syncthreads(); // the next slab is in place; nobody reads this one any more
             }
         }
