@@ -24,6 +24,7 @@ struct LayerArgs {
     const uint32_t* esc_count;
     uint32_t esc_cap;
     uint32_t row_begin; // first escalated row of this chunk
+    uint32_t rows_cap;  // rows the chunk's activations hold (a multiple of BM)
     uint32_t n_rows;    // rows of the input (feature matrix or flows of the packet arrays)
     uint32_t n_labels;  // entries of labels; a label index outside is not written
     // A operand
