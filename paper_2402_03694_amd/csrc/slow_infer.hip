@@ -177,6 +177,181 @@ struct F32Args {
     uint32_t n_in;
 };
 
+// input value k of the row that entry `flow` of the list names
+__device__ __forceinline__ float f32_input_value(const F32Args& a, uint32_t flow, uint32_t k)
+{
+    flow = flow < a.n_rows ? flow : a.n_rows - 1u; // a bad list entry must not leave the input
+    if (a.feat) {
+        float v = a.feat[(size_t)flow * a.feat_ld + k];
+        if (a.mu) {
+            const float d = v - a.mu[k];
+            v = d * a.inv_sigma[k];
+            v = v < -a.clamp ? -a.clamp : v;
+            v = v > a.clamp ? a.clamp : v;
+        }
+        return v;
+    }
+    uint32_t b0 = a.off[flow], e0 = a.off[flow + 1];
+    b0 = b0 < a.n_pkts ? b0 : a.n_pkts;
+    e0 = e0 < a.n_pkts ? e0 : a.n_pkts;
+    const uint32_t np = e0 > b0 ? e0 - b0 : 0;
+    const uint32_t j = k / a.raw_bits, b = k - j * a.raw_bits;
+    if (j >= np) return 0.f;
+    const uint32_t byte_i = b >> 3;
+    const uint32_t word = a.hdr[(size_t)(b0 + j) * a.hdr_words + (byte_i >> 2)];
+    return (float)(((word >> (8u * (byte_i & 3u))) >> (7u - (b & 7u))) & 1u);
+}
+
+// The whole model on eight rows per block: the activations stay in shared memory, the weights pass through it in pieces
+// of 128 outputs x 32 inputs, the next piece requested while the current one is multiplied.  A wave owns two rows, a
+// lane two outputs of them; the sums run in order of the inputs, one multiply and one add per term, each rounded, as
+// in f32_layer (the results are the same bits).  A small batch is a chain of latencies: with one launch per layer on
+// 64 x 64 tiles, 4,096 rows gave work to half of the compute units, one wave per SIMD, and paid six launches.
+constexpr uint32_t kF32Rows = 8, kF32Cols = 128, kF32K = 32, kF32Ld = kF32K + 4; // (row stride: 16-byte reads of 8 consecutive rows on distinct banks)
+constexpr size_t kF32FusedLds = 64 * 1024;
+constexpr uint32_t kF32FusedRows = 1u << 15;
+
+__host__ __device__ inline uint32_t up4(uint32_t x) { return (x + 3u) / 4u * 4u; }
+// row strides of the two activation buffers: input and second hidden layer, first hidden layer and logits
+__host__ __device__ inline uint32_t f32_ld_a(uint32_t n_in, uint32_t h2) { return up4(n_in > h2 ? n_in : h2); }
+__host__ __device__ inline uint32_t f32_ld_b(uint32_t h1, uint32_t c) { return up4(h1 > c ? h1 : c); }
+__host__ __device__ inline size_t f32_fused_lds(uint32_t n_in, uint32_t h1, uint32_t h2, uint32_t c)
+{
+    return ((size_t)kF32Rows * ((size_t)f32_ld_a(n_in, h2) + f32_ld_b(h1, c)) + kF32Cols * kF32Ld) * 4;
+}
+
+struct F32Model {
+    const float *w1, *b1, *w2, *b2, *w3, *b3;
+    uint32_t h1, h2, c;
+    const uint32_t* label_idx;
+    float* logits;
+    uint16_t* labels;
+    uint32_t n_labels;
+};
+
+// this thread's four 16-byte chunks of the weight piece at (c0, k0): zeros outside
+__device__ __forceinline__ void f32_fetch(const float* __restrict__ w, uint32_t K, uint32_t N, bool wide, uint32_t c0, uint32_t k0, uint32_t tid,
+                                          float4 (&r)[4])
+{
+#pragma unroll
+    for (uint32_t q = 0; q < 4u; ++q) {
+        const uint32_t e = tid + 256u * q, col = c0 + e / (kF32K / 4u), k = k0 + e % (kF32K / 4u) * 4u;
+        r[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (col < N && k < K) {
+            const float* p = w + (size_t)col * K + k;
+            if (wide) { // K a multiple of 4 and w on a 16-byte boundary
+                r[q] = *reinterpret_cast<const float4*>(p);
+            } else {
+                r[q].x = p[0];
+                if (k + 1u < K) r[q].y = p[1];
+                if (k + 2u < K) r[q].z = p[2];
+                if (k + 3u < K) r[q].w = p[3];
+            }
+        }
+    }
+}
+
+// out[r][o] = act(sum_k in[r][k] * w[o][k] + b[o]) for the block's rows; the caller has synchronised the block
+__device__ __forceinline__ void f32_rows_layer(const float* in, uint32_t ld_in, uint32_t K, const float* __restrict__ w, const float* __restrict__ bias,
+                                               uint32_t N, float* out, uint32_t ld_out, bool relu, float* Ws)
+{
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, row = (tid >> 6) * 2u;
+    const bool wide = (K & 3u) == 0 && (reinterpret_cast<uintptr_t>(w) & 15u) == 0;
+    const float *x0 = in + row * ld_in, *x1 = x0 + ld_in;
+    const float *p0 = Ws + lane * kF32Ld, *p1 = p0 + 64u * kF32Ld;
+    for (uint32_t c0 = 0; c0 < N; c0 += kF32Cols) {
+        const bool second = c0 + 64u < N; // (few outputs, the last layer: the lanes' second one does not exist)
+        float s00 = 0.f, s01 = 0.f, s10 = 0.f, s11 = 0.f;
+        float4 r[4];
+        f32_fetch(w, K, N, wide, c0, 0, tid, r);
+        for (uint32_t k0 = 0; k0 < K; k0 += kF32K) {
+            __syncthreads(); // the piece before has been read
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) {
+                const uint32_t e = tid + 256u * q;
+                *reinterpret_cast<float4*>(Ws + e / (kF32K / 4u) * kF32Ld + e % (kF32K / 4u) * 4u) = r[q];
+            }
+            __syncthreads();
+            if (k0 + kF32K < K) f32_fetch(w, K, N, wide, c0, k0 + kF32K, tid, r);
+            auto step = [&](float a0, float a1, float w0, float w1) {
+                s00 += a0 * w0;
+                s10 += a1 * w0;
+                s01 += a0 * w1;
+                s11 += a1 * w1;
+            };
+            auto four = [&](uint32_t k) {
+                const float4 a0 = *reinterpret_cast<const float4*>(x0 + k0 + k), a1 = *reinterpret_cast<const float4*>(x1 + k0 + k);
+                const float4 w0 = *reinterpret_cast<const float4*>(p0 + k), w1 = *reinterpret_cast<const float4*>(p1 + k);
+                step(a0.x, a1.x, w0.x, w1.x);
+                step(a0.y, a1.y, w0.y, w1.y);
+                step(a0.z, a1.z, w0.z, w1.z);
+                step(a0.w, a1.w, w0.w, w1.w);
+            };
+            if (!second) {
+                const uint32_t kn = K - k0 < kF32K ? K - k0 : kF32K;
+#pragma unroll 8
+                for (uint32_t k = 0; k < kn; ++k) {
+                    s00 += x0[k0 + k] * p0[k];
+                    s10 += x1[k0 + k] * p0[k];
+                }
+            } else if (k0 + kF32K <= K) {
+#pragma unroll
+                for (uint32_t k = 0; k < kF32K; k += 4u) four(k);
+            } else {
+                for (uint32_t k = 0; k < K - k0; ++k) step(x0[k0 + k], x1[k0 + k], p0[k], p1[k]);
+            }
+        }
+        auto put = [&](uint32_t o, float y0, float y1) {
+            if (o >= N) return;
+            y0 = y0 + bias[o];
+            y1 = y1 + bias[o];
+            out[row * ld_out + o] = (relu && y0 < 0.f) ? 0.f : y0;
+            out[(row + 1u) * ld_out + o] = (relu && y1 < 0.f) ? 0.f : y1;
+        };
+        put(c0 + lane, s00, s10);
+        put(c0 + 64u + lane, s01, s11);
+    }
+}
+
+__global__ __launch_bounds__(256) void f32_mlp(F32Args a, F32Model m)
+{
+    extern __shared__ __attribute__((aligned(16))) float sm[];
+    uint32_t total = *a.esc_count;
+    total = total < a.esc_cap ? total : a.esc_cap;
+    const uint32_t tid = threadIdx.x;
+    const uint32_t lda = f32_ld_a(a.n_in, m.h2), ldb = f32_ld_b(m.h1, m.c);
+    float *A = sm, *B = A + kF32Rows * lda, *Ws = B + kF32Rows * ldb;
+    for (uint32_t row0 = blockIdx.x * kF32Rows; row0 < total; row0 += gridDim.x * kF32Rows) {
+        for (uint32_t e = tid; e < kF32Rows * a.n_in; e += 256u) {
+            const uint32_t r = e / a.n_in, k = e - r * a.n_in;
+            A[r * lda + k] = row0 + r < total ? f32_input_value(a, a.esc_idx[row0 + r], k) : 0.f;
+        }
+        f32_rows_layer(A, lda, a.n_in, m.w1, m.b1, m.h1, B, ldb, true, Ws); // (its first barrier follows the writes above)
+        __syncthreads();
+        f32_rows_layer(B, ldb, m.h1, m.w2, m.b2, m.h2, A, lda, true, Ws);
+        __syncthreads();
+        f32_rows_layer(A, lda, m.h2, m.w3, m.b3, m.c, B, ldb, false, Ws);
+        __syncthreads();
+        if (m.logits)
+            for (uint32_t e = tid; e < kF32Rows * m.c; e += 256u) {
+                const uint32_t r = e / m.c;
+                if (row0 + r < total) m.logits[(size_t)row0 * m.c + e] = B[r * ldb + (e - r * m.c)];
+            }
+        if (tid < kF32Rows && row0 + tid < total) {
+            const float* p = B + tid * ldb;
+            uint32_t best = 0;
+            float bv = p[0];
+            for (uint32_t c = 1; c < m.c; ++c)
+                if (p[c] > bv) {
+                    bv = p[c];
+                    best = c;
+                }
+            const uint32_t dst = m.label_idx[row0 + tid];
+            if (dst < m.n_labels) m.labels[dst] = (uint16_t)best;
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void f32_input(F32Args a, float* __restrict__ z)
 {
     uint32_t total = *a.esc_count;
@@ -187,31 +362,7 @@ __global__ __launch_bounds__(256) void f32_input(F32Args a, float* __restrict__ 
     const uint64_t n = (uint64_t)rows * a.n_in;
     for (uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n; g += (uint64_t)gridDim.x * blockDim.x) {
         const uint32_t r = (uint32_t)(g / a.n_in), k = (uint32_t)(g % a.n_in);
-        uint32_t flow = a.esc_idx[a.row_begin + r];
-        flow = flow < a.n_rows ? flow : a.n_rows - 1u; // a bad list entry must not leave the input
-        float v;
-        if (a.feat) {
-            v = a.feat[(size_t)flow * a.feat_ld + k];
-            if (a.mu) {
-                const float d = v - a.mu[k];
-                v = d * a.inv_sigma[k];
-                v = v < -a.clamp ? -a.clamp : v;
-                v = v > a.clamp ? a.clamp : v;
-            }
-        } else {
-            uint32_t b0 = a.off[flow], e0 = a.off[flow + 1];
-            b0 = b0 < a.n_pkts ? b0 : a.n_pkts;
-            e0 = e0 < a.n_pkts ? e0 : a.n_pkts;
-            const uint32_t np = e0 > b0 ? e0 - b0 : 0;
-            const uint32_t j = k / a.raw_bits, b = k - j * a.raw_bits;
-            v = 0.f;
-            if (j < np) {
-                const uint32_t byte_i = b >> 3;
-                const uint32_t word = a.hdr[(size_t)(b0 + j) * a.hdr_words + (byte_i >> 2)];
-                v = (float)(((word >> (8u * (byte_i & 3u))) >> (7u - (b & 7u))) & 1u);
-            }
-        }
-        z[g] = v;
+        z[g] = f32_input_value(a, a.esc_idx[a.row_begin + r], k);
     }
 }
 
@@ -477,33 +628,47 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
         return SF_OK;
     }
 
+    F32Args f = {};
+    f.esc_idx = esc_idx;
+    f.esc_count = esc_count;
+    f.esc_cap = esc_cap;
+    f.n_rows = n_rows;
+    f.feat = feat;
+    f.feat_ld = feat_ld;
+    f.mu = mlp->mu;
+    f.inv_sigma = mlp->inv_sigma;
+    f.clamp = mlp->clamp;
+    if (raw_src) {
+        f.off = raw_src->flow_off;
+        f.hdr = raw_src->pkt_hdr;
+        f.hdr_words = raw_src->hdr_words;
+        f.raw_bits = raw_cfg->raw_bits;
+        f.raw_pkts = raw_cfg->raw_pkts;
+        f.n_pkts = (uint32_t)raw_src->n_pkts;
+    }
+    f.n_in = mlp->n_in;
+    // The whole model in one launch where a block's activations fit (widths up to about 1,400 together) and the list is
+    // not long: whole call, layer by layer -> one launch: 300 rows through 64-128-128-4 70 -> 16 us, 4,096 rows through
+    // 32-128-128-4 130 -> 17, 20,000 rows through 128-256-256-32 320 -> 179, 600 rows through 128-512-512-32 223 -> 123.
+    // With many rows the taller tiles of f32_layer read each weight less often: 500,000 rows through 64-128-128-4
+    // 982 against 1254 us, 130,000 through 128-256-256-32 832 against 1037 (100,000 through 64-128-128-4: equal).
+    const size_t lds = f32_fused_lds(mlp->n_in, mlp->n_h1, mlp->n_h2, mlp->n_classes);
+    if (lds <= kF32FusedLds && esc_cap <= kF32FusedRows) {
+        const F32Model m = {(const float*)mlp->w1, mlp->b1, (const float*)mlp->w2, mlp->b2, (const float*)mlp->w3, mlp->b3, mlp->n_h1,
+                            mlp->n_h2, mlp->n_classes, scatter ? scatter : esc_idx, logits, labels, n_flows};
+        const uint32_t tiles = (esc_cap + kF32Rows - 1u) / kF32Rows, most = 4u * (uint32_t)ctx->n_cu; // (rows that exist are dealt out in the kernel)
+        f32_mlp<<<tiles < most ? tiles : most, 256, lds, ctx->stream>>>(f, m);
+        SF_LAUNCH_CHECK(ctx, "f32_mlp");
+        return SF_OK;
+    }
     float* z = (float*)ws.take((size_t)R * mlp->n_in * 4);
     float* h1 = (float*)ws.take((size_t)R * ld1 * 4);
     float* h2 = (float*)ws.take((size_t)R * ld2 * 4);
     float* lg = (float*)ws.take((size_t)R * mlp->n_classes * 4);
     if (!z || !h1 || !h2 || !lg) return sf::fail(ctx, SF_ENOMEM, "sf_slow_infer: workspace carve failed");
     for (uint32_t begin = 0; begin < esc_cap; begin += R) {
-        F32Args f = {};
-        f.esc_idx = esc_idx;
-        f.esc_count = esc_count;
-        f.esc_cap = esc_cap;
         f.row_begin = begin;
         f.rows_cap = R;
-        f.n_rows = n_rows;
-        f.feat = feat;
-        f.feat_ld = feat_ld;
-        f.mu = mlp->mu;
-        f.inv_sigma = mlp->inv_sigma;
-        f.clamp = mlp->clamp;
-        if (raw_src) {
-            f.off = raw_src->flow_off;
-            f.hdr = raw_src->pkt_hdr;
-            f.hdr_words = raw_src->hdr_words;
-            f.raw_bits = raw_cfg->raw_bits;
-            f.raw_pkts = raw_cfg->raw_pkts;
-            f.n_pkts = (uint32_t)raw_src->n_pkts;
-        }
-        f.n_in = mlp->n_in;
         auto blocks = [&](uint64_t n) { uint64_t b = (n + 255) / 256; return (uint32_t)(b > 16384 ? 16384 : (b ? b : 1)); };
         f32_input<<<blocks((uint64_t)R * mlp->n_in), 256, 0, ctx->stream>>>(f, z);
         SF_LAUNCH_CHECK(ctx, "f32_input");
