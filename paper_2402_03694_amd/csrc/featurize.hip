@@ -5,8 +5,9 @@
 // computed by the shared device code in featurize_core.h (ordered sums, one sorting network and
 // one merge stage per quantity for the order statistics), so the result does not depend on how
 // flows are spread over lanes.  A window of more than 32 packets is worked on by the whole wave
-// (a sort across the lanes; see below).  A block is one wave: its 64 feature rows are staged in
-// shared memory per window and written out as full 128-byte runs.
+// (a sort across the lanes; see below).  Where lanes are few or flows ragged, four waves split the statistics of 64
+// flows instead (featurize_parts).  Feature rows are staged in shared memory per window and written out as full
+// 128-byte runs.
 #include "common.h"
 #include "featurize_core.h"
 
@@ -369,6 +370,168 @@ __global__ __launch_bounds__(kWave, (KMAX <= 16 ? 3 : (LONG ? 1 : 2))) void feat
     }
 }
 
+// Staged packets of a tile: one column per flow, rows 0..KMAX-1 the sizes, KMAX..2 KMAX-1 the times, then the
+// direction bits and the packet count.  Four words of padding per row: the lanes of a wave that write a row pair
+// each for eight flows then fall on 64 different banks.
+__host__ __device__ constexpr uint32_t stage_stride(uint32_t fpb) { return fpb + 4u; }
+__host__ __device__ constexpr uint32_t stage_words(uint32_t kmax, uint32_t fpb) { return (2u * kmax + 2u) * stage_stride(fpb); }
+
+// (The fused feature + forest kernel has a staging and a part of its own: sharing these two functions with it moved its
+// blocks and made its whole pass 0.5 % slower, 703 -> 707 us on 1,048,576 flows.)
+// One part of one window's statistics for one flow per lane: kind 0 / 2: sums of sizes / times, kind 1 / 3: order
+// statistics of sizes / times.  x: the quantity; col: scratch column, a word every `stride`; dst: where the window's
+// statistics go, one every `ds` floats.
+template <int N, int KMAX>
+__device__ __forceinline__ void window_part(uint32_t kind, const float (&x)[KMAX], uint32_t dmask, int m, uint32_t* col, uint32_t stride,
+                                            float* dst, uint32_t ds)
+{
+    const uint32_t valid = N >= 32 && m >= 32 ? ~0u : (1u << m) - 1u, m1 = dmask & valid, m0 = ~dmask & valid;
+    const int c1 = __popc(m1), c0 = m - c1;
+    if ((kind & 1u) == 0u) {
+        const float sum = sffeat::window_sums<N, KMAX>(x, valid, m0, m1, m, c0, c1, dst + (kind ? 5u : 0u) * ds, ds);
+        if (kind == 0u) {
+            dst[30u * ds] = sum; // (bytes: every partial sum is an integer below 2^24, so this is exact)
+            dst[31u * ds] = (float)m;
+        }
+    } else if (kind == 1u) {
+        sffeat::window_order_sizes<N, KMAX>(x, valid, m1, m, c0, c1, col, stride, dst + 2u * ds, ds);
+    } else {
+        // a time with its sign bit set anywhere in the wave: the order statistics take the general path
+        uint32_t sign_bits = 0;
+#pragma unroll
+        for (int j = 0; j < KMAX; ++j) sign_bits |= __float_as_uint(x[j]);
+        const bool signed_times = __any((int)(sign_bits >> 31));
+        sffeat::window_order_times<N, KMAX>(x, valid, m0, m1, m, c0, c1, signed_times, col, stride, dst + 7u * ds, ds);
+    }
+}
+
+// Fetches the packets of flows flow0 .. flow0 + FPB - 1 (up to dmax <= KMAX of each) into the staged form, by a block of BS
+// lanes, several pieces per lane.
+template <uint32_t FPB, uint32_t BS, int KMAX>
+__device__ __forceinline__ void stage_packets(const FeatArgs& c, uint32_t flow0, uint32_t* behind)
+{
+    constexpr uint32_t SS = stage_stride(FPB);
+    const uint32_t n_flows = c.n_flows, dmax = c.depth[c.n_windows - 1u];
+    constexpr uint32_t P = KMAX / 2; // lanes that fetch one flow's packets, two packets each
+    static_assert(P <= 16 && FPB * P % BS == 0, "every flow's packets are fetched by lanes of one wave, all lanes take part");
+    constexpr uint32_t IT = FPB * P / BS;
+    // consecutive lanes hold consecutive packets of a flow and the flows follow each other in memory, so the loads of a
+    // wave are one contiguous piece (flows longer than the window leave gaps); all offsets are requested before the first
+    // packet, all packets before the first is used
+    uint32_t b[IT], e[IT];
+#pragma unroll
+    for (uint32_t it = 0; it < IT; ++it) {
+        const uint32_t f = (threadIdx.x + it * BS) / P;
+        // a slot past the last flow works on the last flow (its loads stay inside the arrays)
+        const uint32_t flow = flow0 + f < n_flows ? flow0 + f : n_flows - 1u;
+        b[it] = c.off[flow];
+        e[it] = c.off[flow + 1];
+    }
+    uint32_t sz[IT], dd[IT], avail[IT]; // two sizes, two direction bytes
+    float2 tm[IT];
+#pragma unroll
+    for (uint32_t it = 0; it < IT; ++it) {
+        const uint32_t q = threadIdx.x + it * BS, p = q % P;
+        const uint32_t b1 = b[it] < c.n_pkts ? b[it] : c.n_pkts; // clamp: malformed offsets must not leave the arrays
+        uint32_t e1 = e[it] < c.n_pkts ? e[it] : c.n_pkts;
+        e1 = e1 < b1 ? b1 : e1;
+        const uint32_t n = e1 - b1, o = b1 + 2u * p;
+        avail[it] = n < dmax ? n : dmax;
+        sz[it] = 0u;
+        dd[it] = 0u;
+        tm[it] = make_float2(0.f, 0.f);
+        if (2u * p + 1u < avail[it] && (o & 1u) == 0 && c.wide_ok) {
+            sz[it] = *reinterpret_cast<const uint32_t*>(c.size + o);
+            tm[it] = *reinterpret_cast<const float2*>(c.iat + o);
+            dd[it] = *reinterpret_cast<const uint16_t*>(c.dir + o);
+        } else if (2u * p < avail[it]) {
+            const bool two = 2u * p + 1u < avail[it];
+            sz[it] = c.size[o] | (two ? (uint32_t)c.size[o + 1u] << 16 : 0u);
+            tm[it] = make_float2(c.iat[o], two ? c.iat[o + 1u] : 0.f);
+            dd[it] = c.dir[o] | (two ? (uint32_t)c.dir[o + 1u] << 8 : 0u);
+        }
+    }
+#pragma unroll
+    for (uint32_t it = 0; it < IT; ++it) {
+        const uint32_t q = threadIdx.x + it * BS, f = q / P, p = q % P;
+        uint32_t d = ((dd[it] & 1u) | ((dd[it] >> 7) & 2u)) << (2u * p);
+#pragma unroll
+        for (uint32_t k = 1; k < P; k *= 2) d |= (uint32_t)__shfl_xor((int)d, (int)k, 64);
+        float* st = reinterpret_cast<float*>(behind) + f;
+        st[(2u * p) * SS] = (float)(sz[it] & 0xFFFFu);
+        st[(2u * p + 1u) * SS] = (float)(sz[it] >> 16);
+        st[(KMAX + 2u * p) * SS] = tm[it].x;
+        st[(KMAX + 2u * p + 1u) * SS] = tm[it].y;
+        if (p == 0u) {
+            behind[2u * KMAX * SS + f] = d;
+            behind[(2u * KMAX + 1u) * SS + f] = avail[it];
+        }
+    }
+}
+
+// Windows of up to KMAX packets.  A block works on 64 flows with four waves: the packets are fetched once, coalesced, into
+// shared memory; then each wave computes one independent part of every window for all 64 flows (ordered sums or order
+// statistics, of sizes or times), with one quantity in registers.
+// What bounds it: vector arithmetic in large batches, in small ones a wave's latency, which this makes a quarter.  With one
+// lane per flow, as all batches went before and large ones still do (see sf_featurize), all four parts are one wave's
+// serial chain.  The kernel, before -> after: 20,011 ragged flows, windows 3, 9, 20: 19.7 -> 13.4 us; 250,007 ragged flows,
+// windows 8, 16: 37-40 -> 32.6 us; 1,048,576 of those 138 -> 133 us.  (A second tile instead of the second barrier per
+// window: 13.4 -> 12.8 us and 133 -> 141; 64 registers per lane for 16 packets, eight waves per SIMD with 20 spilled:
+// 133 -> 190.)
+template <int KMAX>
+__global__ __launch_bounds__(4 * kWave, KMAX == 8 ? 8 : KMAX == 16 ? 6 : 4) void featurize_parts(FeatArgs a)
+{
+    constexpr uint32_t SS = stage_stride(kWave);
+    constexpr uint32_t kStage = stage_words(KMAX, kWave), kSort = 2u * KMAX * kWave; // two of the waves sort
+    __shared__ uint32_t space[kStage > kSort ? kStage : kSort];
+    __shared__ float tile[kWave * kRow]; // [lane][33]
+    const uint32_t tid = threadIdx.x, slot = tid % kWave, flow0 = blockIdx.x * kWave;
+    const uint32_t kind = __builtin_amdgcn_readfirstlane(tid / kWave);
+    stage_packets<kWave, 4 * kWave, KMAX>(a, flow0, space);
+    __syncthreads();
+    float x[KMAX];
+    const float* st = reinterpret_cast<const float*>(space) + slot + (kind >> 1) * KMAX * SS;
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j) x[j] = st[j * SS];
+    const uint32_t dmask = space[2u * KMAX * SS + slot];
+    const int avail = (int)space[(2u * KMAX + 1u) * SS + slot];
+    __syncthreads(); // the staged packets are in registers: their space is scratch now
+    uint32_t* col = space + (kind >> 1) * (KMAX * kWave) + slot; // the lane's own column
+    float* row = tile + slot * kRow;
+    uint32_t rows = a.n_flows - flow0;
+    rows = rows < (uint32_t)kWave ? rows : (uint32_t)kWave;
+#pragma unroll 1
+    for (uint32_t w = 0; w < a.n_windows; ++w) {
+        // nothing made from the packets for one window is kept for another (registers)
+#pragma unroll
+        for (int j = 0; j < KMAX; ++j) asm volatile("" : "+v"(x[j]));
+        const int dw = (int)a.depth[w];
+        const int m = avail < dw ? avail : dw;
+        // the smallest network that covers every lane's window (wave-uniform choice)
+        if (KMAX >= 32 && __any(m > 16))
+            window_part<KMAX, KMAX>(kind, x, dmask, m, col, kWave, row, 1u);
+        else if (KMAX >= 16 && __any(m > 8))
+            window_part<(KMAX >= 16 ? 16 : KMAX), KMAX>(kind, x, dmask, m, col, kWave, row, 1u);
+        else
+            window_part<8, KMAX>(kind, x, dmask, m, col, kWave, row, 1u);
+        __syncthreads();
+        if (a.store16) {
+            // eight lanes write one staged row (32 consecutive floats = one 128-byte run) as 16-byte pieces
+            const uint32_t c4 = (tid & 7u) * 4u;
+            for (uint32_t r = tid >> 3; r < rows; r += kWave / 2) {
+                const float* src = tile + r * kRow + c4;
+                *reinterpret_cast<float4*>(a.feat + (size_t)(flow0 + r) * a.ld + 32u * w + c4) =
+                    make_float4(src[0], src[1], src[2], src[3]);
+            }
+        } else {
+            // half a wave writes one staged row, a float per lane
+            for (uint32_t r = tid >> 5; r < rows; r += kWave / 8)
+                a.feat[(size_t)(flow0 + r) * a.ld + 32u * w + (tid & 31u)] = tile[r * kRow + (tid & 31u)];
+        }
+        __syncthreads();
+    }
+}
+
 // Raw header bits -> one byte per bit.  A thread unpacks one header word (32 features).
 __global__ __launch_bounds__(256) void unpack_raw(uint32_t n_flows, uint32_t n_pkts, const uint32_t* __restrict__ off,
                                                   const uint32_t* __restrict__ hdr, uint32_t hdr_words,
@@ -442,14 +605,26 @@ extern "C" int sf_featurize(sf_ctx* ctx, const sf_packets* pk, const sf_feat_cfg
     a.store16 = ((uintptr_t)feat & 15u) == 0 && (feat_ld & 3u) == 0;
     const uint32_t dmax = cfg->depth[cfg->n_windows - 1];
     const uint32_t grid = (a.n_flows + kWave - 1) / kWave;
-    if (dmax <= 8)
-        featurize_wave<8, false><<<grid, kWave, 0, ctx->stream>>>(a);
-    else if (dmax <= 16)
-        featurize_wave<16, false><<<grid, kWave, 0, ctx->stream>>>(a);
-    else if (dmax <= 32)
-        featurize_wave<32, false><<<grid, kWave, 0, ctx->stream>>>(a);
-    else
+    // One lane per flow pays where there are enough flows for that kernel's two or three waves per SIMD and, up to 16
+    // packets, where every flow fills the deepest window (wide loads): 1,048,576 x 16 packets, windows 8, 16: 104 us
+    // against 108 in parts; windows of 8: 36.5 against 41.5; 4,194,304 x 32 packets, four windows: 1.11 ms against
+    // 1.22, ragged 1,048,576: 321 us against 351.  Fewer flows, and ragged ones of up to 16 packets, go in parts.
+    const uint32_t per_unit = a.n_flows / (uint32_t)ctx->n_cu;
+    const bool lanes = dmax > 16 ? per_unit >= 2u * 4u * kWave : per_unit >= 3u * 4u * kWave && pk->n_pkts >= (uint64_t)dmax * a.n_flows;
+    if (dmax > 32)
         featurize_wave<32, true><<<grid, kWave, 0, ctx->stream>>>(a);
+    else if (dmax > 16 && lanes)
+        featurize_wave<32, false><<<grid, kWave, 0, ctx->stream>>>(a);
+    else if (dmax > 16)
+        featurize_parts<32><<<grid, 4 * kWave, 0, ctx->stream>>>(a);
+    else if (dmax > 8 && lanes)
+        featurize_wave<16, false><<<grid, kWave, 0, ctx->stream>>>(a);
+    else if (dmax > 8)
+        featurize_parts<16><<<grid, 4 * kWave, 0, ctx->stream>>>(a);
+    else if (lanes)
+        featurize_wave<8, false><<<grid, kWave, 0, ctx->stream>>>(a);
+    else
+        featurize_parts<8><<<grid, 4 * kWave, 0, ctx->stream>>>(a);
     SF_LAUNCH_CHECK(ctx, "featurize");
     if (raw) {
         const uint64_t total = (uint64_t)a.n_flows * cfg->raw_pkts * ((cfg->raw_bits + 31) / 32);
