@@ -410,15 +410,19 @@ int sf_slow_infer_pairs(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32
  * Sections 3.1 and 3.2: features from the first k packets, the fast model on every flow, the gate, the slow
  * model on the flows the gate hands on.
  *
- * sf_featurize_fast_infer: the results of sf_featurize followed by sf_fast_infer (pred, top_votes), but for
- * window depths up to 16 packets and forests that run one lane per flow both steps are ONE kernel that
- * builds each tile of flows' features in shared memory and walks the forest there.  The feature matrix is
- * then written only where the slow model will read it: row i of feat is written iff flow i escalates under
- * the gate given by host_vmin / n_vmin (as sf_route: top_votes < vmin, or vmin[pred]); the other rows are
- * left untouched.  feat = NULL: no row is written (a slow model that reads header bits needs none).
- * Other shapes run the separate kernels and write every row (they need feat).  labels: optional
- * [n_flows]; labels[i] = pred[i], the start of the final label array (pass it to sf_slow_infer with
- * pred = NULL).
+ * sf_featurize_fast_infer: the results of sf_featurize followed by sf_fast_infer (pred, top_votes), where the
+ * shapes allow as ONE kernel that builds each tile of flows' features in shared memory and walks the forest
+ * there.  With window depths up to 16 packets and a forest that fits (below) the feature matrix is then
+ * written only where the slow model will read it: row i of feat is written iff flow i escalates under the
+ * gate given by host_vmin / n_vmin (as sf_route: top_votes < vmin, or vmin[pred]); the other rows are left
+ * untouched, and feat = NULL writes no row (a slow model that reads header bits needs none).  All other
+ * calls write every row and need feat.
+ * The forest fits if B + 16 * n_trees <= 81,408 bytes, where B = 1024 * (32 * n_windows + v) and v = words
+ * of a flow's vote counters = ceil(n_classes / 4) up to 255 trees, ceil(n_classes / 2) from 256 on.  Past
+ * that line it fits if B <= 81,920 and (depth = 1 or B + 16 * n_trees > 162,816), or if B + 16 * n_trees
+ * <= 81,920 and (depth < 4 or B + 80 * n_trees > 162,816).  The batch size does not enter.
+ * labels: optional [n_flows]; labels[i] = pred[i], the start of the final label array (pass it to
+ * sf_slow_infer with pred = NULL).
  *
  * sf_classify: all four steps: sf_featurize_fast_infer, sf_route, sf_slow_infer (with pred given and
  * esc_cap = n_flows); the results are those of the four calls in turn with the same arguments, except for

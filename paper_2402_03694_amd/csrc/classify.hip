@@ -244,16 +244,27 @@ int run_features_and_forest(sf_ctx* ctx, const char* who, const sf_packets* pk, 
     const uint32_t dmax = cfg->depth[cfg->n_windows - 1];
     int rc = sf::forest_setup(ctx, who, &wide, F, c.fa, &result_words);
     if (rc != SF_OK) return rc;
-    // Which calls are fused (and so write only the rows of the flows that are handed on) is part of the interface:
-    // windows of up to 16 packets, and features and results of a flow in at most 80 words of shared memory.
-    const bool fused = cfg->n_windows <= kFusedWindows && dmax <= kFusedDepth && F + result_words <= 80u;
-    if (!fused) {
-        // shapes the fused kernel does not cover: the same results from the separate kernels, with every feature
-        // row written
-        if (!feat || feat_ld < F) return sf::fail(ctx, SF_EINVAL, "%s: this shape needs the feature matrix", who);
+    // Which calls leave feature rows unwritten is part of the interface (serveflow.h), so it does not follow the block
+    // shapes of the present kernel: windows of up to 16 packets, and 80 KB that hold the features and vote counters of 256
+    // flows with as many staged pair-levels of records as the budget gives (none, one or more of every tree).
+    const size_t first = ((size_t)F + result_words) * 1024 + (size_t)c.fa.n_trees * 16;
+    uint32_t staged = 0;
+    const bool under_gate_only =
+        dmax <= kFusedDepth && plan_lds(c.fa, result_words, 256, first <= 80 * 1024 - 512 ? 80 * 1024 - 512 : 160 * 1024 - 1024, &staged) <= 80 * 1024;
+    if (!under_gate_only && (!feat || feat_ld < F)) return sf::fail(ctx, SF_EINVAL, "%s: this shape needs the feature matrix", who);
+    // What the fused kernel is built for: at most two windows, and a tile that leaves a unit two blocks of 128 flows.
+    if (cfg->n_windows > kFusedWindows || dmax > kFusedDepth || F + result_words > 80u) {
+        // other shapes: the same results from the separate kernels, with every feature row written
         rc = sf_featurize(ctx, pk, cfg, feat, feat_ld, nullptr);
         if (rc != SF_OK) return rc;
         return sf_fast_infer(ctx, feat, feat_ld, n, forest, nullptr, pred, top_votes, nullptr);
+    }
+    if (!under_gate_only) {
+        // every row: a threshold above any vote count (the rule gives at most 10,176 trees here)
+        static const uint16_t every = 0xFFFFu;
+        host_vmin = &every;
+        n_vmin = 1;
+        keep_rows = true;
     }
     c.n_pkts = (uint32_t)pk->n_pkts;
     c.off = pk->flow_off;
