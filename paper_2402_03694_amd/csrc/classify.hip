@@ -62,20 +62,20 @@ __device__ __forceinline__ void window_part(uint32_t kind, const float (&x)[KMAX
     const uint32_t valid = (1u << m) - 1u, m1 = dmask & valid, m0 = ~dmask & valid; // (m <= 16)
     const int c1 = __popc(m1), c0 = m - c1;
     if ((kind & 1u) == 0u) {
-        const float sum = sffeat::window_sums<N, KMAX>(x, valid, m0, m1, m, c0, c1, dst + (kind ? 5u : 0u) * fpb, fpb);
+        const float sum = sffeat::window_sums<true, N, KMAX>(x, valid, m0, m1, m, c0, c1, dst + (kind ? 5u : 0u) * fpb, fpb);
         if (kind == 0u) {
             dst[30u * fpb] = sum;
             dst[31u * fpb] = (float)m;
         }
     } else if (kind == 1u) {
-        sffeat::window_order_sizes<N, KMAX>(x, valid, m1, m, c0, c1, col, fpb, dst + 2u * fpb, fpb);
+        sffeat::window_order_sizes<true, N, KMAX>(x, valid, m1, m, c0, c1, col, fpb, dst + 2u * fpb, fpb);
     } else {
         // a time with its sign bit set anywhere in the wave: the order statistics take the general path
         uint32_t sign_bits = 0;
 #pragma unroll
         for (int j = 0; j < KMAX; ++j) sign_bits |= __float_as_uint(x[j]);
         const bool signed_times = __any((int)(sign_bits >> 31));
-        sffeat::window_order_times<N, KMAX>(x, valid, m0, m1, m, c0, c1, signed_times, col, fpb, dst + 7u * fpb, fpb);
+        sffeat::window_order_times<true, N, KMAX>(x, valid, m0, m1, m, c0, c1, signed_times, col, fpb, dst + 7u * fpb, fpb);
     }
 }
 

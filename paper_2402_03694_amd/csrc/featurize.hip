@@ -266,6 +266,7 @@ __device__ __forceinline__ void long_flow_chains(const uint32_t* park, uint32_t 
 template <int KMAX, bool LONG>
 __global__ __launch_bounds__(kWave, (KMAX <= 16 ? 3 : (LONG ? 1 : 2))) void featurize_wave(FeatArgs a)
 {
+    constexpr bool WORDS = KMAX > 16; // form of the group masks, see featurize_core.h
     static_assert(!LONG || KMAX == 32, "the whole-wave path takes over above 32 packets");
     __shared__ uint32_t sort_col[KMAX * kWave]; // [rank][lane]
     __shared__ float tile[kWave * kRow];        // [lane][33]
@@ -314,11 +315,11 @@ __global__ __launch_bounds__(kWave, (KMAX <= 16 ? 3 : (LONG ? 1 : 2))) void feat
         const int m = long_flow ? 0 : m_w; // (the lane's own result for such a flow is overwritten below)
         // the smallest network that covers every lane's window (wave-uniform choice)
         if (KMAX >= 32 && __any(m > 16))
-            sffeat::window_stats<(KMAX >= 32 ? 32 : KMAX), KMAX>(s, t, dmask, m, signed_times, col, kWave, row, 1u);
+            sffeat::window_stats<WORDS, (KMAX >= 32 ? 32 : KMAX), KMAX>(s, t, dmask, m, signed_times, col, kWave, row, 1u);
         else if (KMAX >= 16 && __any(m > 8))
-            sffeat::window_stats<(KMAX >= 16 ? 16 : KMAX), KMAX>(s, t, dmask, m, signed_times, col, kWave, row, 1u);
+            sffeat::window_stats<WORDS, (KMAX >= 16 ? 16 : KMAX), KMAX>(s, t, dmask, m, signed_times, col, kWave, row, 1u);
         else
-            sffeat::window_stats<8, KMAX>(s, t, dmask, m, signed_times, col, kWave, row, 1u);
+            sffeat::window_stats<WORDS, 8, KMAX>(s, t, dmask, m, signed_times, col, kWave, row, 1u);
         if (LONG) {
             // (the sort scratch of the lanes' own windows is free by now: the long flows' values are parked there)
             static_assert(!LONG || kSlots * kSlotWords <= (uint32_t)KMAX * kWave, "parked flows fit the sort scratch");
@@ -388,20 +389,20 @@ __device__ __forceinline__ void window_part(uint32_t kind, const float (&x)[KMAX
     const uint32_t valid = N >= 32 && m >= 32 ? ~0u : (1u << m) - 1u, m1 = dmask & valid, m0 = ~dmask & valid;
     const int c1 = __popc(m1), c0 = m - c1;
     if ((kind & 1u) == 0u) {
-        const float sum = sffeat::window_sums<N, KMAX>(x, valid, m0, m1, m, c0, c1, dst + (kind ? 5u : 0u) * ds, ds);
+        const float sum = sffeat::window_sums<true, N, KMAX>(x, valid, m0, m1, m, c0, c1, dst + (kind ? 5u : 0u) * ds, ds);
         if (kind == 0u) {
             dst[30u * ds] = sum; // (bytes: every partial sum is an integer below 2^24, so this is exact)
             dst[31u * ds] = (float)m;
         }
     } else if (kind == 1u) {
-        sffeat::window_order_sizes<N, KMAX>(x, valid, m1, m, c0, c1, col, stride, dst + 2u * ds, ds);
+        sffeat::window_order_sizes<true, N, KMAX>(x, valid, m1, m, c0, c1, col, stride, dst + 2u * ds, ds);
     } else {
         // a time with its sign bit set anywhere in the wave: the order statistics take the general path
         uint32_t sign_bits = 0;
 #pragma unroll
         for (int j = 0; j < KMAX; ++j) sign_bits |= __float_as_uint(x[j]);
         const bool signed_times = __any((int)(sign_bits >> 31));
-        sffeat::window_order_times<N, KMAX>(x, valid, m0, m1, m, c0, c1, signed_times, col, stride, dst + 7u * ds, ds);
+        sffeat::window_order_times<true, N, KMAX>(x, valid, m0, m1, m, c0, c1, signed_times, col, stride, dst + 7u * ds, ds);
     }
 }
 
@@ -559,6 +560,30 @@ __global__ __launch_bounds__(256) void unpack_raw(uint32_t n_flows, uint32_t n_p
     }
 }
 
+// One lane per flow or four waves per 64 flows (parts)?  Below two waves per SIMD of lanes the parts win everywhere
+// (65,536 flows: 1.05 to 1.25 times as fast).  From there, lanes : parts in microseconds; "ragged": flows of
+// geometric length, mean 10.
+//   a deepest window of 8 or 16 packets and flows of one length that is a multiple of 8 (told from the totals, as the lengths
+//     are on the device): the lanes load whole windows in 16-byte pieces.  1,048,576 flows: windows 8, 16,
+//     104 : 120; window 8, 40 : 48.
+//   else the lanes load packet by packet, each from its own flow, which pays as long as what they read at once stays in the
+//     first-level cache:
+//     up to 4 packets, and from 2,048 flows per unit up to 6 (1,048,576 ragged, window 4, 44 : 50; window 8 the other
+//     way, 53 : 49);
+//     up to 12 packets, or short flows, from 1,536 flows per unit (1,048,576 ragged, windows 5, 10, 120 : 133; but
+//     180,000 25.1 : 24.3, and windows 8, 16, 1,048,576, 139 : 134).
+//   windows of 17 to 32 packets: lanes (4,194,304 x 32 packets, four windows: 1.11 ms against 1.22; ragged 1,048,576: 321
+//     us against 351).
+bool one_lane_pays(uint32_t dmax, uint32_t per_unit, uint32_t n_flows, uint64_t n_pkts)
+{
+    if (per_unit < 2u * 4u * kWave) return false;
+    if (dmax > 16) return true;
+    const uint64_t len = n_pkts / n_flows;
+    if (dmax % 8u == 0 && n_pkts % n_flows == 0 && len % 8u == 0 && len >= dmax) return true;
+    if (dmax <= 8) return dmax <= 4 || (dmax <= 6 && per_unit >= 2048u);
+    return per_unit >= 1536u && (dmax <= 12 || (dmax < 16 && n_pkts <= 12ull * n_flows));
+}
+
 } // namespace
 
 extern "C" int sf_featurize(sf_ctx* ctx, const sf_packets* pk, const sf_feat_cfg* cfg, float* feat,
@@ -605,12 +630,8 @@ extern "C" int sf_featurize(sf_ctx* ctx, const sf_packets* pk, const sf_feat_cfg
     a.store16 = ((uintptr_t)feat & 15u) == 0 && (feat_ld & 3u) == 0;
     const uint32_t dmax = cfg->depth[cfg->n_windows - 1];
     const uint32_t grid = (a.n_flows + kWave - 1) / kWave;
-    // One lane per flow pays where there are enough flows for that kernel's two or three waves per SIMD and, up to 16
-    // packets, where every flow fills the deepest window (wide loads): 1,048,576 x 16 packets, windows 8, 16: 104 us
-    // against 108 in parts; windows of 8: 36.5 against 41.5; 4,194,304 x 32 packets, four windows: 1.11 ms against
-    // 1.22, ragged 1,048,576: 321 us against 351.  Fewer flows, and ragged ones of up to 16 packets, go in parts.
     const uint32_t per_unit = a.n_flows / (uint32_t)ctx->n_cu;
-    const bool lanes = dmax > 16 ? per_unit >= 2u * 4u * kWave : per_unit >= 3u * 4u * kWave && pk->n_pkts >= (uint64_t)dmax * a.n_flows;
+    const bool lanes = one_lane_pays(dmax, per_unit, a.n_flows, pk->n_pkts);
     if (dmax > 32)
         featurize_wave<32, true><<<grid, kWave, 0, ctx->stream>>>(a);
     else if (dmax > 16 && lanes)

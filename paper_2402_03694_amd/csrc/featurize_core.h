@@ -81,22 +81,36 @@ __device__ __forceinline__ void bitonic_merge(uint32_t (&a)[N])
 
 __device__ __forceinline__ bool bit_of(uint32_t m, int j) { return (m >> j) & 1u; }
 
-// All ones where bit j of m is set, else zero (one signed bit-field extract).  Group membership is applied with
-// such words: compare-and-select per packet and group keeps a pair of scalar registers alive for each, more than a
-// wave has (windows of 32 packets spilled 234 of them, 48 vector registers in the fused kernel).
+// Group membership comes in two forms, the template parameter WORDS of everything below.
+// false: compare and select; the comparisons of a packet are shared by all statistics of its window, which keeps a pair of
+//   scalar registers alive per packet and group.  The one-lane kernel takes this form up to 16 packets, where a wave has
+//   the registers: 262,149 flows x 16 packets, windows 8 and 16, 28.9 us against 32.8 with words, which are 11 % more
+//   vector instructions; 1,048,576 flows, window 16, 62.8 against 70.7.
+// true: a word per packet and group that is all ones or zero (one signed bit-field extract), applied with and / xor, and
+//   made again from the masks for each part of the statistics.  For 32 packets, where the pairs outnumber a wave's scalar
+//   registers (234 spilled), and for the kernels that split the parts between waves with few registers each (48 vector
+//   registers spilled in the fused kernel).
 __device__ __forceinline__ uint32_t bit_word(uint32_t m, int j) { return (uint32_t)__builtin_amdgcn_sbfe((int)m, (uint32_t)j, 1u); }
-// Between two parts of the statistics: the words are made again from the masks (one instruction each) instead of
-// being kept in a register per packet and group.
-__device__ __forceinline__ void forget_words(uint32_t& a, uint32_t& b, uint32_t& c) { asm volatile("" : "+v"(a), "+v"(b), "+v"(c)); }
+// between two parts of the statistics: nothing made from the masks is kept in a register
+template <bool WORDS>
+__device__ __forceinline__ void forget_words(uint32_t& a, uint32_t& b, uint32_t& c)
+{
+    if (WORDS) asm volatile("" : "+v"(a), "+v"(b), "+v"(c));
+}
 // x where bit j of m is set, else +0.0
-__device__ __forceinline__ float masked(float x, uint32_t m, int j) { return __uint_as_float(__float_as_uint(x) & bit_word(m, j)); }
+template <bool WORDS>
+__device__ __forceinline__ float masked(float x, uint32_t m, int j)
+{
+    if (WORDS) return __uint_as_float(__float_as_uint(x) & bit_word(m, j));
+    return bit_of(m, j) ? x : 0.f;
+}
 
 // Order statistics of one quantity for the three groups (0: direction 0, 1: direction 1, 2: all packets).
 // v[i]: the value of packet i as a non-negative integer below 2^W that orders like the value.  valid: the
 // window's packets; m1: those of direction 1; m = c0 + c1 packets.  Results are such integers too; for an
 // empty group they are meaningless (the caller writes zeros).  lo/hi: the two middle elements (equal for an
 // odd count).
-template <int N, int W>
+template <bool WORDS, int N, int W>
 __device__ __forceinline__ void order_stats3(const uint32_t (&v)[N], uint32_t valid, uint32_t m1, int m, int c0, int c1,
                                              uint32_t* col, uint32_t stride, uint32_t (&mn)[3], uint32_t (&mx)[3],
                                              uint32_t (&lo)[3], uint32_t (&hi)[3])
@@ -104,10 +118,14 @@ __device__ __forceinline__ void order_stats3(const uint32_t (&v)[N], uint32_t va
     constexpr uint32_t kMask = (1u << W) - 1u;            // W = 31: 0x7FFFFFFF
     constexpr uint32_t kPad = (1u << W) | kMask;          // the largest key; decodes to the value 0
     uint32_t key[N], outside = ~valid;
-    forget_words(valid, outside, m1);
+    forget_words<WORDS>(valid, outside, m1);
 #pragma unroll
-    for (int i = 0; i < N; ++i) // direction 1: top bit set and value complemented; outside the window: kPad
-        key[i] = (v[i] ^ (bit_word(m1, i) & kPad)) | (bit_word(outside, i) & kPad);
+    for (int i = 0; i < N; ++i) { // direction 1: top bit set and value complemented; outside the window: kPad
+        if (WORDS)
+            key[i] = (v[i] ^ (bit_word(m1, i) & kPad)) | (bit_word(outside, i) & kPad);
+        else
+            key[i] = bit_of(valid, i) ? (bit_of(m1, i) ? v[i] ^ kPad : v[i]) : kPad;
+    }
     sort_network<N>(key);
 #pragma unroll
     for (int i = 0; i < N; ++i) col[i * stride] = key[i];
@@ -165,32 +183,37 @@ __device__ __forceinline__ void order_stats_signed(const float (&x)[KMAX], uint3
 
 // Mean and standard deviation of one quantity for the three groups -> dst[k * ds], k = 10 * group (+ 1 for the
 // deviation); returns the sum over all packets.  Two ordered passes: the sums, then the squared deviations.
-template <int N, int KMAX>
+template <bool WORDS, int N, int KMAX>
 __device__ __forceinline__ float window_sums(const float (&x)[KMAX], uint32_t valid, uint32_t m0, uint32_t m1, int m, int c0, int c1,
                                              float* dst, uint32_t ds)
 {
     const bool e0 = c0 == 0, e1 = c1 == 0, ea = m == 0;
-    forget_words(valid, m0, m1);
+    forget_words<WORDS>(valid, m0, m1);
     float s0 = 0.f, s1 = 0.f, sa = 0.f;
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-        sa = sa + masked(x[j], valid, j);
-        s0 = s0 + masked(x[j], m0, j);
-        s1 = s1 + masked(x[j], m1, j);
+        sa = sa + masked<WORDS>(x[j], valid, j);
+        s0 = s0 + masked<WORDS>(x[j], m0, j);
+        s1 = s1 + masked<WORDS>(x[j], m1, j);
     }
     const float n0 = (float)(c0 > 0 ? c0 : 1), n1 = (float)(c1 > 0 ? c1 : 1), na = (float)(m > 0 ? m : 1);
     const float u0 = s0 / n0, u1 = s1 / n1, ua = sa / na;
-    forget_words(valid, m0, m1);
+    forget_words<WORDS>(valid, m0, m1);
     float q0 = 0.f, q1 = 0.f, qa = 0.f;
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-        const uint32_t w1 = bit_word(m1, j);
-        const float ug = __uint_as_float((w1 & __float_as_uint(u1)) | (~w1 & __float_as_uint(u0)));
+        float ug;
+        if (WORDS) {
+            const uint32_t w1 = bit_word(m1, j);
+            ug = __uint_as_float((w1 & __float_as_uint(u1)) | (~w1 & __float_as_uint(u0)));
+        } else {
+            ug = bit_of(m1, j) ? u1 : u0;
+        }
         const float da = x[j] - ua, dg = x[j] - ug;
         const float da2 = da * da, dg2 = dg * dg;
-        qa = qa + masked(da2, valid, j);
-        q0 = q0 + masked(dg2, m0, j);
-        q1 = q1 + masked(dg2, m1, j);
+        qa = qa + masked<WORDS>(da2, valid, j);
+        q0 = q0 + masked<WORDS>(dg2, m0, j);
+        q1 = q1 + masked<WORDS>(dg2, m1, j);
     }
     const float v0 = q0 / n0, v1 = q1 / n1, va = qa / na;
     dst[0 * ds] = e0 ? 0.f : u0;
@@ -204,14 +227,14 @@ __device__ __forceinline__ float window_sums(const float (&x)[KMAX], uint32_t va
 
 // Smallest, largest and median packet size of the three groups -> dst[k * ds], k = 10 * group + 0, 1, 2: sizes as
 // 16-bit integers (exact in binary32).
-template <int N, int KMAX>
+template <bool WORDS, int N, int KMAX>
 __device__ __forceinline__ void window_order_sizes(const float (&s)[KMAX], uint32_t valid, uint32_t m1, int m, int c0, int c1,
                                                    uint32_t* col, uint32_t stride, float* dst, uint32_t ds)
 {
     uint32_t v[N], a[3], b[3], c[3], d[3];
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] = (uint32_t)s[i];
-    order_stats3<N, 16>(v, valid, m1, m, c0, c1, col, stride, a, b, c, d);
+    order_stats3<WORDS, N, 16>(v, valid, m1, m, c0, c1, col, stride, a, b, c, d);
 #pragma unroll
     for (int g = 0; g < 3; ++g) {
         const int cg = g == 0 ? c0 : (g == 1 ? c1 : m);
@@ -224,7 +247,7 @@ __device__ __forceinline__ void window_order_sizes(const float (&s)[KMAX], uint3
 }
 
 // The same for the times; signed_times: wave-uniform, some lane of the wave holds a time with its sign bit set.
-template <int N, int KMAX>
+template <bool WORDS, int N, int KMAX>
 __device__ __forceinline__ void window_order_times(const float (&t)[KMAX], uint32_t valid, uint32_t m0, uint32_t m1, int m, int c0,
                                                    int c1, bool signed_times, uint32_t* col, uint32_t stride, float* dst, uint32_t ds)
 {
@@ -232,7 +255,7 @@ __device__ __forceinline__ void window_order_times(const float (&t)[KMAX], uint3
         uint32_t v[N], a[3], b[3], c[3], d[3];
 #pragma unroll
         for (int i = 0; i < N; ++i) v[i] = __float_as_uint(t[i]);
-        order_stats3<N, 31>(v, valid, m1, m, c0, c1, col, stride, a, b, c, d);
+        order_stats3<WORDS, N, 31>(v, valid, m1, m, c0, c1, col, stride, a, b, c, d);
 #pragma unroll
         for (int g = 0; g < 3; ++g) {
             const int cg = g == 0 ? c0 : (g == 1 ? c1 : m);
@@ -261,7 +284,7 @@ __device__ __forceinline__ void window_order_times(const float (&t)[KMAX], uint3
 // total bytes (k = 30) and packet count (k = 31).  Each result is stored as soon as it is known (the
 // sorting networks need the registers).  signed_times: wave-uniform, some lane of the wave holds a time
 // with its sign bit set.  dst and col must not overlap.
-template <int N, int KMAX>
+template <bool WORDS, int N, int KMAX>
 __device__ __forceinline__ void window_stats(const float (&s)[KMAX], const float (&t)[KMAX], uint32_t dmask, int m,
                                              bool signed_times, uint32_t* col, uint32_t stride, float* dst, uint32_t ds)
 {
@@ -270,12 +293,12 @@ __device__ __forceinline__ void window_stats(const float (&s)[KMAX], const float
     const uint32_t valid = m >= 32 ? ~0u : ((1u << m) - 1u);
     const uint32_t m1 = dmask & valid, m0 = ~dmask & valid;
     const int c1 = __popc(m1), c0 = m - c1;
-    const float bytes = window_sums<N, KMAX>(s, valid, m0, m1, m, c0, c1, dst, ds);
-    window_sums<N, KMAX>(t, valid, m0, m1, m, c0, c1, dst + 5 * ds, ds);
+    const float bytes = window_sums<WORDS, N, KMAX>(s, valid, m0, m1, m, c0, c1, dst, ds);
+    window_sums<WORDS, N, KMAX>(t, valid, m0, m1, m, c0, c1, dst + 5 * ds, ds);
     dst[30 * ds] = bytes; // every partial sum is an integer below 2^24, so this is exact
     dst[31 * ds] = (float)m;
-    window_order_sizes<N, KMAX>(s, valid, m1, m, c0, c1, col, stride, dst + 2 * ds, ds);
-    window_order_times<N, KMAX>(t, valid, m0, m1, m, c0, c1, signed_times, col, stride, dst + 7 * ds, ds);
+    window_order_sizes<WORDS, N, KMAX>(s, valid, m1, m, c0, c1, col, stride, dst + 2 * ds, ds);
+    window_order_times<WORDS, N, KMAX>(t, valid, m0, m1, m, c0, c1, signed_times, col, stride, dst + 7 * ds, ds);
 }
 
 } // namespace sffeat

@@ -1,0 +1,70 @@
+"""What the compiler made of the kernels (read from the library built here): registers spilled to memory and the number of
+vector instructions, for kernels whose time follows them.  A limit stands a little above what the kernel has."""
+import os
+import re
+import struct
+import subprocess
+import tempfile
+
+import pytest
+
+from paper_2402_03694_amd import build as hip_build
+
+LLVM = "/opt/rocm/llvm/bin/"
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def _code_objects(path):
+    """The device code objects of a library: every bundle's entries for the GPU."""
+    with open(path, "rb") as f:
+        data = f.read()
+    at = data.find(MAGIC)
+    while at >= 0:
+        p = at + len(MAGIC) + 8
+        for _ in range(struct.unpack_from("<Q", data, at + len(MAGIC))[0]):
+            offset, size, length = struct.unpack_from("<QQQ", data, p)
+            if b"gfx950" in data[p + 24:p + 24 + length] and size:
+                yield data[at + offset:at + offset + size]
+            p += 24 + length
+        at = data.find(MAGIC, at + 1)
+
+
+def _run(*cmd, **kw):
+    return subprocess.run(cmd, check=True, capture_output=True, text=True, **kw).stdout
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    """{name: {"spilled": vector registers, "vector": vector instructions}}"""
+    if not all(os.path.exists(LLVM + t) for t in ("llvm-readelf", "llvm-objdump")):
+        pytest.skip("no llvm-readelf or llvm-objdump")
+    found = {}
+    for code in _code_objects(hip_build.build(force=False)):
+        with tempfile.NamedTemporaryFile(suffix=".o") as f:
+            f.write(code)
+            f.flush()
+            for block in _run(LLVM + "llvm-readelf", "--notes", f.name).split("\n  - "):
+                name, spilled = re.search(r"\.symbol: +'?(\w+)\.kd", block), re.search(r"\.vgpr_spill_count: +(\d+)", block)
+                if name:
+                    found[name.group(1)] = {"spilled": int(spilled.group(1)), "vector": 0}
+            name = None
+            for line in _run(LLVM + "llvm-objdump", "-d", "--no-show-raw-insn", f.name).splitlines():
+                head = re.match(r"[0-9a-f]+ <(\w+)>:", line)
+                if head:
+                    name = head.group(1)
+                elif name in found and line.lstrip().startswith("v_"):
+                    found[name]["vector"] += 1
+    plain = _run("c++filt", input="\n".join(found)).splitlines()
+    return {n.replace("(anonymous namespace)::", "").replace("void ", "").split("(")[0]: v for n, v in zip(plain, found.values())}
+
+
+@pytest.mark.parametrize("name,most", [("featurize_wave<8, false>", 1230), ("featurize_wave<16, false>", 3200)])
+def test_vector_instructions(kernels, name, most):
+    """The one-lane feature kernel up to 16 packets shares its comparisons between the statistics."""
+    assert kernels[name]["vector"] <= most, kernels[name]
+
+
+@pytest.mark.parametrize("name", ["featurize_wave<8, false>", "featurize_wave<16, false>", "featurize_wave<32, false>", "featurize_parts<8>",
+                                  "featurize_parts<32>"])
+def test_no_spills(kernels, name):
+    assert kernels[name]["spilled"] == 0, kernels[name]
