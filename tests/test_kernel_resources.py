@@ -65,6 +65,8 @@ def test_vector_instructions(kernels, name, most):
 
 
 @pytest.mark.parametrize("name", ["featurize_wave<8, false>", "featurize_wave<16, false>", "featurize_wave<32, false>", "featurize_parts<8>",
-                                  "featurize_parts<32>"])
+                                  "featurize_parts<32>", "mlp_wide_layer<0, false, false>", "mlp_wide_layer<0, true, false>",
+                                  "mlp_wide_layer<1, false, false>", "mlp_wide_layer<1, true, false>", "mlp_wide_layer<2, false, true>",
+                                  "mlp_wide_layer<2, true, true>"])
 def test_no_spills(kernels, name):
     assert kernels[name]["spilled"] == 0, kernels[name]
