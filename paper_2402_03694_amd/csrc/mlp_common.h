@@ -11,9 +11,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 constexpr int BM = 128; // rows per block
-constexpr int BK = 64;  // K per main-loop step
-constexpr int LDT = BK + 8; // shared-memory row stride (elements): 144 bytes keeps 16-byte
-                            // reads of 8 consecutive rows on distinct banks
 
 enum { A_BF16 = 0, A_FEAT = 1, A_RAW = 2 };
 
@@ -69,18 +66,80 @@ static __device__ __forceinline__ void raw_flow_range(const LayerArgs& a, uint32
     n = e0 > b0 ? e0 - b0 : 0;
 }
 
-// raw_bits a multiple of 8: the 8 features [k, k+8), k a multiple of 8, are the 8 bits of one header byte.
-// The word that holds the byte (zero past K and past the flow) ...
-static __device__ __forceinline__ uint32_t raw_word_at(const LayerArgs& a, uint32_t b0, uint32_t n, uint32_t k)
+// Header bits as input: feature k = raw_bits * j + b is bit b of packet j, which is bit 7-(b%8) of header byte b/8; zero past
+// K and past the flow.  The 8 features from (j, b) on are requested first, as the header words that hold them, and turned into
+// bfloat16 0.0 / 1.0 later, when the words have arrived.  Which words these are depends on how the bits lie:
+enum RawForm {
+    RAW_BYTES, // raw_bits a multiple of 8: the features are the bits of one byte, in one word
+    RAW_LONG,  // else from 8 bits a packet: the word with the first feature, the next one if a byte's worth of bits ends there,
+               // and the first word of the next packet if this one ends before
+    RAW_SHORT, // 3 to 7 bits: the only word of up to four packets (7 bits: two, 4 to 6: three); 1 or 2 bits: of up to eight, so
+               // the features themselves as a byte (the one case that waits for its words)
+};
+
+// b < raw_bits + 256 bits from the start of packet j on -> the packet they lead to and the bit in it; per = 1 / raw_bits.
+// (Exact: b + 0.5 is at least half a bit off a multiple of raw_bits, the product's error below 2^-13 for quotients up to 511.)
+static __device__ __forceinline__ void raw_carry(const LayerArgs& a, float per, uint32_t& j, uint32_t& b)
 {
-    const uint32_t j = k / a.raw_bits, b = k - j * a.raw_bits;
-    return k < a.K && j < n ? a.hdr[(size_t)(b0 + j) * a.hdr_words + (b >> 5)] : 0u;
+    const uint32_t whole = a.raw_bits >= 256u ? (b >= a.raw_bits ? 1u : 0u) : (uint32_t)(((float)b + 0.5f) * per);
+    j += whole;
+    b -= whole * a.raw_bits;
 }
 
-// ... and its byte's bits, first bit first, as bfloat16 0.0 / 1.0
-static __device__ __forceinline__ uint4 raw_byte_bits(const LayerArgs& a, uint32_t word, uint32_t k)
+// The words of the features from (j, b) on of a flow whose packets start at b0 (n of them)
+template <int FORM>
+static __device__ __forceinline__ uint4 raw_words_at(const LayerArgs& a, uint32_t b0, uint32_t n, uint32_t j, uint32_t b)
 {
-    const uint32_t byte = word >> (k % a.raw_bits & 24u); // bits 0..7 (b = k mod raw_bits is a multiple of 8)
+    uint4 r = make_uint4(0, 0, 0, 0);
+    const uint32_t end = n < a.raw_pkts ? n : a.raw_pkts;
+    if (j >= end) return r;
+    const uint32_t* row = a.hdr + (size_t)(b0 + j) * a.hdr_words;
+    if (FORM == RAW_BYTES) {
+        r.x = row[b >> 5];
+    } else if (FORM == RAW_LONG) {
+        const uint32_t left = a.raw_bits - b, ahead = 32u - (b & 31u); // features of this packet, of this word
+        r.x = row[b >> 5];
+        if (ahead < 8u && left > ahead) r.y = row[(b >> 5) + 1u];
+        if (left < 8u && j + 1u < end) r.z = row[a.hdr_words];
+    } else if (a.raw_bits >= 3u) {
+        r.x = row[0];
+        if (j + 1u < end) r.y = row[a.hdr_words];
+        if (a.raw_bits < 7u && j + 2u < end) r.z = row[2u * a.hdr_words];
+        if (a.raw_bits < 4u && j + 3u < end) r.w = row[3u * a.hdr_words];
+    } else {
+#pragma unroll 4
+        for (uint32_t q = 0; q < 8u; ++q) {
+            const uint32_t d = (b + q) >> (a.raw_bits - 1u), bit = (b + q) & (a.raw_bits - 1u);
+            if (j + d < end) r.x |= ((row[(size_t)d * a.hdr_words] >> (7u - bit)) & 1u) << (7u - q);
+        }
+    }
+    return r;
+}
+
+// ... and the features in them
+template <int FORM>
+static __device__ __forceinline__ uint4 raw_bits_of(const LayerArgs& a, const uint4& r, uint32_t b)
+{
+    uint32_t byte = r.x; // the features as bits 7..0
+    if (FORM == RAW_BYTES) {
+        byte = r.x >> (b & 24u);
+    } else if (FORM == RAW_LONG) {
+        const uint64_t two = (uint64_t)__builtin_bswap32(r.x) << 32 | __builtin_bswap32(r.y); // first bit first
+        const uint32_t left = a.raw_bits - b;
+        byte = (uint32_t)(two << (b & 31u) >> 56);
+        if (left < 8u) byte = (byte & (0xFF00u >> left)) | (r.z & 0xFFu) >> left;
+    } else if (a.raw_bits >= 3u) {
+        const uint32_t w[4] = {r.x, r.y, r.z, r.w};
+        byte = 0;
+        uint32_t end = a.raw_bits - b; // features up to and with packet p
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            if (p == 2 && a.raw_bits == 7u) break;
+            const uint32_t field = (w[p] & 0xFFu) >> (8u - a.raw_bits);
+            byte |= end <= 8u ? field << (8u - end) : end < 8u + a.raw_bits ? field >> (end - 8u) : 0u;
+            end += a.raw_bits;
+        }
+    }
     uint32_t v[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -89,32 +148,7 @@ static __device__ __forceinline__ uint4 raw_byte_bits(const LayerArgs& a, uint32
     return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-// 8 consecutive raw-bit features [k, k+8) of a flow whose packets start at b0 (n of them) as bfloat16 0.0 / 1.0:
-// feature k = raw_bits * packet + bit; bit b is bit 7-(b%8) of header byte b/8; zero past K and past the flow
-static __device__ __forceinline__ uint4 raw_chunk_at(const LayerArgs& a, uint32_t b0, uint32_t n, uint32_t k)
-{
-    if (k >= a.K) return make_uint4(0, 0, 0, 0);
-    if ((a.raw_bits & 7u) == 0) return raw_byte_bits(a, raw_word_at(a, b0, n, k), k);
-    uint16_t v[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const uint32_t kk = k + q;
-        uint16_t bit = 0;
-        if (kk < a.K) {
-            const uint32_t j = kk / a.raw_bits, b = kk - j * a.raw_bits;
-            if (j < n) {
-                const uint32_t byte_i = b >> 3;
-                const uint32_t word = a.hdr[(size_t)(b0 + j) * a.hdr_words + (byte_i >> 2)];
-                const uint32_t byte = (word >> (8u * (byte_i & 3u))) & 0xFFu;
-                bit = (uint16_t)((byte >> (7u - (b & 7u))) & 1u);
-            }
-        }
-        v[q] = bit ? (uint16_t)0x3F80 : (uint16_t)0; // bfloat16 1.0 or 0.0
-    }
-    return make_uint4(pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7]));
-}
-
-// 8 consecutive K values [k, k+8) of escalated row e as bfloat16, zero past K.
+// 8 consecutive K values [k, k+8) of escalated row e as bfloat16, zero past K (bfloat16 activations or feature rows).
 template <int AMODE>
 static __device__ __forceinline__ uint4 load_a_chunk(const LayerArgs& a, bool row_ok, uint32_t row_in_chunk,
                                               uint32_t flow, uint32_t k)
@@ -154,10 +188,6 @@ static __device__ __forceinline__ uint4 load_a_chunk(const LayerArgs& a, bool ro
         }
         return make_uint4(pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7]));
     }
-    // A_RAW
-    uint32_t b0, n;
-    raw_flow_range(a, flow, b0, n);
-    return raw_chunk_at(a, b0, n, k);
 }
 
 static __device__ __forceinline__ bf16x8 as_bf16x8(uint4 u)

@@ -80,8 +80,8 @@ __device__ __forceinline__ void wave_sync()
 }
 
 // RESIDENT: every slab of a row block has a buffer of its own (K up to WBUF slabs).
-// BYTES: header bits come in whole bytes (A_RAW).
-template <int AMODE, bool RESIDENT, bool BYTES>
+// FORM: how header bits lie (A_RAW).
+template <int AMODE, bool RESIDENT, int FORM>
 __global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const uint4* __restrict__ ws, uint32_t n_cb)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -113,16 +113,25 @@ __global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const
     const uint32_t ck = (tid % (WSLAB / 8)) * 8u;
     // raw-bit input: where the two rows' flows start and how many packets they have, once per row block (not per slab)
     uint32_t raw_b0[2] = {0u, 0u}, raw_n[2] = {0u, 0u};
-    // Slab sl of row block rb as this thread's two chunks.  Header bits in whole bytes are only requested
-    // here, one word of the header per chunk, and turned into bfloat16 when the slab is stored: made here,
-    // the wave would wait for the word, and for every weight request before it, ahead of the slab's MFMAs.
-    auto fetch = [&](uint32_t rb, uint32_t sl, uint4 (&r)[2]) {
+    const float raw_per = AMODE == A_RAW ? 1.f / (float)a.raw_bits : 0.f;
+    // where the thread's columns of a slab stand in a flow's header bits: slab sl of the first three
+    struct Place {
+        uint32_t j, b; // packet, bit
+    };
+    auto place_of = [&](uint32_t sl) {
+        Place p = {0u, sl * WSLAB + ck};
+        if (AMODE == A_RAW) raw_carry(a, raw_per, p.j, p.b);
+        return p;
+    };
+    // Slab sl of row block rb as this thread's two chunks.  Header bits are only requested here, as words, and turned into
+    // bfloat16 when the slab is stored: made here, the wave would wait for the words, and for every weight request
+    // before them, ahead of the slab's MFMAs.  (100,000 rows of 8 x 31 bits through 1024-512: 242 us a call; with the bits
+    // made here 432, of 10 x 477 bits 1,051 and 2,831.)
+    auto fetch = [&](uint32_t rb, uint32_t sl, const Place& p, uint4 (&r)[2]) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            if (AMODE == A_RAW && BYTES)
-                r[u].x = raw_word_at(a, raw_b0[u], raw_n[u], sl * WSLAB + ck);
-            else if (AMODE == A_RAW)
-                r[u] = raw_chunk_at(a, raw_b0[u], raw_n[u], sl * WSLAB + ck);
+            if (AMODE == A_RAW)
+                r[u] = raw_words_at<FORM>(a, raw_b0[u], raw_n[u], p.j, p.b); // (past K: packets that raw_pkts leaves out)
             else if (AMODE == A_FEAT)
                 r[u] = load_a_chunk<AMODE>(a, a.row_begin + rb * WBM + cr[u] < total, 0u, s_flow[cr[u]], sl * WSLAB + ck);
             else { // (lda is K rounded up to whole slabs and the padding holds zeros; a row past the end repeats the last one)
@@ -132,11 +141,11 @@ __global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const
             }
         }
     };
-    auto store = [&](uint32_t buf, uint32_t sl, const uint4 (&r)[2]) {
+    auto store = [&](uint32_t buf, const Place& p, const uint4 (&r)[2]) {
 #pragma unroll
         for (int u = 0; u < 2; ++u)
             *reinterpret_cast<uint4*>(slab + buf * (WBM * WLDS) + cr[u] * WLDS + ck) =
-                AMODE == A_RAW && BYTES ? raw_byte_bits(a, r[u].x, sl * WSLAB + ck) : r[u];
+                AMODE == A_RAW ? raw_bits_of<FORM>(a, r[u], p.b) : r[u];
     };
     // weight operands of a column block: a 32-column block past the end repeats the last one, its results are not
     // stored.  (A wave whose columns all lie past the end still runs the loop: a branch around the refills would
@@ -161,6 +170,7 @@ __global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const
     // stream: the A operand runs two slabs ahead of the MFMAs, on into the next item
     constexpr bool kSeamless = AMODE == A_BF16;
     bool filled = false; // the first slabs of the item are in place
+    Place ahead = {0u, 0u}; // of the slab that is requested next
 
     for (uint32_t item = blockIdx.x; item < n_items; item += units) {
         const uint32_t rb = walk ? item : item % rb_count, cb_first = walk ? 0u : item / rb_count;
@@ -185,8 +195,10 @@ __global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const
                 }
             }
             uint4 r0[2], r1[2];
-            fetch(rb, 0, r0);
-            if (n_slabs > 1u) fetch(rb, 1, r1);
+            const Place p0 = place_of(0), p1 = place_of(1);
+            ahead = place_of(2);
+            fetch(rb, 0, p0, r0);
+            if (n_slabs > 1u) fetch(rb, 1, p1, r1);
             if (item == blockIdx.x) { // (later items find the ring filled and their first bias in place)
                 operands_of(cb_first, wl);
                 s_bias[lane] = bias_of(cb_first);
@@ -198,11 +210,11 @@ __global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const
                 }
             }
             buf = 0;
-            store(0, 0, r0);
-            if (n_slabs > 1u) store(1, 1, r1);
+            store(0, p0, r0);
+            if (n_slabs > 1u) store(1, p1, r1);
             if (RESIDENT && n_slabs > 2u) {
-                fetch(rb, 2, r0);
-                store(2, 2, r0);
+                fetch(rb, 2, ahead, r0);
+                store(2, ahead, r0);
             }
             __syncthreads();
 #pragma unroll
@@ -252,7 +264,8 @@ __global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const
                             want = kSeamless;
                         }
                     }
-                    if (want) fetch(rb2, sl2, ra);
+                    if (sl2 == 0u) ahead = place_of(0);
+                    if (want) fetch(rb2, sl2, ahead, ra);
                 }
                 const uint4* src[WNI]; // this slab's refills: the next slab of the column block, or the next tile's first
 #pragma unroll
@@ -279,7 +292,11 @@ __global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if (!RESIDENT) {
-                    if (want) store(nbuf + 1u < WBUF ? nbuf + 1u : 0u, sl2, ra);
+                    if (want) store(nbuf + 1u < WBUF ? nbuf + 1u : 0u, ahead, ra);
+                    if (AMODE == A_RAW) { // (on to the next slab)
+                        ahead.b += WSLAB;
+                        raw_carry(a, raw_per, ahead.j, ahead.b);
+                    }
                     __syncthreads(); // the slab after the next is in place; nobody reads this one any more
                 }
                 buf = nbuf;
@@ -328,10 +345,10 @@ __global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const
     }
 }
 
-template <int AMODE, bool RESIDENT, bool BYTES>
+template <int AMODE, bool RESIDENT, int FORM>
 int launch_wide(sf_ctx* ctx, int slot, LayerArgs a, const void* w_ordered, uint32_t rows_cap)
 {
-    auto* kernel = mlp_wide_layer<AMODE, RESIDENT, BYTES>;
+    auto* kernel = mlp_wide_layer<AMODE, RESIDENT, FORM>;
     SF_ALLOW_LDS(ctx, slot, kernel);
     a.rows_cap = rows_cap;
     const uint32_t n_cb = (a.ldh + WBN - 1) / WBN;
@@ -342,11 +359,11 @@ int launch_wide(sf_ctx* ctx, int slot, LayerArgs a, const void* w_ordered, uint3
     return SF_OK;
 }
 
-template <int AMODE, bool BYTES>
+template <int AMODE, int FORM>
 int launch_wide(sf_ctx* ctx, int slot, const LayerArgs& a, const void* w_ordered, uint32_t rows_cap)
 {
-    if ((a.K + WSLAB - 1) / WSLAB <= WBUF) return launch_wide<AMODE, true, BYTES>(ctx, slot, a, w_ordered, rows_cap);
-    return launch_wide<AMODE, false, BYTES>(ctx, slot + 1, a, w_ordered, rows_cap);
+    if ((a.K + WSLAB - 1) / WSLAB <= WBUF) return launch_wide<AMODE, true, FORM>(ctx, slot, a, w_ordered, rows_cap);
+    return launch_wide<AMODE, false, FORM>(ctx, slot + 1, a, w_ordered, rows_cap);
 }
 
 } // namespace
@@ -355,10 +372,11 @@ namespace sf {
 
 int wide_layer(sf_ctx* ctx, int amode, const sfmlp::LayerArgs& a, const void* w_ordered, uint32_t rows_cap)
 {
-    if (amode == A_BF16) return launch_wide<A_BF16, false>(ctx, sf::kLdsWide, a, w_ordered, rows_cap);
-    if (amode == A_FEAT) return launch_wide<A_FEAT, false>(ctx, sf::kLdsWide + 2, a, w_ordered, rows_cap);
-    if ((a.raw_bits & 7u) == 0) return launch_wide<A_RAW, true>(ctx, sf::kLdsWide + 4, a, w_ordered, rows_cap);
-    return launch_wide<A_RAW, false>(ctx, sf::kLdsWide + 6, a, w_ordered, rows_cap);
+    if (amode == A_BF16) return launch_wide<A_BF16, 0>(ctx, sf::kLdsWide, a, w_ordered, rows_cap);
+    if (amode == A_FEAT) return launch_wide<A_FEAT, 0>(ctx, sf::kLdsWide + 2, a, w_ordered, rows_cap);
+    if ((a.raw_bits & 7u) == 0) return launch_wide<A_RAW, RAW_BYTES>(ctx, sf::kLdsWide + 4, a, w_ordered, rows_cap);
+    if (a.raw_bits > 8u) return launch_wide<A_RAW, RAW_LONG>(ctx, sf::kLdsWide + 6, a, w_ordered, rows_cap);
+    return launch_wide<A_RAW, RAW_SHORT>(ctx, sf::kLdsWide + 8, a, w_ordered, rows_cap);
 }
 
 } // namespace sf

@@ -65,8 +65,13 @@ def test_vector_instructions(kernels, name, most):
 
 
 @pytest.mark.parametrize("name", ["featurize_wave<8, false>", "featurize_wave<16, false>", "featurize_wave<32, false>", "featurize_parts<8>",
-                                  "featurize_parts<32>", "mlp_wide_layer<0, false, false>", "mlp_wide_layer<0, true, false>",
-                                  "mlp_wide_layer<1, false, false>", "mlp_wide_layer<1, true, false>", "mlp_wide_layer<2, false, true>",
-                                  "mlp_wide_layer<2, true, true>"])
+                                  "featurize_parts<32>"] + ["mlp_wide_layer<%s>" % t for t in (
+                                      "0, false, 0", "0, true, 0", "1, false, 0", "1, true, 0", "2, false, 0", "2, true, 0", "2, false, 1", "2, true, 1",
+                                      "2, true, 2")])
 def test_no_spills(kernels, name):
     assert kernels[name]["spilled"] == 0, kernels[name]
+
+
+def test_few_spills(kernels):
+    """Header bits of 1 to 7 a packet, K streamed: outside the loop over K."""
+    assert kernels["mlp_wide_layer<2, false, 2>"]["spilled"] <= 4
