@@ -210,6 +210,7 @@ __device__ __forceinline__ float f32_input_value(const F32Args& a, uint32_t flow
 constexpr uint32_t kF32Rows = 8, kF32Cols = 128, kF32K = 32, kF32Ld = kF32K + 4; // (row stride: 16-byte reads of 8 consecutive rows on distinct banks)
 constexpr size_t kF32FusedLds = 64 * 1024;
 constexpr uint32_t kF32FusedRows = 1u << 15;
+constexpr double kF32FusedTerms = 5.2e9;
 
 __host__ __device__ inline uint32_t up4(uint32_t x) { return (x + 3u) / 4u * 4u; }
 // row strides of the two activation buffers: input and second hidden layer, first hidden layer and logits
@@ -218,6 +219,13 @@ __host__ __device__ inline uint32_t f32_ld_b(uint32_t h1, uint32_t c) { return u
 __host__ __device__ inline size_t f32_fused_lds(uint32_t n_in, uint32_t h1, uint32_t h2, uint32_t c)
 {
     return ((size_t)kF32Rows * ((size_t)f32_ld_a(n_in, h2) + f32_ld_b(h1, c)) + kF32Cols * kF32Ld) * 4;
+}
+
+// terms of the sums of one row, columns in whole waves
+inline double f32_terms(uint32_t n_in, uint32_t h1, uint32_t h2, uint32_t c)
+{
+    const auto waves = [](uint32_t n) { return (double)((n + 63u) / 64u * 64u); };
+    return n_in * waves(h1) + h1 * waves(h2) + h2 * waves(c);
 }
 
 struct F32Model {
@@ -647,13 +655,17 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
         f.n_pkts = (uint32_t)raw_src->n_pkts;
     }
     f.n_in = mlp->n_in;
-    // The whole model in one launch where a block's activations fit (widths up to about 1,400 together) and the list is
-    // not long: whole call, layer by layer -> one launch: 300 rows through 64-128-128-4 70 -> 16 us, 4,096 rows through
-    // 32-128-128-4 130 -> 17, 20,000 rows through 128-256-256-32 320 -> 179, 600 rows through 128-512-512-32 223 -> 123.
-    // With many rows the taller tiles of f32_layer read each weight less often: 500,000 rows through 64-128-128-4
-    // 982 against 1254 us, 130,000 through 128-256-256-32 832 against 1037 (100,000 through 64-128-128-4: equal).
+    // The whole model in one launch where a block's activations fit (widths up to about 1,400 together), up to 32,768 rows and
+    // as long as the terms of all sums stay under the line: a block of eight rows reads every weight again, the taller tiles
+    // of f32_layer read it once for 64 rows.  Whole call in us, layer by layer : one launch: 300 rows through 64-128-128-4
+    // 70 : 16, 4,096 rows through 32-128-128-4 130 : 17, 20,000 rows through 128-256-256-32 310 : 158, 600 rows through
+    // 128-512-512-32 223 : 123.  Around the line (5.2e9 terms): 24,576 rows through 32-400-400-10 513 : 515, 32,768 through
+    // 32-350-350-10 496 : 497, 16,384 through 32-512-512-10 531 : 444, 10,000 through 128-650-650-10 724 : 744.  Past it: 32,768
+    // through 128-650-650-10 1,244 : 2,130, 24,576 through 128-450-450-10 651 : 820.  Long lists through narrow models: 500,000
+    // rows through 64-128-128-4 982 : 1,254, 100,000 equal.
     const size_t lds = f32_fused_lds(mlp->n_in, mlp->n_h1, mlp->n_h2, mlp->n_classes);
-    if (lds <= kF32FusedLds && esc_cap <= kF32FusedRows) {
+    const double terms = esc_cap * f32_terms(mlp->n_in, mlp->n_h1, mlp->n_h2, mlp->n_classes);
+    if (lds <= kF32FusedLds && esc_cap <= kF32FusedRows && terms <= kF32FusedTerms) {
         const F32Model m = {(const float*)mlp->w1, mlp->b1, (const float*)mlp->w2, mlp->b2, (const float*)mlp->w3, mlp->b3, mlp->n_h1,
                             mlp->n_h2, mlp->n_classes, scatter ? scatter : esc_idx, logits, labels, n_flows};
         const uint32_t tiles = (esc_cap + kF32Rows - 1u) / kF32Rows, most = 4u * (uint32_t)ctx->n_cu; // (rows that exist are dealt out in the kernel)
