@@ -72,18 +72,29 @@ __global__ __launch_bounds__(FPB_ * W) void forest_votes(FastArgs a)
         row = row < a.n_rows ? row : a.n_rows - 1u; // a bad list entry must not leave the matrix
     }
     {
-        // the W lanes of a flow each copy their share of its row into the flow's column
+        // the W lanes of a flow each copy their share of its row into the flow's column, several pieces requested before the
+        // first is stored (one after the other, a large batch took 40 us for 32 features where memory needs 28)
         const float* x = a.feat + (size_t)row * a.ld;
+        const uint32_t first = FPB >= 64u ? __builtin_amdgcn_readfirstlane(grp) : grp; // (whole waves: the loop is scalar)
         if ((a.ld & 3u) == 0 && (F & 3u) == 0 && (reinterpret_cast<uintptr_t>(a.feat) & 15u) == 0) {
-            for (uint32_t q = grp; q < F / 4u; q += W) {
-                const float4 v = reinterpret_cast<const float4*>(x)[q];
+            constexpr uint32_t AT_ONCE = W >= 8 ? 2 : 8 / W;
+            auto put = [&](uint32_t q, const float4& v) {
                 xT[(4 * q + 0) * FPB + slot] = v.x;
                 xT[(4 * q + 1) * FPB + slot] = v.y;
                 xT[(4 * q + 2) * FPB + slot] = v.z;
                 xT[(4 * q + 3) * FPB + slot] = v.w;
+            };
+            uint32_t q = first;
+            for (; q + (AT_ONCE - 1u) * W < F / 4u; q += AT_ONCE * W) {
+                float4 v[AT_ONCE];
+#pragma unroll
+                for (uint32_t u = 0; u < AT_ONCE; ++u) v[u] = reinterpret_cast<const float4*>(x)[q + u * W];
+#pragma unroll
+                for (uint32_t u = 0; u < AT_ONCE; ++u) put(q + u * W, v[u]);
             }
+            for (; q < F / 4u; q += W) put(q, reinterpret_cast<const float4*>(x)[q]);
         } else {
-            for (uint32_t f = grp; f < F; f += W) xT[f * FPB + slot] = x[f];
+            for (uint32_t f = first; f < F; f += W) xT[f * FPB + slot] = x[f];
         }
     }
     forest_walk<FPB_, W, ILP, TAIL, WANT_LEAF, GBDT, false>(a, xT, i, row, live);
@@ -170,10 +181,21 @@ int check_model(sf_ctx* ctx, const char* who, const TreeModel& m)
 //     (1,048,576 flows: 450 -> 420; where they hold no more it is slower: 200 trees 272 against 293).
 //   fewer than 48 trees: 128 x 4, five trees at once per lane; eight lanes would walk a handful each
 //     (1,000,000 flows, 16 trees of depth 8: 62 against 76).
+//   256 flows, one lane each, in large batches where lanes that share a flow have nothing to share or stand in each other's
+//     way:
+//     a walk so short that reading the rows is all there is: 32 features, from 1,400 flows per unit (with up to four trees from
+//     750), few and shallow trees (200,000 flows, four trees of depth 4 8.7 us against 9.6; 1,048,576 flows, one tree of depth 8 35 against 45, 12 of depth 4 44 against 51, 24 of depth 4 53 against 63; but 16 of
+//     depth 6 1.13 times as long, and with 64 features equal);
+//     trees of depth 13 and 14, whose records (87 KB a tree) the caches cannot hold for eight trees at a time:
+//     1,048,576 flows, 32 features, 64 trees of depth 13 0.86 times as long, 100,000 flows, 100 trees 0.82.
 // Boosted form: lanes split the classes, not the trees (see forest_walk), so a few large shares are better than
-// many uneven ones: 256 x 2 (1,048,576 flows, 200 trees of depth 8: 585 against 599 for 64 x 4), 64 x 4 up to
-// 3 * 128 flows per unit (30,000 flows 39 against 83 with one lane per flow), 16 x 16 for few flows.
-TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n_rows, uint32_t n_cu, size_t* lds)
+// many uneven ones: 256 x 2 (1,048,576 flows, 200 trees of depth 8: 585 against 599 for 64 x 4; with 32 features three blocks a
+// unit, 1.1 to 1.2 times as fast as two with more staged), 64 x 4 up to 3 * 128 flows per unit (30,000 flows 39 against 83 with one
+// lane per flow; two classes leave half of its lanes idle: with 40 trees or more 256 x 2 from 256 flows per unit, 95,000 flows
+// x 60 trees of depth 8 1.3 times as fast), 16 x 16 for few flows.  One class, and with 32 features three, leave a lane idle
+// that 256 x 1 does not have (1,048,576 flows x 60 trees, three classes: depth 8 0.89, depth 1 0.76 times as long as 256 x 2).
+// fused: for the fused feature + forest kernel, which has no block of one lane per flow.
+TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n_rows, uint32_t n_cu, bool fused, size_t* lds)
 {
     const uint32_t few = 24u * n_cu, many = 3u * 128u * n_cu;
     auto fit = [&](TileShape s, size_t first, uint32_t least) {
@@ -192,10 +214,25 @@ TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n
         return s;
     }
     if (gbdt) {
-        fit(kTile256x2g, 80 * 1024, 1);
-        if (n_rows >= many && *lds <= 80 * 1024) return kTile256x2g; // (one block per unit is slower than the smaller tile)
+        const bool one_lane = a.n_classes == 1u || (a.n_classes == 3u && a.n_features <= 32u);
+        fit(one_lane ? kTile256x1g : kTile256x2g, 160 * 1024 / 3 - 256, 1);
+        if (one_lane && n_rows >= many && *lds <= 80 * 1024) return kTile256x1g;
+        if (n_rows >= (a.n_classes <= 2u && a.n_trees >= 40u ? 256u * n_cu : many) && *lds <= 80 * 1024) return kTile256x2g; // (one block per unit is slower than the smaller tile)
         fit(kTile64x4g, 40 * 1024, 1);
         return kTile64x4g;
+    }
+    bool one_lane;
+    if (fused)
+        one_lane = false;
+    else if (a.depth >= 13u)
+        one_lane = a.n_trees >= 64u && n_rows >= many;
+    else
+        one_lane = a.n_features <= 32u && (n_rows >= 1400u * n_cu
+                                               ? (a.depth <= 5u ? a.n_trees < 48u : a.depth <= 7u ? a.n_trees <= 12u : a.depth <= 9u && a.n_trees <= 4u)
+                                               : n_rows >= 750u * n_cu && a.depth <= 7u && a.n_trees <= 4u);
+    if (one_lane) {
+        fit(kTile256x1, 160 * 1024 / 3 - 256, 1);
+        if (*lds <= 80 * 1024) return kTile256x1;
     }
     if (a.n_trees < 48u) {
         fit(kTile128x4, 40 * 1024, 1);
@@ -285,14 +322,16 @@ int run_trees(sf_ctx* ctx, const char* who, const float* feat, uint32_t feat_ld,
     a.pred = out.pred;
     a.top = out.top_votes;
     a.leaf_idx = out.leaf_idx;
-    const TileShape shape = choose_shape(a, result_words, gbdt, n_flows, (uint32_t)ctx->n_cu, &lds);
+    const TileShape shape = choose_shape(a, result_words, gbdt, n_flows, (uint32_t)ctx->n_cu, false, &lds);
     if (lds > 160 * 1024) return sf::fail(ctx, SF_EUNSUPPORTED, "%s: %zu bytes of shared memory needed", who, lds);
     const int slot = sf::kLdsForest + 2 * (int)shape;
     switch (shape) {
-    case kTile128x8: return launch_votes<128, 8, 3, 1, false>(ctx, a, lds, slot);
-    case kTile128x4: return launch_votes<128, 4, 5, 2, false>(ctx, a, lds, slot);
-    case kTile64x8: return launch_votes<64, 8, 3, 1, false>(ctx, a, lds, slot);
+    case kTile128x8: return launch_votes<128, 8, 3, 2, false>(ctx, a, lds, slot);
+    case kTile128x4: return launch_votes<128, 4, 5, 4, false>(ctx, a, lds, slot);
+    case kTile64x8: return launch_votes<64, 8, 3, 2, false>(ctx, a, lds, slot);
     case kTile16x32: return launch_votes<16, 32, 5, 2, false>(ctx, a, lds, slot);
+    case kTile256x1: return launch_votes<256, 1, 10, 5, false>(ctx, a, lds, slot);
+    case kTile256x1g: return launch_votes<256, 1, 10, 5, true>(ctx, a, lds, slot);
     case kTile256x2g: return launch_votes<256, 2, 5, 2, true>(ctx, a, lds, slot);
     case kTile64x4g: return launch_votes<64, 4, 5, 2, true>(ctx, a, lds, slot);
     default: return launch_votes<16, 16, 5, 2, true>(ctx, a, lds, slot);
@@ -324,7 +363,7 @@ int forest_setup(sf_ctx* ctx, const char* who, const sf_forest* f, uint32_t feat
 
 sfforest::TileShape forest_shape(sfforest::FastArgs& a, uint32_t result_words, uint32_t n_rows, uint32_t n_cu, size_t* lds)
 {
-    return choose_shape(a, result_words, false, n_rows, n_cu, lds);
+    return choose_shape(a, result_words, false, n_rows, n_cu, true, lds);
 }
 } // namespace sf
 

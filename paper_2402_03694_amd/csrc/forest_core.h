@@ -90,12 +90,14 @@ inline size_t plan_lds(const FastArgs& a, uint32_t result_words, uint32_t fpb, s
 }
 
 // The shapes a block of the walk comes in (flows x lanes per flow), see choose_shape
-enum TileShape { kTile128x8, kTile128x4, kTile64x8, kTile16x32, kTile256x2g, kTile64x4g, kTile16x16g };
-constexpr uint32_t kTileFlows[] = {128, 128, 64, 16, 256, 64, 16};
+enum TileShape { kTile128x8, kTile128x4, kTile64x8, kTile16x32, kTile256x1, kTile256x2g, kTile64x4g, kTile16x16g, kTile256x1g };
+constexpr uint32_t kTileFlows[] = {128, 128, 64, 16, 256, 256, 64, 16, 256};
 
 // Shared memory of a block behind the feature tile xT ([n_features][FPB] floats, FPB flows per block):
 // vote counters (or margins), then the staged top records.
-// kIlp trees are walked at once per lane, kIlpTail in a last round when at most that many are left.
+// kIlp trees are walked at once per lane, in a last round as many as are left if that is at most kIlpTail (with idle slots
+// instead: 1,048,576 flows x 32 features, 4 trees of depth 13 on four lanes a flow 77 us against 62, 12 trees 155 against 120;
+// 64 trees on eight lanes 1.06 times as long).
 // A block is FPB * W lanes; W lanes share one flow: group g = lane index / FPB.  With FPB a multiple of 64 a
 // group is whole waves, so all lanes of a wave walk the same trees (their record gathers fall on the same few
 // cache lines) and everything derived from the tree number is scalar.
@@ -114,8 +116,8 @@ template <int FPB_, int W, int kIlp, int kIlpTail, bool WANT_LEAF, bool GBDT, bo
 __device__ __forceinline__ void forest_walk(const FastArgs& a, float* xT, uint32_t i, uint32_t row, bool live)
 {
     constexpr uint32_t FPB = FPB_, BS = FPB * W; // flows and lanes per block
-    constexpr uint32_t kColShift = FPB == 256 ? 10 : FPB == 128 ? 9 : FPB == 64 ? 8 : FPB == 32 ? 7 : FPB == 16 ? 6 : FPB == 8 ? 5 : 4; // log2(bytes per feature column)
-    static_assert((4u << (kColShift - 2)) == 4u * FPB, "flows per block is a power of two from 4 to 256");
+    constexpr uint32_t kColShift = FPB == 256 ? 10 : FPB == 128 ? 9 : FPB == 64 ? 8 : 6; // log2(bytes per feature column)
+    static_assert((1u << kColShift) == 4u * FPB, "16, 64, 128 or 256 flows per block");
     const uint32_t F = a.n_features, C = a.n_classes, T = a.n_trees;
     const uint32_t top_recs = recs_upto(a.top_pairs);      // records per tree held in shared memory
     // vote counters, 32 / vote_bits classes per word, one column per FLOW: [vote_words][FPB]; the W lanes of
@@ -196,13 +198,12 @@ __device__ __forceinline__ void forest_walk(const FastArgs& a, float* xT, uint32
 #pragma unroll
         for (int u = 0; u < G; ++u) {
             uint32_t t;
-            if (GBDT && W > 1) {
+            if (GBDT) {
                 const uint32_t q = q0 + u, rnd = my_classes ? q / my_classes : 0u;
                 cls[u] = grp + W * (q - rnd * my_classes);
                 t = my_classes ? rnd * C + cls[u] : T;
             } else {
                 t = (q0 + u) * W + grp;
-                if (GBDT) cls[u] = t % C;
             }
             o[u] = 0;
             tv[u] = q0 + u < per_grp && t < T;
@@ -264,19 +265,29 @@ __device__ __forceinline__ void forest_walk(const FastArgs& a, float* xT, uint32
         for (int u = 0; u < G; ++u) {
             if (tv[u]) {
                 const uint32_t l = lab[u] < C ? lab[u] : C - 1u; // clamp: a bad label must not leave the tile
-                // only this lane touches its column; the add is one shared-memory instruction
+                // the flow's W lanes add to one column, from different waves: the add has to be atomic (one instruction)
                 atomicAdd(&vcol[(l >> per_shift) * FPB], 1u << ((l & ((1u << per_shift) - 1u)) * a.vote_bits));
                 if (WANT_LEAF && live) a.leaf_idx[(size_t)i * T + tt[u]] = (uint16_t)leaf[u];
             }
         }
     };
     {
+        // a last round of up to kIlpTail trees runs with exactly as many (idle slots would gather like the others)
         const uint32_t rem = per_grp % (uint32_t)kIlp;
-        const bool short_tail = rem != 0 && rem <= (uint32_t)kIlpTail;
-        const uint32_t full_end = short_tail ? per_grp - rem : per_grp; // (a longer tail runs as a full group with idle slots)
+        const bool short_tail = rem <= (uint32_t)kIlpTail;
+        const uint32_t full_end = short_tail ? per_grp - rem : per_grp;
         uint32_t q0 = 0;
         for (; q0 < full_end; q0 += kIlp) walk_group(std::integral_constant<int, kIlp>{}, q0);
-        if (short_tail) walk_group(std::integral_constant<int, kIlpTail>{}, q0);
+        static_assert(kIlpTail >= 1 && kIlpTail <= 5, "rounds of one to five trees");
+        if (FPB < 64u) { // (small batches: a kernel's length counts, 93 trees of depth 6 on 1,000 flows 5.1 us against 5.3)
+            if (short_tail && rem != 0u) walk_group(std::integral_constant<int, kIlpTail>{}, q0);
+        } else if (short_tail && rem != 0u) {
+            if (rem == 1u) walk_group(std::integral_constant<int, 1>{}, q0);
+            if (kIlpTail >= 2 && rem == 2u) walk_group(std::integral_constant<int, 2>{}, q0);
+            if (kIlpTail >= 3 && rem == 3u) walk_group(std::integral_constant<int, 3>{}, q0);
+            if (kIlpTail >= 4 && rem == 4u) walk_group(std::integral_constant<int, 4>{}, q0);
+            if (kIlpTail >= 5 && rem == 5u) walk_group(std::integral_constant<int, 5>{}, q0);
+        }
     }
 #undef SF_PAIR_STEP
 #undef SF_FEAT_0
