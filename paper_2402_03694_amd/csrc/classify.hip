@@ -8,21 +8,22 @@
 // feature matrix (256 bytes per flow written, then read again) is neither written nor read for the
 // flows that stay with the fast model.
 //
-// The block has the walk's shape (several lanes per flow in different waves, see forest_core.h), so the
+// The block has the walk's shape.  Where several lanes in different waves share a flow (see forest_core.h), the
 // statistics are split between the waves too: a flow's 32 statistics of a window are four independent parts
 // (ordered sums and order statistics, of sizes and of times), and a wave computes one part of one window for
-// its flows.  A part needs one quantity in registers, so the kernel stays within the 64 registers at which a
-// compute unit holds 32 waves.
+// its flows.  A part needs one quantity in registers, so the kernel comes down to the 64 registers at which a
+// compute unit holds 32 waves (with windows of up to 16 packets 13 to 17 of them are spilled in the feature phase).
+// Large batches with few trees, which are the feature phase above all, go one lane per flow.
 //
 // Shared memory of a block: the tile [32 * windows][flows] floats; behind it, one after the other, the packets
-// of the tile's flows as columns, the scratch columns of the sorting networks, and what the walk needs (vote
-// counters, staged top records).
+// of the tile's flows as columns (several lanes per flow), the scratch columns of the sorting networks, and what the
+// walk needs (vote counters, staged top records).
 #include "featurize_core.h"
 #include "forest_core.h"
 
 namespace sf {
 int forest_setup(sf_ctx* ctx, const char* who, const sf_forest* f, uint32_t feat_ld, sfforest::FastArgs& a, uint32_t* result_words);
-sfforest::TileShape forest_shape(sfforest::FastArgs& a, uint32_t result_words, uint32_t n_rows, uint32_t n_cu, size_t* lds);
+sfforest::TileShape forest_shape(sfforest::FastArgs& a, uint32_t result_words, uint32_t n_rows, uint32_t n_cu, uint32_t dmax, size_t* lds);
 }
 
 namespace {
@@ -39,7 +40,8 @@ struct ClassifyArgs {
     const uint8_t* dir;
     uint32_t n_windows;
     uint32_t depth[kFusedWindows];
-    uint32_t wide_ok; // the packet arrays start on 8-byte (size, time, direction) boundaries
+    uint32_t wide_ok;  // the packet arrays start on 8-byte (size, time, direction) boundaries
+    uint32_t wide16_ok; // sizes and times on 16-byte ones
     FastArgs fa;      // n_flows, model, outputs, gate; n_features = 32 * n_windows
 };
 
@@ -79,22 +81,14 @@ __device__ __forceinline__ void window_part(uint32_t kind, const float (&x)[KMAX
     }
 }
 
-// FPB flows per block, W lanes per flow (the walk's shape).
-// One wave per 64 flows did all of this before (256 flows per block, one lane per flow).  The kernel, before -> after:
-// 1,048,576 flows x 16 packets, windows of 8 and 16, 100 trees of depth 12, a quarter of the rows kept: 572 -> 541 us;
-// windows of 5 and 10, depth 10, no rows: 468 -> 385 us; 97 ragged flows: 51 -> 11 us.  What bounds it: the walk's
-// gathers (forest_core.h) and about 80 us of vector arithmetic for the statistics; smaller tiles (64 x 8) overlap the
-// two no better and hold fewer staged records (whole pass 716 -> 773 us).
-template <int FPB_, int W, int ILP, int TAIL, int KMAX, bool KEEP_ROWS>
-__global__ __launch_bounds__(FPB_ * W, 8) void featurize_forest(ClassifyArgs c)
+// The features of a tile by parts: FPB flows, W >= 4 lanes per flow.
+template <int FPB_, int W, int KMAX>
+__device__ __forceinline__ void features_by_parts(const ClassifyArgs& c, float* xT, uint32_t* behind)
 {
     constexpr uint32_t FPB = FPB_, BS = FPB * W, SS = stage_stride(FPB), UNITS = feature_units(FPB, W);
     constexpr uint32_t P = KMAX / 2; // lanes that fetch one flow's packets, two packets each
     static_assert((FPB * P) % 64u == 0 && (P == 4 || P == 8), "every flow's packets are fetched by lanes of one wave, whole waves take part");
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const FastArgs& a = c.fa;
-    float* xT = reinterpret_cast<float*>(smem_raw); // [32 * windows][FPB]
-    uint32_t* behind = reinterpret_cast<uint32_t*>(xT + (size_t)a.n_features * FPB);
     const uint32_t tid = threadIdx.x, flow0 = blockIdx.x * FPB;
     for (uint32_t q = tid; q < FPB * P; q += BS) {
         // consecutive lanes hold consecutive packets of a flow and the flows follow each other in memory, so the
@@ -180,15 +174,80 @@ __global__ __launch_bounds__(FPB_ * W, 8) void featurize_forest(ClassifyArgs c)
                 window_part<8, KMAX>(kind, x, dmask, m, col, FPB, dst);
         }
     }
+}
+
+// The features of a tile of 256 flows, one lane per flow: all statistics of a flow are one lane's serial chain, but its packets
+// are fetched straight into registers and a comparison serves all of a window's statistics.
+template <int KMAX>
+__device__ __forceinline__ void features_by_lanes(const ClassifyArgs& c, float* xT, uint32_t* behind)
+{
+    constexpr uint32_t FPB = 256;
+    const uint32_t tid = threadIdx.x, i = blockIdx.x * FPB + tid;
+    // a lane past the last flow works on the last flow (its loads stay inside the arrays)
+    const uint32_t flow = i < c.fa.n_flows ? i : c.fa.n_flows - 1u;
+    uint32_t o = c.off[flow], e = c.off[flow + 1];
+    o = o < c.n_pkts ? o : c.n_pkts; // clamp: malformed offsets must not leave the arrays
+    e = e < c.n_pkts ? e : c.n_pkts;
+    const uint32_t n = e > o ? e - o : 0u, dmax = c.depth[c.n_windows - 1u];
+    const int avail = (int)(n < dmax ? n : dmax);
+    float s[KMAX], t[KMAX];
+    uint32_t dmask = 0;
+    if (avail == KMAX && (o & 7u) == 0 && c.wide16_ok) {
+        // whole window present and 16-byte aligned (array bases included): wide loads
+        sffeat::RawPackets<KMAX> raw;
+        sffeat::load_wide<KMAX>(c.size, c.iat, c.dir, o, raw);
+        sffeat::decode_wide<KMAX>(raw, s, t, dmask);
+    } else {
+        sffeat::load_each<KMAX>(c.size, c.iat, c.dir, o, avail, s, t, dmask);
+    }
+    // a time with its sign bit set anywhere in the wave: the order statistics take the general path
+    uint32_t sign_bits = 0;
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j) sign_bits |= __float_as_uint(t[j]);
+    const bool signed_times = __any((int)(sign_bits >> 31));
+    // windows from the last to the first: every one but the first takes the first window's columns (not written yet) as the
+    // scratch of its sorting networks, the first the space behind the tile
+    for (int w = (int)c.n_windows - 1; w >= 0; --w) {
+        const int dw = (int)c.depth[w];
+        const int m = avail < dw ? avail : dw;
+        // every address below is the lane's own column: no two lanes (or waves) share a word
+        uint32_t* col = (w > 0 ? reinterpret_cast<uint32_t*>(xT) : behind) + tid;
+        float* dst = xT + (size_t)(32 * w) * FPB + tid;
+        // the smallest network that covers every lane's window (wave-uniform choice)
+        if (KMAX >= 16 && __any(m > 8))
+            sffeat::window_stats<false, KMAX, KMAX>(s, t, dmask, m, signed_times, col, FPB, dst, FPB);
+        else
+            sffeat::window_stats<false, 8, KMAX>(s, t, dmask, m, signed_times, col, FPB, dst, FPB);
+    }
+}
+
+// FPB flows per block, W lanes per flow (the walk's shape).
+// One wave per 64 flows did all of this before (256 flows per block, one lane per flow).  The kernel, before -> after:
+// 1,048,576 flows x 16 packets, windows of 8 and 16, 100 trees of depth 12, a quarter of the rows kept: 572 -> 541 us;
+// windows of 5 and 10, depth 10, no rows: 468 -> 385 us; 97 ragged flows: 51 -> 11 us.  What bounds it: the walk's
+// gathers (forest_core.h) and about 80 us of vector arithmetic for the statistics; smaller tiles (64 x 8) overlap the
+// two no better and hold fewer staged records (whole pass 716 -> 773 us).
+template <int FPB_, int W, int ILP, int TAIL, int KMAX, bool KEEP_ROWS>
+__global__ __launch_bounds__(FPB_ * W, W == 1 ? 2 : 8) void featurize_forest(ClassifyArgs c)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    const FastArgs& a = c.fa;
+    float* xT = reinterpret_cast<float*>(smem_raw); // [32 * windows][flows]
+    uint32_t* behind = reinterpret_cast<uint32_t*>(xT + (size_t)a.n_features * FPB_);
+    if constexpr (W == 1)
+        features_by_lanes<KMAX>(c, xT, behind);
+    else
+        features_by_parts<FPB_, W, KMAX>(c, xT, behind);
     __syncthreads(); // the space behind the tile is free: the walk may stage its records there
-    const uint32_t i = flow0 + tid % FPB;
-    forest_walk<FPB_, W, ILP, TAIL, false, false, KEEP_ROWS>(a, xT, i, i, i < a.n_flows);
+    const uint32_t i = blockIdx.x * FPB_ + threadIdx.x % FPB_;
+    forest_walk<FPB_, W, ILP, TAIL, false, false, false, KEEP_ROWS>(a, xT, i, i, i < a.n_flows);
 }
 
 template <int FPB, int W, int ILP, int TAIL, int KMAX, bool KEEP_ROWS>
 int launch_fused(sf_ctx* ctx, const ClassifyArgs& c, size_t lds, int slot)
 {
-    const size_t behind = stage_words(KMAX, FPB) > scratch_words(KMAX, FPB, W) ? stage_words(KMAX, FPB) : scratch_words(KMAX, FPB, W);
+    const size_t parts = stage_words(KMAX, FPB) > scratch_words(KMAX, FPB, W) ? stage_words(KMAX, FPB) : scratch_words(KMAX, FPB, W);
+    const size_t behind = W == 1 ? (size_t)(c.depth[0] > 8u ? 16 : 8) * FPB : parts; // (one lane per flow: the first window's network)
     const size_t lds_feat = ((size_t)c.fa.n_features * FPB + behind) * 4;
     if (lds_feat > lds) lds = lds_feat;
     auto* kernel = featurize_forest<FPB, W, ILP, TAIL, KMAX, KEEP_ROWS>;
@@ -205,7 +264,8 @@ int launch_shape(sf_ctx* ctx, const ClassifyArgs& c, TileShape shape, size_t lds
     case kTile128x8: return launch_fused<128, 8, 3, 1, KMAX, KEEP_ROWS>(ctx, c, lds, slot);
     case kTile128x4: return launch_fused<128, 4, 5, 2, KMAX, KEEP_ROWS>(ctx, c, lds, slot + 1);
     case kTile64x8: return launch_fused<64, 8, 3, 1, KMAX, KEEP_ROWS>(ctx, c, lds, slot + 2);
-    default: return launch_fused<16, 32, 5, 2, KMAX, KEEP_ROWS>(ctx, c, lds, slot + 3);
+    case kTile16x32: return launch_fused<16, 32, 5, 2, KMAX, KEEP_ROWS>(ctx, c, lds, slot + 3);
+    default: return launch_fused<256, 1, 10, 5, KMAX, KEEP_ROWS>(ctx, c, lds, slot + 4);
     }
 }
 
@@ -274,6 +334,7 @@ int run_features_and_forest(sf_ctx* ctx, const char* who, const sf_packets* pk, 
     c.n_windows = cfg->n_windows;
     for (uint32_t w = 0; w < kFusedWindows; ++w) c.depth[w] = w < cfg->n_windows ? cfg->depth[w] : 0;
     c.wide_ok = (((uintptr_t)c.size | (uintptr_t)c.iat | (uintptr_t)c.dir) & 7u) == 0;
+    c.wide16_ok = c.wide_ok && (((uintptr_t)c.size | (uintptr_t)c.iat) & 15u) == 0;
     c.fa.n_flows = n;
     c.fa.n_rows = n;
     c.fa.pred = pred;
@@ -286,8 +347,8 @@ int run_features_and_forest(sf_ctx* ctx, const char* who, const sf_packets* pk, 
     c.fa.n_vmin = n_vmin;
     for (uint32_t k = 0; k < SF_MAX_CLASSES; ++k) c.fa.vmin[k] = host_vmin[k < n_vmin ? k : n_vmin - 1];
     size_t lds = 0;
-    const TileShape shape = sf::forest_shape(c.fa, result_words, n, (uint32_t)ctx->n_cu, &lds);
-    const int slot = sf::kLdsClassify + (keep_rows ? 8 : 0) + (dmax > 8 ? 4 : 0);
+    const TileShape shape = sf::forest_shape(c.fa, result_words, n, (uint32_t)ctx->n_cu, dmax, &lds);
+    const int slot = sf::kLdsClassify + (keep_rows ? 10 : 0) + (dmax > 8 ? 5 : 0);
     if (dmax <= 8) return keep_rows ? launch_shape<8, true>(ctx, c, shape, lds, slot) : launch_shape<8, false>(ctx, c, shape, lds, slot);
     return keep_rows ? launch_shape<16, true>(ctx, c, shape, lds, slot) : launch_shape<16, false>(ctx, c, shape, lds, slot);
 }

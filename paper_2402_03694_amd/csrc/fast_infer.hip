@@ -97,7 +97,7 @@ __global__ __launch_bounds__(FPB_ * W) void forest_votes(FastArgs a)
             for (uint32_t f = first; f < F; f += W) xT[f * FPB + slot] = x[f];
         }
     }
-    forest_walk<FPB_, W, ILP, TAIL, WANT_LEAF, GBDT, false>(a, xT, i, row, live);
+    forest_walk<FPB_, W, ILP, TAIL, (!GBDT && FPB >= 64u), WANT_LEAF, GBDT, false>(a, xT, i, row, live);
 }
 
 template <int FPB, int W, int ILP, int TAIL, bool GBDT>
@@ -170,6 +170,27 @@ int check_model(sf_ctx* ctx, const char* who, const TreeModel& m)
     return SF_OK;
 }
 
+// The most trees for which the fused feature + forest kernel does a batch with one lane per flow (256 flows a block).  Splitting a
+// flow's statistics between waves costs a third more instructions and pays where lanes are few or the walk is long; with few
+// trees the kernel is its feature phase.  How well the blocks fill their rounds decides the rest (`full`, percent: two blocks a
+// unit, with one window three).  One lane : best other shape, in us, ten classes: 1,048,576 flows of 16 packets, windows 8, 16:
+// 5 trees 98 : 136, 47 trees of depth 4 216 : 245; window 16: 5 trees 64 : 94, 47 trees 130 : 155; ragged, window 8: 5 trees 50 : 66,
+// 32 trees of depth 4 92 : 101, of depth 12 equal.  100,000 flows, windows 8, 16 (one round, 76 %): 5 trees 15 : 20.5, 47 trees 31 : 32.
+// 140,000 (a second round with 7 % of its blocks): 8 trees equal, 47 trees 1.25 times as long.
+uint32_t fused_one_lane_trees(uint32_t depth, uint32_t n_windows, uint32_t dmax, uint32_t n_rows, uint32_t n_cu)
+{
+    if (n_rows < 150u * n_cu) return 0u;
+    const uint32_t blocks = (n_rows - 1u) / 256u + 1u, at_once = (n_windows == 1u ? 3u : 2u) * n_cu;
+    const uint32_t rounds = (blocks + at_once - 1u) / at_once, full = (uint32_t)(100ull * blocks / ((uint64_t)rounds * at_once));
+    if (dmax <= 8u) {
+        if (n_windows == 2u) return full < 75u ? 0u : 6u;
+        if (full < 45u) return 0u;
+        return rounds <= 2u || depth > 8u ? 6u : depth <= 6u ? 80u : 24u;
+    }
+    if (n_windows == 2u) return full < 60u ? 6u : rounds == 1u ? 47u : full < 90u ? 24u : 64u;
+    return full < 45u ? 6u : full < 60u ? 12u : full < 75u ? 32u : 64u;
+}
+
 // The shape of a block and its shared memory, by batch size and model.  All figures are the walk's time in
 // microseconds for 64 features and 100 trees of depth 12 unless another model is named.
 //   few flows: 16 flows x 32 lanes, nothing staged, so that even a small batch gives every compute unit a block and
@@ -194,8 +215,8 @@ int check_model(sf_ctx* ctx, const char* who, const TreeModel& m)
 // lane per flow; two classes leave half of its lanes idle: with 40 trees or more 256 x 2 from 256 flows per unit, 95,000 flows
 // x 60 trees of depth 8 1.3 times as fast), 16 x 16 for few flows.  One class, and with 32 features three, leave a lane idle
 // that 256 x 1 does not have (1,048,576 flows x 60 trees, three classes: depth 8 0.89, depth 1 0.76 times as long as 256 x 2).
-// fused: for the fused feature + forest kernel, which has no block of one lane per flow.
-TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n_rows, uint32_t n_cu, bool fused, size_t* lds)
+// dmax: packets of the deepest window (fused kernel), 0 for the stand-alone walk.
+TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n_rows, uint32_t n_cu, uint32_t dmax, size_t* lds)
 {
     const uint32_t few = 24u * n_cu, many = 3u * 128u * n_cu;
     auto fit = [&](TileShape s, size_t first, uint32_t least) {
@@ -222,8 +243,8 @@ TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n
         return kTile64x4g;
     }
     bool one_lane;
-    if (fused)
-        one_lane = false;
+    if (dmax)
+        one_lane = a.n_trees <= fused_one_lane_trees(a.depth, a.n_features / 32u, dmax, n_rows, n_cu);
     else if (a.depth >= 13u)
         one_lane = a.n_trees >= 64u && n_rows >= many;
     else
@@ -322,7 +343,7 @@ int run_trees(sf_ctx* ctx, const char* who, const float* feat, uint32_t feat_ld,
     a.pred = out.pred;
     a.top = out.top_votes;
     a.leaf_idx = out.leaf_idx;
-    const TileShape shape = choose_shape(a, result_words, gbdt, n_flows, (uint32_t)ctx->n_cu, false, &lds);
+    const TileShape shape = choose_shape(a, result_words, gbdt, n_flows, (uint32_t)ctx->n_cu, 0u, &lds);
     if (lds > 160 * 1024) return sf::fail(ctx, SF_EUNSUPPORTED, "%s: %zu bytes of shared memory needed", who, lds);
     const int slot = sf::kLdsForest + 2 * (int)shape;
     switch (shape) {
@@ -361,9 +382,9 @@ int forest_setup(sf_ctx* ctx, const char* who, const sf_forest* f, uint32_t feat
     return setup_trees(ctx, who, m, false, feat_ld, a, result_words);
 }
 
-sfforest::TileShape forest_shape(sfforest::FastArgs& a, uint32_t result_words, uint32_t n_rows, uint32_t n_cu, size_t* lds)
+sfforest::TileShape forest_shape(sfforest::FastArgs& a, uint32_t result_words, uint32_t n_rows, uint32_t n_cu, uint32_t dmax, size_t* lds)
 {
-    return choose_shape(a, result_words, false, n_rows, n_cu, true, lds);
+    return choose_shape(a, result_words, false, n_rows, n_cu, dmax, lds);
 }
 } // namespace sf
 

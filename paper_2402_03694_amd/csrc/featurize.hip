@@ -41,47 +41,6 @@ __device__ __forceinline__ void flow_range(const FeatArgs& a, uint32_t i, uint32
     n = e - b;
 }
 
-// A flow's packet records as loaded by the wide path (whole deepest window present, 16-byte aligned)
-template <int KMAX>
-struct RawPackets {
-    uint4 sz[KMAX / 8];
-    float4 tm[KMAX / 4];
-    uint2 dr[KMAX / 8];
-};
-
-template <int KMAX>
-__device__ __forceinline__ void load_wide(const FeatArgs& a, uint32_t o, RawPackets<KMAX>& r)
-{
-#pragma unroll
-    for (int c = 0; c < KMAX / 8; ++c) {
-        r.sz[c] = *reinterpret_cast<const uint4*>(a.size + o + 8 * c);
-        r.tm[2 * c] = *reinterpret_cast<const float4*>(a.iat + o + 8 * c);
-        r.tm[2 * c + 1] = *reinterpret_cast<const float4*>(a.iat + o + 8 * c + 4);
-        r.dr[c] = *reinterpret_cast<const uint2*>(a.dir + o + 8 * c);
-    }
-}
-
-template <int KMAX>
-__device__ __forceinline__ void decode_wide(const RawPackets<KMAX>& r, float (&s)[KMAX], float (&t)[KMAX], uint32_t& dmask)
-{
-    dmask = 0;
-#pragma unroll
-    for (int c = 0; c < KMAX / 8; ++c) {
-        const uint32_t w[4] = {r.sz[c].x, r.sz[c].y, r.sz[c].z, r.sz[c].w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            s[8 * c + 2 * k] = (float)(w[k] & 0xFFFFu);
-            s[8 * c + 2 * k + 1] = (float)(w[k] >> 16);
-        }
-        const float4 t0 = r.tm[2 * c], t1 = r.tm[2 * c + 1];
-        t[8 * c + 0] = t0.x; t[8 * c + 1] = t0.y; t[8 * c + 2] = t0.z; t[8 * c + 3] = t0.w;
-        t[8 * c + 4] = t1.x; t[8 * c + 5] = t1.y; t[8 * c + 6] = t1.z; t[8 * c + 7] = t1.w;
-        const uint32_t dw[2] = {r.dr[c].x, r.dr[c].y};
-#pragma unroll
-        for (int k = 0; k < 8; ++k) dmask |= ((dw[k >> 2] >> (8 * (k & 3))) & 1u) << (8 * c + k);
-    }
-}
-
 // ---- windows deeper than 32 packets ---------------------------------------------------------------------
 // A lane keeps at most 32 packets in registers (a 64-element network per lane needs more registers than a
 // lane has, and its straight-line code no longer fits the instruction cache).  A flow whose window holds
@@ -283,21 +242,11 @@ __global__ __launch_bounds__(kWave, (KMAX <= 16 ? 3 : (LONG ? 1 : 2))) void feat
     uint32_t dmask = 0;
     if (avail == KMAX && (o & 7u) == 0 && a.wide_ok) {
         // whole window present and 16-byte aligned (array bases included): wide loads
-        RawPackets<KMAX> raw;
-        load_wide<KMAX>(a, o, raw);
-        decode_wide<KMAX>(raw, s, t, dmask);
+        sffeat::RawPackets<KMAX> raw;
+        sffeat::load_wide<KMAX>(a.size, a.iat, a.dir, o, raw);
+        sffeat::decode_wide<KMAX>(raw, s, t, dmask);
     } else {
-#pragma unroll
-        for (int j = 0; j < KMAX; ++j) {
-            if (j < avail) {
-                s[j] = (float)a.size[o + j];
-                t[j] = a.iat[o + j];
-                dmask |= (uint32_t)(a.dir[o + j] & 1u) << j;
-            } else {
-                s[j] = 0.f;
-                t[j] = 0.f;
-            }
-        }
+        sffeat::load_each<KMAX>(a.size, a.iat, a.dir, o, avail, s, t, dmask);
     }
     // a time with its sign bit set anywhere in the wave: the order statistics take the general path
     uint32_t sign_bits = 0;

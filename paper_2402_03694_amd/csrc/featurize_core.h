@@ -28,6 +28,65 @@
 
 namespace sffeat {
 
+// A flow's packet records as loaded by the wide path (whole deepest window present, 16-byte aligned)
+template <int KMAX>
+struct RawPackets {
+    uint4 sz[KMAX / 8];
+    float4 tm[KMAX / 4];
+    uint2 dr[KMAX / 8];
+};
+
+template <int KMAX>
+__device__ __forceinline__ void load_wide(const uint16_t* size, const float* iat, const uint8_t* dir, uint32_t o, RawPackets<KMAX>& r)
+{
+#pragma unroll
+    for (int c = 0; c < KMAX / 8; ++c) {
+        r.sz[c] = *reinterpret_cast<const uint4*>(size + o + 8 * c);
+        r.tm[2 * c] = *reinterpret_cast<const float4*>(iat + o + 8 * c);
+        r.tm[2 * c + 1] = *reinterpret_cast<const float4*>(iat + o + 8 * c + 4);
+        r.dr[c] = *reinterpret_cast<const uint2*>(dir + o + 8 * c);
+    }
+}
+
+template <int KMAX>
+__device__ __forceinline__ void decode_wide(const RawPackets<KMAX>& r, float (&s)[KMAX], float (&t)[KMAX], uint32_t& dmask)
+{
+    dmask = 0;
+#pragma unroll
+    for (int c = 0; c < KMAX / 8; ++c) {
+        const uint32_t w[4] = {r.sz[c].x, r.sz[c].y, r.sz[c].z, r.sz[c].w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            s[8 * c + 2 * k] = (float)(w[k] & 0xFFFFu);
+            s[8 * c + 2 * k + 1] = (float)(w[k] >> 16);
+        }
+        const float4 t0 = r.tm[2 * c], t1 = r.tm[2 * c + 1];
+        t[8 * c + 0] = t0.x; t[8 * c + 1] = t0.y; t[8 * c + 2] = t0.z; t[8 * c + 3] = t0.w;
+        t[8 * c + 4] = t1.x; t[8 * c + 5] = t1.y; t[8 * c + 6] = t1.z; t[8 * c + 7] = t1.w;
+        const uint32_t dw[2] = {r.dr[c].x, r.dr[c].y};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) dmask |= ((dw[k >> 2] >> (8 * (k & 3))) & 1u) << (8 * c + k);
+    }
+}
+
+// The first `avail` packets from o on, one by one; zeros behind them
+template <int KMAX>
+__device__ __forceinline__ void load_each(const uint16_t* size, const float* iat, const uint8_t* dir, uint32_t o, int avail, float (&s)[KMAX],
+                                          float (&t)[KMAX], uint32_t& dmask)
+{
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j) {
+        if (j < avail) {
+            s[j] = (float)size[o + j];
+            t[j] = iat[o + j];
+            dmask |= (uint32_t)(dir[o + j] & 1u) << j;
+        } else {
+            s[j] = 0.f;
+            t[j] = 0.f;
+        }
+    }
+}
+
 // float -> unsigned key with the same order (negative values: all bits flipped, others: sign set)
 __device__ __forceinline__ uint32_t order_key(float x)
 {

@@ -95,9 +95,10 @@ constexpr uint32_t kTileFlows[] = {128, 128, 64, 16, 256, 256, 64, 16, 256};
 
 // Shared memory of a block behind the feature tile xT ([n_features][FPB] floats, FPB flows per block):
 // vote counters (or margins), then the staged top records.
-// kIlp trees are walked at once per lane, in a last round as many as are left if that is at most kIlpTail (with idle slots
-// instead: 1,048,576 flows x 32 features, 4 trees of depth 13 on four lanes a flow 77 us against 62, 12 trees 155 against 120;
-// 64 trees on eight lanes 1.06 times as long).
+// kIlp trees are walked at once per lane, kIlpTail in a last round when at most that many are left; EXACT: in that round just as
+// many as are left (the walk alone in blocks of whole waves: 1,048,576 flows x 32 features, 4 trees of depth 13 on four lanes a
+// flow 77 us against 62, 12 trees 155 against 120, 64 trees on eight lanes 1.06 times as long; not in small batches and in the
+// fused kernel, where the longer kernel costs as much: 93 trees of depth 6 on 1,000 flows 5.1 us against 5.3).
 // A block is FPB * W lanes; W lanes share one flow: group g = lane index / FPB.  With FPB a multiple of 64 a
 // group is whole waves, so all lanes of a wave walk the same trees (their record gathers fall on the same few
 // cache lines) and everything derived from the tree number is scalar.
@@ -112,7 +113,7 @@ constexpr uint32_t kTileFlows[] = {128, 128, 64, 16, 256, 256, 64, 16, 256};
 // live: false for lanes past the end (they walk a valid tile column and write nothing).
 // The caller has filled xT (no barrier needed before the call: this function synchronises the block
 // before the first read of the tile).
-template <int FPB_, int W, int kIlp, int kIlpTail, bool WANT_LEAF, bool GBDT, bool KEEP_ROWS>
+template <int FPB_, int W, int kIlp, int kIlpTail, bool EXACT, bool WANT_LEAF, bool GBDT, bool KEEP_ROWS>
 __device__ __forceinline__ void forest_walk(const FastArgs& a, float* xT, uint32_t i, uint32_t row, bool live)
 {
     constexpr uint32_t FPB = FPB_, BS = FPB * W; // flows and lanes per block
@@ -272,21 +273,22 @@ __device__ __forceinline__ void forest_walk(const FastArgs& a, float* xT, uint32
         }
     };
     {
-        // a last round of up to kIlpTail trees runs with exactly as many (idle slots would gather like the others)
+        // A last round of up to kIlpTail trees runs as one of kIlpTail (a longer one as a full one with idle slots), with EXACT as
+        // one of just as many trees: idle slots gather like the others.
         const uint32_t rem = per_grp % (uint32_t)kIlp;
-        const bool short_tail = rem <= (uint32_t)kIlpTail;
+        const bool short_tail = rem != 0 && rem <= (uint32_t)kIlpTail;
         const uint32_t full_end = short_tail ? per_grp - rem : per_grp;
         uint32_t q0 = 0;
         for (; q0 < full_end; q0 += kIlp) walk_group(std::integral_constant<int, kIlp>{}, q0);
-        static_assert(kIlpTail >= 1 && kIlpTail <= 5, "rounds of one to five trees");
-        if (FPB < 64u) { // (small batches: a kernel's length counts, 93 trees of depth 6 on 1,000 flows 5.1 us against 5.3)
-            if (short_tail && rem != 0u) walk_group(std::integral_constant<int, kIlpTail>{}, q0);
-        } else if (short_tail && rem != 0u) {
-            if (rem == 1u) walk_group(std::integral_constant<int, 1>{}, q0);
-            if (kIlpTail >= 2 && rem == 2u) walk_group(std::integral_constant<int, 2>{}, q0);
-            if (kIlpTail >= 3 && rem == 3u) walk_group(std::integral_constant<int, 3>{}, q0);
-            if (kIlpTail >= 4 && rem == 4u) walk_group(std::integral_constant<int, 4>{}, q0);
-            if (kIlpTail >= 5 && rem == 5u) walk_group(std::integral_constant<int, 5>{}, q0);
+        if (EXACT) {
+            static_assert(!EXACT || (kIlpTail >= 1 && kIlpTail <= 5), "rounds of one to five trees");
+            if (short_tail && rem == 1u) walk_group(std::integral_constant<int, 1>{}, q0);
+            if (kIlpTail >= 2 && short_tail && rem == 2u) walk_group(std::integral_constant<int, 2>{}, q0);
+            if (kIlpTail >= 3 && short_tail && rem == 3u) walk_group(std::integral_constant<int, 3>{}, q0);
+            if (kIlpTail >= 4 && short_tail && rem == 4u) walk_group(std::integral_constant<int, 4>{}, q0);
+            if (kIlpTail >= 5 && short_tail && rem == 5u) walk_group(std::integral_constant<int, 5>{}, q0);
+        } else if (short_tail) {
+            walk_group(std::integral_constant<int, kIlpTail>{}, q0);
         }
     }
 #undef SF_PAIR_STEP

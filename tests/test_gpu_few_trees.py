@@ -1,6 +1,7 @@
-"""Forests of few trees, and of trees too deep for the caches, in batches large enough for one lane per flow: the walk on both
-sides of the lines in fast_infer.hip, with a last block that is nearly empty; and every length of a last round of trees where
-several lanes share a flow.  Votes, predictions, leaf numbers and margins bit for bit against the oracle."""
+"""Forests of few trees, and of trees too deep for the caches, in batches large enough for one lane per flow: the walk alone and
+the fused feature + forest kernel on both sides of the lines in fast_infer.hip, with a last block that is nearly empty; and
+every length of a last round of trees where several lanes share a flow.  Votes, predictions, leaf numbers, scores and kept rows
+bit for bit against the oracle."""
 from types import SimpleNamespace
 
 import numpy as np
@@ -11,6 +12,7 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 CU = 256                                  # compute units of the device
+SENTINEL = -777.0
 
 
 def _model(rng, T, d, C, F, feat):
@@ -48,6 +50,59 @@ def test_walk(n, F, T, d, C, pad):
     assert np.array_equal(_u16(g_pred), pred) and np.array_equal(_u16(g_top), top) and np.array_equal(_u16(g_votes), votes)
     if want_leaf:
         assert np.array_equal(_u16(g_leaf), leaf)
+
+
+ROUND2, ROUND3 = 512 * CU, 768 * CU       # flows in one round of blocks, with two windows and with one
+
+
+@pytest.mark.parametrize("n,depths,longest,T,d,C,negative,shift,skew,pad", [
+    (150 * CU, (8, 16), 20, 6, 5, 10, False, 0, 0, 0), (150 * CU - 1, (8, 16), 20, 6, 5, 10, False, 0, 0, 0), (150 * CU + 1, (5, 12), 14, 1, 12, 4, True, 1, 0, 3),
+    (ROUND2 * 6 // 10 + 300, (1, 16), 16, 47, 3, 33, True, 0, 1, 0), (ROUND2 + 77, (8, 16), 16, 6, 4, 10, False, 0, 0, 1), (ROUND2 + 77, (8, 16), 16, 7, 4, 10, False, 0, 0, 0),
+    (2 * ROUND2 - 5, (9, 16), 18, 64, 2, 10, False, 0, 0, 0), (ROUND2 * 8 // 10, (3, 7), 9, 6, 6, 10, True, 0, 1, 0), (ROUND2 * 8 // 10, (3, 7), 9, 7, 6, 10, False, 3, 0, 0),
+    (150 * CU + 9, (16,), 16, 6, 8, 10, True, 0, 0, 0), (ROUND3 // 2 + 1, (9,), 30, 12, 4, 5, False, 1, 0, 2), (ROUND3 * 7 // 10, (16,), 16, 32, 3, 10, False, 0, 1, 0),
+    (ROUND3 - 100, (12,), 16, 64, 3, 10, True, 0, 0, 0), (ROUND3 // 2 + 33, (8,), 8, 6, 5, 10, True, 0, 0, 0), (ROUND3 // 2 + 33, (1,), 3, 5, 13, 10, False, 2, 1, 1),
+    (2 * ROUND3 + 77, (4,), 6, 50, 2, 10, True, 0, 0, 0), (2 * ROUND3 + 1, (8,), 9, 20, 7, 10, False, 0, 0, 0)])
+def test_fused(n, depths, longest, T, d, C, negative, shift, skew, pad):
+    import torch
+    import paper_2402_03694_amd as sf
+    rng = np.random.default_rng(n + 31 * T + d)
+    full = rng.random(n) < 0.5
+    lens = np.where(full, min(longest, 16), rng.integers(0, longest + 1, size=n))
+    off = np.zeros(n + 1, np.uint32)
+    off[1:] = np.cumsum(lens)
+    off += np.uint32(shift)                # (the first packets of the arrays belong to no flow)
+    m = int(off[-1])
+    iat = np.exp(rng.normal(-6, 2, size=m)).astype(np.float32)
+    if negative:                           # some waves with, most without
+        iat[rng.integers(0, m, size=300)] *= -1
+    pk = SimpleNamespace(n_flows=n, flow_off=off, pkt_size=rng.integers(0, 65536, size=m, dtype=np.uint16), pkt_iat=iat,
+                         pkt_dir=rng.integers(0, 2, size=m, dtype=np.uint8), pkt_hdr=None)
+    feat, _ = oracle.featurize(pk.flow_off, pk.pkt_size, pk.pkt_iat, pk.pkt_dir, depths, n_threads=8)
+    F = 32 * len(depths)
+    model = _model(rng, T, d, C, F, feat[:4096])
+    _, pred, top, _ = oracle.fast_infer(feat, model, want_votes=False, n_threads=8)
+    vmin = rng.integers(int(np.median(top)), int(top.max()) + 2, size=C).astype(int).tolist()
+    dev = "cuda:0"
+    d_pk = sf.packets_to_device(pk, dev)
+    if skew:                               # arrays one element off the alignment of the wide loads
+        off_by = lambda t: torch.cat([t[:1], t])[1:]
+        d_pk = sf.DevicePackets(d_pk.flow_off, off_by(d_pk.pkt_size), off_by(d_pk.pkt_iat), off_by(d_pk.pkt_dir))
+    forest = sf.forest_to_device(model, dev)
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(n, T, d))
+    got = torch.full((n, F + pad), SENTINEL, dtype=torch.float32, device=dev)
+    g = lambda: torch.full((n,), -1, dtype=torch.int16, device=dev)
+    g_pred, g_top, g_lab = g(), g(), g()
+    ctx.sf_featurize_fast_infer(d_pk, list(depths), forest, vmin, got, g_pred, g_top, labels=g_lab)
+    torch.cuda.synchronize()
+    assert np.array_equal(_u16(g_pred), pred) and np.array_equal(_u16(g_top), top) and np.array_equal(_u16(g_lab), pred)
+    keep = top < np.asarray(vmin)[pred]
+    got = got.cpu().numpy()
+    assert np.array_equal(got[keep][:, :F].view(np.uint32), feat[keep].view(np.uint32))
+    assert np.all(got[~keep] == SENTINEL) and np.all(got[:, F:] == SENTINEL)
+    g_pred, g_top = g(), g()               # no rows wanted
+    ctx.sf_featurize_fast_infer(d_pk, list(depths), forest, vmin, None, g_pred, g_top)
+    torch.cuda.synchronize()
+    assert np.array_equal(_u16(g_pred), pred) and np.array_equal(_u16(g_top), top)
 
 
 @pytest.mark.parametrize("n,F,T,d,C", [(384 * CU + 5, 32, 9, 5, 3), (384 * CU, 20, 31, 4, 3), (384 * CU + 3, 64, 9, 4, 3), (384 * CU + 200, 64, 13, 3, 1),
@@ -102,3 +157,22 @@ def test_walk_rate():
     pred, top = (torch.empty(n, dtype=torch.int16, device=dev) for _ in range(2))
     copy = torch.empty_like(feat)
     assert _median_us(lambda: ctx.sf_fast_infer(feat, model, pred, top)) <= 1.13 * _median_us(lambda: copy.copy_(feat))
+
+
+def test_fused_rate():
+    """Features and five trees in one call take at most 1.32 of the time of the features alone (1.14; four lanes a flow 1.55)."""
+    import torch
+    import paper_2402_03694_amd as sf
+    n, dev, depths = 1 << 20, "cuda:0", [8, 16]
+    rng = np.random.default_rng(2)
+    m = 16 * n
+    pk = sf.DevicePackets(torch.arange(0, m + 1, 16, dtype=torch.int32, device=dev), torch.randint(40, 1500, (m,), dtype=torch.int16, device=dev),
+                          torch.rand(m, device=dev), torch.randint(0, 2, (m,), dtype=torch.uint8, device=dev))
+    feat = torch.empty((n, 64), device=dev)
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(n, 5, 4))
+    ctx.sf_featurize(pk, depths, feat)
+    model = sf.forest_to_device(_model(rng, 5, 4, 10, 64, feat[:4096].cpu().numpy()), dev)
+    ctx.sf_forest_pack(model)
+    pred, top = (torch.empty(n, dtype=torch.int16, device=dev) for _ in range(2))
+    alone = _median_us(lambda: ctx.sf_featurize(pk, depths, feat))
+    assert _median_us(lambda: ctx.sf_featurize_fast_infer(pk, depths, model, 1, feat, pred, top)) <= 1.32 * alone
