@@ -213,8 +213,9 @@ uint32_t fused_one_lane_trees(uint32_t depth, uint32_t n_windows, uint32_t dmax,
 // many uneven ones: 256 x 2 (1,048,576 flows, 200 trees of depth 8: 585 against 599 for 64 x 4; with 32 features three blocks a
 // unit, 1.1 to 1.2 times as fast as two with more staged), 64 x 4 up to 3 * 128 flows per unit (30,000 flows 39 against 83 with one
 // lane per flow; two classes leave half of its lanes idle: with 40 trees or more 256 x 2 from 256 flows per unit, 95,000 flows
-// x 60 trees of depth 8 1.3 times as fast), 16 x 16 for few flows.  One class, and with 32 features three, leave a lane idle
-// that 256 x 1 does not have (1,048,576 flows x 60 trees, three classes: depth 8 0.89, depth 1 0.76 times as long as 256 x 2).
+// x 60 trees of depth 8 1.3 times as fast), 16 x 16 for few flows.  One class and three, and with 32 features five, leave lanes
+// idle that 256 x 1 does not have (three classes, 1,048,576 flows x 32 features: 150 trees of depth 6 316 against 341, 60 of depth 1
+// 82 against 120; five classes, 25 trees of depth 4 71 against 81; five classes and 64 features 1.02 to 1.16 times as long).
 // dmax: packets of the deepest window (fused kernel), 0 for the stand-alone walk.
 TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n_rows, uint32_t n_cu, uint32_t dmax, size_t* lds)
 {
@@ -235,7 +236,7 @@ TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n
         return s;
     }
     if (gbdt) {
-        const bool one_lane = a.n_classes == 1u || (a.n_classes == 3u && a.n_features <= 32u);
+        const bool one_lane = a.n_classes == 1u || a.n_classes == 3u || (a.n_classes == 5u && a.n_features <= 32u);
         fit(one_lane ? kTile256x1g : kTile256x2g, 160 * 1024 / 3 - 256, 1);
         if (one_lane && n_rows >= many && *lds <= 80 * 1024) return kTile256x1g;
         if (n_rows >= (a.n_classes <= 2u && a.n_trees >= 40u ? 256u * n_cu : many) && *lds <= 80 * 1024) return kTile256x2g; // (one block per unit is slower than the smaller tile)

@@ -189,7 +189,7 @@ __device__ __forceinline__ void forest_walk(const FastArgs& a, float* xT, uint32
     // the same number of rounds so that the loop stays wave-uniform; a slot past the last tree repeats it and
     // does not vote
     const uint32_t my_classes = GBDT ? (C > grp ? (C - grp + W - 1u) / W : 0u) : 0u;
-    uint32_t per_grp = GBDT ? (T + C - 1u) / C * ((C + W - 1u) / W) : (T + W - 1u) / W;
+    uint32_t per_grp = GBDT && W > 1 ? (T + C - 1u) / C * ((C + W - 1u) / W) : (T + W - 1u) / W;
     if (FPB >= 64u && grp >= (GBDT ? C : T)) per_grp = 0; // (whole waves without a share)
     // one group: ILP trees from position q0 of the lane group's list
     auto walk_group = [&](auto ilp_tag, uint32_t q0) {
@@ -199,7 +199,7 @@ __device__ __forceinline__ void forest_walk(const FastArgs& a, float* xT, uint32
 #pragma unroll
         for (int u = 0; u < G; ++u) {
             uint32_t t;
-            if (GBDT) {
+            if (GBDT && W > 1) {
                 const uint32_t q = q0 + u, rnd = my_classes ? q / my_classes : 0u;
                 cls[u] = grp + W * (q - rnd * my_classes);
                 t = my_classes ? rnd * C + cls[u] : T;
@@ -252,7 +252,7 @@ __device__ __forceinline__ void forest_walk(const FastArgs& a, float* xT, uint32
 #pragma unroll
             for (int u = 0; u < G; ++u) { // ascending u = ascending tree: the order of the sum
                 if (tv[u]) {
-                    float* m = reinterpret_cast<float*>(&vcol[cls[u] * FPB]);
+                    float* m = reinterpret_cast<float*>(&vcol[(W > 1 ? cls[u] : tt[u] % C) * FPB]);
                     *m = *m + val[u];
                     if (WANT_LEAF && live) a.leaf_idx[(size_t)i * T + tt[u]] = (uint16_t)leaf[u];
                 }

@@ -107,7 +107,8 @@ def test_fused(n, depths, longest, T, d, C, negative, shift, skew, pad):
 
 @pytest.mark.parametrize("n,F,T,d,C", [(384 * CU + 5, 32, 9, 5, 3), (384 * CU, 20, 31, 4, 3), (384 * CU + 3, 64, 9, 4, 3), (384 * CU + 200, 64, 13, 3, 1),
                                        (384 * CU + 1, 128, 4, 6, 1), (256 * CU + 7, 32, 41, 4, 2), (256 * CU - 1, 64, 41, 3, 2), (9000, 40, 12, 5, 1),
-                                       (7000, 128, 66, 2, 33), (384 * CU + 9, 128, 64, 2, 64)])
+                                       (7000, 128, 66, 2, 33), (384 * CU + 9, 128, 64, 2, 64),
+                                       (384 * CU + 11, 32, 23, 4, 5), (384 * CU + 11, 64, 23, 4, 5), (384 * CU - 1, 32, 11, 3, 5)])
 def test_margins(n, F, T, d, C):
     """The boosted form on both sides of its lines; sums of binary32 margins in tree order, bit for bit."""
     import torch
@@ -176,3 +177,22 @@ def test_fused_rate():
     pred, top = (torch.empty(n, dtype=torch.int16, device=dev) for _ in range(2))
     alone = _median_us(lambda: ctx.sf_featurize(pk, depths, feat))
     assert _median_us(lambda: ctx.sf_featurize_fast_infer(pk, depths, model, 1, feat, pred, top)) <= 1.32 * alone
+
+
+def test_margins_rate():
+    """Three classes, 150 trees of depth 6 on a million rows of 32 features take at most 8.9 of the time of copying the rows
+    (7.9; with the general split of the classes among lanes 9.9)."""
+    import torch
+    import paper_2402_03694_amd as sf
+    n, dev = 1 << 20, "cuda:0"
+    rng = np.random.default_rng(3)
+    feat = torch.randn((n, 32), device=dev)
+    m = _model(rng, 150, 6, 3, 32, feat[:4096].cpu().numpy())
+    m.leaf_value, m.base = rng.normal(0, 0.5, size=(150, 64)).astype(np.float32), np.zeros(3, np.float32)
+    model = sf.gbdt_to_device(m, dev)
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(n, 150, 6))
+    ctx.sf_gbdt_pack(model)
+    pred, score = torch.empty(n, dtype=torch.int16, device=dev), torch.empty(n, device=dev)
+    copy = torch.empty_like(feat)
+    ratio = _median_us(lambda: ctx.sf_gbdt_infer(feat, model, sf.SF_SCORE_LC, pred, score)) / _median_us(lambda: copy.copy_(feat))
+    assert ratio <= 8.9
