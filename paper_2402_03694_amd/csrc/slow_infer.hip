@@ -658,7 +658,7 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
     // The whole model in one launch where a block's activations fit (widths up to about 1,400 together), up to 32,768 rows and
     // as long as the terms of all sums stay under the line: a block of eight rows reads every weight again, the taller tiles
     // of f32_layer read it once for 64 rows.  Whole call in us, layer by layer : one launch: 300 rows through 64-128-128-4
-    // 70 : 16, 4,096 rows through 32-128-128-4 130 : 17, 20,000 rows through 128-256-256-32 310 : 158, 600 rows through
+    // 70 : 16, 4,096 rows through 32-128-128-4 130 : 17, 16,000 rows through 128-256-256-32 301 : 139, 600 rows through
     // 128-512-512-32 223 : 123.  Around the line (5.2e9 terms): 24,576 rows through 32-400-400-10 513 : 515, 32,768 through
     // 32-350-350-10 496 : 497, 16,384 through 32-512-512-10 531 : 444, 10,000 through 128-650-650-10 724 : 744.  Past it: 32,768
     // through 128-650-650-10 1,244 : 2,130, 24,576 through 128-450-450-10 651 : 820.  Long lists through narrow models: 500,000
