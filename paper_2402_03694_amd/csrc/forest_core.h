@@ -14,7 +14,7 @@
 //
 // The feature tile (F * 4 bytes per flow) is what fills shared memory, so it also limits how many flows a
 // compute unit can hold.  Several waves therefore work on the same tile, each on its share of the trees: the
-// unit then runs up to 32 waves instead of 8 and the address path stays 82-84 % busy (65 % before).  A wave's
+// unit then runs up to 32 waves instead of 8 and the address path stays 81 % busy (65 % before; 72 % in the fused kernel).  A wave's
 // lanes all walk the SAME trees, for different flows: lanes that split the trees of one flow between them
 // (as this code did before, for shapes with few resident waves) spread every record load over two to four
 // times as many cache lines.  Measured, the walk alone, before -> after: 1,048,576 flows x 64 features, 100
