@@ -11,9 +11,12 @@ LIB = os.path.join(HERE, "libserveflow_hip.so")
 # -ffp-contract=off: the feature statistics are defined with one rounding per operation.
 # The packed-fp32 feature is switched off for device code (hipcc's host pass does not know
 # the feature and says so; that warning is harmless).
+# Sums of MFMAs stay in ordinary vector registers: the epilogues work on them, and a copy out of an accumulation
+# register costs an instruction each.
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-Wall", "-Wno-unused-function",
 ]
 

@@ -66,7 +66,8 @@ struct Carve {
 // whole of a compute unit's, once per context and kernel (the context remembers which).
 constexpr int kLdsLimitBytes = 160 * 1024;
 enum LdsSlot { kLdsForest = 0 /* 9 block shapes, leaf numbers wanted or not */, kLdsTreeWalk = 18, kLdsWide = 19 /* 5 operand forms, K resident or streamed */,
-               kLdsFused = 29, kLdsClassify = 30 /* 5 block shapes x 2 window depths x rows kept or not */ };
+               kLdsFused = 29, kLdsClassify = 30 /* 5 block shapes x 2 window depths x rows kept or not */,
+               kLdsRows = 50 /* input up to 64 or 128 x 5 widths */ };
 #define SF_ALLOW_LDS(ctx, slot, func)                                                                         \
     do {                                                                                                      \
         if (!((ctx)->lds_ready & (1ull << (slot)))) {                                                         \

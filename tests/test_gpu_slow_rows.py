@@ -1,0 +1,100 @@
+"""The slow model's register form where it can go wrong: runs of rows that end in a full pass, a low one or a tile of one or two
+row blocks, widths around the column blocks (odd numbers of them, a width just past a multiple of 128), inputs that are not whole
+k-steps, one class and all 32, label indices apart from the input rows, no input map, no logits.
+Logits against the same model in 64 bits with the hidden activations rounded to bfloat16; labels: the arg-max of the logits."""
+import pytest
+
+from test_gpu_wide_tiles import DEV, _check, _model, _reference
+
+pytestmark = pytest.mark.gpu
+
+UNITS = 256          # compute units: a run is the rows divided by this
+CAP = 128 * UNITS + 1  # the shortest list that takes this form
+
+
+def _run(rows, cap, dims, mapped, pairs, with_logits=True):
+    import torch
+    import paper_2402_03694_amd as sf
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + 7 * dims[1] + dims[0])
+    n = cap + 77
+    mlp = _model(g, dims, mapped)
+    feat = torch.randn((n, dims[0] + 4), device=DEV, generator=g)
+    idx = torch.randperm(n, device=DEV, generator=g)[:cap].to(torch.int32)
+    dst = torch.randperm(n, device=DEV, generator=g)[:cap].to(torch.int32) if pairs else idx
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(n, 0, 0, *dims[:3]))
+    torch.cuda.synchronize()
+    if rows % 2:
+        ctx.sf_mlp_order(mlp)  # (else the call orders the weights in its workspace)
+    logits = torch.full((cap, dims[3]), float("nan"), device=DEV) if with_logits else None
+    labels = torch.full((n,), -1, dtype=torch.int16, device=DEV)
+    count = torch.tensor([rows], dtype=torch.int32, device=DEV)
+    if pairs:
+        ctx.sf_slow_infer_pairs(mlp, feat, idx, dst, count, labels, logits=logits)
+    else:
+        ctx.sf_slow_infer(mlp, idx, count, labels, feat=feat, logits=logits)
+    torch.cuda.synchronize()
+    return mlp, feat[idx[:rows].long(), :dims[0]], logits, labels, dst[:rows], n
+
+
+@pytest.mark.parametrize("rows", [1, 31, 33, 32 * UNITS + 1, 64 * UNITS + 5, 96 * UNITS + 1, 128 * UNITS, 128 * UNITS + 1, 160 * UNITS + 3, 256 * UNITS,
+                                  256 * UNITS + 1, 288 * UNITS + 40, 360 * UNITS + 9, 416 * UNITS + 31])
+def test_runs(rows):
+    out = _run(rows, max(rows, CAP), (64, 160, 96, 10), mapped=True, pairs=rows % 3 == 0)
+    _check(out[0], _reference(out[0], out[1]), *out[2:])
+
+
+@pytest.mark.parametrize("dims", [(64, 512, 512, 10), (128, 512, 512, 32), (128, 510, 500, 1), (4, 33, 64, 2), (64, 128, 256, 17), (100, 129, 31, 16),
+                                  (32, 256, 225, 9), (96, 300, 200, 7), (68, 384, 384, 32), (64, 385, 481, 8), (124, 480, 1, 3), (60, 1, 40, 5)])
+def test_widths(dims):
+    rows = 290 * UNITS + 11 # one pass of 256 rows a block, then one or two row blocks
+    out = _run(rows, rows, dims, mapped=dims[1] % 2 == 0, pairs=False)
+    _check(out[0], _reference(out[0], out[1]), *out[2:])
+
+
+@pytest.mark.parametrize("dims", [(128, 257, 200, 10), (64, 512, 448, 4)])
+def test_low_pass(dims):
+    rows = 100 * UNITS # three or four row blocks a block
+    out = _run(rows, CAP, dims, mapped=True, pairs=True)
+    _check(out[0], _reference(out[0], out[1]), *out[2:])
+
+
+def test_labels_alone():
+    import torch
+    rows = 260 * UNITS
+    full = _run(rows, rows, (64, 256, 256, 10), True, False)
+    alone = _run(rows, rows, (64, 256, 256, 10), True, False, with_logits=False)
+    assert torch.equal(full[3], alone[3])
+
+
+def test_values_past_the_finite():
+    """Infinite and missing inputs stay with their own rows, and a hidden NaN counts as zero (the input map keeps NaN, relu does not)."""
+    import torch
+    import paper_2402_03694_amd as sf
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    n, dims = CAP + 1000, (64, 256, 128, 10)
+    mlp = _model(g, dims, True)
+    feat = torch.randn((n, 64), device=DEV, generator=g)
+    idx = torch.arange(n, device=DEV, dtype=torch.int32)
+    count = torch.tensor([n], dtype=torch.int32, device=DEV)
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(n, 0, 0, *dims[:3]))
+    outs = []
+    for bad in (False, True):
+        x = feat.clone()
+        if bad:
+            x[5, 3], x[64, 0], x[40000 % n, 63] = float("inf"), float("nan"), float("-inf")
+        logits = torch.empty((n, 10), device=DEV)
+        labels = torch.empty(n, dtype=torch.int16, device=DEV)
+        torch.cuda.synchronize()
+        ctx.sf_slow_infer(mlp, idx, count, labels, feat=x, logits=logits)
+        torch.cuda.synchronize()
+        outs.append(logits)
+    same = torch.ones(n, dtype=torch.bool, device=DEV)
+    same[[5, 64, 40000 % n]] = False
+    assert torch.equal(outs[0][same], outs[1][same])
+    # every hidden value of the first layer is NaN, so zero; the rest follows from the biases
+    h = torch.relu(mlp.b2.double()).float().to(torch.bfloat16).double()
+    want = h @ mlp.w3.double().t() + mlp.b3.double()
+    assert float((outs[1][64].double() - want).abs().max()) < 1e-2
+    assert torch.isfinite(outs[1]).all()

@@ -67,7 +67,8 @@ def test_vector_instructions(kernels, name, most):
 @pytest.mark.parametrize("name", ["featurize_wave<8, false>", "featurize_wave<16, false>", "featurize_wave<32, false>", "featurize_parts<8>",
                                   "featurize_parts<32>"] + ["mlp_wide_layer<%s>" % t for t in (
                                       "0, false, 0", "0, true, 0", "1, false, 0", "1, true, 0", "2, false, 0", "2, true, 0", "2, false, 1", "2, true, 1",
-                                      "2, true, 2")])
+                                      "2, true, 2")] + [
+                                      "mlp_rows<%s>" % t for t in ("4, 4, false", "8, 4, false", "12, 4, false", "16, 4, true", "16, 4, false", "16, 8, true")])
 def test_no_spills(kernels, name):
     assert kernels[name]["spilled"] == 0, kernels[name]
 
