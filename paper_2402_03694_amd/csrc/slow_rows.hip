@@ -447,8 +447,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void mlp_rows(RowsArgs a)
         m.s_b3 = b3;
         m.H = reinterpret_cast<uint16_t*>(xall);
         m.s_flow = reinterpret_cast<uint32_t*>(m.H + 64 * sftiles::LDH);
-        m.s_part = reinterpret_cast<float*>(m.s_flow + 2 * sftiles::FBM);
-        m.s_mu = m.s_part + 2 * 16 * 64;
+        m.s_part = nullptr; // (one sum per logit)
+        m.s_mu = reinterpret_cast<float*>(m.s_flow + 2 * sftiles::FBM);
         m.s_is = m.s_mu + sftiles::HMAX;
         __syncthreads(); // the passes are done with the shared memory
         for (uint32_t q = tid; q < 128u; q += kWaves * 64u) { // (n_in is at most 128)
@@ -459,19 +459,19 @@ __global__ __launch_bounds__(kWaves * 64, 1) void mlp_rows(RowsArgs a)
         // (columns split over the waves as evenly as whole column blocks allow)
         if (NB1 < 16 && a.nb2 <= (uint32_t)NB1) {
             if (rest == 1u)
-                sftiles::run_tiles<kWaves, NB1 / kWaves, 1>(a, m, wave, first, 1u, row_end);
+                sftiles::run_tiles<kWaves, NB1 / kWaves, 1, true>(a, m, wave, first, 1u, row_end);
             else
-                sftiles::run_tiles<kWaves, NB1 / kWaves, 2>(a, m, wave, first, 1u, row_end);
+                sftiles::run_tiles<kWaves, NB1 / kWaves, 2, true>(a, m, wave, first, 1u, row_end);
         } else {
             if (rest == 1u)
-                sftiles::run_tiles<kWaves, 16 / kWaves, 1>(a, m, wave, first, 1u, row_end);
+                sftiles::run_tiles<kWaves, 16 / kWaves, 1, true>(a, m, wave, first, 1u, row_end);
             else
-                sftiles::run_tiles<kWaves, 16 / kWaves, 2>(a, m, wave, first, 1u, row_end);
+                sftiles::run_tiles<kWaves, 16 / kWaves, 2, true>(a, m, wave, first, 1u, row_end);
         }
     }
 }
 
-constexpr size_t kTileLds = (size_t)64 * sftiles::LDH * 2 + 2 * sftiles::FBM * 4 + 2 * 16 * 64 * 4 + 2 * sftiles::HMAX * 4;
+constexpr size_t kTileLds = (size_t)64 * sftiles::LDH * 2 + 2 * sftiles::FBM * 4 + 2 * sftiles::HMAX * 4;
 
 } // namespace
 

@@ -74,6 +74,8 @@ constexpr int kRing = 4;   // weight operands of this many k-steps are in flight
 
 __device__ __forceinline__ uint32_t weight_lane(uint32_t lane) { return (lane & ~12u) | ((lane & 4u) << 1) | ((lane & 8u) >> 1); }
 
+// ONE_SUM: a logit is one sum, from its bias on in order of K, as in the register form (a row's result does not depend on whether it
+// falls into a pass or a tile); else two halves of K are summed side by side.
 // W: waves of the block, NI: 32-column blocks per wave (W * NI up to 16), MI: 32-row blocks of the tile
 
 // first kRing k-steps of a wave's weight operands (column blocks nb0 .. nb0+NI, clamped to the last real one)
@@ -276,13 +278,14 @@ struct FusedSmem {
     float *s_b1, *s_b2, *s_b3, *s_part, *s_mu, *s_is;
 };
 
-template <int W, int NI, int MI>
+template <int W, int NI, int MI, bool ONE_SUM = false>
 __device__ __forceinline__ void run_tiles(const FusedArgs& a, const FusedSmem& m, uint32_t wave, uint32_t row_begin,
                                           uint32_t n_tiles, uint32_t row_end)
 {
     constexpr uint32_t TM = MI * 32u; // rows per tile
     constexpr int kXr = kChunks<W>;
-    constexpr uint32_t KH = 2; // shares of K in the last layer
+    constexpr uint32_t KH = ONE_SUM ? 1 : 2; // shares of K in the last layer
+    constexpr int kW3 = ONE_SUM ? 32 : 16;   // its weight operands that are requested at once
     static_assert(W >= 2 * MI && W * NI <= 16, "a wave for every row block and half of K, 512 columns at most");
     uint16_t* H = m.H;
     uint32_t* s_flow = m.s_flow;
@@ -364,12 +367,12 @@ __device__ __forceinline__ void run_tiles(const FusedArgs& a, const FusedSmem& m
         // accumulators are dead, so a whole half-layer of weight operands fits in registers; they are requested
         // before the barrier so that their latency overlaps it.
         const uint32_t rb = wave % (uint32_t)MI, kh = wave / (uint32_t)MI;
-        const bool l3 = W == 2 * MI ? true : kh < KH; // (the branch would otherwise cost registers)
+        const bool l3 = W == (int)KH * MI ? true : kh < KH; // (the branch would otherwise cost registers)
         const uint32_t KS3 = k3p / 16u, khalf = KS3 / KH, kbeg = (l3 ? kh : 0u) * khalf; // KS3 is a multiple of 4
-        uint4 wv[16];
+        uint4 wv[kW3];
         if (l3) {
 #pragma unroll
-            for (int s3 = 0; s3 < 16; ++s3)
+            for (int s3 = 0; s3 < kW3; ++s3)
                 wv[s3] = a.w3s[(size_t)(kbeg + ((uint32_t)s3 < khalf ? (uint32_t)s3 : khalf - 1u)) * 64u + lane];
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -386,30 +389,36 @@ __device__ __forceinline__ void run_tiles(const FusedArgs& a, const FusedSmem& m
         {
             f32x16 c3, c3b;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) c3[v] = c3b[v] = 0.f;
+            for (int v = 0; v < 16; ++v) {
+                c3[v] = ONE_SUM ? m.s_b3[8u * (v >> 2) + 4u * (lane >> 5) + (v & 3)] : 0.f;
+                c3b[v] = 0.f;
+            }
             const uint16_t* arow = H + (rb * 32u + (lane & 31u)) * LDH + 8u * (lane >> 5);
             if (l3) {
-                for (uint32_t kb = 0; kb < khalf; kb += 16u) {
+                for (uint32_t kb = 0; kb < khalf; kb += kW3) {
                     if (kb) {
 #pragma unroll
-                        for (int s3 = 0; s3 < 16; ++s3)
+                        for (int s3 = 0; s3 < kW3; ++s3)
                             wv[s3] = a.w3s[(size_t)(kbeg + (kb + s3 < khalf ? kb + s3 : khalf - 1u)) * 64u + lane];
                     }
 #pragma unroll
-                    for (int s3 = 0; s3 < 16; s3 += 2) {
+                    for (int s3 = 0; s3 < kW3; s3 += 2) {
                         if (kb + s3 < khalf)
                             c3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                                 as_frag(wv[s3]), as_frag(*reinterpret_cast<const uint4*>(arow + (kbeg + kb + s3) * 16u)), c3, 0, 0, 0);
-                        if (kb + s3 + 1 < khalf)
-                            c3b = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                as_frag(wv[s3 + 1]), as_frag(*reinterpret_cast<const uint4*>(arow + (kbeg + kb + s3 + 1) * 16u)), c3b, 0, 0, 0);
+                        if (kb + s3 + 1 < khalf) {
+                            f32x16& to = ONE_SUM ? c3 : c3b;
+                            to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                as_frag(wv[s3 + 1]), as_frag(*reinterpret_cast<const uint4*>(arow + (kbeg + kb + s3 + 1) * 16u)), to, 0, 0, 0);
+                        }
                     }
                 }
             }
 #pragma unroll
-            for (int v = 0; v < 16; ++v) c3[v] += c3b[v];
+            for (int v = 0; v < 16; ++v)
+                if (!ONE_SUM) c3[v] += c3b[v];
             float* part = m.s_part + rb * (16 * 64);
-            if (l3 && kh == 1u) {
+            if (!ONE_SUM && l3 && kh == 1u) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) part[v * 64 + lane] = c3[v];
             }
@@ -424,7 +433,7 @@ __device__ __forceinline__ void run_tiles(const FusedArgs& a, const FusedSmem& m
                 for (int v = 0; v < 16; ++v) {
                     const uint32_t c = 8u * (v >> 2) + 4u * (lane >> 5) + (v & 3); // ascending in v
                     if (c < a.c) {
-                        const float y = c3[v] + part[v * 64 + lane] + m.s_b3[c];
+                        const float y = ONE_SUM ? c3[v] : c3[v] + part[v * 64 + lane] + m.s_b3[c];
                         if (a.logits && row_ok) a.logits[(size_t)(row0 + r) * a.c + c] = y;
                         if (best == kNoFlow || y > bv) {
                             bv = y;

@@ -59,6 +59,29 @@ def test_low_pass(dims):
     _check(out[0], _reference(out[0], out[1]), *out[2:])
 
 
+@pytest.mark.parametrize("dims", [(64, 512, 512, 10), (100, 130, 70, 32)])
+def test_place_in_the_list(dims):
+    """A row's logits are the same bits wherever in the list it stands: in a full pass, a low one or a tile."""
+    import torch
+    import paper_2402_03694_amd as sf
+    g = torch.Generator(device=DEV)
+    g.manual_seed(9)
+    mlp = _model(g, dims, True)
+    feat = torch.randn((512, dims[0]), device=DEV, generator=g)
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(400 * UNITS, 0, 0, *dims[:3]))
+    labels = torch.empty(512, dtype=torch.int16, device=DEV)
+    first = None
+    for rows in (256 * UNITS, 60 * UNITS, 30 * UNITS, 120 * UNITS, 290 * UNITS):
+        idx = (torch.arange(max(rows, CAP), device=DEV) * 5 % 512).to(torch.int32)
+        logits = torch.empty((len(idx), dims[3]), device=DEV)
+        torch.cuda.synchronize()
+        # (pairs: a list may be longer than there are input rows)
+        ctx.sf_slow_infer_pairs(mlp, feat, idx, idx, torch.tensor([rows], dtype=torch.int32, device=DEV), labels, logits=logits)
+        torch.cuda.synchronize()
+        first = logits[:512].clone() if first is None else first
+        assert torch.equal(logits[:rows], first[torch.arange(rows, device=DEV) % 512])
+
+
 def test_labels_alone():
     import torch
     rows = 260 * UNITS
