@@ -22,7 +22,7 @@ namespace {
 constexpr unsigned long long kEmpty = 0ull;
 constexpr unsigned long long kGone = ~0ull; // removed during this step; cleared by the next step's repack
 
-struct Slot {
+struct alignas(16) Slot {
     unsigned long long id;
     uint32_t val;
     uint32_t stamp;
@@ -43,21 +43,6 @@ __device__ __forceinline__ uint32_t slot_of(unsigned long long id, uint32_t mask
     return (uint32_t)id & mask;
 }
 
-// One atomic per wave instead of one per lane: the lanes for which want is set get consecutive positions
-// base .. base + count - 1 (base from a single atomicAdd by the first of them).  All lanes that are active at
-// the call take part; the result is meaningful only where want is set.
-__device__ __forceinline__ uint32_t wave_claim(uint32_t* counter, bool want)
-{
-    const unsigned long long m = __ballot(want);
-    if (m == 0) return 0;
-    const uint32_t lane = threadIdx.x & 63u;
-    const int leader = __ffsll((long long)m) - 1;
-    uint32_t base = 0;
-    if ((int)lane == leader) base = atomicAdd(counter, (uint32_t)__popcll(m));
-    base = (uint32_t)__shfl((int)base, leader, 64);
-    return base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-}
-
 __device__ __forceinline__ void wave_count(uint32_t* counter, bool want)
 {
     const unsigned long long m = __ballot(want);
@@ -69,8 +54,7 @@ struct JoinArgs {
     uint32_t* used[2]; // per side, one word per kChunk slots: non-zero once a record was stored there since the last sweep
     uint32_t mask;  // slots per table - 1
     uint32_t now, timeout;
-    Slot* list;     // scratch: survivors, side s in list[s * slots ...]
-    uint32_t* counters; // scratch: [0] survivors of side 0, [1] survivors of side 1
+    Slot* list;     // scratch: survivors, those of a stretch of kChunk slots in its own place in list[side * slots ...]
     uint32_t* n_pairs;
     uint32_t* pair_q3;
     uint32_t* pair_q2;
@@ -78,22 +62,19 @@ struct JoinArgs {
     uint32_t* stats;
 };
 
-__global__ void join_zero(uint32_t* counters, uint32_t* n_pairs, uint32_t* stats)
-{
-    if (threadIdx.x < 2) counters[threadIdx.x] = 0;
-    if (threadIdx.x == 2) *n_pairs = 0;
-    if (stats && threadIdx.x >= 4 && threadIdx.x < 8) stats[threadIdx.x - 4] = 0;
-}
-
-// survivors of both tables -> list (side s occupies list[s * slots ...]); every slot is cleared.
-// A wave takes kChunk consecutive slots of one side per trip and claims the list positions of all its
-// survivors with ONE atomic (a counter that every wave of the grid adds to is the bottleneck otherwise:
-// same-address atomics retire a few nanoseconds apart).
+// Survivors of both tables -> list, stretch by stretch; every slot is cleared.  A wave takes kChunk consecutive slots of one side
+// per trip, all of them requested before the first is looked at and kept in registers.  A stretch's survivors go to its own
+// place in the list, closed by an entry without a flow ID that carries the number of records dropped, so there is no counter
+// that every wave adds to.  (With one counter per side, and every slot read twice, the sweep of 2^20 slots a side took 25 to 38 us.)
 constexpr uint32_t kChunkTrips = 16;             // slots per lane per trip
 constexpr uint32_t kChunk = 64u * kChunkTrips;   // slots per wave per trip
 
 __global__ __launch_bounds__(256) void join_collect(JoinArgs a)
 {
+    if (blockIdx.x == 0) { // what the launches behind this one add to
+        if (threadIdx.x == 0) *a.n_pairs = 0;
+        if (a.stats && threadIdx.x < 4u) a.stats[threadIdx.x] = 0;
+    }
     const uint32_t slots = a.mask + 1u;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, n_waves = (gridDim.x * blockDim.x) >> 6;
@@ -101,47 +82,34 @@ __global__ __launch_bounds__(256) void join_collect(JoinArgs a)
     for (uint32_t c = wave; c < 2u * chunks_per_side; c += n_waves) {
         const uint32_t side = c >= chunks_per_side ? 1u : 0u;
         const uint32_t first = (c - side * chunks_per_side) * kChunk;
+        const uint32_t n = slots - first < kChunk ? slots - first : kChunk;
+        Slot* out = a.list + (size_t)side * slots + first;
         // nothing was stored in this stretch since it was last swept: every slot is still empty
         uint32_t* used = a.used[side] + (c - side * chunks_per_side);
-        if (*used == 0u) continue; // the same word in every lane: the wave skips together
+        if (*used == 0u) { // the same word in every lane: the wave skips together
+            if (lane == 0) out[0] = Slot{kEmpty, 0u, 0u};
+            continue;
+        }
         if (lane == 0) *used = 0u; // the sweep below empties the stretch (the re-insert marks what it refills)
-        Slot* t = a.table[side];
-        // pass 1: who survives (one 64-bit lane mask per trip, the same in every lane)
-        unsigned long long keep[kChunkTrips];
-        uint32_t n_keep = 0, n_old = 0;
+        Slot* t = a.table[side] + first;
+        Slot v[kChunkTrips];
 #pragma unroll
         for (uint32_t j = 0; j < kChunkTrips; ++j) {
-            const uint32_t q = first + j * 64u + lane;
-            bool live = false, old = false;
-            if (q < slots) {
-                const Slot v = t[q];
-                live = v.id != kEmpty && v.id != kGone;
-                old = live && (a.now - v.stamp > a.timeout); // unsigned: wraps like the tick counter
-            }
-            keep[j] = __ballot(live && !old);
-            n_keep += (uint32_t)__popcll(keep[j]);
+            const uint32_t q = j * 64u + lane;
+            v[j] = q < n ? t[q] : Slot{kEmpty, 0u, 0u};
+        }
+        uint32_t n_keep = 0, n_old = 0; // (the same in every lane)
+#pragma unroll
+        for (uint32_t j = 0; j < kChunkTrips; ++j) {
+            const bool live = v[j].id != kEmpty && v[j].id != kGone;
+            const bool old = live && (a.now - v[j].stamp > a.timeout); // unsigned: wraps like the tick counter
+            const unsigned long long keep = __ballot(live && !old);
+            if (live && !old) out[n_keep + (uint32_t)__popcll(keep & ((1ull << lane) - 1ull))] = v[j];
+            if (v[j].id != kEmpty) t[j * 64u + lane].id = kEmpty;
+            n_keep += (uint32_t)__popcll(keep);
             n_old += (uint32_t)__popcll(__ballot(old));
         }
-        uint32_t base = 0;
-        if (lane == 0) {
-            if (n_keep) base = atomicAdd(&a.counters[side], n_keep);
-            if (n_old && a.stats) atomicAdd(&a.stats[kExpired], n_old);
-        }
-        base = (uint32_t)__shfl((int)base, 0, 64);
-        // pass 2: move the survivors, clear every used slot
-#pragma unroll
-        for (uint32_t j = 0; j < kChunkTrips; ++j) {
-            const uint32_t q = first + j * 64u + lane;
-            if (q < slots) {
-                const Slot v = t[q];
-                if (v.id != kEmpty) {
-                    if ((keep[j] >> lane) & 1ull)
-                        a.list[(size_t)side * slots + base + (uint32_t)__popcll(keep[j] & ((1ull << lane) - 1ull))] = v;
-                    t[q].id = kEmpty;
-                }
-            }
-            base += (uint32_t)__popcll(keep[j]);
-        }
+        if (lane == 0 && n_keep < n) out[n_keep] = Slot{kEmpty, n_old, 0u}; // (a stretch without room for it dropped nothing)
     }
 }
 
@@ -173,76 +141,95 @@ __device__ __forceinline__ bool insert_slot(Slot* table, uint32_t* used, uint32_
 __global__ __launch_bounds__(256) void join_reinsert(JoinArgs a)
 {
     const uint32_t slots = a.mask + 1u;
-    for (uint32_t side = 0; side < 2u; ++side) {
-        const uint32_t n = a.counters[side];
-        for (uint32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < n; g += gridDim.x * blockDim.x) {
-            const Slot v = a.list[(size_t)side * slots + g];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, n_waves = (gridDim.x * blockDim.x) >> 6;
+    const uint32_t chunks_per_side = (slots + kChunk - 1u) / kChunk;
+    for (uint32_t c = wave; c < 2u * chunks_per_side; c += n_waves) {
+        const uint32_t side = c >= chunks_per_side ? 1u : 0u;
+        const uint32_t first = (c - side * chunks_per_side) * kChunk;
+        const uint32_t n = slots - first < kChunk ? slots - first : kChunk;
+        const Slot* in = a.list + (size_t)side * slots + first;
+        for (uint32_t e0 = 0; e0 < n; e0 += 64u) {
+            Slot v = {kEmpty, 0u, 0u};
+            if (e0 + lane < n) v = in[e0 + lane];
+            const unsigned long long none = __ballot(v.id == kEmpty);
+            const uint32_t end = none ? (uint32_t)__ffsll((long long)none) - 1u : 64u; // the list's last entry
             bool dup = false;
-            insert_slot(a.table[side], a.used[side], a.mask, v.id, v.val, v.stamp, &dup); // cannot fail: it fitted before
+            if (lane < end) insert_slot(a.table[side], a.used[side], a.mask, v.id, v.val, v.stamp, &dup); // cannot fail: it fitted before
+            if (lane == end && e0 + lane < n && v.val && a.stats) atomicAdd(&a.stats[kExpired], v.val);
+            if (end < 64u) break;
         }
     }
 }
 
 // arrivals of one side: SIDE 0 = queue 3 (own table 0, partner table 1), SIDE 1 = queue 2.
 // what: 0 stored to wait, 1 matched, 2 no room (or a reserved ID), 3 already waiting on this side, 4 no record
+//
+// A block's pairs take consecutive positions with one atomic: every wave of the grid adding to the one counter is what bounds
+// the launch otherwise (the adds to one address retire a few nanoseconds apart).
+constexpr uint32_t kArriveThreads = 512;
+
 template <int SIDE>
-__device__ __forceinline__ void arrive_one(const JoinArgs& a, const unsigned long long* __restrict__ ids,
-                                           const uint32_t* __restrict__ vals, uint32_t n, uint32_t g)
+__global__ __launch_bounds__(kArriveThreads) void join_arrive(JoinArgs a, const unsigned long long* __restrict__ ids,
+                                                              const uint32_t* __restrict__ vals, uint32_t n)
 {
+    __shared__ uint32_t s_count[kArriveThreads / 64u], s_base;
     Slot* own = a.table[SIDE];
     Slot* other = a.table[1 - SIDE];
-    int what = 4;
-    uint32_t val = 0, pair_val = 0;
-    unsigned long long id = kEmpty;
-    if (g < n) {
-        id = ids[g];
-        val = vals[g];
-        what = 2; // stays so for the two reserved IDs, which cannot be stored
-    }
-    if (id != kEmpty && id != kGone) {
-        // partner waiting on the other side?
-        bool matched = false;
-        uint32_t pv = 0;
-        uint32_t p = slot_of(id, a.mask);
-        for (uint32_t tries = 0; tries <= a.mask; ++tries, p = (p + 1u) & a.mask) {
-            const unsigned long long seen = other[p].id;
-            if (seen == kEmpty) break;
-            if (seen == id) {
-                // take it out; only one arrival can win the slot
-                if (atomicCAS(&other[p].id, id, kGone) == id) {
-                    pv = other[p].val;
-                    matched = true;
-                }
-                break;
-            }
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint32_t rounded = (n + kArriveThreads - 1u) / kArriveThreads * kArriveThreads; // whole blocks stay in the loop together
+    for (uint32_t g = blockIdx.x * kArriveThreads + threadIdx.x; g < rounded; g += gridDim.x * kArriveThreads) {
+        int what = 4;
+        uint32_t val = 0, pair_val = 0;
+        unsigned long long id = kEmpty;
+        if (g < n) {
+            id = ids[g];
+            val = vals[g];
+            what = 2; // stays so for the two reserved IDs, which cannot be stored
         }
-        bool dup = false, stored = true;
-        if (!matched) stored = insert_slot(own, a.used[SIDE], a.mask, id, val, a.now, &dup);
-        what = matched ? 1 : (!stored ? 2 : (dup ? 3 : 0));
-        pair_val = pv;
-    }
-    // the wave's pairs take consecutive positions with one atomic
-    const uint32_t at = wave_claim(a.n_pairs, what == 1);
-    if (what == 1) {
-        if (at < a.pair_cap) {
+        if (id != kEmpty && id != kGone) {
+            // partner waiting on the other side?
+            bool matched = false;
+            uint32_t p = slot_of(id, a.mask);
+            for (uint32_t tries = 0; tries <= a.mask; ++tries, p = (p + 1u) & a.mask) {
+                const Slot seen = other[p]; // (its value was written by an earlier launch: the whole slot in one load)
+                if (seen.id == kEmpty) break;
+                if (seen.id == id) {
+                    // take it out; only one arrival can win the slot
+                    matched = atomicCAS(&other[p].id, id, kGone) == id;
+                    pair_val = seen.val;
+                    break;
+                }
+            }
+            bool dup = false, stored = true;
+            if (!matched) stored = insert_slot(own, a.used[SIDE], a.mask, id, val, a.now, &dup);
+            what = matched ? 1 : (!stored ? 2 : (dup ? 3 : 0));
+        }
+        const unsigned long long pairs = __ballot(what == 1);
+        if (lane == 0) s_count[wave] = (uint32_t)__popcll(pairs);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t all = 0;
+            for (uint32_t w = 0; w < kArriveThreads / 64u; ++w) {
+                const uint32_t k = s_count[w];
+                s_count[w] = all;
+                all += k;
+            }
+            s_base = all ? atomicAdd(a.n_pairs, all) : 0u;
+        }
+        __syncthreads();
+        const uint32_t at = s_base + s_count[wave] + (uint32_t)__popcll(pairs & ((1ull << lane) - 1ull));
+        if (what == 1 && at < a.pair_cap) {
             a.pair_q3[at] = SIDE == 0 ? val : pair_val;
             a.pair_q2[at] = SIDE == 0 ? pair_val : val;
         }
+        if (a.stats) {
+            wave_count(&a.stats[kPairOverflow], what == 1 && at >= a.pair_cap);
+            wave_count(&a.stats[kDropped], what == 2);
+            wave_count(&a.stats[kDuplicate], what == 3);
+        }
+        __syncthreads(); // the block's counts have been read
     }
-    if (a.stats) {
-        wave_count(&a.stats[kPairOverflow], what == 1 && at >= a.pair_cap);
-        wave_count(&a.stats[kDropped], what == 2);
-        wave_count(&a.stats[kDuplicate], what == 3);
-    }
-}
-
-template <int SIDE>
-__global__ __launch_bounds__(256) void join_arrive(JoinArgs a, const unsigned long long* __restrict__ ids,
-                                                   const uint32_t* __restrict__ vals, uint32_t n)
-{
-    const uint32_t rounded = (n + 63u) & ~63u; // whole waves stay in the loop together
-    for (uint32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < rounded; g += gridDim.x * blockDim.x)
-        arrive_one<SIDE>(a, ids, vals, n, g);
 }
 
 // live records of one side -> arrays, in no particular order
@@ -272,9 +259,9 @@ int check_table(sf_ctx* ctx, const char* who, const sf_join_table* t)
     return SF_OK;
 }
 
-uint32_t grid_for(uint64_t items)
+uint32_t grid_for(uint64_t items, uint32_t threads = 256)
 {
-    uint64_t b = (items + 255) / 256;
+    uint64_t b = (items + threads - 1) / threads;
     return (uint32_t)(b < 1 ? 1 : (b > 4096 ? 4096 : b));
 }
 
@@ -284,7 +271,7 @@ namespace sf {
 size_t join_scratch_bytes(uint32_t cap_log2)
 {
     if (cap_log2 < 4 || cap_log2 > 28) return 0;
-    return align_up(((size_t)2 << cap_log2) * sizeof(Slot)) + kAlign; // survivor list of both sides + counters
+    return align_up(((size_t)2 << cap_log2) * sizeof(Slot)) + kAlign; // survivor list of both sides, and room to spare
 }
 } // namespace sf
 
@@ -320,8 +307,7 @@ extern "C" int sf_join_step(sf_ctx* ctx, const sf_join_table* table, uint32_t no
     const uint32_t slots = 1u << table->cap_log2;
     sf::Carve ws(ctx);
     Slot* list = (Slot*)ws.take((size_t)2 * slots * sizeof(Slot));
-    uint32_t* counters = (uint32_t*)ws.take(sf::kAlign);
-    if (!list || !counters)
+    if (!list || !ws.take(sf::kAlign))
         return sf::fail(ctx, SF_ENOMEM, "sf_join_step: workspace has %zu bytes, a step on this table needs %zu",
                         ctx->ws_bytes, sf_join_workspace_bytes(table->cap_log2));
     JoinArgs a;
@@ -333,24 +319,21 @@ extern "C" int sf_join_step(sf_ctx* ctx, const sf_join_table* table, uint32_t no
     a.now = now;
     a.timeout = timeout;
     a.list = list;
-    a.counters = counters;
     a.n_pairs = n_pairs;
     a.pair_q3 = pair_q3;
     a.pair_q2 = pair_q2;
     a.pair_cap = pair_cap;
     a.stats = stats;
-    join_zero<<<1, 64, 0, ctx->stream>>>(counters, n_pairs, stats);
-    SF_LAUNCH_CHECK(ctx, "join_zero");
     join_collect<<<grid_for(2ull * slots / kChunkTrips), 256, 0, ctx->stream>>>(a);
     SF_LAUNCH_CHECK(ctx, "join_collect");
-    join_reinsert<<<grid_for(slots), 256, 0, ctx->stream>>>(a);
+    join_reinsert<<<grid_for(2ull * slots / kChunkTrips), 256, 0, ctx->stream>>>(a);
     SF_LAUNCH_CHECK(ctx, "join_reinsert");
     if (n3) {
-        join_arrive<0><<<grid_for(n3), 256, 0, ctx->stream>>>(a, (const unsigned long long*)q3_id, q3_val, n3);
+        join_arrive<0><<<grid_for(n3, kArriveThreads), kArriveThreads, 0, ctx->stream>>>(a, (const unsigned long long*)q3_id, q3_val, n3);
         SF_LAUNCH_CHECK(ctx, "join_arrive<3>");
     }
     if (n2) {
-        join_arrive<1><<<grid_for(n2), 256, 0, ctx->stream>>>(a, (const unsigned long long*)q2_id, q2_val, n2);
+        join_arrive<1><<<grid_for(n2, kArriveThreads), kArriveThreads, 0, ctx->stream>>>(a, (const unsigned long long*)q2_id, q2_val, n2);
         SF_LAUNCH_CHECK(ctx, "join_arrive<2>");
     }
     return SF_OK;
