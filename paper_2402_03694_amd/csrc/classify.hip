@@ -20,6 +20,7 @@
 // walk needs (vote counters, staged top records).
 #include "featurize_core.h"
 #include "forest_core.h"
+#include "forest_wave.h"
 
 namespace sf {
 int forest_setup(sf_ctx* ctx, const char* who, const sf_forest* f, uint32_t feat_ld, sfforest::FastArgs& a, uint32_t* result_words);
@@ -225,8 +226,8 @@ __device__ __forceinline__ void features_by_lanes(const ClassifyArgs& c, float* 
 // One wave per 64 flows did all of this before (256 flows per block, one lane per flow).  The kernel, before -> after:
 // 1,048,576 flows x 16 packets, windows of 8 and 16, 100 trees of depth 12, a quarter of the rows kept: 572 -> 541 us;
 // windows of 5 and 10, depth 10, no rows: 468 -> 385 us; 97 ragged flows: 51 -> 11 us.  What bounds it: the walk's
-// gathers (forest_core.h) and about 80 us of vector arithmetic for the statistics; smaller tiles (64 x 8) overlap the
-// two no better and hold fewer staged records (whole pass 716 -> 773 us).
+// gathers (forest_core.h) and about 80 us of vector arithmetic for the statistics.  With a wave to a tree behind the same
+// features (forest_wave.h; 128 flows, eight lanes a flow for the statistics): 500 -> 439 us and 367 -> 336.
 template <int FPB_, int W, int ILP, int TAIL, int KMAX, bool KEEP_ROWS>
 __global__ __launch_bounds__(FPB_ * W, W == 1 ? 2 : 8) void featurize_forest(ClassifyArgs c)
 {
@@ -239,8 +240,12 @@ __global__ __launch_bounds__(FPB_ * W, W == 1 ? 2 : 8) void featurize_forest(Cla
     else
         features_by_parts<FPB_, W, KMAX>(c, xT, behind);
     __syncthreads(); // the space behind the tile is free: the walk may stage its records there
-    const uint32_t i = blockIdx.x * FPB_ + threadIdx.x % FPB_;
-    forest_walk<FPB_, W, ILP, TAIL, false, false, false, KEEP_ROWS>(a, xT, i, i, i < a.n_flows);
+    if constexpr (ILP == 0) { // a wave to a tree
+        forest_walk_waves<FPB_ / 64, 4, false, KEEP_ROWS>(a, xT, blockIdx.x * FPB_, a.n_flows);
+    } else {
+        const uint32_t i = blockIdx.x * FPB_ + threadIdx.x % FPB_;
+        forest_walk<FPB_, W, ILP, TAIL, false, false, false, KEEP_ROWS>(a, xT, i, i, i < a.n_flows);
+    }
 }
 
 template <int FPB, int W, int ILP, int TAIL, int KMAX, bool KEEP_ROWS>
@@ -261,7 +266,7 @@ template <int KMAX, bool KEEP_ROWS>
 int launch_shape(sf_ctx* ctx, const ClassifyArgs& c, TileShape shape, size_t lds, int slot)
 {
     switch (shape) {
-    case kTile128x8: return launch_fused<128, 8, 3, 1, KMAX, KEEP_ROWS>(ctx, c, lds, slot);
+    case kTile128Waves: return launch_fused<128, 8, 0, 0, KMAX, KEEP_ROWS>(ctx, c, lds, slot);
     case kTile128x4: return launch_fused<128, 4, 5, 2, KMAX, KEEP_ROWS>(ctx, c, lds, slot + 1);
     case kTile64x8: return launch_fused<64, 8, 3, 1, KMAX, KEEP_ROWS>(ctx, c, lds, slot + 2);
     case kTile16x32: return launch_fused<16, 32, 5, 2, KMAX, KEEP_ROWS>(ctx, c, lds, slot + 3);

@@ -18,7 +18,7 @@ struct sf_ctx {
     int device;
     int n_cu;          // compute units of the device
     uint32_t* d_flags; // 64 words at the head of the workspace: validation counters etc.
-    uint64_t lds_ready; // bit per kernel (sf::LdsSlot): its dynamic shared-memory limit has been raised
+    uint64_t lds_ready[2]; // bit per kernel (sf::LdsSlot): its dynamic shared-memory limit has been raised
     char err[512];
 };
 
@@ -67,13 +67,13 @@ struct Carve {
 constexpr int kLdsLimitBytes = 160 * 1024;
 enum LdsSlot { kLdsForest = 0 /* 9 block shapes, leaf numbers wanted or not */, kLdsTreeWalk = 18, kLdsWide = 19 /* 5 operand forms, K resident or streamed */,
                kLdsFused = 29, kLdsClassify = 30 /* 5 block shapes x 2 window depths x rows kept or not */,
-               kLdsRows = 50 /* input up to 64 or 128 x 5 widths */ };
+               kLdsRows = 50 /* input up to 64 or 128 x 5 widths */, kLdsTrees = 60 /* 5 block shapes, voting or boosted */ };
 #define SF_ALLOW_LDS(ctx, slot, func)                                                                         \
     do {                                                                                                      \
-        if (!((ctx)->lds_ready & (1ull << (slot)))) {                                                         \
+        if (!((ctx)->lds_ready[(slot) >> 6] & (1ull << ((slot) & 63)))) {                                     \
             SF_HIP((ctx), hipFuncSetAttribute((const void*)(func), hipFuncAttributeMaxDynamicSharedMemorySize, \
                                               sf::kLdsLimitBytes));                                           \
-            (ctx)->lds_ready |= 1ull << (slot);                                                               \
+            (ctx)->lds_ready[(slot) >> 6] |= 1ull << ((slot) & 63);                                           \
         }                                                                                                     \
     } while (0)
 

@@ -7,9 +7,11 @@
 //
 // Work split: a block holds a tile of flows, each flow's feature row as a shared-memory column
 // [feature][flow], so the data-dependent fetch x[feat] of every lane of a wave lands in its own bank; the waves
-// of the block split the trees between them.  The kernel here copies the rows of its tile into that layout; the
-// walk itself and the packed record format are in forest_core.h.
+// of the block split the trees between them.  The kernels here copy the rows of their tile into that layout; the
+// walk itself comes in two forms: forest_wave.h (a wave to a tree: most calls with many trees and flows) and
+// forest_core.h (the others, and the packed record format).
 #include "forest_core.h"
+#include "forest_wave.h"
 
 namespace {
 
@@ -115,6 +117,79 @@ int launch_votes(sf_ctx* ctx, const FastArgs& a, size_t lds, int slot)
     return SF_OK;
 }
 
+// The same in the form of forest_wave.h: 64 U flows a block, any number of waves
+template <int U, int KW, bool GBDT>
+__global__ __launch_bounds__(1024, 8) void forest_trees(FastArgs a)
+{
+    constexpr uint32_t FPB = 64 * U;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    const uint32_t F = a.n_features, flow0 = blockIdx.x * FPB;
+    float* xT = reinterpret_cast<float*>(smem_raw); // [F][FPB]
+    uint32_t n = a.n_flows;
+    if (a.idx_count) {
+        const uint32_t c = *a.idx_count;
+        n = c < n ? c : n;
+        if (flow0 >= n) return; // the list ends before this block's tile (whole block leaves)
+    }
+    // A wave copies 16 columns of 64 rows at a time, a row to a lane: 64 bytes of a row are requested together.
+    const uint32_t waves = blockDim.x >> 6, lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool wide = (a.ld & 3u) == 0 && (F & 3u) == 0 && (reinterpret_cast<uintptr_t>(a.feat) & 15u) == 0;
+    const uint32_t units = (F + 15u) / 16u * U;
+    for (uint32_t k = wave; k < units; k += waves) {
+        const uint32_t slot = lane + 64u * (k % U), f0 = k / U * 16u;
+        uint32_t row = flow0 + slot;
+        row = row < n ? row : n - 1u; // a slot past the end holds a valid row
+        if (a.idx) {
+            row = a.idx[row];
+            row = row < a.n_rows ? row : a.n_rows - 1u; // a bad list entry must not leave the matrix
+        }
+        const float* x = a.feat + (size_t)row * a.ld + f0;
+        float* dst = xT + (size_t)f0 * FPB + slot;
+        if (wide) {
+            float4 v[4];
+#pragma unroll
+            for (uint32_t u = 0; u < 4u; ++u)
+                if (f0 + 4u * u < F) v[u] = reinterpret_cast<const float4*>(x)[u];
+#pragma unroll
+            for (uint32_t u = 0; u < 4u; ++u)
+                if (f0 + 4u * u < F) {
+                    dst[(4u * u + 0u) * FPB] = v[u].x;
+                    dst[(4u * u + 1u) * FPB] = v[u].y;
+                    dst[(4u * u + 2u) * FPB] = v[u].z;
+                    dst[(4u * u + 3u) * FPB] = v[u].w;
+                }
+        } else {
+            for (uint32_t u = 0; u < 16u && f0 + u < F; ++u) dst[u * FPB] = x[u];
+        }
+    }
+    forest_walk_waves<U, KW, GBDT, false>(a, xT, flow0, n);
+}
+
+template <int U, int KW, bool GBDT>
+int launch_trees(sf_ctx* ctx, const FastArgs& a, uint32_t result_words, uint32_t waves, int slot)
+{
+    const size_t lds = wave_walk_lds(a.n_features, result_words, GBDT, 64u * U, waves, KW);
+    SF_ALLOW_LDS(ctx, slot, (forest_trees<U, KW, GBDT>));
+    forest_trees<U, KW, GBDT><<<(a.n_flows - 1u) / (64u * U) + 1u, 64u * waves, lds, ctx->stream>>>(a);
+    SF_LAUNCH_CHECK(ctx, "forest_trees");
+    return SF_OK;
+}
+
+// A block of forest_trees: 64 * u flows, window of kw pair-levels, waves
+struct WaveShape {
+    uint32_t u, kw, waves;
+};
+
+template <bool GBDT>
+int launch_trees(sf_ctx* ctx, const FastArgs& a, uint32_t result_words, const WaveShape& s)
+{
+    const int slot = sf::kLdsTrees + (GBDT ? 5 : 0);
+    if (s.u == 4u) return s.kw == 4u ? launch_trees<4, 4, GBDT>(ctx, a, result_words, s.waves, slot) : launch_trees<4, 3, GBDT>(ctx, a, result_words, s.waves, slot + 1);
+    if (s.u == 2u) return s.kw == 4u ? launch_trees<2, 4, GBDT>(ctx, a, result_words, s.waves, slot + 2) : launch_trees<2, 3, GBDT>(ctx, a, result_words, s.waves, slot + 3);
+    return launch_trees<1, 4, GBDT>(ctx, a, result_words, s.waves, slot + 4);
+}
+
 } // namespace
 
 namespace sf {
@@ -191,31 +266,81 @@ uint32_t fused_one_lane_trees(uint32_t depth, uint32_t n_windows, uint32_t dmax,
     return full < 45u ? 6u : full < 60u ? 12u : full < 75u ? 32u : 64u;
 }
 
+// Which calls the form with a wave to a tree takes (forest_wave.h), and the block; false: the shapes of choose_shape.  Times are
+// the walk's in us, this form : the best shape that choose_shape knows; 100 trees and ten classes unless another number is named.
+//
+// Voting form: sixteen waves a block, two blocks a unit (32 waves, all it holds).
+//   Trees: from 48, a wave's trees are walked in rounds of sixteen and filling the tile has to be paid for (400,000 flows x 64
+//     features, depth 12: 70 trees 107 : 127, 47 85 : 96, 20 55 : 52); where the walk is short, from 96 (depth 8: 100 trees 84 : 96, 70
+//     69 : 68) or 192 (depth 4: 100 trees on 96 features 69 : 63, 200 trees as long or 1.1 times as fast).
+//   Flows: not where the blocks' last round has few of them, 128 to 192 flows a unit (0.97 times as fast in the mean of 550
+//     models, at worst 0.81; 1.12 times below, 1.16 above) and 256 to 320 (1.05 in the mean, one in eight 0.91 to 0.97; 1.17 above).
+//   Window: four pair-levels from depth 7 (400,000 x 64 features: depth 7 88 : 105, 10 105 : 119, 12 143 : 167, 13 277 : 357; three
+//     pair-levels 101, 113, 153, 281), three where depth ends there or shared memory has no room for more (128 features: depth 6
+//     86 : 101, 12 180 : 225; one block a unit with four 132, 215).
+//   256 flows a block from 1,200 flows a unit, where two such blocks fit (32 features, depth 12: 1,048,576 flows 284 : 357, with 128
+//     flows 314; 200,000 flows 80, with 128 72 : 82); 64 features have room for three pair-levels only (depth 6 67 : 79 and 8 84 : 96,
+//     with 128 flows 77, 88; deeper 128 flows are better: 112 and 105 at depth 10).
+//   64 flows a block up to 64 flows a unit, so that every unit has a block (8,000 flows 11.7 : 13.0; 20,000 flows 17 with 64, 15.8 with 128
+//     : 18.4; 65,536 26 : 33).
+//
+// Boosted form, a wave to a class: 5 to 16 classes, in large batches with up to 64 features 3 and 4 too; the largest tile that
+// leaves every unit a block and with which 18 waves or more are resident, four pair-levels before three (120 trees of depth 8,
+// 400,000 flows x 64 features: 3 classes 145 : 197, 5 113 : 171, 8 103 : 156, 10 104 : 156, 16 97 : 163; 96 features: 4 classes 149 : 137, 5
+// 147 : 202, 10 131 : 164; two classes 202 : 154; 10,000 flows, 3 and 4 classes 1.4 times as long; 8,000 flows, ten classes 13 : 20).
+bool waves_take(uint32_t n_trees, uint32_t depth, uint32_t n_rows, uint32_t n_cu)
+{
+    const uint32_t per_cu = n_rows / n_cu; // (few flows: blocks of 16, see choose_shape)
+    if (n_rows <= 24u * n_cu || (n_rows > 128u * n_cu && per_cu < 192u) || (n_rows > 256u * n_cu && per_cu < 320u)) return false;
+    return n_trees >= (depth <= 4u ? 192u : depth == 6u || depth == 8u ? 96u : 48u);
+}
+
+bool choose_waves(const FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n_rows, uint32_t n_cu, WaveShape* s)
+{
+    auto take = [&](uint32_t u, uint32_t kw, uint32_t waves, uint32_t least) { // least: waves a unit has to hold
+        *s = {u, kw, waves};
+        const uint32_t blocks = (uint32_t)(160u * 1024u / wave_walk_lds(a.n_features, result_words, gbdt, 64u * u, waves, kw));
+        return (blocks * waves < 32u ? blocks : 32u / waves) * waves >= least;
+    };
+    const bool deep = a.depth > 6u;
+    if (gbdt) {
+        const uint32_t C = a.n_classes;
+        if (n_rows <= 24u * n_cu || C > 16u || C < (a.n_features <= 64u && n_rows >= 384u * n_cu ? 3u : 5u)) return false;
+        for (uint32_t u = n_rows >= 320u * n_cu ? 4u : n_rows >= 128u * n_cu ? 2u : 1u; u >= 2u; u /= 2u)
+            if ((deep && take(u, 4, C, 18)) || take(u, 3, C, 18)) return true;
+        return take(1, 4, C, 18);
+    }
+    if (!waves_take(a.n_trees, a.depth, n_rows, n_cu)) return false;
+    if (n_rows <= 64u * n_cu) return take(1, 4, 16, 32);
+    if (n_rows >= 1200u * n_cu) {
+        if (deep && take(4, 4, 16, 32)) return true;
+        if (a.depth <= 8u && a.depth != 7u && take(4, 3, 16, 32)) return true;
+    }
+    return (deep && take(2, 4, 16, 32)) || take(2, 3, 16, 32);
+}
+
 // The shape of a block and its shared memory, by batch size and model.  All figures are the walk's time in
 // microseconds for 64 features and 100 trees of depth 12 unless another model is named.
 //   few flows: 16 flows x 32 lanes, nothing staged, so that even a small batch gives every compute unit a block and
 //     a lane only a few trees one after the other.  4,000 flows: 11 us against 15 (64x8) and 54 (one lane per
 //     flow); 10,000 flows: 17.6 against 16.1.  The line is 24 flows per compute unit (6,144).
-//   otherwise 64 x 8, four blocks per compute unit where 40 KB hold the tile and a pair-level of records; with
-//     enough flows to fill the chip with tiles twice as large (3 * 128 flows per unit: 80,000 flows 44 against 48 us,
-//     160,000 flows 78 against 77) 128 x 8 where its 80 KB hold one pair-level more than the smaller tile
-//     (1,048,576 flows: 450 -> 420; where they hold no more it is slower: 200 trees 272 against 293).
+//   otherwise 64 x 8, four blocks per compute unit where 40 KB hold the tile and a pair-level of records; in the fused
+//     kernel 128 flows in the form with a wave to a tree for the sizes that form takes (waves_take; the kernel in us before : after,
+//     ten classes: 1,048,576 flows, windows 8 and 16, 100 trees of depth 12 500 : 439, no rows kept 479 : 395; windows 5 and 10, depth
+//     10 367 : 336; 400,000 flows, 250 trees of depth 12 479 : 368, 100 of depth 8 133 : 126; 18,000 ragged flows 24 : 19, 65,000 43 : 34).
 //   fewer than 48 trees: 128 x 4, five trees at once per lane; eight lanes would walk a handful each
 //     (1,000,000 flows, 16 trees of depth 8: 62 against 76).
-//   256 flows, one lane each, in large batches where lanes that share a flow have nothing to share or stand in each other's
-//     way:
+//   256 flows, one lane each, in large batches where lanes that share a flow have nothing to share:
 //     a walk so short that reading the rows is all there is: 32 features, from 1,400 flows per unit (with up to four trees from
 //     750), few and shallow trees (200,000 flows, four trees of depth 4 8.7 us against 9.6; 1,048,576 flows, one tree of depth 8 35 against 45, 12 of depth 4 44 against 51, 24 of depth 4 53 against 63; but 16 of
-//     depth 6 1.13 times as long, and with 64 features equal);
-//     trees of depth 13 and 14, whose records (87 KB a tree) the caches cannot hold for eight trees at a time:
-//     1,048,576 flows, 32 features, 64 trees of depth 13 0.86 times as long, 100,000 flows, 100 trees 0.82.
+//     depth 6 1.13 times as long, and with 64 features equal).
 // Boosted form: lanes split the classes, not the trees (see forest_walk), so a few large shares are better than
 // many uneven ones: 256 x 2 (1,048,576 flows, 200 trees of depth 8: 585 against 599 for 64 x 4; with 32 features three blocks a
 // unit, 1.1 to 1.2 times as fast as two with more staged), 64 x 4 up to 3 * 128 flows per unit (30,000 flows 39 against 83 with one
 // lane per flow; two classes leave half of its lanes idle: with 40 trees or more 256 x 2 from 256 flows per unit, 95,000 flows
-// x 60 trees of depth 8 1.3 times as fast), 16 x 16 for few flows.  One class and three, and with 32 features five, leave lanes
+// x 60 trees of depth 8 1.3 times as fast), 16 x 16 for few flows.  One class and three leave lanes
 // idle that 256 x 1 does not have (three classes, 1,048,576 flows x 32 features: 150 trees of depth 6 316 against 341, 60 of depth 1
-// 82 against 120; five classes, 25 trees of depth 4 71 against 81; five classes and 64 features 1.02 to 1.16 times as long).
+// 82 against 120).
 // dmax: packets of the deepest window (fused kernel), 0 for the stand-alone walk.
 TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n_rows, uint32_t n_cu, uint32_t dmax, size_t* lds)
 {
@@ -236,7 +361,7 @@ TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n
         return s;
     }
     if (gbdt) {
-        const bool one_lane = a.n_classes == 1u || a.n_classes == 3u || (a.n_classes == 5u && a.n_features <= 32u);
+        const bool one_lane = a.n_classes == 1u || a.n_classes == 3u;
         fit(one_lane ? kTile256x1g : kTile256x2g, 160 * 1024 / 3 - 256, 1);
         if (one_lane && n_rows >= many && *lds <= 80 * 1024) return kTile256x1g;
         if (n_rows >= (a.n_classes <= 2u && a.n_trees >= 40u ? 256u * n_cu : many) && *lds <= 80 * 1024) return kTile256x2g; // (one block per unit is slower than the smaller tile)
@@ -246,8 +371,6 @@ TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n
     bool one_lane;
     if (dmax)
         one_lane = a.n_trees <= fused_one_lane_trees(a.depth, a.n_features / 32u, dmax, n_rows, n_cu);
-    else if (a.depth >= 13u)
-        one_lane = a.n_trees >= 64u && n_rows >= many;
     else
         one_lane = a.n_features <= 32u && (n_rows >= 1400u * n_cu
                                                ? (a.depth <= 5u ? a.n_trees < 48u : a.depth <= 7u ? a.n_trees <= 12u : a.depth <= 9u && a.n_trees <= 4u)
@@ -260,16 +383,11 @@ TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n
         fit(kTile128x4, 40 * 1024, 1);
         return kTile128x4;
     }
-    fit(kTile64x8, 40 * 1024, 1);
-    if (n_rows >= many) {
-        uint32_t top = 0;
-        const size_t wide = plan_lds(a, result_words, 128, 80 * 1024, &top);
-        if (wide <= 80 * 1024 && top > a.top_pairs) {
-            a.top_pairs = top;
-            *lds = wide;
-            return kTile128x8;
-        }
+    if (dmax && n_rows > 64u * n_cu && waves_take(a.n_trees, a.depth, n_rows, n_cu)) {
+        *lds = wave_walk_lds(a.n_features, result_words, false, 128, 16, 4);
+        return kTile128Waves;
     }
+    fit(kTile64x8, 40 * 1024, 1);
     return kTile64x8;
 }
 
@@ -344,11 +462,13 @@ int run_trees(sf_ctx* ctx, const char* who, const float* feat, uint32_t feat_ld,
     a.pred = out.pred;
     a.top = out.top_votes;
     a.leaf_idx = out.leaf_idx;
+    WaveShape wave;
+    if (!a.leaf_idx && choose_waves(a, result_words, gbdt, n_flows, (uint32_t)ctx->n_cu, &wave))
+        return gbdt ? launch_trees<true>(ctx, a, result_words, wave) : launch_trees<false>(ctx, a, result_words, wave);
     const TileShape shape = choose_shape(a, result_words, gbdt, n_flows, (uint32_t)ctx->n_cu, 0u, &lds);
     if (lds > 160 * 1024) return sf::fail(ctx, SF_EUNSUPPORTED, "%s: %zu bytes of shared memory needed", who, lds);
     const int slot = sf::kLdsForest + 2 * (int)shape;
     switch (shape) {
-    case kTile128x8: return launch_votes<128, 8, 3, 2, false>(ctx, a, lds, slot);
     case kTile128x4: return launch_votes<128, 4, 5, 4, false>(ctx, a, lds, slot);
     case kTile64x8: return launch_votes<64, 8, 3, 2, false>(ctx, a, lds, slot);
     case kTile16x32: return launch_votes<16, 32, 5, 2, false>(ctx, a, lds, slot);

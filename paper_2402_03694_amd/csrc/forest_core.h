@@ -20,7 +20,7 @@
 // times as many cache lines.  Measured, the walk alone, before -> after: 1,048,576 flows x 64 features, 100
 // trees of depth 12: 0.588 -> 0.42 ms; depth 10: 0.375 -> 0.29 ms; 4,194,304 flows x 128 features, 500 trees of
 // depth 10: 10.2 -> 6.2 ms; 65,536 flows, 200 trees of depth 10: 70 -> 46 us; 97 flows, 100 trees of depth 12:
-// 53 -> 11 us.
+// 53 -> 11 us.  Larger batches of many trees have a form of their own now, forest_wave.h.
 #pragma once
 
 #include <type_traits>
@@ -90,8 +90,68 @@ inline size_t plan_lds(const FastArgs& a, uint32_t result_words, uint32_t fpb, s
 }
 
 // The shapes a block of the walk comes in (flows x lanes per flow), see choose_shape
-enum TileShape { kTile128x8, kTile128x4, kTile64x8, kTile16x32, kTile256x1, kTile256x2g, kTile64x4g, kTile16x16g, kTile256x1g };
+enum TileShape { kTile128Waves, kTile128x4, kTile64x8, kTile16x32, kTile256x1, kTile256x2g, kTile64x4g, kTile16x16g, kTile256x1g };
 constexpr uint32_t kTileFlows[] = {128, 128, 64, 16, 256, 256, 64, 16, 256};
+
+// A flow's result from its column of class margins: label, score of the softmax (in binary64) and what else was asked for
+__device__ __forceinline__ void boosted_result(const FastArgs& a, const float* mcol, uint32_t stride, uint32_t i, uint32_t row)
+{
+    const uint32_t C = a.n_classes;
+    uint32_t bc = 0;
+    float bm = mcol[0];
+    for (uint32_t c = 1; c < C; ++c) {
+        const float m = mcol[c * stride];
+        if (m > bm) { // strict: the lowest class wins a tie
+            bm = m;
+            bc = c;
+        }
+    }
+    double z = 0.0;
+    for (uint32_t c = 0; c < C; ++c) z += exp((double)mcol[c * stride] - (double)bm);
+    double sc;
+    if (a.score_kind == SF_SCORE_ENTROPY) {
+        double h = 0.0;
+        for (uint32_t c = 0; c < C; ++c) {
+            const double p = exp((double)mcol[c * stride] - (double)bm) / z;
+            if (p > 0.0) h -= p * log(p);
+        }
+        sc = h;
+    } else {
+        sc = 1.0 - 1.0 / z; // the largest probability is exp(0) / z
+    }
+    if (a.margins)
+        for (uint32_t c = 0; c < C; ++c) a.margins[(size_t)i * C + c] = mcol[c * stride];
+    a.pred[i] = (uint16_t)bc;
+    a.score[i] = (float)sc;
+    if (a.labels) a.labels[row] = (uint16_t)bc;
+}
+
+// A flow's result from its column of packed vote counters
+__device__ __forceinline__ void vote_result(const FastArgs& a, const uint32_t* vcol, uint32_t stride, uint32_t i, uint32_t row,
+                                            uint32_t& best, uint32_t& bestv)
+{
+    best = 0;
+    bestv = 0;
+    const uint32_t C = a.n_classes, per_shift = a.vote_bits == 8 ? 2u : 1u, vote_words = (C + (1u << per_shift) - 1u) >> per_shift;
+    const uint32_t vmask = (1u << a.vote_bits) - 1u;
+    for (uint32_t w = 0; w < vote_words; ++w) {
+        const uint32_t word = vcol[w * stride];
+        for (uint32_t k = 0; k < (1u << per_shift); ++k) {
+            const uint32_t c = (w << per_shift) + k;
+            if (c < C) {
+                const uint32_t v = (word >> (k * a.vote_bits)) & vmask;
+                if (a.votes) a.votes[(size_t)i * C + c] = (uint16_t)v;
+                if (c == 0 || v > bestv) {
+                    bestv = v;
+                    best = c;
+                }
+            }
+        }
+    }
+    a.pred[i] = (uint16_t)best;
+    a.top[i] = (uint16_t)bestv;
+    if (a.labels) a.labels[row] = (uint16_t)best;
+}
 
 // Shared memory of a block behind the feature tile xT ([n_features][FPB] floats, FPB flows per block):
 // vote counters (or margins), then the staged top records.
@@ -297,57 +357,13 @@ __device__ __forceinline__ void forest_walk(const FastArgs& a, float* xT, uint32
     if (W > 1) __syncthreads(); // all lanes of a flow have added their votes before its first lane reads them
     if (GBDT) {
         if (!live || grp != 0) return;
-        const float* mcol = reinterpret_cast<const float*>(vcol);
-        uint32_t bc = 0;
-        float bm = mcol[0];
-        for (uint32_t c = 1; c < C; ++c) {
-            const float m = mcol[c * FPB];
-            if (m > bm) { // strict: the lowest class wins a tie
-                bm = m;
-                bc = c;
-            }
-        }
-        double z = 0.0;
-        for (uint32_t c = 0; c < C; ++c) z += exp((double)mcol[c * FPB] - (double)bm);
-        double sc;
-        if (a.score_kind == SF_SCORE_ENTROPY) {
-            double h = 0.0;
-            for (uint32_t c = 0; c < C; ++c) {
-                const double p = exp((double)mcol[c * FPB] - (double)bm) / z;
-                if (p > 0.0) h -= p * log(p);
-            }
-            sc = h;
-        } else {
-            sc = 1.0 - 1.0 / z; // the largest probability is exp(0) / z
-        }
-        if (a.margins)
-            for (uint32_t c = 0; c < C; ++c) a.margins[(size_t)i * C + c] = mcol[c * FPB];
-        a.pred[i] = (uint16_t)bc;
-        a.score[i] = (float)sc;
-        if (a.labels) a.labels[row] = (uint16_t)bc;
+        boosted_result(a, reinterpret_cast<const float*>(vcol), FPB, i, row);
         return;
     }
     bool keep = false;
     if (live && grp == 0) {
-        uint32_t best = 0, bestv = 0;
-        const uint32_t vmask = (1u << a.vote_bits) - 1u;
-        for (uint32_t w = 0; w < vote_words; ++w) {
-            const uint32_t word = vT[w * FPB + slot];
-            for (uint32_t k = 0; k < (1u << per_shift); ++k) {
-                const uint32_t c = (w << per_shift) + k;
-                if (c < C) {
-                    const uint32_t v = (word >> (k * a.vote_bits)) & vmask;
-                    if (a.votes) a.votes[(size_t)i * C + c] = (uint16_t)v;
-                    if (c == 0 || v > bestv) {
-                        bestv = v;
-                        best = c;
-                    }
-                }
-            }
-        }
-        a.pred[i] = (uint16_t)best;
-        a.top[i] = (uint16_t)bestv;
-        if (a.labels) a.labels[row] = (uint16_t)best;
+        uint32_t best, bestv;
+        vote_result(a, vT + slot, FPB, i, row, best, bestv);
         if (KEEP_ROWS) keep = bestv < a.vmin[a.n_vmin > 1u ? (best < a.n_vmin ? best : a.n_vmin - 1u) : 0u];
     }
     if (KEEP_ROWS) {
