@@ -4,8 +4,8 @@
 // theta (the single-tree tier), and either of them over the rows of an earlier list (the
 // second gate of a three-tier cascade, Section 3.1), which writes flow numbers, not rows.
 //
-// Two launches, no spinning between blocks: the first counts the escalated flows of each
-// block's contiguous chunk; the second adds up the counts of the blocks before it, then
+// Small batches: one launch (route_once).  Others: two launches, no spinning between blocks: the first counts
+// the escalated flows of each block's contiguous chunk; the second adds up the counts of the blocks before it, then
 // re-evaluates the gate and writes the indices in order (a wave-level prefix sum of per-lane
 // pop-counts gives each lane its write position).  The count stays on the device.
 #include <cmath>
@@ -21,6 +21,9 @@ constexpr int kBlock = 256;
 constexpr int kPerLane = 8;                // consecutive flows per lane per tile
 constexpr int kTile = kBlock * kPerLane;   // flows per block per tile
 constexpr uint32_t kMaxBlocks = 4096;
+constexpr int kOnceBlock = 1024;                  // small batches: one launch, see route_once
+constexpr uint32_t kOnceTile = kOnceBlock * kPerLane;
+constexpr uint32_t kOnceRows = 8u * kOnceTile, kOnceRowsTwo = 5u * kOnceTile; // gates that read one array, two arrays
 
 struct RouteArgs {
     const uint16_t* top;
@@ -56,12 +59,36 @@ __device__ __forceinline__ bool ratio_below(uint32_t top, uint32_t total, float 
     return (double)top < (double)theta * (double)total;
 }
 
-// 8-bit mask of the lane's rows [base, base+8) that escalate; n = live_rows(a)
-__device__ __forceinline__ uint32_t gate_mask(const RouteArgs& a, uint32_t n, uint32_t base)
+// eight consecutive 16-bit values from base on, a multiple of 8: one load where p is 16-byte aligned
+__device__ __forceinline__ void load8(const uint16_t* p, uint32_t base, uint16_t (&v)[kPerLane])
+{
+    if ((reinterpret_cast<uintptr_t>(p) & 15u) == 0) {
+        const uint4 w = *reinterpret_cast<const uint4*>(p + base);
+        const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[2 * k] = (uint16_t)(ww[k] & 0xFFFFu);
+            v[2 * k + 1] = (uint16_t)(ww[k] >> 16);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kPerLane; ++k) v[k] = p[base + k];
+    }
+}
+
+// 8-bit mask of the lane's rows [base, base+8) that escalate; n = live_rows(a), vmin: the thresholds in shared memory
+__device__ __forceinline__ uint32_t gate_mask(const RouteArgs& a, const uint16_t* vmin, uint32_t n, uint32_t base)
 {
     uint32_t m = 0;
     if (base >= n) return 0;
     if (a.score) {
+        if (base + kPerLane <= n && (reinterpret_cast<uintptr_t>(a.score) & 15u) == 0) {
+            const float4 v0 = *reinterpret_cast<const float4*>(a.score + base), v1 = *reinterpret_cast<const float4*>(a.score + base + 4);
+            const float v[kPerLane] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+            for (int k = 0; k < kPerLane; ++k) m |= (v[k] > a.score_thr ? 1u : 0u) << k;
+            return m;
+        }
         for (int k = 0; k < kPerLane; ++k) {
             const uint32_t i = base + k;
             if (i < n) m |= (a.score[i] > a.score_thr ? 1u : 0u) << k;
@@ -69,30 +96,33 @@ __device__ __forceinline__ uint32_t gate_mask(const RouteArgs& a, uint32_t n, ui
         return m;
     }
     if (a.total) {
+        if (base + kPerLane <= n) {
+            uint16_t v[kPerLane], tot[kPerLane];
+            load8(a.top, base, v);
+            load8(a.total, base, tot);
+#pragma unroll
+            for (int k = 0; k < kPerLane; ++k) m |= (ratio_below(v[k], tot[k], a.theta) ? 1u : 0u) << k;
+            return m;
+        }
         for (int k = 0; k < kPerLane; ++k) {
             const uint32_t i = base + k;
             if (i < n) m |= (ratio_below(a.top[i], a.total[i], a.theta) ? 1u : 0u) << k;
         }
         return m;
     }
-    if (base + kPerLane <= n && a.n_vmin == 1) {
-        // base is a multiple of 8: the 16-byte load is aligned whenever top is
+    if (base + kPerLane <= n) {
         uint16_t v[kPerLane];
-        if ((reinterpret_cast<uintptr_t>(a.top) & 15u) == 0) {
-            const uint4 w = *reinterpret_cast<const uint4*>(a.top + base);
-            const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+        load8(a.top, base, v);
+        if (a.n_vmin == 1) {
+            const uint16_t th = a.vmin[0];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                v[2 * k] = (uint16_t)(ww[k] & 0xFFFFu);
-                v[2 * k + 1] = (uint16_t)(ww[k] >> 16);
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < kPerLane; ++k) v[k] = a.top[base + k];
+            for (int k = 0; k < kPerLane; ++k) m |= (v[k] < th ? 1u : 0u) << k;
+            return m;
         }
-        const uint16_t th = a.vmin[0];
+        uint16_t p[kPerLane];
+        load8(a.pred, base, p);
 #pragma unroll
-        for (int k = 0; k < kPerLane; ++k) m |= (v[k] < th ? 1u : 0u) << k;
+        for (int k = 0; k < kPerLane; ++k) m |= (v[k] < vmin[p[k] < a.n_vmin ? p[k] : a.n_vmin - 1u] ? 1u : 0u) << k;
         return m;
     }
     for (int k = 0; k < kPerLane; ++k) {
@@ -102,12 +132,20 @@ __device__ __forceinline__ uint32_t gate_mask(const RouteArgs& a, uint32_t n, ui
             if (a.n_vmin > 1) {
                 uint32_t p = a.pred[i];
                 p = p < a.n_vmin ? p : a.n_vmin - 1;
-                th = a.vmin[p];
+                th = vmin[p];
             }
             m |= (a.top[i] < th ? 1u : 0u) << k;
         }
     }
     return m;
+}
+
+// the thresholds, into shared memory (a lane-dependent index into the kernel's arguments is a load from memory per row)
+__device__ __forceinline__ void stage_vmin(const RouteArgs& a, uint16_t* vmin)
+{
+    if (a.n_vmin <= 1u) return;
+    if (threadIdx.x < SF_MAX_CLASSES) vmin[threadIdx.x] = a.vmin[threadIdx.x];
+    __syncthreads();
 }
 
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v)
@@ -143,10 +181,12 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
 __global__ __launch_bounds__(kBlock) void route_count(RouteArgs a)
 {
     __shared__ uint32_t sm[kBlock / 64];
+    __shared__ uint16_t s_vmin[SF_MAX_CLASSES];
+    stage_vmin(a, s_vmin);
     const uint32_t begin = blockIdx.x * a.chunk;
     const uint32_t n = live_rows(a);
     uint32_t c = 0;
-    for (uint32_t t = 0; t < a.chunk; t += kTile) c += __popc(gate_mask(a, n, begin + t + threadIdx.x * kPerLane));
+    for (uint32_t t = 0; t < a.chunk; t += kTile) c += __popc(gate_mask(a, s_vmin, n, begin + t + threadIdx.x * kPerLane));
     const uint32_t inc = wave_inclusive_scan(c);
     if ((threadIdx.x & 63) == 63) sm[threadIdx.x >> 6] = inc;
     __syncthreads();
@@ -160,6 +200,8 @@ __global__ __launch_bounds__(kBlock) void route_count(RouteArgs a)
 __global__ __launch_bounds__(kBlock) void route_scatter(RouteArgs a)
 {
     __shared__ uint32_t sm[kBlock / 64];
+    __shared__ uint16_t s_vmin[SF_MAX_CLASSES];
+    stage_vmin(a, s_vmin);
     // sum of the counts of all earlier blocks (every lane ends up with the block-wide total)
     uint32_t part = 0;
     for (uint32_t b = threadIdx.x; b < blockIdx.x; b += kBlock) part += a.counts[b];
@@ -169,7 +211,7 @@ __global__ __launch_bounds__(kBlock) void route_scatter(RouteArgs a)
     const uint32_t n = live_rows(a);
     for (uint32_t t = 0; t < a.chunk; t += kTile) {
         const uint32_t base = begin + t + threadIdx.x * kPerLane;
-        const uint32_t m = gate_mask(a, n, base);
+        const uint32_t m = gate_mask(a, s_vmin, n, base);
         uint32_t tile_total;
         uint32_t pos = run + block_exclusive_scan(__popc(m), sm, tile_total);
 #pragma unroll
@@ -178,6 +220,43 @@ __global__ __launch_bounds__(kBlock) void route_scatter(RouteArgs a)
         run += tile_total;
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *a.esc_count = run;
+}
+
+// Both steps in one launch, for small batches: a block evaluates the gate for all rows before its own (up to seven tiles, from
+// the cache) instead of reading counts that another launch left.  In us, this : two launches: one threshold, 97 to 40,000
+// flows 5.3 : 8.1, 65,536 6.0 : 8.1, 98,304 7.2 : 8.1, 200,000 10.8 : 8.2; a score 4.7 : 7.7, 65,536 5.8 : 7.8; a threshold per class up to
+// 20,000 flows 5.8 : 8.7, 40,000 6.4 : 8.8, 65,536 8.4 : 8.8; shares of a leaf 5.1 : 8.3, 40,000 7.4 : 8.1, 65,536 10.1 : 8.2.
+__global__ __launch_bounds__(kOnceBlock) void route_once(RouteArgs a)
+{
+    __shared__ uint32_t s_own[kOnceBlock / 64], s_before[kOnceBlock / 64];
+    const uint32_t n = live_rows(a), begin = blockIdx.x * kOnceTile;
+    if (begin >= n && blockIdx.x != 0) return; // (a list that ends before this block)
+    __shared__ uint16_t s_vmin[SF_MAX_CLASSES];
+    stage_vmin(a, s_vmin);
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, at = threadIdx.x * kPerLane;
+    const uint32_t m = gate_mask(a, s_vmin, n, begin + at);
+    uint32_t before = 0;
+#pragma unroll 4
+    for (uint32_t t = 0; t < begin; t += kOnceTile) before += __popc(gate_mask(a, s_vmin, n, t + at));
+    const uint32_t own = wave_inclusive_scan(__popc(m));
+    before = wave_inclusive_scan(before);
+    if (lane == 63u) {
+        s_own[wave] = own;
+        s_before[wave] = before;
+    }
+    __syncthreads();
+    uint32_t first = 0, mine = 0, all = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kOnceBlock / 64u; ++w) {
+        first += s_before[w];
+        mine += w < wave ? s_own[w] : 0u;
+        all += s_own[w];
+    }
+    uint32_t pos = first + mine + own - __popc(m);
+#pragma unroll
+    for (int k = 0; k < kPerLane; ++k)
+        if (m & (1u << k)) a.esc_idx[pos++] = a.src_idx ? a.src_idx[begin + at + k] : begin + at + k;
+    if (threadIdx.x == 0 && (n <= begin || n - begin <= kOnceTile)) *a.esc_count = first + all; // the block with the last row
 }
 
 __global__ void route_zero(uint32_t* esc_count) { *esc_count = 0; }
@@ -349,6 +428,11 @@ int launch_route(sf_ctx* ctx, const char* who, RouteArgs& a, uint32_t* esc_idx, 
     a.counts = counts;
     a.esc_idx = esc_idx;
     a.esc_count = esc_count;
+    if (a.n <= (a.total || a.n_vmin > 1u ? kOnceRowsTwo : kOnceRows)) {
+        route_once<<<(a.n - 1u) / kOnceTile + 1u, kOnceBlock, 0, ctx->stream>>>(a);
+        SF_LAUNCH_CHECK(ctx, "route_once");
+        return SF_OK;
+    }
     route_count<<<grid, kBlock, 0, ctx->stream>>>(a);
     SF_LAUNCH_CHECK(ctx, "route_count");
     route_scatter<<<grid, kBlock, 0, ctx->stream>>>(a);
