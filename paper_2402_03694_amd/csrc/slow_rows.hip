@@ -335,8 +335,8 @@ struct Rows {
             const uint32_t row = row0 + i * 32u + (lane & 31u);
             float* lg = a.logits + (size_t)row * a.c;
             const bool write = a.logits && row < row_end;
-            uint32_t best = 0xFFFFFFFFu;
-            float bv = 0.f;
+            uint32_t best = 8u * half;
+            float bv = sftiles::label_start(half, out[i][0]);
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 if (16u * e >= a.c) break;
@@ -346,15 +346,12 @@ struct Rows {
                     const float y = out[i][8 * e + v];
                     const bool there = c < a.c;
                     if (write && there) lg[c] = y;
-                    const bool take = there && (best == 0xFFFFFFFFu || y > bv);
+                    const bool take = there && y > bv;
                     bv = take ? y : bv;
                     best = take ? c : best;
                 }
             }
-            // the other half of the row: larger value wins, the lower class on a tie
-            const float ov = __shfl_xor(bv, 32, 64);
-            const uint32_t ob = (uint32_t)__shfl_xor((int)best, 32, 64);
-            if (ob != 0xFFFFFFFFu && (best == 0xFFFFFFFFu || ov > bv || (ov == bv && ob < best))) best = ob;
+            best = sftiles::label_of(best, bv);
             if (i == 0 || half) label = best;
         }
         if (own_ok && dst < a.n_labels) a.labels[dst] = (uint16_t)label;

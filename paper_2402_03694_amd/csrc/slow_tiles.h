@@ -69,6 +69,18 @@ __device__ __forceinline__ uint32_t relu_pair(float lo, float hi)
     return pack_bf16(__builtin_amdgcn_fmed3f(lo, 0.f, 3.402823466e38f), __builtin_amdgcn_fmed3f(hi, 0.f, 3.402823466e38f));
 }
 
+// The label of a row whose classes two lanes hold, lane l and lane l ^ 32: class 0 first, then every class that is strictly larger
+// than all before it.  A NaN is larger than nothing, and nothing than a NaN in class 0, which counts as infinity here; so what a
+// lane holds is never NaN, and the two lanes come to the same label.
+// A lane starts before its first class (the lower lane's is class 0, whose logit is y0) and takes c where y > bv.
+__device__ __forceinline__ float label_start(uint32_t half, float y0) { return half ? -__builtin_inff() : y0 == y0 ? y0 : __builtin_inff(); }
+__device__ __forceinline__ uint32_t label_of(uint32_t best, float bv)
+{
+    const float ov = __shfl_xor(bv, 32, 64);
+    const uint32_t ob = (uint32_t)__shfl_xor((int)best, 32, 64);
+    return ov > bv || (ov == bv && ob < best) ? ob : best; // (a lane without classes holds -infinity and a number past the last)
+}
+
 constexpr int kMI = 4;     // 32-row blocks of the tallest tile (128 rows)
 constexpr int kRing = 4;   // weight operands of this many k-steps are in flight (K is padded to 16 * kRing)
 
@@ -427,24 +439,22 @@ __device__ __forceinline__ void run_tiles(const FusedArgs& a, const FusedSmem& m
                 // the accumulator is transposed: lane l holds 16 classes of row l%32, lane l^32 the others
                 const uint32_t r = rb * 32u + (lane & 31u);
                 const bool row_ok = row0 + r < row_end;
-                uint32_t best = kNoFlow;
+                uint32_t best = 4u * (lane >> 5);
                 float bv = 0.f;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const uint32_t c = 8u * (v >> 2) + 4u * (lane >> 5) + (v & 3); // ascending in v
+                    const float y = ONE_SUM ? c3[v] : c3[v] + part[v * 64 + lane] + m.s_b3[c];
+                    if (v == 0) bv = label_start(lane >> 5, y);
                     if (c < a.c) {
-                        const float y = ONE_SUM ? c3[v] : c3[v] + part[v * 64 + lane] + m.s_b3[c];
                         if (a.logits && row_ok) a.logits[(size_t)(row0 + r) * a.c + c] = y;
-                        if (best == kNoFlow || y > bv) {
+                        if (y > bv) {
                             bv = y;
                             best = c;
                         }
                     }
                 }
-                // combine the two halves of the row: larger value wins, the lower class on a tie
-                const float ov = __shfl_xor(bv, 32, 64);
-                const uint32_t ob = (uint32_t)__shfl_xor((int)best, 32, 64);
-                if (ob != kNoFlow && (best == kNoFlow || ov > bv || (ov == bv && ob < best))) best = ob;
+                best = label_of(best, bv);
                 if (lane < 32u && row_ok) {
                     const uint32_t dst = a.scatter ? a.scatter[row0 + r] : flow_cur[r];
                     if (dst < a.n_labels) a.labels[dst] = (uint16_t)best;

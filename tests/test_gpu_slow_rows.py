@@ -90,6 +90,47 @@ def test_labels_alone():
     assert torch.equal(full[3], alone[3])
 
 
+def _labels(logits):
+    """The oracle's rule: class 0 first, then every class that is strictly larger than the best before it."""
+    import numpy as np
+    v = logits.cpu().numpy()
+    best, label = v[:, 0].copy(), np.zeros(len(v), np.int16)
+    for c in range(1, v.shape[1]):
+        take = v[:, c] > best   # (false beside a NaN)
+        best[take], label[take] = v[take, c], c
+    return label
+
+
+@pytest.mark.parametrize("classes,bad", [(10, {0: "nan"}), (10, {8: "nan"}), (10, {4: "nan"}), (10, {c: "nan" for c in range(10)}), (4, {0: "nan", 3: "nan"}),
+                                         (32, {c: "nan" for c in (4, 8, 12, 16, 20)}), (32, {c: "nan" for c in range(8, 16)}), (17, {16: "nan"}),
+                                         (10, {c: "-inf" for c in range(10)}), (10, {0: "-inf", 1: "nan", 8: "nan", 9: "inf"}), (9, {3: "inf", 8: "inf"})])
+@pytest.mark.parametrize("rows,cap", [(416 * UNITS + 31, 416 * UNITS + 31), (100 * UNITS, CAP), (63 * UNITS, CAP), (20 * UNITS, CAP), (100 * UNITS, 128 * UNITS),
+                                      (50, 60)])
+def test_labels_of_missing_logits(rows, cap, classes, bad):
+    """Logits that are NaN or infinite: the label does not follow from where the row stands (full pass and tile, low pass, tiles of two and
+    one row blocks, the tiles of shorter lists), and neither half of the classes hides the other's."""
+    import numpy as np
+    import torch
+    import paper_2402_03694_amd as sf
+    g = torch.Generator(device=DEV)
+    g.manual_seed(classes + len(bad))
+    dims = (64, 160, 96, classes)
+    mlp = _model(g, dims, True)
+    for c, v in bad.items():
+        mlp.b3[c] = float(v)
+    feat = torch.randn((cap, 64), device=DEV, generator=g)
+    idx = torch.arange(cap, device=DEV, dtype=torch.int32)
+    logits = torch.empty((cap, classes), device=DEV)
+    labels = torch.full((cap,), -1, dtype=torch.int16, device=DEV)
+    count = torch.tensor([rows], dtype=torch.int32, device=DEV)
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(cap, 0, 0, *dims[:3]))
+    torch.cuda.synchronize()
+    ctx.sf_slow_infer(mlp, idx, count, labels, feat=feat, logits=logits)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.isnan(logits[:rows]).all(0).cpu(), torch.tensor([bad.get(c) == "nan" for c in range(classes)]))
+    assert np.array_equal(labels[:rows].cpu().numpy(), _labels(logits[:rows]))
+
+
 def test_values_past_the_finite():
     """Infinite and missing inputs stay with their own rows, and a hidden NaN counts as zero (the input map keeps NaN, relu does not)."""
     import torch
