@@ -9,9 +9,10 @@
 // consecutive rows fall on distinct banks); the weights are re-ordered once per call so that
 // the 8 K-values a lane needs for an MFMA B operand are contiguous and a wave's operand is one
 // contiguous kilobyte, and are then read straight from the cache into registers.  There is no
-// barrier inside a layer's K loop.  The last layer (at most 32 classes) runs on all eight waves
-// (four row blocks x two halves of K), followed by a per-row arg-max in registers and the
-// scatter of the label.
+// barrier inside a layer's K loop.  The last layer (at most 32 classes) takes a wave per row block, so that a
+// logit is one sum in order of K as in the register form, followed by a per-row arg-max in registers and the scatter of the
+// label.  (Two waves per row block, halves of K added at the end, against one, in us: 64-512-512-10 8,000 rows 15.7 : 16.3, 32,768
+// rows 23.9 : 23.3, 300,000 rows 200-512-512-10 280 : 276; but a row's logits then followed the list's capacity.)
 // Long lists of rows with up to 128 values go through the register form instead (slow_rows.hip); the rule is at slow_fused().
 // Blocks are persistent.  The rows that exist (the device-side escalation count) are cut into
 // row blocks of 32 and dealt out evenly: every block gets a run of consecutive row blocks, the runs
@@ -76,8 +77,7 @@ __global__ __launch_bounds__(kWaves * 64) void mlp_fused(FusedArgs a)
     m.s_b1 = reinterpret_cast<float*>(m.s_flow + 2 * FBM);                      // [HMAX], zero past h1
     m.s_b2 = m.s_b1 + HMAX;                                                     // [HMAX], zero past h2
     m.s_b3 = m.s_b2 + HMAX;                                                     // [32], zero past c
-    m.s_part = m.s_b3 + 32;                                                     // [4][16][64] last-layer partial sums
-    m.s_mu = m.s_part + 4 * 16 * 64;                                            // [HMAX] input map (0 / 1 if none)
+    m.s_mu = m.s_b3 + 32;                                                       // [HMAX] input map (0 / 1 if none)
     m.s_is = m.s_mu + HMAX;                                                     // [HMAX]
     // the wave index is the same in every lane: say so, and everything derived from it (column
     // block, weight pointers) lives in scalar registers
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(kWaves * 64) void mlp_fused(FusedArgs a)
     if (rest == 1u || rest == 2u) run_tiles<kWaves, kNI, 2>(a, m, wave, row_begin + n_full * FBM, 1u, row_end);
 }
 
-constexpr size_t kFusedLds = (size_t)FBM * LDH * 2 + 2 * FBM * 4 + (4 * HMAX + 32) * 4 + 4 * 16 * 64 * 4;
+constexpr size_t kFusedLds = (size_t)FBM * LDH * 2 + 2 * FBM * 4 + (4 * HMAX + 32) * 4;
 
 } // namespace
 

@@ -444,7 +444,6 @@ __global__ __launch_bounds__(kWaves * 64, 1) void mlp_rows(RowsArgs a)
         m.s_b3 = b3;
         m.H = reinterpret_cast<uint16_t*>(xall);
         m.s_flow = reinterpret_cast<uint32_t*>(m.H + 64 * sftiles::LDH);
-        m.s_part = nullptr; // (one sum per logit)
         m.s_mu = reinterpret_cast<float*>(m.s_flow + 2 * sftiles::FBM);
         m.s_is = m.s_mu + sftiles::HMAX;
         __syncthreads(); // the passes are done with the shared memory
@@ -456,14 +455,14 @@ __global__ __launch_bounds__(kWaves * 64, 1) void mlp_rows(RowsArgs a)
         // (columns split over the waves as evenly as whole column blocks allow)
         if (NB1 < 16 && a.nb2 <= (uint32_t)NB1) {
             if (rest == 1u)
-                sftiles::run_tiles<kWaves, NB1 / kWaves, 1, true>(a, m, wave, first, 1u, row_end);
+                sftiles::run_tiles<kWaves, NB1 / kWaves, 1>(a, m, wave, first, 1u, row_end);
             else
-                sftiles::run_tiles<kWaves, NB1 / kWaves, 2, true>(a, m, wave, first, 1u, row_end);
+                sftiles::run_tiles<kWaves, NB1 / kWaves, 2>(a, m, wave, first, 1u, row_end);
         } else {
             if (rest == 1u)
-                sftiles::run_tiles<kWaves, 16 / kWaves, 1, true>(a, m, wave, first, 1u, row_end);
+                sftiles::run_tiles<kWaves, 16 / kWaves, 1>(a, m, wave, first, 1u, row_end);
             else
-                sftiles::run_tiles<kWaves, 16 / kWaves, 2, true>(a, m, wave, first, 1u, row_end);
+                sftiles::run_tiles<kWaves, 16 / kWaves, 2>(a, m, wave, first, 1u, row_end);
         }
     }
 }

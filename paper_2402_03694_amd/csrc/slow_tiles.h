@@ -86,8 +86,8 @@ constexpr int kRing = 4;   // weight operands of this many k-steps are in flight
 
 __device__ __forceinline__ uint32_t weight_lane(uint32_t lane) { return (lane & ~12u) | ((lane & 4u) << 1) | ((lane & 8u) >> 1); }
 
-// ONE_SUM: a logit is one sum, from its bias on in order of K, as in the register form (a row's result does not depend on whether it
-// falls into a pass or a tile); else two halves of K are summed side by side.
+// A logit is one sum, from its bias on in order of K, in the tiles as in the passes of the register form: a row's logits do not depend
+// on where in a list it stands, nor on the list's capacity or the input's alignment, which decide between the forms.
 // W: waves of the block, NI: 32-column blocks per wave (W * NI up to 16), MI: 32-row blocks of the tile
 
 // first kRing k-steps of a wave's weight operands (column blocks nb0 .. nb0+NI, clamped to the last real one)
@@ -280,25 +280,23 @@ __device__ __forceinline__ void store_chunk(bool has_map, const float* s_mu, con
 //   layer 1    MFMA, then the next tile's flow ids are parked in shared memory, epilogue -> H
 //   layer 2    MFMA, epilogue -> H; the last layer's weight operands are requested
 //   layer 3    the next tile's feature rows are requested (they arrive while layer 3 runs);
-//              waves = MI row blocks x 2 halves of K (waves beyond that idle); halves are
-//              summed through shared memory
+//              a wave takes a row block (waves beyond MI idle)
 // Rows from row_end on belong to another block (or do not exist): they read as zeros and nothing of
 // theirs is stored.
 struct FusedSmem {
     uint16_t* H;      // [32 MI][LDH]; also the input tile
     uint32_t* s_flow; // [2][128]: this tile, next tile
-    float *s_b1, *s_b2, *s_b3, *s_part, *s_mu, *s_is;
+    float *s_b1, *s_b2, *s_b3, *s_mu, *s_is;
 };
 
-template <int W, int NI, int MI, bool ONE_SUM = false>
+template <int W, int NI, int MI>
 __device__ __forceinline__ void run_tiles(const FusedArgs& a, const FusedSmem& m, uint32_t wave, uint32_t row_begin,
                                           uint32_t n_tiles, uint32_t row_end)
 {
     constexpr uint32_t TM = MI * 32u; // rows per tile
     constexpr int kXr = kChunks<W>;
-    constexpr uint32_t KH = ONE_SUM ? 1 : 2; // shares of K in the last layer
-    constexpr int kW3 = ONE_SUM ? 32 : 16;   // its weight operands that are requested at once
-    static_assert(W >= 2 * MI && W * NI <= 16, "a wave for every row block and half of K, 512 columns at most");
+    constexpr int kW3 = HMAX / 16; // weight operands of the last layer
+    static_assert(W >= MI && W * NI <= 16, "a wave for every row block, 512 columns at most");
     uint16_t* H = m.H;
     uint32_t* s_flow = m.s_flow;
     const uint32_t k1p = up(a.n_in, kPadK), k2p = up(a.h1, kPadK), k3p = up(a.h2, kPadK);
@@ -375,17 +373,17 @@ __device__ __forceinline__ void run_tiles(const FusedArgs& a, const FusedSmem& m
         wave_gemm<NI, MI>(H, LDH, a.w2s, k2p / 16u, wave * NI, nb2, lane, acc, fb, a.w1s, k1p / 16u, nb1);
         __syncthreads();
         store_hidden<NI, MI>(H, acc, n0, k3p, nb2, lane);
-        // layer 3: wave = (row block rb, half kh of K); waves beyond MI x 2 only keep the barriers.  The hidden
-        // accumulators are dead, so a whole half-layer of weight operands fits in registers; they are requested
-        // before the barrier so that their latency overlaps it.
-        const uint32_t rb = wave % (uint32_t)MI, kh = wave / (uint32_t)MI;
-        const bool l3 = W == (int)KH * MI ? true : kh < KH; // (the branch would otherwise cost registers)
-        const uint32_t KS3 = k3p / 16u, khalf = KS3 / KH, kbeg = (l3 ? kh : 0u) * khalf; // KS3 is a multiple of 4
+        // layer 3: wave = row block; waves beyond MI only keep the barriers.  The hidden accumulators are dead, so all its
+        // weight operands fit in registers; they are requested before the barrier so that their latency overlaps it.
+        const bool l3 = wave < (uint32_t)MI;
+        const uint32_t KS3 = k3p / 16u; // a multiple of 4
+        const uint32_t last3 = l3 ? KS3 - 4u : 0u; // (the other waves request the first four again and again: a branch here costs registers)
         uint4 wv[kW3];
-        if (l3) {
 #pragma unroll
-            for (int s3 = 0; s3 < kW3; ++s3)
-                wv[s3] = a.w3s[(size_t)(kbeg + ((uint32_t)s3 < khalf ? (uint32_t)s3 : khalf - 1u)) * 64u + lane];
+        for (int g = 0; g < kW3 / 4; ++g) {
+            const uint4* w = a.w3s + (4u * g < last3 ? 4u * g : last3) * 64u + lane;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) wv[4 * g + q] = w[q * 64];
         }
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
@@ -399,52 +397,39 @@ __device__ __forceinline__ void run_tiles(const FusedArgs& a, const FusedSmem& m
         }
         __builtin_amdgcn_sched_barrier(0);
         {
-            f32x16 c3, c3b;
+            f32x16 c3;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                c3[v] = ONE_SUM ? m.s_b3[8u * (v >> 2) + 4u * (lane >> 5) + (v & 3)] : 0.f;
-                c3b[v] = 0.f;
-            }
-            const uint16_t* arow = H + (rb * 32u + (lane & 31u)) * LDH + 8u * (lane >> 5);
+            for (int v = 0; v < 16; ++v) c3[v] = m.s_b3[8u * (v >> 2) + 4u * (lane >> 5) + (v & 3)];
+            const uint16_t* arow = H + (wave * 32u + (lane & 31u)) * LDH + 8u * (lane >> 5);
             if (l3) {
-                for (uint32_t kb = 0; kb < khalf; kb += kW3) {
-                    if (kb) {
+                // the activation operands of two k-steps are read while the two before are multiplied
+                auto read2 = [&](uint4 (&f)[2], int s3) {
 #pragma unroll
-                        for (int s3 = 0; s3 < kW3; ++s3)
-                            wv[s3] = a.w3s[(size_t)(kbeg + (kb + s3 < khalf ? kb + s3 : khalf - 1u)) * 64u + lane];
-                    }
+                    for (int q = 0; q < 2; ++q) f[q] = *reinterpret_cast<const uint4*>(arow + (s3 + q) * 16);
+                };
+                uint4 fa[2][2];
+                read2(fa[0], 0);
 #pragma unroll
-                    for (int s3 = 0; s3 < kW3; s3 += 2) {
-                        if (kb + s3 < khalf)
-                            c3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                as_frag(wv[s3]), as_frag(*reinterpret_cast<const uint4*>(arow + (kbeg + kb + s3) * 16u)), c3, 0, 0, 0);
-                        if (kb + s3 + 1 < khalf) {
-                            f32x16& to = ONE_SUM ? c3 : c3b;
-                            to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                as_frag(wv[s3 + 1]), as_frag(*reinterpret_cast<const uint4*>(arow + (kbeg + kb + s3 + 1) * 16u)), to, 0, 0, 0);
-                        }
-                    }
+                for (int s3 = 0; s3 < kW3; s3 += 2) {
+                    if ((uint32_t)(s3 & ~3) >= KS3) continue;
+                    if (s3 + 2 < kW3) read2(fa[(s3 / 2 + 1) & 1], s3 + 2); // (past the layer's K: not used)
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+                        c3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(wv[s3 + q]), as_frag(fa[(s3 / 2) & 1][q]), c3, 0, 0, 0);
                 }
             }
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if (!ONE_SUM) c3[v] += c3b[v];
-            float* part = m.s_part + rb * (16 * 64);
-            if (!ONE_SUM && l3 && kh == 1u) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) part[v * 64 + lane] = c3[v];
-            }
             __syncthreads(); // also: every wave is done reading H
-            if (l3 && kh == 0u) {
+            if (l3) {
                 // the accumulator is transposed: lane l holds 16 classes of row l%32, lane l^32 the others
-                const uint32_t r = rb * 32u + (lane & 31u);
+                const uint32_t r = wave * 32u + (lane & 31u);
                 const bool row_ok = row0 + r < row_end;
                 uint32_t best = 4u * (lane >> 5);
                 float bv = 0.f;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const uint32_t c = 8u * (v >> 2) + 4u * (lane >> 5) + (v & 3); // ascending in v
-                    const float y = ONE_SUM ? c3[v] : c3[v] + part[v * 64 + lane] + m.s_b3[c];
+                    const float y = c3[v];
                     if (v == 0) bv = label_start(lane >> 5, y);
                     if (c < a.c) {
                         if (a.logits && row_ok) a.logits[(size_t)(row0 + r) * a.c + c] = y;

@@ -82,6 +82,33 @@ def test_place_in_the_list(dims):
         assert torch.equal(logits[:rows], first[torch.arange(rows, device=DEV) % 512])
 
 
+@pytest.mark.parametrize("dims", [(64, 512, 512, 10), (100, 130, 70, 32), (128, 300, 500, 7), (4, 40, 20, 1), (64, 384, 160, 17)])
+@pytest.mark.parametrize("rows", [40, 20011, 128 * UNITS])
+def test_forms_agree(dims, rows):
+    """A row's logits are the same bits whatever decides between the forms: the list's capacity, the input's row stride, its alignment."""
+    import torch
+    import paper_2402_03694_amd as sf
+    g = torch.Generator(device=DEV)
+    g.manual_seed(dims[1] + rows)
+    mlp = _model(g, dims, True)
+    x = torch.randn((CAP, dims[0]), device=DEV, generator=g)
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(CAP, 0, 0, *dims[:3]))
+    outs = []
+    for cap, ld, offset in ((rows, dims[0], 0), (128 * UNITS, dims[0], 0), (CAP, dims[0], 0), (CAP, dims[0] + 1, 0), (CAP, dims[0], 1)):
+        flat = torch.zeros(CAP * ld + 1, device=DEV)
+        feat = flat[offset:offset + CAP * ld].view(CAP, ld)
+        feat[:, :dims[0]] = x
+        logits = torch.full((cap, dims[3]), float("nan"), device=DEV)
+        labels = torch.full((CAP,), -1, dtype=torch.int16, device=DEV)
+        idx = torch.arange(cap, device=DEV, dtype=torch.int32)
+        torch.cuda.synchronize()
+        ctx.sf_slow_infer(mlp, idx, torch.tensor([rows], dtype=torch.int32, device=DEV), labels, feat=feat, logits=logits)
+        torch.cuda.synchronize()
+        outs.append((logits[:rows], labels))
+    for logits, labels in outs[1:]:
+        assert torch.equal(logits, outs[0][0]) and torch.equal(labels, outs[0][1])
+
+
 def test_labels_alone():
     import torch
     rows = 260 * UNITS
