@@ -11,8 +11,8 @@
 // contiguous kilobyte, and are then read straight from the cache into registers.  There is no
 // barrier inside a layer's K loop.  The last layer (at most 32 classes) takes a wave per row block, so that a
 // logit is one sum in order of K as in the register form, followed by a per-row arg-max in registers and the scatter of the
-// label.  (Two waves per row block, halves of K added at the end, against one, in us: 64-512-512-10 8,000 rows 15.7 : 16.3, 32,768
-// rows 23.9 : 23.3, 300,000 rows 200-512-512-10 280 : 276; but a row's logits then followed the list's capacity.)
+// label.  (Two waves per row block, halves of K added at the end, were no faster, 64-512-512-10 8,000 rows 15.6 against 15.1 us, 32,768
+// rows 23.8 against 23.1, and a row's logits then followed the list's capacity.)
 // Long lists of rows with up to 128 values go through the register form instead (slow_rows.hip); the rule is at slow_fused().
 // Blocks are persistent.  The rows that exist (the device-side escalation count) are cut into
 // row blocks of 32 and dealt out evenly: every block gets a run of consecutive row blocks, the runs
@@ -206,11 +206,13 @@ int slow_fused(sf_ctx* ctx, void* ws, bool ws_is_ordered, const float* feat, uin
     a.b3 = m->b3;
     a.logits = logits;
     a.labels = labels;
-    // Register form: lists that may give a compute unit more than 128 rows (up to there the tiles' eight waves are as fast or
-    // faster: 10,007 rows through 64-512-512-10 16.8 : 17.1 us, 96-300-200-10 13.1 : 14.7, 24,500 rows 32-256-256-10 16.5 : 16.4; past it,
-    // 40,000 rows 38.3 : 34.7, 29.9 : 28.7, 24.5 : 21.0), and models whose second layer is not wide for the first one's depth
-    // (a column block's work beside its MFMAs is the same whatever the depth: 300,000 rows 60-40-500-10 106 : 112 us, 64-200-500-10
+    // Register form: lists that may give a compute unit more than 128 rows, and models whose second layer is not wide for the first
+    // one's depth (a column block's work beside its MFMAs is the same whatever the depth: 300,000 rows 60-40-500-10 106 : 112 us, 64-200-500-10
     // 137 : 130, 24,500 of them 19.1 : 24.4).
+    // The capacity decides, since the count is on the device, and a long list may hold few rows.  In us, tiles of eight waves : this
+    // form under a capacity of 300,000: 64-512-512-10 8,000 rows 15.2 : 14.5, 16,000 15.1 : 16.2, 32,000 23.1 : 23.3, 60,000 43 : 35;
+    // 96-300-200-10 11.3 : 10.4, 11.2 : 12.5, 17.6 : 17.2, 33 : 27; 32-256-256-10 9.7 : 9.9, 9.9 : 10.0, 13.3 : 15.6, 26 : 20.5.  So a line
+    // further up would lose more on full lists than it gave on sparse ones.
     const uint32_t nb1 = up(a.h1, 32) / 32u, nb2 = up(a.h2, 32) / 32u;
     if (esc_cap > 128u * (uint32_t)ctx->n_cu && nb2 <= 2u * nb1 && a.n_in <= 128 && (a.n_in & 3u) == 0 && (feat_ld & 3u) == 0 &&
         ((uintptr_t)feat & 15u) == 0) {

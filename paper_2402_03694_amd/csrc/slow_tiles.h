@@ -3,6 +3,8 @@
 // (slow_fused.hip) and by the register form (slow_rows.hip), which ends a run of rows with such a tile.
 #pragma once
 
+#include <type_traits>
+
 #include "mlp_common.h"
 
 namespace sftiles {
@@ -236,19 +238,28 @@ template <int W>
 constexpr int kChunks = 16 / W;
 
 // raw feature values [k, k+8) of one flow (zeros for a missing flow or past n_in)
+// WHOLE: rows in whole 16-byte elements, and no branch: a thread's requests go out together, not one after the other's arrival
+template <bool WHOLE>
 __device__ __forceinline__ void load_chunk(const FusedArgs& a, uint32_t flow, uint32_t k, float (&z)[8])
 {
+    const bool there = flow != kNoFlow;
+    const float* p = a.feat + (size_t)(there ? flow : 0u) * a.feat_ld;
+    if (WHOLE) {
+        const bool in0 = k < a.n_in, in1 = k + 4u < a.n_in;
+        const float4 x0 = *reinterpret_cast<const float4*>(p + (in0 ? k : 0u)), x1 = *reinterpret_cast<const float4*>(p + (in1 ? k + 4u : 0u));
+        const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
 #pragma unroll
-    for (int q = 0; q < 8; ++q) z[q] = 0.f;
-    if (flow == kNoFlow) return;
-    const float* p = a.feat + (size_t)flow * a.feat_ld + k;
-    if (k + 8u <= a.n_in && (a.feat_ld & 3u) == 0 && (reinterpret_cast<uintptr_t>(a.feat) & 15u) == 0) {
+        for (int q = 0; q < 8; ++q) z[q] = there && (q < 4 ? in0 : in1) ? x[q] : 0.f;
+        return;
+    }
+    p += k;
+    if (there && k + 8u <= a.n_in && (a.feat_ld & 3u) == 0 && (reinterpret_cast<uintptr_t>(a.feat) & 15u) == 0) {
         const float4 x0 = reinterpret_cast<const float4*>(p)[0], x1 = reinterpret_cast<const float4*>(p)[1];
         z[0] = x0.x; z[1] = x0.y; z[2] = x0.z; z[3] = x0.w;
         z[4] = x1.x; z[5] = x1.y; z[6] = x1.z; z[7] = x1.w;
     } else {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) z[q] = k + q < a.n_in ? p[q] : 0.f;
+        for (int q = 0; q < 8; ++q) z[q] = there && k + q < a.n_in ? p[q] : 0.f;
     }
 }
 
@@ -305,8 +316,25 @@ __device__ __forceinline__ void run_tiles(const FusedArgs& a, const FusedSmem& m
     const uint32_t nb1 = up(a.h1, 32) / 32u, nb2 = up(a.h2, 32) / 32u;
     const uint32_t chunks = k1p / 8u;
     const bool in_regs = TM * chunks <= (uint32_t)kXr * W * 64u; // the whole input tile fits the threads' registers
+    const bool whole = ((a.n_in | a.feat_ld) & 3u) == 0 && (reinterpret_cast<uintptr_t>(a.feat) & 15u) == 0;
     const bool has_map = a.mu != nullptr;
     float xr[kXr][8];
+    auto request_rows = [&](const uint32_t* flows, uint32_t tid) {
+        auto each = [&](auto w) {
+#pragma unroll
+            for (int u = 0; u < kXr; ++u) {
+                const uint32_t g = tid + u * W * 64u, r = g / chunks, k = (g - r * chunks) * 8u;
+                load_chunk<decltype(w)::value>(a, r < TM ? flows[r] : kNoFlow, k, xr[u]);
+            }
+        };
+        if (whole)
+            each(std::true_type{});
+        else
+            each(std::false_type{});
+    };
+    // weight operands of layer 1's first k-steps; from here on every GEMM leaves the ring filled for the next one
+    uint4 fb[kRing][NI];
+    ring_fill(fb, a.w1s, k1p / 16u, wave * NI, nb1, threadIdx.x & 63u);
     __syncthreads(); // the previous run of tiles (if any) is done with the tile and the flow ids
     {
         // first tile: flow ids and feature rows are fetched here, with nothing to overlap them
@@ -316,17 +344,8 @@ __device__ __forceinline__ void run_tiles(const FusedArgs& a, const FusedSmem& m
         asm volatile("" : "+v"(tid));
         if (tid < TM) s_flow[tid] = row_begin + tid < row_end ? clamp_row(a.esc_idx[row_begin + tid], a.n_rows) : kNoFlow;
         __syncthreads();
-        if (in_regs) {
-#pragma unroll
-            for (int u = 0; u < kXr; ++u) {
-                const uint32_t g = tid + u * W * 64u, r = g / chunks, k = (g - r * chunks) * 8u;
-                load_chunk(a, r < TM ? s_flow[r] : kNoFlow, k, xr[u]);
-            }
-        }
+        if (in_regs) request_rows(s_flow, tid);
     }
-    // weight operands of layer 1's first k-steps; from here on every GEMM leaves the ring filled for the next one
-    uint4 fb[kRing][NI];
-    ring_fill(fb, a.w1s, k1p / 16u, wave * NI, nb1, threadIdx.x & 63u);
     uint32_t cur = 0;
     for (uint32_t ti = 0; ti < n_tiles; ++ti) {
         const uint32_t row0 = row_begin + ti * TM;
@@ -353,7 +372,7 @@ __device__ __forceinline__ void run_tiles(const FusedArgs& a, const FusedSmem& m
             for (uint32_t g = tid; g < TM * chunks; g += W * 64u) {
                 const uint32_t r = g / chunks, k = (g - r * chunks) * 8u;
                 float z[8];
-                load_chunk(a, flow_cur[r], k, z);
+                load_chunk<false>(a, flow_cur[r], k, z);
                 store_chunk(has_map, m.s_mu, m.s_is, a.clamp, H + r * ldx + k, k, z);
             }
         }
@@ -373,77 +392,70 @@ __device__ __forceinline__ void run_tiles(const FusedArgs& a, const FusedSmem& m
         wave_gemm<NI, MI>(H, LDH, a.w2s, k2p / 16u, wave * NI, nb2, lane, acc, fb, a.w1s, k1p / 16u, nb1);
         __syncthreads();
         store_hidden<NI, MI>(H, acc, n0, k3p, nb2, lane);
-        // layer 3: wave = row block; waves beyond MI only keep the barriers.  The hidden accumulators are dead, so all its
-        // weight operands fit in registers; they are requested before the barrier so that their latency overlaps it.
-        const bool l3 = wave < (uint32_t)MI;
-        const uint32_t KS3 = k3p / 16u; // a multiple of 4
-        const uint32_t last3 = l3 ? KS3 - 4u : 0u; // (the other waves request the first four again and again: a branch here costs registers)
-        uint4 wv[kW3];
+        // layer 3: wave = row block.  The hidden accumulators are dead, so all its weight operands fit in registers; they are
+        // requested before the barrier so that their latency overlaps it.  Behind the barrier the next tile's feature rows are requested,
+        // consumed at the top of the next iteration.  The waves beyond MI have a branch of their own (with the two parts that are
+        // theirs under branches instead, the operands cost registers in all of it).
+        if (wave >= (uint32_t)MI) {
+            __builtin_amdgcn_sched_barrier(0);
+            __syncthreads();
+            if (has_next && in_regs) request_rows(flow_next, tid);
+            __syncthreads();
+        } else {
+            const uint32_t KS3 = k3p / 16u; // a multiple of 4
+            uint4 wv[kW3];
 #pragma unroll
-        for (int g = 0; g < kW3 / 4; ++g) {
-            const uint4* w = a.w3s + (4u * g < last3 ? 4u * g : last3) * 64u + lane;
+            for (int g = 0; g < kW3 / 4; ++g) {
+                const uint4* w = a.w3s + (4u * g < KS3 ? 4u * g : KS3 - 4u) * 64u + lane;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) wv[4 * g + q] = w[q * 64];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();
-        // the next tile's feature rows: requested now, consumed at the top of the next iteration
-        if (has_next && in_regs) {
-#pragma unroll
-            for (int u = 0; u < kXr; ++u) {
-                const uint32_t g = tid + u * W * 64u, r = g / chunks, k = (g - r * chunks) * 8u;
-                load_chunk(a, r < TM ? flow_next[r] : kNoFlow, k, xr[u]);
+                for (int q = 0; q < 4; ++q) wv[4 * g + q] = w[q * 64];
             }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        {
+            __builtin_amdgcn_sched_barrier(0);
+            __syncthreads();
+            if (has_next && in_regs) request_rows(flow_next, tid);
+            __builtin_amdgcn_sched_barrier(0);
             f32x16 c3;
 #pragma unroll
             for (int v = 0; v < 16; ++v) c3[v] = m.s_b3[8u * (v >> 2) + 4u * (lane >> 5) + (v & 3)];
             const uint16_t* arow = H + (wave * 32u + (lane & 31u)) * LDH + 8u * (lane >> 5);
-            if (l3) {
-                // the activation operands of two k-steps are read while the two before are multiplied
-                auto read2 = [&](uint4 (&f)[2], int s3) {
+            // the activation operands of two k-steps are read while the two before are multiplied
+            auto read2 = [&](uint4 (&f)[2], int s3) {
 #pragma unroll
-                    for (int q = 0; q < 2; ++q) f[q] = *reinterpret_cast<const uint4*>(arow + (s3 + q) * 16);
-                };
-                uint4 fa[2][2];
-                read2(fa[0], 0);
+                for (int q = 0; q < 2; ++q) f[q] = *reinterpret_cast<const uint4*>(arow + (s3 + q) * 16);
+            };
+            uint4 fa[2][2];
+            read2(fa[0], 0);
 #pragma unroll
-                for (int s3 = 0; s3 < kW3; s3 += 2) {
-                    if ((uint32_t)(s3 & ~3) >= KS3) continue;
-                    if (s3 + 2 < kW3) read2(fa[(s3 / 2 + 1) & 1], s3 + 2); // (past the layer's K: not used)
-                    __builtin_amdgcn_sched_barrier(0);
+            for (int s3 = 0; s3 < kW3; s3 += 2) {
+                if ((uint32_t)(s3 & ~3) >= KS3) continue;
+                if (s3 + 2 < kW3) read2(fa[(s3 / 2 + 1) & 1], s3 + 2); // (past the layer's K: not used)
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int q = 0; q < 2; ++q)
-                        c3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(wv[s3 + q]), as_frag(fa[(s3 / 2) & 1][q]), c3, 0, 0, 0);
-                }
+                for (int q = 0; q < 2; ++q)
+                    c3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(wv[s3 + q]), as_frag(fa[(s3 / 2) & 1][q]), c3, 0, 0, 0);
             }
             __syncthreads(); // also: every wave is done reading H
-            if (l3) {
-                // the accumulator is transposed: lane l holds 16 classes of row l%32, lane l^32 the others
-                const uint32_t r = wave * 32u + (lane & 31u);
-                const bool row_ok = row0 + r < row_end;
-                uint32_t best = 4u * (lane >> 5);
-                float bv = 0.f;
+            // the accumulator is transposed: lane l holds 16 classes of row l%32, lane l^32 the others
+            const uint32_t r = wave * 32u + (lane & 31u);
+            const bool row_ok = row0 + r < row_end;
+            uint32_t best = 4u * (lane >> 5);
+            float bv = label_start(lane >> 5, c3[0]);
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const uint32_t c = 8u * (v >> 2) + 4u * (lane >> 5) + (v & 3); // ascending in v
-                    const float y = c3[v];
-                    if (v == 0) bv = label_start(lane >> 5, y);
-                    if (c < a.c) {
-                        if (a.logits && row_ok) a.logits[(size_t)(row0 + r) * a.c + c] = y;
-                        if (y > bv) {
-                            bv = y;
-                            best = c;
-                        }
+            for (int v = 0; v < 16; ++v) {
+                const uint32_t c = 8u * (v >> 2) + 4u * (lane >> 5) + (v & 3); // ascending in v
+                const float y = c3[v];
+                if (c < a.c) {
+                    if (a.logits && row_ok) a.logits[(size_t)(row0 + r) * a.c + c] = y;
+                    if (y > bv) {
+                        bv = y;
+                        best = c;
                     }
                 }
-                best = label_of(best, bv);
-                if (lane < 32u && row_ok) {
-                    const uint32_t dst = a.scatter ? a.scatter[row0 + r] : flow_cur[r];
-                    if (dst < a.n_labels) a.labels[dst] = (uint16_t)best;
-                }
+            }
+            best = label_of(best, bv);
+            if (lane < 32u && row_ok) {
+                const uint32_t dst = a.scatter ? a.scatter[row0 + r] : flow_cur[r];
+                if (dst < a.n_labels) a.labels[dst] = (uint16_t)best;
             }
         }
         cur ^= 1u;

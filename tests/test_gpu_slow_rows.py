@@ -109,6 +109,14 @@ def test_forms_agree(dims, rows):
         assert torch.equal(logits, outs[0][0]) and torch.equal(labels, outs[0][1])
 
 
+@pytest.mark.parametrize("n_in", [1, 3, 8, 30, 68, 70, 127, 132, 200, 510, 512])
+@pytest.mark.parametrize("rows,cap", [(1, 1), (64, 70), (40 * UNITS, 40 * UNITS), (70 * UNITS + 5, 70 * UNITS + 5), (30 * UNITS + 3, CAP), (50 * UNITS, CAP)])
+def test_input_rows(n_in, rows, cap):
+    """Tiles whose input comes in whole 16-byte elements and not, held in registers for the next tile and not, rows missing at the end."""
+    out = _run(rows, cap, (n_in, 70, 40, 6), mapped=n_in % 2 == 0, pairs=False)
+    _check(out[0], _reference(out[0], out[1]), *out[2:])
+
+
 def test_labels_alone():
     import torch
     rows = 260 * UNITS
