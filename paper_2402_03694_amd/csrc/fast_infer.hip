@@ -324,23 +324,32 @@ bool choose_waves(const FastArgs& a, uint32_t result_words, bool gbdt, uint32_t 
 //   few flows: 16 flows x 32 lanes, nothing staged, so that even a small batch gives every compute unit a block and
 //     a lane only a few trees one after the other.  4,000 flows: 11 us against 15 (64x8) and 54 (one lane per
 //     flow); 10,000 flows: 17.6 against 16.1.  The line is 24 flows per compute unit (6,144).
-//   otherwise 64 x 8, four blocks per compute unit where 40 KB hold the tile and a pair-level of records; in the fused
+//   otherwise 64 x 8, four blocks per compute unit where 40 KB hold the tile and a pair-level of records.  The stand-alone walk of what
+//     the form with a wave to a tree does not take (48 to 95 trees of depth 6 or 8, to 191 up to depth 4, calls that want leaf numbers)
+//     takes 128 x 8 from 3,000 flows per unit (with leaf numbers 2,000), where its 80 KB hold one pair-level more than the smaller tile
+//     (1,048,576 flows, 80 trees of depth 8 on 96 features 231 : 246 for 64 x 8, on 64 193 : 199; 150 of depth 4 on 128 251 : 267; with leaf numbers
+//     100 trees of depth 12 878 : 906; 600,000 flows, 100 trees of depth 10 with leaf numbers on 32 features 328 : 342, 64 of depth 6 on 96
+//     features 1.05 times as long; 270,000 flows up to 1.1: blocks twice as large share out less evenly).  In the fused
 //     kernel 128 flows in the form with a wave to a tree for the sizes that form takes (waves_take; the kernel in us before : after,
 //     ten classes: 1,048,576 flows, windows 8 and 16, 100 trees of depth 12 500 : 439, no rows kept 479 : 395; windows 5 and 10, depth
 //     10 367 : 336; 400,000 flows, 250 trees of depth 12 479 : 368, 100 of depth 8 133 : 126; 18,000 ragged flows 24 : 19, 65,000 43 : 34).
 //   fewer than 48 trees: 128 x 4, five trees at once per lane; eight lanes would walk a handful each
 //     (1,000,000 flows, 16 trees of depth 8: 62 against 76).
-//   256 flows, one lane each, in large batches where lanes that share a flow have nothing to share:
+//   256 flows, one lane each, in large batches where lanes that share a flow have nothing to share or stand in each other's way:
 //     a walk so short that reading the rows is all there is: 32 features, from 1,400 flows per unit (with up to four trees from
 //     750), few and shallow trees (200,000 flows, four trees of depth 4 8.7 us against 9.6; 1,048,576 flows, one tree of depth 8 35 against 45, 12 of depth 4 44 against 51, 24 of depth 4 53 against 63; but 16 of
-//     depth 6 1.13 times as long, and with 64 features equal).
+//     depth 6 1.13 times as long, and with 64 features equal);
+//     trees of depth 13 and 14 with leaf numbers, whose records (87 KB a tree) the caches cannot hold for eight trees at a time, from 64 trees and
+//     1,700 flows per unit (1,048,576 flows, 100 trees of depth 13 1330 against 1608, 64 of depth 14 821 against 912; 460,000 flows, 80 trees of depth 13
+//     1.04 times as fast, 330,000 equal, 270,000 0.96).
 // Boosted form: lanes split the classes, not the trees (see forest_walk), so a few large shares are better than
 // many uneven ones: 256 x 2 (1,048,576 flows, 200 trees of depth 8: 585 against 599 for 64 x 4; with 32 features three blocks a
 // unit, 1.1 to 1.2 times as fast as two with more staged), 64 x 4 up to 3 * 128 flows per unit (30,000 flows 39 against 83 with one
 // lane per flow; two classes leave half of its lanes idle: with 40 trees or more 256 x 2 from 256 flows per unit, 95,000 flows
 // x 60 trees of depth 8 1.3 times as fast), 16 x 16 for few flows.  One class and three leave lanes
 // idle that 256 x 1 does not have (three classes, 1,048,576 flows x 32 features: 150 trees of depth 6 316 against 341, 60 of depth 1
-// 82 against 120).
+// 82 against 120); five classes (calls with leaf numbers) only with 75 trees or more, 17 to 32 features and 3,000 flows per unit (1,048,576 flows x
+// 32 features, 100 trees of depth 8 554 against 592, of depth 5 525 against 541; 50 of depth 8 282 against 277, on 16 features 265 against 254).
 // dmax: packets of the deepest window (fused kernel), 0 for the stand-alone walk.
 TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n_rows, uint32_t n_cu, uint32_t dmax, size_t* lds)
 {
@@ -361,7 +370,8 @@ TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n
         return s;
     }
     if (gbdt) {
-        const bool one_lane = a.n_classes == 1u || a.n_classes == 3u;
+        const bool one_lane = a.n_classes == 1u || a.n_classes == 3u ||
+                              (a.n_classes == 5u && a.n_features > 16u && a.n_features <= 32u && a.n_trees >= 75u && n_rows >= 3000u * n_cu);
         fit(one_lane ? kTile256x1g : kTile256x2g, 160 * 1024 / 3 - 256, 1);
         if (one_lane && n_rows >= many && *lds <= 80 * 1024) return kTile256x1g;
         if (n_rows >= (a.n_classes <= 2u && a.n_trees >= 40u ? 256u * n_cu : many) && *lds <= 80 * 1024) return kTile256x2g; // (one block per unit is slower than the smaller tile)
@@ -372,9 +382,10 @@ TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n
     if (dmax)
         one_lane = a.n_trees <= fused_one_lane_trees(a.depth, a.n_features / 32u, dmax, n_rows, n_cu);
     else
-        one_lane = a.n_features <= 32u && (n_rows >= 1400u * n_cu
-                                               ? (a.depth <= 5u ? a.n_trees < 48u : a.depth <= 7u ? a.n_trees <= 12u : a.depth <= 9u && a.n_trees <= 4u)
-                                               : n_rows >= 750u * n_cu && a.depth <= 7u && a.n_trees <= 4u);
+        one_lane = (a.depth >= 13u && a.n_trees >= 64u && n_rows >= 1700u * n_cu) ||
+                   (a.n_features <= 32u && (n_rows >= 1400u * n_cu
+                                                ? (a.depth <= 5u ? a.n_trees < 48u : a.depth <= 7u ? a.n_trees <= 12u : a.depth <= 9u && a.n_trees <= 4u)
+                                                : n_rows >= 750u * n_cu && a.depth <= 7u && a.n_trees <= 4u));
     if (one_lane) {
         fit(kTile256x1, 160 * 1024 / 3 - 256, 1);
         if (*lds <= 80 * 1024) return kTile256x1;
@@ -388,6 +399,15 @@ TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n
         return kTile128Waves;
     }
     fit(kTile64x8, 40 * 1024, 1);
+    if (!dmax && n_rows >= (a.leaf_idx ? 2000u : 3000u) * n_cu) {
+        uint32_t top = 0;
+        const size_t wide = plan_lds(a, result_words, 128, 80 * 1024, &top);
+        if (wide <= 80 * 1024 && top > a.top_pairs) {
+            a.top_pairs = top;
+            *lds = wide;
+            return kTile128x8;
+        }
+    }
     return kTile64x8;
 }
 
@@ -470,6 +490,7 @@ int run_trees(sf_ctx* ctx, const char* who, const float* feat, uint32_t feat_ld,
     const int slot = sf::kLdsForest + 2 * (int)shape;
     switch (shape) {
     case kTile128x4: return launch_votes<128, 4, 5, 4, false>(ctx, a, lds, slot);
+    case kTile128x8: return launch_votes<128, 8, 3, 2, false>(ctx, a, lds, slot);
     case kTile64x8: return launch_votes<64, 8, 3, 2, false>(ctx, a, lds, slot);
     case kTile16x32: return launch_votes<16, 32, 5, 2, false>(ctx, a, lds, slot);
     case kTile256x1: return launch_votes<256, 1, 10, 5, false>(ctx, a, lds, slot);

@@ -90,8 +90,8 @@ inline size_t plan_lds(const FastArgs& a, uint32_t result_words, uint32_t fpb, s
 }
 
 // The shapes a block of the walk comes in (flows x lanes per flow), see choose_shape
-enum TileShape { kTile128Waves, kTile128x4, kTile64x8, kTile16x32, kTile256x1, kTile256x2g, kTile64x4g, kTile16x16g, kTile256x1g };
-constexpr uint32_t kTileFlows[] = {128, 128, 64, 16, 256, 256, 64, 16, 256};
+enum TileShape { kTile128Waves, kTile128x4, kTile64x8, kTile16x32, kTile256x1, kTile256x2g, kTile64x4g, kTile16x16g, kTile256x1g, kTile128x8 };
+constexpr uint32_t kTileFlows[] = {128, 128, 64, 16, 256, 256, 64, 16, 256, 128};
 
 // A flow's result from its column of class margins: label, score of the softmax (in binary64) and what else was asked for
 __device__ __forceinline__ void boosted_result(const FastArgs& a, const float* mcol, uint32_t stride, uint32_t i, uint32_t row)

@@ -60,6 +60,30 @@ def test_votes(n, F, T, d, C, pad):
     assert np.array_equal(_u16(lab), want)
 
 
+@pytest.mark.parametrize("n,F,T,d,leaves", [
+    (1700 * CU - 1, 32, 64, 13, True), (1700 * CU, 32, 64, 13, True), (1700 * CU + 255, 64, 65, 13, True), (1700 * CU + 1, 20, 63, 13, True), (1700 * CU + 1, 33, 64, 14, True),
+    (3000 * CU - 1, 96, 49, 8, False), (3000 * CU, 96, 49, 8, False), (3000 * CU + 1, 64, 81, 8, False), (3000 * CU + 127, 96, 50, 6, False), (3000 * CU + 129, 127, 130, 4, False),
+    (2000 * CU - 1, 64, 60, 10, True), (2000 * CU, 64, 60, 10, True), (2000 * CU + 127, 95, 48, 7, True)])
+def test_large_batches_outside(n, F, T, d, leaves):
+    """What that form does not take in large batches: leaf numbers, a medium number of shallow trees (128 x 8, and one lane per flow for deep
+    trees with leaf numbers), at the lines and with a last tile of one flow."""
+    import torch
+    import paper_2402_03694_amd as sf
+    rng = np.random.default_rng(n + T)
+    feat = _feat(rng, n, F)
+    m = _model(rng, T, d, 10, F, np.nan_to_num(feat[:4096]))
+    votes, pred, top, leaf = oracle.fast_infer(feat, m, want_leaves=leaves, n_threads=8)
+    dev = "cuda:0"
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(n, T, d))
+    g = lambda *s: torch.full(s, -1, dtype=torch.int16, device=dev)
+    g_pred, g_top, g_votes, g_leaf = g(n), g(n), g(n, 10), g(n, T) if leaves else None
+    ctx.sf_fast_infer(torch.from_numpy(feat).to(dev), sf.forest_to_device(m, dev), g_pred, g_top, votes=g_votes, leaf_idx=g_leaf)
+    torch.cuda.synchronize()
+    assert np.array_equal(_u16(g_pred), pred) and np.array_equal(_u16(g_top), top) and np.array_equal(_u16(g_votes), votes)
+    if leaves:
+        assert np.array_equal(_u16(g_leaf), leaf)
+
+
 @pytest.mark.parametrize("n,F,T,d,C", [
     (24 * CU + 1, 32, 60, 6, 6), (24 * CU + 63, 64, 51, 8, 16), (24 * CU + 1, 64, 30, 5, 17), (128 * CU - 1, 96, 25, 7, 5), (128 * CU, 64, 61, 8, 10),
     (128 * CU + 129, 96, 33, 9, 6), (128 * CU + 1, 10, 70, 3, 16), (128 * CU + 2, 64, 4, 8, 7), (320 * CU + 5, 64, 41, 8, 10), (320 * CU + 255, 64, 48, 5, 16),
@@ -86,6 +110,28 @@ def test_margins(n, F, T, d, C, based):
     assert np.array_equal(_u16(g_pred), pred)
     # the two binary64 exponentials agree to 1e-13; rounding to binary32 adds half a unit
     assert np.all(np.abs(score.cpu().numpy() - lc) <= 0.5 * np.spacing(np.abs(lc).astype(np.float32)) + 1e-13)
+
+
+@pytest.mark.parametrize("n,F,T,d", [(3000 * CU - 1, 32, 75, 5), (3000 * CU, 32, 75, 5), (3000 * CU + 1, 17, 80, 6), (3000 * CU + 255, 32, 74, 4)])
+def test_five_classes_leaf_numbers(n, F, T, d):
+    """Leaf numbers of boosted models with five classes: margins, scores' classes and leaf numbers on both sides of the lines."""
+    import torch
+    import paper_2402_03694_amd as sf
+    rng = np.random.default_rng(n + T)
+    feat = _feat(rng, n, F)
+    m = _model(rng, T, d, 5, F, np.nan_to_num(feat[:4096]))
+    m.leaf_value = rng.normal(0, 0.5, size=(T, 1 << d)).astype(np.float32)
+    m.base = rng.uniform(-0.5, 0.5, size=5).astype(np.float32)
+    want, pred, _, _ = oracle.gbdt_infer(feat, m, n_threads=8)
+    leaf = oracle.fast_infer(feat, m, want_leaves=True, n_threads=8)[3]
+    dev = "cuda:0"
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(n, T, d))
+    margins = torch.full((n, 5), float("nan"), dtype=torch.float32, device=dev)
+    g_pred, g_leaf = torch.full((n,), -1, dtype=torch.int16, device=dev), torch.full((n, T), -1, dtype=torch.int16, device=dev)
+    ctx.sf_gbdt_infer(torch.from_numpy(feat).to(dev), sf.gbdt_to_device(m, dev), sf.SF_SCORE_LC, g_pred, torch.empty(n, device=dev), margins=margins, leaf_idx=g_leaf)
+    torch.cuda.synchronize()
+    assert np.array_equal(margins.cpu().numpy().view(np.uint32), want.view(np.uint32))
+    assert np.array_equal(_u16(g_pred), pred) and np.array_equal(_u16(g_leaf), leaf)
 
 
 @pytest.mark.parametrize("n,depths,longest,T,d,C,negative,shift,skew", [
