@@ -271,10 +271,22 @@ uint32_t fused_one_lane_trees(uint32_t depth, uint32_t n_windows, uint32_t dmax,
 //
 // Voting form: sixteen waves a block, two blocks a unit (32 waves, all it holds).
 //   Trees: from 48, a wave's trees are walked in rounds of sixteen and filling the tile has to be paid for (400,000 flows x 64
-//     features, depth 12: 70 trees 107 : 127, 47 85 : 96, 20 55 : 52); where the walk is short, from 96 (depth 8: 100 trees 84 : 96, 70
-//     69 : 68) or 192 (depth 4: 100 trees on 96 features 69 : 63, 200 trees as long or 1.1 times as fast).
+//     features, depth 12: 70 trees 107 : 127, 47 85 : 96, 20 55 : 52).  An odd depth gains most: the level left over is read from the window,
+//     where the other form reads a record of the last pair-level from memory (64 trees of depth 5 50 : 61, of 7 67 : 72; depth 3, 200 trees
+//     0.76 times as long).  Shallow trees of even depth gain less: from 96 at depth 6 and 8 (depth 8: 100 trees 84 : 96, 70 69 : 68), 192 up to
+//     depth 4.  Depth 2 not up to 64 flows a unit (8,000 flows 9.7 : 9.4) nor, with more than 64 features and less than 400 trees, past 384
+//     (400,000 x 128, 200 trees 92 : 83); depth 1 in large batches of up to 64 features (1,048,576 x 64, 200 trees 0.86 times as long, x 96
+//     1.10, 100,000 x 32 1.10).  More than 112 features leave room for three pair-levels only: depth 7 to 10 from 64 trees past 384 flows
+//     a unit (400,000 x 128, 48 trees of depth 7 79 : 75, of depth 9 97 : 94, 64 0.97 to 1.01 times as long).
+//   In the fused kernel the tile is 128 flows always: nothing of depth 1, 2 and 4 (1,048,576 flows, windows 8 and 16, 200 trees of depth 4 1.06
+//     times as long as 64 x 8, 5 and 8 1.17; 400,000, depth 1 1.16 and 1.28; but two windows, 300 trees of depth 4, 1,048,576 flows 0.95).  With
+//     windows of up to 8 packets, whose features are done soon and leave the unit to the other form's walk, depth 3 from 300 trees, 5 from 192, 6 not
+//     at all, 7, 9 and 10 from 64 past 256 flows a unit (400,000 flows, windows 5 and 8: 48 trees of depth 5 1.14 times as long, of depth 7 1.08, 64 of
+//     depth 9 0.99; 192 of depth 3 1.03, of depth 6 1.09; 60,000, 48 trees of depth 7 0.90).
 //   Flows: not where the blocks' last round has few of them, 128 to 192 flows a unit (0.97 times as fast in the mean of 550
-//     models, at worst 0.81; 1.12 times below, 1.16 above) and 256 to 320 (1.05 in the mean, one in eight 0.91 to 0.97; 1.17 above).
+//     models, at worst 0.81; 1.12 times below, 1.16 above) and 256 to 320 (1.05 in the mean, one in eight 0.91 to 0.97; 1.17 above); models that
+//     gain little not from 384 to 432 either (100,003 flows: 200 trees of depth 4 1.05 times as long, of depth 2 1.02 to 1.08, 100 of depth 8 on 96
+//     features 1.03, 64 of depth 9 on 128 1.05; fused, 192 trees of depth 6 1.09, windows 5 and 8, 192 of depth 8 1.10, 64 of depth 10 1.03).
 //   Window: four pair-levels from depth 7 (400,000 x 64 features: depth 7 88 : 105, 10 105 : 119, 12 143 : 167, 13 277 : 357; three
 //     pair-levels 101, 113, 153, 281), three where depth ends there or shared memory has no room for more (128 features: depth 6
 //     86 : 101, 12 180 : 225; one block a unit with four 132, 215).
@@ -287,12 +299,35 @@ uint32_t fused_one_lane_trees(uint32_t depth, uint32_t n_windows, uint32_t dmax,
 // Boosted form, a wave to a class: 5 to 16 classes, in large batches with up to 64 features 3 and 4 too; the largest tile that
 // leaves every unit a block and with which 18 waves or more are resident, four pair-levels before three (120 trees of depth 8,
 // 400,000 flows x 64 features: 3 classes 145 : 197, 5 113 : 171, 8 103 : 156, 10 104 : 156, 16 97 : 163; 96 features: 4 classes 149 : 137, 5
-// 147 : 202, 10 131 : 164; two classes 202 : 154; 10,000 flows, 3 and 4 classes 1.4 times as long; 8,000 flows, ten classes 13 : 20).
-bool waves_take(uint32_t n_trees, uint32_t depth, uint32_t n_rows, uint32_t n_cu)
+// 147 : 202, 10 131 : 164; two classes 202 : 154; 10,000 flows, 3 and 4 classes 1.4 times as long; 8,000 flows, ten classes 13 : 20).  64 flows a block for trees up
+// to depth 6 past 128 flows a unit only where four such blocks fit (128 features, 60 trees of depth 6, 400,000 flows: 8 classes with three blocks
+// 94 : 89, 6 with four 0.91 times as long).
+// dmax: packets of the deepest window (fused kernel), 0 for the stand-alone walk.
+bool waves_take(uint32_t n_trees, uint32_t depth, uint32_t n_features, uint32_t dmax, uint32_t n_rows, uint32_t n_cu)
 {
     const uint32_t per_cu = n_rows / n_cu; // (few flows: blocks of 16, see choose_shape)
     if (n_rows <= 24u * n_cu || (n_rows > 128u * n_cu && per_cu < 192u) || (n_rows > 256u * n_cu && per_cu < 320u)) return false;
-    return n_trees >= (depth <= 4u ? 192u : depth == 6u || depth == 8u ? 96u : 48u);
+    const bool short_windows = dmax != 0u && dmax <= 8u, even = depth == 6u || depth == 8u;
+    if (n_rows > 384u * n_cu && per_cu < 432u) {
+        if (dmax ? (even && n_trees > 128u && n_trees < 256u) || (short_windows && depth <= 10u && n_trees < (depth == 5u ? 256u : even ? 0u : 96u))
+                 : (depth == 2u && n_trees < 400u) || (depth == 4u && n_trees < 300u) || (even && n_features >= 96u && n_trees < 128u) ||
+                       (n_features > 112u && depth >= 7u && depth <= 10u && n_trees < 96u))
+            return false;
+    }
+    if (dmax && (depth <= 2u || depth == 4u)) return depth == 4u && n_features > 32u && !short_windows && n_trees >= 256u && per_cu >= 3000u;
+    switch (depth) {
+    case 1: return n_trees >= 192u && n_features <= 64u && per_cu >= 1200u;
+    case 2: return n_trees >= 192u && n_rows > 64u * n_cu && (n_features <= 64u || n_rows <= 384u * n_cu || n_trees >= 400u);
+    case 3: return n_trees >= (short_windows ? 300u : 192u);
+    case 4: return n_trees >= 192u;
+    case 5: return n_trees >= (short_windows && n_rows > 256u * n_cu ? 192u : 48u);
+    case 6: return n_trees >= 96u && !short_windows;
+    case 8: return n_trees >= 96u;
+    case 7:
+    case 9:
+    case 10: return n_trees >= ((short_windows && n_rows > 256u * n_cu) || (n_features > 112u && n_rows > 384u * n_cu) ? 64u : 48u);
+    default: return n_trees >= 48u;
+    }
 }
 
 bool choose_waves(const FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n_rows, uint32_t n_cu, WaveShape* s)
@@ -308,9 +343,9 @@ bool choose_waves(const FastArgs& a, uint32_t result_words, bool gbdt, uint32_t 
         if (n_rows <= 24u * n_cu || C > 16u || C < (a.n_features <= 64u && n_rows >= 384u * n_cu ? 3u : 5u)) return false;
         for (uint32_t u = n_rows >= 320u * n_cu ? 4u : n_rows >= 128u * n_cu ? 2u : 1u; u >= 2u; u /= 2u)
             if ((deep && take(u, 4, C, 18)) || take(u, 3, C, 18)) return true;
-        return take(1, 4, C, 18);
+        return take(1, 4, C, !deep && n_rows >= 128u * n_cu && C > 4u ? 4u * C : 18u);
     }
-    if (!waves_take(a.n_trees, a.depth, n_rows, n_cu)) return false;
+    if (!waves_take(a.n_trees, a.depth, a.n_features, 0u, n_rows, n_cu)) return false;
     if (n_rows <= 64u * n_cu) return take(1, 4, 16, 32);
     if (n_rows >= 1200u * n_cu) {
         if (deep && take(4, 4, 16, 32)) return true;
@@ -394,7 +429,7 @@ TileShape choose_shape(FastArgs& a, uint32_t result_words, bool gbdt, uint32_t n
         fit(kTile128x4, 40 * 1024, 1);
         return kTile128x4;
     }
-    if (dmax && n_rows > 64u * n_cu && waves_take(a.n_trees, a.depth, n_rows, n_cu)) {
+    if (dmax && n_rows > 64u * n_cu && waves_take(a.n_trees, a.depth, a.n_features, dmax, n_rows, n_cu)) {
         *lds = wave_walk_lds(a.n_features, result_words, false, 128, 16, 4);
         return kTile128Waves;
     }

@@ -26,7 +26,11 @@ SHAPES = [(24 * CU, 64, 100, 7, 10, 0), (24 * CU + 1, 64, 48, 7, 10, 0), (24 * C
           (192 * CU - 1, 64, 50, 10, 10, 0), (192 * CU, 64, 50, 10, 10, 4), (256 * CU, 32, 53, 12, 10, 0), (320 * CU, 64, 48, 13, 2, 0),
           (64 * CU + 2, 128, 300, 10, 32, 0), (64 * CU + 129, 127, 64, 7, 10, 2), (64 * CU + 3, 64, 95, 8, 10, 0), (64 * CU + 3, 70, 51, 5, 64, 2),
           (1200 * CU - 1, 32, 49, 11, 10, 0), (1200 * CU + 1, 32, 51, 12, 10, 0), (1200 * CU + 255, 64, 97, 8, 5, 0), (1200 * CU, 64, 52, 5, 10, 0),
-          ] + [(64 * CU + 40 + d, 64, 192 + d, d, 10, 0) for d in (1, 2, 3, 4)] + [(64 * CU + T, 40, T, 7, 10, 0) for T in (55, 56, 57, 62)]
+          ] + [(64 * CU + 40 + d, 64, 192 + d, d, 10, 0) for d in (1, 2, 3, 4)] + [(64 * CU + T, 40, T, 7, 10, 0) for T in (55, 56, 57, 62)] + [
+              # the lines of the models that gain little
+              (1200 * CU + 40, 64, 193, 1, 10, 0), (1200 * CU - 1, 64, 193, 1, 10, 0), (1200 * CU, 65, 193, 1, 10, 0), (256 * CU, 65, 200, 2, 10, 0), (320 * CU, 65, 399, 2, 10, 0),
+              (320 * CU + 1, 65, 400, 2, 10, 0), (384 * CU + 1, 64, 193, 4, 10, 0), (384 * CU, 64, 193, 4, 10, 0), (432 * CU, 64, 193, 4, 10, 0), (384 * CU + 1, 97, 49, 7, 10, 0),
+              (432 * CU, 113, 63, 7, 10, 0), (432 * CU, 113, 64, 7, 10, 0), (384 * CU, 113, 63, 10, 10, 0), (384 * CU + 1, 113, 95, 9, 10, 0), (384 * CU + 1, 96, 127, 8, 10, 0)]
 
 
 @pytest.mark.parametrize("n,F,T,d,C,pad", SHAPES)
@@ -88,7 +92,7 @@ def test_large_batches_outside(n, F, T, d, leaves):
     (24 * CU + 1, 32, 60, 6, 6), (24 * CU + 63, 64, 51, 8, 16), (24 * CU + 1, 64, 30, 5, 17), (128 * CU - 1, 96, 25, 7, 5), (128 * CU, 64, 61, 8, 10),
     (128 * CU + 129, 96, 33, 9, 6), (128 * CU + 1, 10, 70, 3, 16), (128 * CU + 2, 64, 4, 8, 7), (320 * CU + 5, 64, 41, 8, 10), (320 * CU + 255, 64, 48, 5, 16),
     (320 * CU, 32, 36, 13, 9), (320 * CU + 1, 4, 40, 1, 12), (320 * CU, 64, 35, 2, 8), (384 * CU, 64, 14, 8, 3), (384 * CU - 1, 64, 14, 8, 3), (384 * CU + 1, 32, 21, 9, 4),
-    (384 * CU, 96, 12, 8, 4)])
+    (384 * CU, 96, 12, 8, 4), (128 * CU, 128, 24, 6, 8), (128 * CU - 1, 128, 24, 6, 8), (192 * CU + 1, 128, 18, 6, 6), (192 * CU + 1, 112, 24, 6, 8)])
 @pytest.mark.parametrize("based", [True, False])
 def test_margins(n, F, T, d, C, based):
     import torch
@@ -137,6 +141,8 @@ def test_five_classes_leaf_numbers(n, F, T, d):
 @pytest.mark.parametrize("n,depths,longest,T,d,C,negative,shift,skew", [
     (64 * CU, (8, 16), 20, 50, 7, 10, False, 1, 0), (64 * CU + 1, (8, 16), 20, 50, 7, 10, True, 0, 0), (64 * CU + 127, (8,), 9, 48, 9, 33, False, 0, 1),
     (128 * CU, (1, 9), 12, 300, 5, 10, False, 0, 0), (128 * CU + 1, (2, 16), 18, 97, 8, 7, False, 0, 0), (192 * CU + 130, (6, 12), 14, 61, 10, 10, True, 3, 0),
-    (64 * CU + 2, (5,), 7, 197, 2, 4, False, 0, 1), (320 * CU + 1, (16,), 16, 49, 11, 2, False, 0, 0)])
+    (64 * CU + 2, (5,), 7, 197, 2, 4, False, 0, 1), (320 * CU + 1, (16,), 16, 49, 11, 2, False, 0, 0), (64 * CU + 3, (5, 8), 9, 192, 5, 10, False, 0, 0),
+    (192 * CU, (5, 8), 9, 48, 5, 10, False, 0, 0), (320 * CU, (5, 8), 9, 191, 5, 10, False, 0, 0), (320 * CU, (5, 8), 9, 192, 5, 10, False, 0, 0), (64 * CU + 5, (8,), 8, 300, 3, 10, False, 0, 0), (64 * CU + 3, (3, 9), 9, 197, 3, 10, False, 0, 0), (320 * CU, (4, 8), 8, 64, 9, 10, True, 0, 0),
+    (320 * CU, (4, 8), 8, 63, 10, 10, False, 0, 0), (64 * CU + 4, (4, 8), 8, 48, 11, 10, False, 0, 0), (432 * CU, (8, 16), 16, 97, 6, 10, False, 0, 0), (432 * CU - 1, (8, 16), 16, 192, 6, 10, False, 0, 0), (3000 * CU + 1, (2, 9), 9, 256, 4, 10, False, 0, 0)])
 def test_fused(n, depths, longest, T, d, C, negative, shift, skew):
     _fused_tiles(n, depths, longest, T, d, C, negative, shift, skew)
