@@ -64,8 +64,8 @@ struct JoinArgs {
 
 // Survivors of both tables -> list, stretch by stretch; every slot is cleared.  A wave takes kChunk consecutive slots of one side
 // per trip, all of them requested before the first is looked at and kept in registers.  A stretch's survivors go to its own
-// place in the list, closed by an entry without a flow ID that carries the number of records dropped, so there is no counter
-// that every wave adds to.  (With one counter per side, and every slot read twice, the sweep of 2^20 slots a side took 25 to 38 us.)
+// place in the list, whose last entry, unless every slot survived, has no flow ID and carries the number of survivors and of
+// records dropped, so there is no counter that every wave adds to.  (With one counter per side, and every slot read twice, the sweep of 2^20 slots a side took 25 to 38 us.)
 constexpr uint32_t kChunkTrips = 16;             // slots per lane per trip
 constexpr uint32_t kChunk = 64u * kChunkTrips;   // slots per wave per trip
 
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void join_collect(JoinArgs a)
         // nothing was stored in this stretch since it was last swept: every slot is still empty
         uint32_t* used = a.used[side] + (c - side * chunks_per_side);
         if (*used == 0u) { // the same word in every lane: the wave skips together
-            if (lane == 0) out[0] = Slot{kEmpty, 0u, 0u};
+            if (lane == 0) out[n - 1u] = Slot{kEmpty, 0u, 0u};
             continue;
         }
         if (lane == 0) *used = 0u; // the sweep below empties the stretch (the re-insert marks what it refills)
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(256) void join_collect(JoinArgs a)
             n_keep += (uint32_t)__popcll(keep);
             n_old += (uint32_t)__popcll(__ballot(old));
         }
-        if (lane == 0 && n_keep < n) out[n_keep] = Slot{kEmpty, n_old, 0u}; // (a stretch without room for it dropped nothing)
+        if (lane == 0 && n_keep < n) out[n - 1u] = Slot{kEmpty, n_old, n_keep}; // (a stretch without room for it dropped nothing)
     }
 }
 
@@ -138,26 +138,26 @@ __device__ __forceinline__ bool insert_slot(Slot* table, uint32_t* used, uint32_
     return false;
 }
 
-__global__ __launch_bounds__(256) void join_reinsert(JoinArgs a)
+// A block takes a stretch's survivors, all its waves at once: an insertion is a chain of dependent accesses, and half-full tables have 512
+// to a stretch.  (A wave to a stretch, 64 at a time: 2^14 slots a side, half full, 60 us a step without arrivals, 28 with a lane to every survivor.)
+__global__ __launch_bounds__(512) void join_reinsert(JoinArgs a)
 {
     const uint32_t slots = a.mask + 1u;
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, n_waves = (gridDim.x * blockDim.x) >> 6;
     const uint32_t chunks_per_side = (slots + kChunk - 1u) / kChunk;
-    for (uint32_t c = wave; c < 2u * chunks_per_side; c += n_waves) {
+    for (uint32_t c = blockIdx.x; c < 2u * chunks_per_side; c += gridDim.x) {
         const uint32_t side = c >= chunks_per_side ? 1u : 0u;
         const uint32_t first = (c - side * chunks_per_side) * kChunk;
         const uint32_t n = slots - first < kChunk ? slots - first : kChunk;
         const Slot* in = a.list + (size_t)side * slots + first;
-        for (uint32_t e0 = 0; e0 < n; e0 += 64u) {
-            Slot v = {kEmpty, 0u, 0u};
-            if (e0 + lane < n) v = in[e0 + lane];
-            const unsigned long long none = __ballot(v.id == kEmpty);
-            const uint32_t end = none ? (uint32_t)__ffsll((long long)none) - 1u : 64u; // the list's last entry
+        Slot v = {kEmpty, 0u, 0u};
+        if (threadIdx.x < 64u && threadIdx.x < n) v = in[threadIdx.x]; // (requested beside the count)
+        const Slot last = in[n - 1u];
+        const uint32_t n_keep = last.id == kEmpty ? last.stamp : n;
+        if (threadIdx.x == 0 && last.id == kEmpty && last.val && a.stats) atomicAdd(&a.stats[kExpired], last.val);
+        for (uint32_t e = threadIdx.x; e < n_keep; e += blockDim.x) {
+            if (e >= 64u) v = in[e];
             bool dup = false;
-            if (lane < end) insert_slot(a.table[side], a.used[side], a.mask, v.id, v.val, v.stamp, &dup); // cannot fail: it fitted before
-            if (lane == end && e0 + lane < n && v.val && a.stats) atomicAdd(&a.stats[kExpired], v.val);
-            if (end < 64u) break;
+            insert_slot(a.table[side], a.used[side], a.mask, v.id, v.val, v.stamp, &dup); // cannot fail: it fitted before
         }
     }
 }
@@ -326,7 +326,9 @@ extern "C" int sf_join_step(sf_ctx* ctx, const sf_join_table* table, uint32_t no
     a.stats = stats;
     join_collect<<<grid_for(2ull * slots / kChunkTrips), 256, 0, ctx->stream>>>(a);
     SF_LAUNCH_CHECK(ctx, "join_collect");
-    join_reinsert<<<grid_for(2ull * slots / kChunkTrips), 256, 0, ctx->stream>>>(a);
+    // (few stretches: eight waves each, all that a half-full table has work for; from 2^19 slots two)
+    const uint32_t threads = slots < (1u << 19) ? 512u : 128u;
+    join_reinsert<<<grid_for(2ull * ((slots + kChunk - 1u) / kChunk), 1u), threads, 0, ctx->stream>>>(a);
     SF_LAUNCH_CHECK(ctx, "join_reinsert");
     if (n3) {
         join_arrive<0><<<grid_for(n3, kArriveThreads), kArriveThreads, 0, ctx->stream>>>(a, (const unsigned long long*)q3_id, q3_val, n3);

@@ -103,6 +103,49 @@ def test_random_stream_matches_oracle(cap_log2, n, seed):
     assert total_pairs > n // 4
 
 
+@pytest.mark.parametrize("cap_log2,live3,live2", [(4, 16, 15), (4, 1, 0), (6, 64, 63), (7, 65, 128), (10, 1024, 1023), (11, 2048, 64), (12, 65, 4096), (13, 4100, 2050),
+                                                  (19, 200000, 262144), (20, 524288, 1000)])
+def test_many_survivors(cap_log2, live3, live2):
+    """Records that wait through many steps: stretches in which every slot survives, all but one, one more or less than a wave's worth; then
+    half of them are too old, then all."""
+    rng = np.random.default_rng(cap_log2 + live3)
+    ids = rng.choice(1 << 60, size=live3 + live2, replace=False).astype(np.uint64) + np.uint64(1)
+    a, b = ids[:live3], ids[live3:]
+    old3, old2 = live3 // 2, live2 // 2
+    g = GpuJoin(cap_log2)
+    v3, v2 = np.arange(live3, dtype=np.uint32), np.arange(live2, dtype=np.uint32) + np.uint32(1 << 24)
+    assert g.step(10, 100, a[:old3], v3[:old3], b[:old2], v2[:old2]) == ([], 0, [0, 0, 0, 0])
+    assert g.step(20, 100, a[old3:], v3[old3:], b[old2:], v2[old2:]) == ([], 0, [0, 0, 0, 0])
+    want = lambda i, v, k: sorted((int(x), int(y), 10 if q < k else 20) for q, (x, y) in enumerate(zip(i, v)))
+    for now in (21, 22, 110):
+        assert g.step(now, 100, [], [], [], []) == ([], 0, [0, 0, 0, 0])
+        assert g.pending(3) == want(a, v3, old3) and g.pending(2) == want(b, v2, old2), now
+    assert g.step(111, 100, [], [], [], []) == ([], 0, [old3 + old2, 0, 0, 0])
+    assert g.pending(3) == sorted((int(x), int(y), 20) for x, y in zip(a[old3:], v3[old3:]))
+    assert g.pending(2) == sorted((int(x), int(y), 20) for x, y in zip(b[old2:], v2[old2:]))
+    assert g.step(121, 100, [], [], [], []) == ([], 0, [live3 - old3 + live2 - old2, 0, 0, 0])
+    assert g.pending(3) == [] and g.pending(2) == []
+
+
+def test_half_full_rate():
+    """A step on half-full tables of 2^14 slots takes at most 3.2 of the time of a step on nearly empty ones (2.2; 7.9 with a wave to 1,024 slots'
+    survivors)."""
+    import torch
+    import paper_2402_03694_amd as sf
+    from test_gpu_few_trees import _median_us
+    ctx = sf.ServeFlow(sf.sf_join_workspace_bytes(14))
+    dev, times = "cuda:0", []
+    pair, n_pairs = torch.zeros(1, dtype=torch.int32, device=dev), torch.zeros(1, dtype=torch.int32, device=dev)
+    for live in (1 << 13, 300):
+        ids = np.random.default_rng(live).choice(1 << 60, size=2 * live, replace=False).astype(np.int64) + 1
+        q3, q2 = torch.from_numpy(ids[:live]).to(dev), torch.from_numpy(ids[live:]).to(dev)
+        vals = torch.arange(live, dtype=torch.int32, device=dev)
+        table = sf.DeviceJoinTable(14)
+        ctx.sf_join_step(table, 1, 1 << 30, q3, vals, q2, vals, pair, pair, n_pairs)
+        times.append(_median_us(lambda: ctx.sf_join_step(table, 2, 1 << 30, None, None, None, None, pair, pair, n_pairs)))
+    assert times[0] <= 3.2 * times[1], times
+
+
 def test_full_table_duplicates_and_pair_overflow_are_counted_not_fatal():
     g = GpuJoin(4, pair_cap=2)            # 16 slots per side
     ids = np.arange(1, 41, dtype=np.uint64)
