@@ -76,12 +76,17 @@ __device__ __forceinline__ void load8(const uint16_t* p, uint32_t base, uint16_t
     }
 }
 
+// What decides: one threshold on the votes, one per class, a real-valued score, a share of a leaf.  (A kernel for each: with all four
+// in one, one threshold for 4,194,304 flows took 11.8 us, now 9.6; a threshold per class 12.9, now 10.7.)
+enum Gate { kGateOne, kGateClass, kGateScore, kGateRatio };
+
 // 8-bit mask of the lane's rows [base, base+8) that escalate; n = live_rows(a), vmin: the thresholds in shared memory
+template <Gate G>
 __device__ __forceinline__ uint32_t gate_mask(const RouteArgs& a, const uint16_t* vmin, uint32_t n, uint32_t base)
 {
     uint32_t m = 0;
     if (base >= n) return 0;
-    if (a.score) {
+    if (G == kGateScore) {
         if (base + kPerLane <= n && (reinterpret_cast<uintptr_t>(a.score) & 15u) == 0) {
             const float4 v0 = *reinterpret_cast<const float4*>(a.score + base), v1 = *reinterpret_cast<const float4*>(a.score + base + 4);
             const float v[kPerLane] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
@@ -95,7 +100,7 @@ __device__ __forceinline__ uint32_t gate_mask(const RouteArgs& a, const uint16_t
         }
         return m;
     }
-    if (a.total) {
+    if (G == kGateRatio) {
         if (base + kPerLane <= n) {
             uint16_t v[kPerLane], tot[kPerLane];
             load8(a.top, base, v);
@@ -110,16 +115,17 @@ __device__ __forceinline__ uint32_t gate_mask(const RouteArgs& a, const uint16_t
         }
         return m;
     }
-    if (base + kPerLane <= n) {
+    if (G == kGateOne && base + kPerLane <= n) {
         uint16_t v[kPerLane];
         load8(a.top, base, v);
-        if (a.n_vmin == 1) {
-            const uint16_t th = a.vmin[0];
+        const uint16_t th = a.vmin[0];
 #pragma unroll
-            for (int k = 0; k < kPerLane; ++k) m |= (v[k] < th ? 1u : 0u) << k;
-            return m;
-        }
-        uint16_t p[kPerLane];
+        for (int k = 0; k < kPerLane; ++k) m |= (v[k] < th ? 1u : 0u) << k;
+        return m;
+    }
+    if (base + kPerLane <= n) {
+        uint16_t v[kPerLane], p[kPerLane];
+        load8(a.top, base, v);
         load8(a.pred, base, p);
 #pragma unroll
         for (int k = 0; k < kPerLane; ++k) m |= (v[k] < vmin[p[k] < a.n_vmin ? p[k] : a.n_vmin - 1u] ? 1u : 0u) << k;
@@ -129,7 +135,7 @@ __device__ __forceinline__ uint32_t gate_mask(const RouteArgs& a, const uint16_t
         const uint32_t i = base + k;
         if (i < n) {
             uint16_t th = a.vmin[0];
-            if (a.n_vmin > 1) {
+            if (G == kGateClass) {
                 uint32_t p = a.pred[i];
                 p = p < a.n_vmin ? p : a.n_vmin - 1;
                 th = vmin[p];
@@ -143,7 +149,6 @@ __device__ __forceinline__ uint32_t gate_mask(const RouteArgs& a, const uint16_t
 // the thresholds, into shared memory (a lane-dependent index into the kernel's arguments is a load from memory per row)
 __device__ __forceinline__ void stage_vmin(const RouteArgs& a, uint16_t* vmin)
 {
-    if (a.n_vmin <= 1u) return;
     if (threadIdx.x < SF_MAX_CLASSES) vmin[threadIdx.x] = a.vmin[threadIdx.x];
     __syncthreads();
 }
@@ -178,15 +183,16 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
     return before + inc - v;
 }
 
+template <Gate G>
 __global__ __launch_bounds__(kBlock) void route_count(RouteArgs a)
 {
     __shared__ uint32_t sm[kBlock / 64];
     __shared__ uint16_t s_vmin[SF_MAX_CLASSES];
-    stage_vmin(a, s_vmin);
+    if (G == kGateClass) stage_vmin(a, s_vmin);
     const uint32_t begin = blockIdx.x * a.chunk;
     const uint32_t n = live_rows(a);
     uint32_t c = 0;
-    for (uint32_t t = 0; t < a.chunk; t += kTile) c += __popc(gate_mask(a, s_vmin, n, begin + t + threadIdx.x * kPerLane));
+    for (uint32_t t = 0; t < a.chunk; t += kTile) c += __popc(gate_mask<G>(a, s_vmin, n, begin + t + threadIdx.x * kPerLane));
     const uint32_t inc = wave_inclusive_scan(c);
     if ((threadIdx.x & 63) == 63) sm[threadIdx.x >> 6] = inc;
     __syncthreads();
@@ -197,11 +203,12 @@ __global__ __launch_bounds__(kBlock) void route_count(RouteArgs a)
     }
 }
 
+template <Gate G>
 __global__ __launch_bounds__(kBlock) void route_scatter(RouteArgs a)
 {
     __shared__ uint32_t sm[kBlock / 64];
     __shared__ uint16_t s_vmin[SF_MAX_CLASSES];
-    stage_vmin(a, s_vmin);
+    if (G == kGateClass) stage_vmin(a, s_vmin);
     // sum of the counts of all earlier blocks (every lane ends up with the block-wide total)
     uint32_t part = 0;
     for (uint32_t b = threadIdx.x; b < blockIdx.x; b += kBlock) part += a.counts[b];
@@ -211,7 +218,7 @@ __global__ __launch_bounds__(kBlock) void route_scatter(RouteArgs a)
     const uint32_t n = live_rows(a);
     for (uint32_t t = 0; t < a.chunk; t += kTile) {
         const uint32_t base = begin + t + threadIdx.x * kPerLane;
-        const uint32_t m = gate_mask(a, s_vmin, n, base);
+        const uint32_t m = gate_mask<G>(a, s_vmin, n, base);
         uint32_t tile_total;
         uint32_t pos = run + block_exclusive_scan(__popc(m), sm, tile_total);
 #pragma unroll
@@ -226,18 +233,19 @@ __global__ __launch_bounds__(kBlock) void route_scatter(RouteArgs a)
 // the cache) instead of reading counts that another launch left.  In us, this : two launches: one threshold, 97 to 40,000
 // flows 5.3 : 8.1, 65,536 6.0 : 8.1, 98,304 7.2 : 8.1, 200,000 10.8 : 8.2; a score 4.7 : 7.7, 65,536 5.8 : 7.8; a threshold per class up to
 // 20,000 flows 5.8 : 8.7, 40,000 6.4 : 8.8, 65,536 8.4 : 8.8; shares of a leaf 5.1 : 8.3, 40,000 7.4 : 8.1, 65,536 10.1 : 8.2.
+template <Gate G>
 __global__ __launch_bounds__(kOnceBlock) void route_once(RouteArgs a)
 {
     __shared__ uint32_t s_own[kOnceBlock / 64], s_before[kOnceBlock / 64];
     const uint32_t n = live_rows(a), begin = blockIdx.x * kOnceTile;
     if (begin >= n && blockIdx.x != 0) return; // (a list that ends before this block)
     __shared__ uint16_t s_vmin[SF_MAX_CLASSES];
-    stage_vmin(a, s_vmin);
+    if (G == kGateClass) stage_vmin(a, s_vmin);
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, at = threadIdx.x * kPerLane;
-    const uint32_t m = gate_mask(a, s_vmin, n, begin + at);
+    const uint32_t m = gate_mask<G>(a, s_vmin, n, begin + at);
     uint32_t before = 0;
 #pragma unroll 4
-    for (uint32_t t = 0; t < begin; t += kOnceTile) before += __popc(gate_mask(a, s_vmin, n, t + at));
+    for (uint32_t t = 0; t < begin; t += kOnceTile) before += __popc(gate_mask<G>(a, s_vmin, n, t + at));
     const uint32_t own = wave_inclusive_scan(__popc(m));
     before = wave_inclusive_scan(before);
     if (lane == 63u) {
@@ -407,7 +415,22 @@ __global__ __launch_bounds__(256) void sel_pick(const uint32_t* __restrict__ his
     }
 }
 
-// shared launch of the two kernels; a.top, a.pred, a.total, a.theta, a.src_*, a.n, a.n_vmin and
+template <Gate G>
+int launch_gate(sf_ctx* ctx, const RouteArgs& a, uint32_t grid)
+{
+    if (a.n <= (G == kGateRatio || G == kGateClass ? kOnceRowsTwo : kOnceRows)) {
+        route_once<G><<<(a.n - 1u) / kOnceTile + 1u, kOnceBlock, 0, ctx->stream>>>(a);
+        SF_LAUNCH_CHECK(ctx, "route_once");
+        return SF_OK;
+    }
+    route_count<G><<<grid, kBlock, 0, ctx->stream>>>(a);
+    SF_LAUNCH_CHECK(ctx, "route_count");
+    route_scatter<G><<<grid, kBlock, 0, ctx->stream>>>(a);
+    SF_LAUNCH_CHECK(ctx, "route_scatter");
+    return SF_OK;
+}
+
+// shared launch of the gate; a.top, a.pred, a.total, a.theta, a.src_*, a.n, a.n_vmin and
 // a.vmin are filled by the caller.  counts: kMaxBlocks words of device scratch, or NULL to take
 // them from the context's workspace.
 int launch_route(sf_ctx* ctx, const char* who, RouteArgs& a, uint32_t* esc_idx, uint32_t* esc_count,
@@ -428,16 +451,9 @@ int launch_route(sf_ctx* ctx, const char* who, RouteArgs& a, uint32_t* esc_idx, 
     a.counts = counts;
     a.esc_idx = esc_idx;
     a.esc_count = esc_count;
-    if (a.n <= (a.total || a.n_vmin > 1u ? kOnceRowsTwo : kOnceRows)) {
-        route_once<<<(a.n - 1u) / kOnceTile + 1u, kOnceBlock, 0, ctx->stream>>>(a);
-        SF_LAUNCH_CHECK(ctx, "route_once");
-        return SF_OK;
-    }
-    route_count<<<grid, kBlock, 0, ctx->stream>>>(a);
-    SF_LAUNCH_CHECK(ctx, "route_count");
-    route_scatter<<<grid, kBlock, 0, ctx->stream>>>(a);
-    SF_LAUNCH_CHECK(ctx, "route_scatter");
-    return SF_OK;
+    if (a.score) return launch_gate<kGateScore>(ctx, a, grid);
+    if (a.total) return launch_gate<kGateRatio>(ctx, a, grid);
+    return a.n_vmin > 1u ? launch_gate<kGateClass>(ctx, a, grid) : launch_gate<kGateOne>(ctx, a, grid);
 }
 
 int zero_count(sf_ctx* ctx, uint32_t* esc_count)

@@ -1,12 +1,12 @@
-"""The gate of small batches in one launch: sizes around its tiles of 8,192 rows and around the lines to the two launches (40,960 rows for
-gates that read two arrays, 65,536 for the others), every gate, arrays off the alignment of the wide loads, lists shorter than their
+"""The gate, each of its kernels: one launch for small batches, sizes around its tiles of 8,192 rows and around the lines to the two launches (40,960 rows for
+gates that read two arrays, 65,536 for the others) and above, where blocks take several tiles, every gate, arrays off the alignment of the wide loads, lists shorter than their
 capacity, NaN scores.  Lists and counts exactly as numpy gives them."""
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [1, 7, 8, 9, 511, 8191, 8192, 8193, 16385, 24576 + 5, 40959, 40960, 40961, 49152 + 3, 65535, 65536, 65537]
+SIZES = [1, 7, 8, 9, 511, 8191, 8192, 8193, 16385, 24576 + 5, 40959, 40960, 40961, 49152 + 3, 65535, 65536, 65537, (1 << 20) + 5, (1 << 23) + 9]
 
 
 def _case(n, off):
