@@ -206,7 +206,10 @@ int slow_fused(sf_ctx* ctx, void* ws, bool ws_is_ordered, const float* feat, uin
     a.b3 = m->b3;
     a.logits = logits;
     a.labels = labels;
-    // Register form: lists that may give a compute unit more than 128 rows, and models whose second layer is not wide for the first
+    // Register form: lists that may give a compute unit more than 128 rows (192 where the passes have no
+    // registers left to run ahead, more than 64 inputs and 384 columns in the first layer, unless their pieces are whole and the second layer
+    // small: tiles : this form, 128-455-469-17 33,000 rows 39.3 : 46.6 us, 49,152 38.9 : 47, 60,000 about equal; 128-512-512-10 36.2 : 39.4; but
+    // 96-512-100-7 26.8 : 23.4), and models whose second layer is not wide for the first
     // one's depth (a column block's work beside its MFMAs is the same whatever the depth: 300,000 rows 60-40-500-10 106 : 112 us, 64-200-500-10
     // 137 : 130, 24,500 of them 19.1 : 24.4).
     // The capacity decides, since the count is on the device, and a long list may hold few rows.  In us, tiles of eight waves : this
@@ -214,7 +217,9 @@ int slow_fused(sf_ctx* ctx, void* ws, bool ws_is_ordered, const float* feat, uin
     // 96-300-200-10 11.3 : 10.4, 11.2 : 12.5, 17.6 : 17.2, 33 : 27; 32-256-256-10 9.7 : 9.9, 9.9 : 10.0, 13.3 : 15.6, 26 : 20.5.  So a line
     // further up would lose more on full lists than it gave on sparse ones.
     const uint32_t nb1 = up(a.h1, 32) / 32u, nb2 = up(a.h2, 32) / 32u;
-    if (esc_cap > 128u * (uint32_t)ctx->n_cu && nb2 <= 2u * nb1 && a.n_in <= 128 && (a.n_in & 3u) == 0 && (feat_ld & 3u) == 0 &&
+    const bool tight = a.n_in > 64u && nb1 > 12u && (nb1 < 16u || nb2 > 12u || nb2 % 2u != 0);
+    const uint32_t line = tight ? 192u : 128u;
+    if (esc_cap > line * (uint32_t)ctx->n_cu && nb2 <= 2u * nb1 && a.n_in <= 128 && (a.n_in & 3u) == 0 && (feat_ld & 3u) == 0 &&
         ((uintptr_t)feat & 15u) == 0) {
         sfrows::RowsArgs r;
         static_cast<FusedArgs&>(r) = a;

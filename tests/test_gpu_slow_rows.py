@@ -9,7 +9,7 @@ from test_gpu_wide_tiles import DEV, _check, _model, _reference
 pytestmark = pytest.mark.gpu
 
 UNITS = 256          # compute units: a run is the rows divided by this
-CAP = 128 * UNITS + 1  # the shortest list that takes this form
+CAP = 128 * UNITS + 1  # the shortest list that takes this form (192 * UNITS + 1 for some with more than 64 inputs and 384 columns in the first layer)
 
 
 def _run(rows, cap, dims, mapped, pairs, with_logits=True):
@@ -82,7 +82,7 @@ def test_place_in_the_list(dims):
         assert torch.equal(logits[:rows], first[torch.arange(rows, device=DEV) % 512])
 
 
-@pytest.mark.parametrize("dims", [(64, 512, 512, 10), (100, 130, 70, 32), (128, 300, 500, 7), (4, 40, 20, 1), (64, 384, 160, 17)])
+@pytest.mark.parametrize("dims", [(64, 512, 512, 10), (100, 130, 70, 32), (128, 300, 500, 7), (4, 40, 20, 1), (64, 384, 160, 17), (96, 400, 200, 9)])
 @pytest.mark.parametrize("rows", [40, 20011, 128 * UNITS])
 def test_forms_agree(dims, rows):
     """A row's logits are the same bits whatever decides between the forms: the list's capacity, the input's row stride, its alignment."""
@@ -91,15 +91,16 @@ def test_forms_agree(dims, rows):
     g = torch.Generator(device=DEV)
     g.manual_seed(dims[1] + rows)
     mlp = _model(g, dims, True)
-    x = torch.randn((CAP, dims[0]), device=DEV, generator=g)
-    ctx = sf.ServeFlow(sf.sf_workspace_bytes(CAP, 0, 0, *dims[:3]))
+    n = 192 * UNITS + 1
+    x = torch.randn((n, dims[0]), device=DEV, generator=g)
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(n, 0, 0, *dims[:3]))
     outs = []
-    for cap, ld, offset in ((rows, dims[0], 0), (128 * UNITS, dims[0], 0), (CAP, dims[0], 0), (CAP, dims[0] + 1, 0), (CAP, dims[0], 1)):
-        flat = torch.zeros(CAP * ld + 1, device=DEV)
-        feat = flat[offset:offset + CAP * ld].view(CAP, ld)
+    for cap, ld, offset in ((rows, dims[0], 0), (128 * UNITS, dims[0], 0), (CAP, dims[0], 0), (n - 1, dims[0], 0), (n, dims[0], 0), (n, dims[0] + 1, 0), (n, dims[0], 1)):
+        flat = torch.zeros(n * ld + 1, device=DEV)
+        feat = flat[offset:offset + n * ld].view(n, ld)
         feat[:, :dims[0]] = x
         logits = torch.full((cap, dims[3]), float("nan"), device=DEV)
-        labels = torch.full((CAP,), -1, dtype=torch.int16, device=DEV)
+        labels = torch.full((n,), -1, dtype=torch.int16, device=DEV)
         idx = torch.arange(cap, device=DEV, dtype=torch.int32)
         torch.cuda.synchronize()
         ctx.sf_slow_infer(mlp, idx, torch.tensor([rows], dtype=torch.int32, device=DEV), labels, feat=feat, logits=logits)
