@@ -68,11 +68,19 @@ def test_vector_instructions(kernels, name, most):
                                   "featurize_parts<32>"] + ["mlp_wide_layer<%s>" % t for t in (
                                       "0, false, 0", "0, true, 0", "1, false, 0", "1, true, 0", "2, false, 0", "2, true, 0", "2, false, 1", "2, true, 1",
                                       "2, true, 2")] + [
-                                      "mlp_rows<%s>" % t for t in ("4, 4, false", "8, 4, false", "12, 4, false", "16, 4, true", "16, 4, false", "16, 8, true")])
+                                      "mlp_rows<%s>" % t for t in ("4, 4, false", "8, 4, false", "12, 4, false", "16, 4, true", "16, 4, false", "4, 8, false",
+                                                                   "8, 8, false", "12, 8, false", "16, 8, true")] + ["mlp_fused"] + [
+                                      "forest_trees<%d, %d, false>" % t for t in ((4, 4), (4, 3), (2, 4), (2, 3), (1, 4))] + [
+                                      "featurize_forest<128, 8, 0, 0, 8, %s>" % t for t in ("true", "false")])
 def test_no_spills(kernels, name):
     assert kernels[name]["spilled"] == 0, kernels[name]
 
 
-def test_few_spills(kernels):
-    """Header bits of 1 to 7 a packet, K streamed: outside the loop over K."""
-    assert kernels["mlp_wide_layer<2, false, 2>"]["spilled"] <= 4
+@pytest.mark.parametrize("name,most", [
+    ("mlp_wide_layer<2, false, 2>", 4),   # header bits of 1 to 7 a packet, K streamed: outside the loop over K
+    ("mlp_rows<16, 8, false>", 4),        # 14 with as many operands in accumulation registers as the narrower forms, and 4 % slower
+    ("forest_trees<4, 4, true>", 4), ("forest_trees<4, 3, true>", 4), ("forest_trees<2, 4, true>", 4), ("forest_trees<2, 3, true>", 4),
+    ("forest_trees<1, 4, true>", 4),      # behind the walk, the softmax in binary64
+    ("featurize_forest<128, 8, 0, 0, 16, true>", 16), ("featurize_forest<128, 8, 0, 0, 16, false>", 16)])  # the feature phase of 16 packets
+def test_few_spills(kernels, name, most):
+    assert kernels[name]["spilled"] <= most, kernels[name]
