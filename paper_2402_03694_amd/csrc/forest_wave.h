@@ -11,12 +11,13 @@
 //     there are; the block-wide table of forest_walk holds fewer levels the more trees there are.
 // The leaf's label (or margin) is added while the next tree's first levels are walked.
 //
-// The walk alone, before -> after: 1,048,576 flows x 64 features, 100 trees of depth 12 435 -> 347 us, x 32 features 363 -> 284; 4,194,304
-// x 128 features, 500 trees of depth 10 6.6 -> 4.9 ms; 65,536 flows, 200 trees of depth 10 48 -> 38 us; 20,011 flows x 96 features, 150 trees of
-// depth 9 23 -> 19.5; boosted, 1,048,576 x 64, 200 trees of depth 8, ten classes 570 -> 413 us.  What is left is shared memory (a
-// feature read per visit) and vector arithmetic.  Tried and no better: scheduling barriers between the reads of a level's
-// records, of its features and its tests; eight flows a lane; nine waves a block to make room for four pair-levels beside 256 flows
-// of 64 features (337 us at 100 trees, but the trees rarely divide by nine).
+// The walk alone, before -> after: 1,048,576 flows x 64 features, 100 trees of depth 12 with splits drawn at random from the
+// flows' values 435 -> 347 us, on the benchmark's workload 458 -> 400 to 416; x 32 features 363 -> 284; 4,194,304 x 128 features, 500 trees of depth
+// 10 6.6 -> 4.9 ms; 65,536 flows, 200 trees of depth 10 48 -> 38 us; 20,011 flows x 96 features, 150 trees of depth 9 23 -> 19.5; boosted,
+// 1,048,576 x 64, 200 trees of depth 8, ten classes 570 -> 413 us.  Which calls take it: waves_take and choose_waves (fast_infer.hip).
+// What is left is shared memory (a feature read per visit) and vector arithmetic.  Tried and no better: scheduling barriers between
+// the reads of a level's records, of its features and its tests; eight flows a lane; nine waves a block to make room for four pair-levels
+// beside 256 flows of 64 features (337 us at 100 trees, but the trees rarely divide by nine).
 #pragma once
 
 #include "forest_core.h"
