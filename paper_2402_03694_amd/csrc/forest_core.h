@@ -51,6 +51,7 @@ struct FastArgs {
     uint32_t n_flows;          // rows to classify (the capacity of the list when idx is given)
     const uint32_t* idx;       // subset form: row j is flow idx[j]; NULL = row j is flow j
     const uint32_t* idx_count; // subset form: device-side length of idx
+    uint32_t short_list;       // subset form: lists of up to this many rows are walked 64 flows to a block (forest_trees)
     uint32_t n_rows;           // subset form: rows of feat (list entries are clamped below it)
     uint16_t* labels;          // subset form, optional: labels[idx[j]] = pred of row j
     // boosted form: leaves hold margins instead of labels, tree t adds to class t % n_classes

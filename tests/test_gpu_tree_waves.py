@@ -64,6 +64,33 @@ def test_votes(n, F, T, d, C, pad):
     assert np.array_equal(_u16(lab), want)
 
 
+@pytest.mark.parametrize("n,F,T,d,C", [(70 * CU, 64, 52, 9, 10), (320 * CU, 33, 97, 7, 40), (1200 * CU, 32, 51, 10, 10), (1200 * CU + 3, 30, 300, 5, 7)])
+def test_short_lists(n, F, T, d, C):
+    """Lists far shorter than their capacity, whose blocks then take 64 flows each: around that line, one row, tiles of one flow, none."""
+    import torch
+    import paper_2402_03694_amd as sf
+    rng = np.random.default_rng(n + T)
+    feat = _feat(rng, n, F)
+    m = _model(rng, T, d, C, F, np.nan_to_num(feat[:4096]))
+    _, pred, top, _ = oracle.fast_infer(feat, m, n_threads=8)
+    dev = "cuda:0"
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(n, T, d))
+    d_feat, d_m = torch.from_numpy(feat).to(dev), sf.forest_to_device(m, dev)
+    for rows in (0, 1, 63, 65, 8 * CU, 24 * CU + 1, n // 4, n // 4 + 1, 64 * CU, 64 * CU + 1, 128 * CU, 128 * CU + 1):
+        rows = min(rows, n)
+        take = np.sort(rng.permutation(n)[:rows]).astype(np.uint32)
+        idx = np.full(n, 0xFFFFFFFF, np.uint32)
+        idx[:rows] = take
+        g_pred, g_top, lab = (torch.full((n,), -1, dtype=torch.int16, device=dev) for _ in range(3))
+        ctx.sf_fast_infer_subset(d_feat, torch.from_numpy(idx.view(np.int32)).to(dev), torch.tensor([rows], dtype=torch.int32, device=dev), d_m, g_pred, g_top, labels=lab)
+        torch.cuda.synchronize()
+        assert np.array_equal(_u16(g_pred)[:rows], pred[take]) and np.array_equal(_u16(g_top)[:rows], top[take]), rows
+        assert np.all(_u16(g_pred)[rows:] == 0xFFFF) and np.all(_u16(g_top)[rows:] == 0xFFFF), rows
+        want = np.full(n, 0xFFFF, np.uint16)
+        want[take] = pred[take]
+        assert np.array_equal(_u16(lab), want), rows
+
+
 @pytest.mark.parametrize("n,F,T,d,leaves", [
     (1700 * CU - 1, 32, 64, 13, True), (1700 * CU, 32, 64, 13, True), (1700 * CU + 255, 64, 65, 13, True), (1700 * CU + 1, 20, 63, 13, True), (1700 * CU + 1, 33, 64, 14, True),
     (3000 * CU - 1, 96, 49, 8, False), (3000 * CU, 96, 49, 8, False), (3000 * CU + 1, 64, 81, 8, False), (3000 * CU + 127, 96, 50, 6, False), (3000 * CU + 129, 127, 130, 4, False),
