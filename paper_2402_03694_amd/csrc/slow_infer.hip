@@ -11,6 +11,8 @@
 // The row count comes from the device-side escalation count; blocks past it exit.
 //
 // binary32 models (small, used for the small workload) run on plain vector arithmetic.
+#include <type_traits>
+
 #include "mlp_common.h"
 
 namespace sf {
@@ -202,23 +204,28 @@ __device__ __forceinline__ float f32_input_value(const F32Args& a, uint32_t flow
     return (float)(((word >> (8u * (byte_i & 3u))) >> (7u - (b & 7u))) & 1u);
 }
 
-// The whole model on eight rows per block: the activations stay in shared memory, the weights pass through it in pieces
-// of 128 outputs x 32 inputs, the next piece requested while the current one is multiplied.  A wave owns two rows, a
-// lane two outputs of them; the sums run in order of the inputs, one multiply and one add per term, each rounded, as
-// in f32_layer (the results are the same bits).  A small batch is a chain of latencies: with one launch per layer on
-// 64 x 64 tiles, 4,096 rows gave work to half of the compute units, one wave per SIMD, and paid six launches.
-constexpr uint32_t kF32Rows = 8, kF32Cols = 128, kF32K = 32, kF32Ld = kF32K + 4; // (row stride: 16-byte reads of 8 consecutive rows on distinct banks)
-constexpr size_t kF32FusedLds = 64 * 1024;
-constexpr uint32_t kF32FusedRows = 1u << 15;
-constexpr double kF32FusedTerms = 5.2e9;
+// The whole model on 16 rows per block, or on 4 while that leaves a compute unit at most two blocks: the activations stay in
+// shared memory, the weights go straight from the cache into registers.  A lane owns one row R = 16 (4) and up to four output
+// columns of it: the R lanes of a group hold consecutive weights of a column, four to a lane, loaded as they lie, and the one a
+// step needs is broadcast among them by the multiplication itself (a data-parallel operand), so that a term costs its multiply
+// and its add and nothing else; a row's input serves all columns of the lane.  The sums run in order of the inputs, one multiply
+// and one add per term, each rounded, as in f32_layer (the results are the same bits).  What bounds it is that arithmetic (two
+// instructions a term, no packed ones) and, for few rows, latencies: the chain of loads in front, and the code itself, which a
+// launch fetches anew, so there is one copy of each loop.  Weights and activations both through shared memory, whose reads cost
+// as much as the arithmetic, with two barriers per 32 inputs : this, whole call in us: one row through 32-128-128-4 13.7 : 8.0,
+// 2,000 15.3 : 10.4, 4,096 16.9 : 13.4; 200 rows through 64-256-256-10 38 : 17, 16,000 through 128-256-256-32 133 : 114 (77 % of
+// the arithmetic's rate), 600 through 128-512-512-32 126 : 49.
+constexpr uint32_t kF32Rows = 16, kF32FewRows = 4, kF32Waves = 8;
+constexpr size_t kF32FusedLds = 160 * 1024 - 512;
+constexpr double kF32FusedTerms = 1.5e10;
 
-__host__ __device__ inline uint32_t up4(uint32_t x) { return (x + 3u) / 4u * 4u; }
-// row strides of the two activation buffers: input and second hidden layer, first hidden layer and logits
-__host__ __device__ inline uint32_t f32_ld_a(uint32_t n_in, uint32_t h2) { return up4(n_in > h2 ? n_in : h2); }
-__host__ __device__ inline uint32_t f32_ld_b(uint32_t h1, uint32_t c) { return up4(h1 > c ? h1 : c); }
+__host__ __device__ inline uint32_t up16(uint32_t x) { return (x + 15u) / 16u * 16u; }
+// row strides of the two activation buffers: input and second hidden layer, first hidden layer and logits (whole groups of
+// 16 inputs and a piece of four: 16 rows' pieces lie on distinct banks)
+__host__ __device__ inline uint32_t f32_ld(uint32_t x, uint32_t y) { return up16(x > y ? x : y) + 4u; }
 __host__ __device__ inline size_t f32_fused_lds(uint32_t n_in, uint32_t h1, uint32_t h2, uint32_t c)
 {
-    return ((size_t)kF32Rows * ((size_t)f32_ld_a(n_in, h2) + f32_ld_b(h1, c)) + kF32Cols * kF32Ld) * 4;
+    return ((size_t)kF32Rows * ((size_t)f32_ld(n_in, h2) + f32_ld(h1, c)) + 32) * 4; // (inputs are read up to 16 past a row)
 }
 
 // terms of the sums of one row, columns in whole waves
@@ -237,115 +244,192 @@ struct F32Model {
     uint32_t n_labels;
 };
 
-// this thread's four 16-byte chunks of the weight piece at (c0, k0): zeros outside
-__device__ __forceinline__ void f32_fetch(const float* __restrict__ w, uint32_t K, uint32_t N, bool wide, uint32_t c0, uint32_t k0, uint32_t tid,
-                                          float4 (&r)[4])
+// x of lane L of the R this lane belongs to
+template <uint32_t R, uint32_t L>
+__device__ __forceinline__ float of_lane(float x)
 {
+    constexpr int kCtrl = R == 16u ? 0x150 + (int)L /* row_newbcast */ : (int)(L * 0x55u) /* quad_perm */;
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), kCtrl, 0xF, 0xF, true));
+}
+
+// One layer as the lanes see it
+struct F32Layer {
+    const float *w, *bias;
+    uint32_t K, N;
+    bool wide; // rows of whole 16-byte pieces
+};
+// Columns of a lane: a wave takes 64 / R times as many at a time, so few that all waves have some.
+template <uint32_t R>
+__device__ __forceinline__ uint32_t f32_cols(uint32_t N)
+{
+    constexpr uint32_t kAll = 64u / R * kF32Waves;
+    return R == 16u ? (N > 2u * kAll ? 4u : N > kAll ? 2u : 1u) : 1u;
+}
+
+// A lane's weights of 64 inputs: with 16 lanes to a group 4, with four lanes 16 in pieces of 16 inputs
+template <uint32_t R>
+constexpr int kF32Pieces = 16 / R;
+template <uint32_t R>
+struct F32Weights {
+    float4 v[R == 16u ? 4 : 1][kF32Pieces<R>];
+};
+
+// [k, k + 64) of this lane's B columns from c0 on (past the last column: that one again; past K: zeros); none from N on
+template <uint32_t R, int B>
+__device__ __forceinline__ void f32_weights(const F32Layer& l, uint32_t c0, uint32_t k0, uint32_t lane, F32Weights<R>& r)
+{
+    if (c0 >= l.N) return;
 #pragma unroll
-    for (uint32_t q = 0; q < 4u; ++q) {
-        const uint32_t e = tid + 256u * q, col = c0 + e / (kF32K / 4u), k = k0 + e % (kF32K / 4u) * 4u;
-        r[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (col < N && k < K) {
-            const float* p = w + (size_t)col * K + k;
-            if (wide) { // K a multiple of 4 and w on a 16-byte boundary
-                r[q] = *reinterpret_cast<const float4*>(p);
+    for (int b = 0; b < B; ++b) {
+        const uint32_t col = c0 + 64u / R * b + lane / R;
+        const float* p = l.w + (size_t)(col < l.N ? col : l.N - 1u) * l.K;
+#pragma unroll
+        for (int q = 0; q < kF32Pieces<R>; ++q) {
+            const uint32_t k = k0 + 4u * R * q + 4u * (lane % R);
+            float4& v = r.v[b][q];
+            if (l.wide) {
+                v = k < l.K ? *reinterpret_cast<const float4*>(p + k) : make_float4(0.f, 0.f, 0.f, 0.f);
             } else {
-                r[q].x = p[0];
-                if (k + 1u < K) r[q].y = p[1];
-                if (k + 2u < K) r[q].z = p[2];
-                if (k + 3u < K) r[q].w = p[3];
+                v.x = k < l.K ? p[k] : 0.f;
+                v.y = k + 1u < l.K ? p[k + 1u] : 0.f;
+                v.z = k + 2u < l.K ? p[k + 2u] : 0.f;
+                v.w = k + 3u < l.K ? p[k + 3u] : 0.f;
             }
         }
     }
 }
-
-// out[r][o] = act(sum_k in[r][k] * w[o][k] + b[o]) for the block's rows; the caller has synchronised the block
-__device__ __forceinline__ void f32_rows_layer(const float* in, uint32_t ld_in, uint32_t K, const float* __restrict__ w, const float* __restrict__ bias,
-                                               uint32_t N, float* out, uint32_t ld_out, bool relu, float* Ws)
+template <uint32_t R>
+__device__ __forceinline__ void f32_first_weights(const F32Layer& l, uint32_t wave, uint32_t lane, F32Weights<R>& r)
 {
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, row = (tid >> 6) * 2u;
-    const bool wide = (K & 3u) == 0 && (reinterpret_cast<uintptr_t>(w) & 15u) == 0;
-    const float *x0 = in + row * ld_in, *x1 = x0 + ld_in;
-    const float *p0 = Ws + lane * kF32Ld, *p1 = p0 + 64u * kF32Ld;
-    for (uint32_t c0 = 0; c0 < N; c0 += kF32Cols) {
-        const bool second = c0 + 64u < N; // (few outputs, the last layer: the lanes' second one does not exist)
-        float s00 = 0.f, s01 = 0.f, s10 = 0.f, s11 = 0.f;
-        float4 r[4];
-        f32_fetch(w, K, N, wide, c0, 0, tid, r);
-        for (uint32_t k0 = 0; k0 < K; k0 += kF32K) {
-            __syncthreads(); // the piece before has been read
+    const uint32_t cols = f32_cols<R>(l.N), c0 = wave * (64u / R) * cols;
+    if (R == 16u && cols == 4u)
+        f32_weights<R, R == 16u ? 4 : 1>(l, c0, 0, lane, r);
+    else if (R == 16u && cols == 2u)
+        f32_weights<R, R == 16u ? 2 : 1>(l, c0, 0, lane, r);
+    else
+        f32_weights<R, 1>(l, c0, 0, lane, r);
+}
+
+// out[r][o] = act(sum_k in[r][k] * w[o][k] + b[o]) for this wave's columns; w holds the first weights on entry.  Terms are
+// taken 16 at a time; those past K are zero times zero (a sum that starts at +0 is never -0, so they leave it as it is).
+template <uint32_t R, int B>
+__device__ __forceinline__ void f32_columns(const F32Layer& l, const float* in, uint32_t ld_in, float* out, uint32_t ld_out, bool relu, uint32_t wave,
+                                            uint32_t lane, F32Weights<R>& w)
+{
+    constexpr uint32_t kCols = 64u / R, kStep = kCols * B * kF32Waves;
+    const float* x = in + lane % R * ld_in;
+    for (uint32_t c0 = wave * kCols * B; c0 < l.N; c0 += kStep) {
+        float s[B], bias[B];
 #pragma unroll
-            for (uint32_t q = 0; q < 4u; ++q) {
-                const uint32_t e = tid + 256u * q;
-                *reinterpret_cast<float4*>(Ws + e / (kF32K / 4u) * kF32Ld + e % (kF32K / 4u) * 4u) = r[q];
+        for (int b = 0; b < B; ++b) {
+            const uint32_t col = c0 + kCols * b + lane / R;
+            bias[b] = l.bias[col < l.N ? col : l.N - 1u];
+            s[b] = 0.f;
+        }
+        float4 xv[2][4]; // the inputs of 16 terms, the next ones read while one's are summed
+        auto read = [&](float4 (&to)[4], uint32_t k) {
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) to[q] = *reinterpret_cast<const float4*>(x + k + 4u * q);
+        };
+        // four terms whose weights lane L of a column's group holds
+        auto four = [&](auto L, const float4& xq, uint32_t piece) {
+            float p[B];
+            auto term = [&](float xk, auto part) {
+#pragma unroll
+                for (int b = 0; b < B; ++b) p[b] = of_lane<R, decltype(L)::value>(part(w.v[b][piece])) * xk;
+#pragma unroll
+                for (int b = 0; b < B; ++b) s[b] += p[b];
+            };
+            term(xq.x, [](const float4& v) { return v.x; });
+            term(xq.y, [](const float4& v) { return v.y; });
+            term(xq.z, [](const float4& v) { return v.z; });
+            term(xq.w, [](const float4& v) { return v.w; });
+        };
+        auto sixteen = [&](auto g, uint32_t k) {
+            constexpr uint32_t l0 = R == 16u ? 4u * decltype(g)::value : 0u, piece = R == 16u ? 0u : decltype(g)::value;
+            const float4(&xq)[4] = xv[decltype(g)::value & 1u];
+            read(xv[(decltype(g)::value + 1u) & 1u], k + 16u); // (past K: not used)
+            __builtin_amdgcn_sched_barrier(0);
+            four(std::integral_constant<uint32_t, l0>{}, xq[0], piece), four(std::integral_constant<uint32_t, l0 + 1u>{}, xq[1], piece);
+            four(std::integral_constant<uint32_t, l0 + 2u>{}, xq[2], piece), four(std::integral_constant<uint32_t, l0 + 3u>{}, xq[3], piece);
+        };
+        read(xv[0], 0);
+#pragma nounroll
+        for (uint32_t k = 0; k < l.K; k += 64u) {
+            // the next weights, of this pass or the first of the next one, are requested ahead of the arithmetic
+            F32Weights<R> ahead;
+            const bool more = k + 64u < l.K;
+            f32_weights<R, B>(l, more ? c0 : c0 + kStep, more ? k + 64u : 0u, lane, ahead);
+            sixteen(std::integral_constant<uint32_t, 0>{}, k);
+            if (k + 16u < l.K) {
+                sixteen(std::integral_constant<uint32_t, 1>{}, k + 16u);
+                if (k + 32u < l.K) {
+                    sixteen(std::integral_constant<uint32_t, 2>{}, k + 32u);
+                    if (k + 48u < l.K) sixteen(std::integral_constant<uint32_t, 3>{}, k + 48u);
+                }
+            }
+            w = ahead;
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const uint32_t col = c0 + kCols * b + lane / R;
+            const float y = s[b] + bias[b];
+            if (col < l.N) out[lane % R * ld_out + col] = (relu && y < 0.f) ? 0.f : y;
+        }
+    }
+}
+
+template <uint32_t R>
+__device__ __forceinline__ void f32_rows(const F32Args& a, const F32Model& m, uint32_t total, float* sm)
+{
+    constexpr uint32_t kThreads = kF32Waves * 64;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t lda = f32_ld(a.n_in, m.h2), ldb = f32_ld(m.h1, m.c);
+    float *A = sm, *B = A + R * lda;
+    auto layer_at = [&](uint32_t i) {
+        F32Layer l;
+        l.w = i == 0 ? m.w1 : i == 1u ? m.w2 : m.w3;
+        l.bias = i == 0 ? m.b1 : i == 1u ? m.b2 : m.b3;
+        l.K = i == 0 ? a.n_in : i == 1u ? m.h1 : m.h2;
+        l.N = i == 0 ? m.h1 : i == 1u ? m.h2 : m.c;
+        l.wide = (l.K & 3u) == 0 && (reinterpret_cast<uintptr_t>(l.w) & 15u) == 0;
+        return l;
+    };
+    // the first weights of a layer are requested ahead of what the layer waits for
+    F32Weights<R> w;
+    f32_first_weights<R>(layer_at(0), wave, lane, w);
+    for (uint32_t row0 = blockIdx.x * R; row0 < total; row0 += gridDim.x * R) {
+        const uint32_t k_in = up16(a.n_in);
+        for (uint32_t e = tid; e < R * k_in; e += kThreads) {
+            const uint32_t r = e / k_in, k = e - r * k_in;
+            A[r * lda + k] = k < a.n_in && row0 + r < total ? f32_input_value(a, a.esc_idx[row0 + r], k) : 0.f;
+        }
+        __syncthreads();
+#pragma nounroll
+        for (uint32_t i = 0; i < 3u; ++i) { // (a loop, so that the code is there once)
+            const F32Layer l = layer_at(i);
+            const float* in = i == 1u ? B : A;
+            float* out = i == 1u ? A : B;
+            const uint32_t ld_in = i == 1u ? ldb : lda, ld_out = i == 1u ? lda : ldb, cols = f32_cols<R>(l.N);
+            if (R == 16u && cols == 4u)
+                f32_columns<R, R == 16u ? 4 : 1>(l, in, ld_in, out, ld_out, i < 2u, wave, lane, w);
+            else if (R == 16u && cols == 2u)
+                f32_columns<R, R == 16u ? 2 : 1>(l, in, ld_in, out, ld_out, i < 2u, wave, lane, w);
+            else
+                f32_columns<R, 1>(l, in, ld_in, out, ld_out, i < 2u, wave, lane, w);
+            f32_first_weights<R>(layer_at(i < 2u ? i + 1u : 0u), wave, lane, w);
+            if (tid < R * 16u) { // zeros behind the outputs: the next layer's inputs past K
+                const uint32_t c = up16(l.N) - 16u + (tid & 15u);
+                if (c >= l.N) out[(tid >> 4) * ld_out + c] = 0.f;
             }
             __syncthreads();
-            if (k0 + kF32K < K) f32_fetch(w, K, N, wide, c0, k0 + kF32K, tid, r);
-            auto step = [&](float a0, float a1, float w0, float w1) {
-                s00 += a0 * w0;
-                s10 += a1 * w0;
-                s01 += a0 * w1;
-                s11 += a1 * w1;
-            };
-            auto four = [&](uint32_t k) {
-                const float4 a0 = *reinterpret_cast<const float4*>(x0 + k0 + k), a1 = *reinterpret_cast<const float4*>(x1 + k0 + k);
-                const float4 w0 = *reinterpret_cast<const float4*>(p0 + k), w1 = *reinterpret_cast<const float4*>(p1 + k);
-                step(a0.x, a1.x, w0.x, w1.x);
-                step(a0.y, a1.y, w0.y, w1.y);
-                step(a0.z, a1.z, w0.z, w1.z);
-                step(a0.w, a1.w, w0.w, w1.w);
-            };
-            if (!second) {
-                const uint32_t kn = K - k0 < kF32K ? K - k0 : kF32K;
-#pragma unroll 8
-                for (uint32_t k = 0; k < kn; ++k) {
-                    s00 += x0[k0 + k] * p0[k];
-                    s10 += x1[k0 + k] * p0[k];
-                }
-            } else if (k0 + kF32K <= K) {
-#pragma unroll
-                for (uint32_t k = 0; k < kF32K; k += 4u) four(k);
-            } else {
-                for (uint32_t k = 0; k < K - k0; ++k) step(x0[k0 + k], x1[k0 + k], p0[k], p1[k]);
-            }
         }
-        auto put = [&](uint32_t o, float y0, float y1) {
-            if (o >= N) return;
-            y0 = y0 + bias[o];
-            y1 = y1 + bias[o];
-            out[row * ld_out + o] = (relu && y0 < 0.f) ? 0.f : y0;
-            out[(row + 1u) * ld_out + o] = (relu && y1 < 0.f) ? 0.f : y1;
-        };
-        put(c0 + lane, s00, s10);
-        put(c0 + 64u + lane, s01, s11);
-    }
-}
-
-__global__ __launch_bounds__(256) void f32_mlp(F32Args a, F32Model m)
-{
-    extern __shared__ __attribute__((aligned(16))) float sm[];
-    uint32_t total = *a.esc_count;
-    total = total < a.esc_cap ? total : a.esc_cap;
-    const uint32_t tid = threadIdx.x;
-    const uint32_t lda = f32_ld_a(a.n_in, m.h2), ldb = f32_ld_b(m.h1, m.c);
-    float *A = sm, *B = A + kF32Rows * lda, *Ws = B + kF32Rows * ldb;
-    for (uint32_t row0 = blockIdx.x * kF32Rows; row0 < total; row0 += gridDim.x * kF32Rows) {
-        for (uint32_t e = tid; e < kF32Rows * a.n_in; e += 256u) {
-            const uint32_t r = e / a.n_in, k = e - r * a.n_in;
-            A[r * lda + k] = row0 + r < total ? f32_input_value(a, a.esc_idx[row0 + r], k) : 0.f;
-        }
-        f32_rows_layer(A, lda, a.n_in, m.w1, m.b1, m.h1, B, ldb, true, Ws); // (its first barrier follows the writes above)
-        __syncthreads();
-        f32_rows_layer(B, ldb, m.h1, m.w2, m.b2, m.h2, A, lda, true, Ws);
-        __syncthreads();
-        f32_rows_layer(A, lda, m.h2, m.w3, m.b3, m.c, B, ldb, false, Ws);
-        __syncthreads();
         if (m.logits)
-            for (uint32_t e = tid; e < kF32Rows * m.c; e += 256u) {
+            for (uint32_t e = tid; e < R * m.c; e += kThreads) {
                 const uint32_t r = e / m.c;
                 if (row0 + r < total) m.logits[(size_t)row0 * m.c + e] = B[r * ldb + (e - r * m.c)];
             }
-        if (tid < kF32Rows && row0 + tid < total) {
+        if (tid < R && row0 + tid < total) {
             const float* p = B + tid * ldb;
             uint32_t best = 0;
             float bv = p[0];
@@ -358,6 +442,17 @@ __global__ __launch_bounds__(256) void f32_mlp(F32Args a, F32Model m)
             if (dst < m.n_labels) m.labels[dst] = (uint16_t)best;
         }
     }
+}
+
+__global__ __launch_bounds__(kF32Waves * 64, 4) void f32_mlp(F32Args a, F32Model m, uint32_t few)
+{
+    extern __shared__ __attribute__((aligned(16))) float sm[];
+    uint32_t total = *a.esc_count;
+    total = total < a.esc_cap ? total : a.esc_cap;
+    if (total <= few)
+        f32_rows<kF32FewRows>(a, m, total, sm);
+    else
+        f32_rows<kF32Rows>(a, m, total, sm);
 }
 
 __global__ __launch_bounds__(256) void f32_input(F32Args a, float* __restrict__ z)
@@ -655,21 +750,23 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
         f.n_pkts = (uint32_t)raw_src->n_pkts;
     }
     f.n_in = mlp->n_in;
-    // The whole model in one launch where a block's activations fit (widths up to about 1,400 together), up to 32,768 rows and
-    // as long as the terms of all sums stay under the line: a block of eight rows reads every weight again, the taller tiles
-    // of f32_layer read it once for 64 rows.  Whole call in us, layer by layer : one launch: 300 rows through 64-128-128-4
-    // 70 : 16, 4,096 rows through 32-128-128-4 130 : 17, 16,000 rows through 128-256-256-32 301 : 139, 600 rows through
-    // 128-512-512-32 223 : 123.  Around the line (5.2e9 terms): 24,576 rows through 32-400-400-10 513 : 515, 32,768 through
-    // 32-350-350-10 496 : 497, 16,384 through 32-512-512-10 531 : 444, 10,000 through 128-650-650-10 724 : 744.  Past it: 32,768
-    // through 128-650-650-10 1,244 : 2,130, 24,576 through 128-450-450-10 651 : 820.  Long lists through narrow models: 500,000
-    // rows through 64-128-128-4 982 : 1,254, 100,000 equal.
+    // The whole model in one launch where a block's activations fit (widths up to about 2,400 together) and as long as the terms of
+    // all sums stay under the line: past it the tiles of f32_layer, which read a weight once for 64 rows, are a little faster.  Whole
+    // call in us, layer by layer : one launch: 300 rows (of 30,000) through 100-1100-1100-50 632 : 282, 40,000 rows through
+    // 128-256-256-32 409 : 279, 24,576 through 128-450-450-10 642 : 444, 100,000 through 64-128-128-4 259 : 202; around the line 30,000
+    // through 20-600-600-10 (12.6e9 terms) 955 : 794, 500,000 through 64-128-128-4 (16e9) 913 : 995, 200,000 through 128-256-256-32
+    // (23e9) 1,274 : 1,377, 32,768 through 128-650-650-10 (19e9) 1,224 : 1,307.
+    // Four rows a block while that gives a compute unit at most two: 2,000 rows through 32-128-128-4 12.9 : 10.4, 1,500 through
+    // 64-200-256-10 28.7 : 21.7; four of them against one of 16 rows, 4,096 rows, 18.6 : 13.4.  (Rows that exist: the kernel deals them out.)
     const size_t lds = f32_fused_lds(mlp->n_in, mlp->n_h1, mlp->n_h2, mlp->n_classes);
     const double terms = esc_cap * f32_terms(mlp->n_in, mlp->n_h1, mlp->n_h2, mlp->n_classes);
-    if (lds <= kF32FusedLds && esc_cap <= kF32FusedRows && terms <= kF32FusedTerms) {
+    if (lds <= kF32FusedLds && terms <= kF32FusedTerms) {
         const F32Model m = {(const float*)mlp->w1, mlp->b1, (const float*)mlp->w2, mlp->b2, (const float*)mlp->w3, mlp->b3, mlp->n_h1,
                             mlp->n_h2, mlp->n_classes, scatter ? scatter : esc_idx, logits, labels, n_flows};
-        const uint32_t tiles = (esc_cap + kF32Rows - 1u) / kF32Rows, most = 4u * (uint32_t)ctx->n_cu; // (rows that exist are dealt out in the kernel)
-        f32_mlp<<<tiles < most ? tiles : most, 256, lds, ctx->stream>>>(f, m);
+        SF_ALLOW_LDS(ctx, sf::kLdsF32, f32_mlp);
+        const uint32_t few = 2u * kF32FewRows * (uint32_t)ctx->n_cu;
+        const uint32_t tiles = (esc_cap + kF32FewRows - 1u) / kF32FewRows, most = 4u * (uint32_t)ctx->n_cu;
+        f32_mlp<<<tiles < most ? tiles : most, kF32Waves * 64, lds, ctx->stream>>>(f, m, few);
         SF_LAUNCH_CHECK(ctx, "f32_mlp");
         return SF_OK;
     }
