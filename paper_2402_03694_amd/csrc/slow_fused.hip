@@ -19,6 +19,7 @@
 // differ by at most one, and a block walks its run in tiles of four row blocks; what is left at
 // the end of a run (one to three row blocks) is a last, lower tile (two row blocks high when that
 // is enough), so the blocks finish together and few rows fill the whole device.
+#include "slow_few.h"
 #include "slow_rows.h"
 #include "slow_tiles.h"
 
@@ -68,9 +69,8 @@ __global__ __launch_bounds__(256) void reorder_weights(ReorderArgs r)
     }
 }
 
-__global__ __launch_bounds__(kWaves * 64) void mlp_fused(FusedArgs a)
+__device__ __forceinline__ FusedSmem fused_smem(unsigned char* smem)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     FusedSmem m;
     m.H = reinterpret_cast<uint16_t*>(smem);                                    // [128][LDH]; also the input tile
     m.s_flow = reinterpret_cast<uint32_t*>(smem + (size_t)FBM * LDH * 2);       // [2][128]: this tile, next tile
@@ -79,9 +79,13 @@ __global__ __launch_bounds__(kWaves * 64) void mlp_fused(FusedArgs a)
     m.s_b3 = m.s_b2 + HMAX;                                                     // [32], zero past c
     m.s_mu = m.s_b3 + 32;                                                       // [HMAX] input map (0 / 1 if none)
     m.s_is = m.s_mu + HMAX;                                                     // [HMAX]
-    // the wave index is the same in every lane: say so, and everything derived from it (column
-    // block, weight pointers) lives in scalar registers
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    return m;
+}
+
+// One row block a block goes through few(row, end of the rows), more through the tiles.
+template <class Few>
+__device__ __forceinline__ void fused_rows(const FusedArgs& a, const FusedSmem& m, uint32_t wave, Few few)
+{
     uint32_t total = *a.esc_count;
     total = total < a.esc_cap ? total : a.esc_cap;
     // this block's run of row blocks: the runs of the grid differ by at most one row block
@@ -94,6 +98,7 @@ __global__ __launch_bounds__(kWaves * 64) void mlp_fused(FusedArgs a)
     uint32_t row_end = (rb_first + rb_count) * 32u;
     row_end = row_end < total ? row_end : total;
 
+    if (rb_count == 1u && few(row_begin, row_end)) return;
     for (uint32_t q = threadIdx.x; q < (uint32_t)HMAX; q += kWaves * 64u) {
         m.s_b1[q] = q < a.h1 ? a.b1[q] : 0.f;
         m.s_b2[q] = q < a.h2 ? a.b2[q] : 0.f;
@@ -109,7 +114,48 @@ __global__ __launch_bounds__(kWaves * 64) void mlp_fused(FusedArgs a)
     if (rest == 1u || rest == 2u) run_tiles<kWaves, kNI, 2>(a, m, wave, row_begin + n_full * FBM, 1u, row_end);
 }
 
+__global__ __launch_bounds__(kWaves * 64) void mlp_fused(FusedArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    // the wave index is the same in every lane: say so, and everything derived from it (column
+    // block, weight pointers) lives in scalar registers
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    fused_rows(a, fused_smem(smem), wave, [](uint32_t, uint32_t) { return false; });
+}
+
+// ... with few rows a block in the form of slow_few.h (a kernel for each of its shapes: code that a short list never runs costs it
+// time all the same, 0.7 us with all eight in one kernel)
+template <int KS1, int N1, int N2>
+__global__ __launch_bounds__(kWaves * 64) void mlp_few(FusedArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const FusedSmem m = fused_smem(smem);
+    fused_rows(a, m, wave, [&](uint32_t row0, uint32_t row_end) {
+        few_tile<kWaves, KS1, N1, N2>(a, m, wave, row0, row_end);
+        return true;
+    });
+}
+
+
 constexpr size_t kFusedLds = (size_t)FBM * LDH * 2 + 2 * FBM * 4 + (4 * HMAX + 32) * 4;
+static_assert(kFewH <= FBM * LDH, "the few rows' activations in the tile's place");
+
+template <int KS1, int N1, int N2>
+int launch_few(sf_ctx* ctx, const FusedArgs& a, uint32_t grid)
+{
+    SF_ALLOW_LDS(ctx, sf::kLdsFew + (KS1 == 8 ? 4 : 0) + (N1 - 1) * 2 + (N2 - 1), (mlp_few<KS1, N1, N2>));
+    mlp_few<KS1, N1, N2><<<grid, kWaves * 64, kFusedLds, ctx->stream>>>(a);
+    SF_LAUNCH_CHECK(ctx, "mlp_few");
+    return SF_OK;
+}
+
+template <int KS1>
+int launch_few(sf_ctx* ctx, const FusedArgs& a, uint32_t grid)
+{
+    if (a.h1 > 32u * kWaves) return a.h2 > 32u * kWaves ? launch_few<KS1, 2, 2>(ctx, a, grid) : launch_few<KS1, 2, 1>(ctx, a, grid);
+    return a.h2 > 32u * kWaves ? launch_few<KS1, 1, 2>(ctx, a, grid) : launch_few<KS1, 1, 1>(ctx, a, grid);
+}
 
 } // namespace
 
@@ -230,11 +276,12 @@ int slow_fused(sf_ctx* ctx, void* ws, bool ws_is_ordered, const float* feat, uin
         r.ks3 = up(a.h2, kPadK) / 16u;
         return sfrows::run(ctx, r);
     }
-    SF_ALLOW_LDS(ctx, sf::kLdsFused, mlp_fused);
     const uint32_t rb_cap = (esc_cap + 31u) / 32u;
     uint32_t grid = (uint32_t)ctx->n_cu; // one block per compute unit (its shared memory fills the unit)
     if (grid > rb_cap) grid = rb_cap;
     if (grid == 0) grid = 1;
+    if (a.n_in <= kFewInput) return a.n_in <= 64u ? launch_few<4>(ctx, a, grid) : launch_few<8>(ctx, a, grid);
+    SF_ALLOW_LDS(ctx, sf::kLdsFused, mlp_fused);
     mlp_fused<<<grid, kWaves * 64, kFusedLds, ctx->stream>>>(a);
     SF_LAUNCH_CHECK(ctx, "mlp_fused");
     return SF_OK;
