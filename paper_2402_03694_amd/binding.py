@@ -11,6 +11,11 @@ from typing import Optional, Sequence
 
 import torch
 
+try:
+    from . import _marshal
+except ImportError as e:
+    raise ImportError("_marshal.so is missing or does not load (%s): build it with paper_2402_03694_amd.build.build()" % e) from e
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # SERVEFLOW_LIB names another build of the same library (the host-sanitized one of build.build_host_sanitized)
 LIB_PATH = os.environ.get("SERVEFLOW_LIB") or os.path.join(_HERE, "libserveflow_hip.so")
@@ -183,7 +188,7 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
-def _ptr(t: Optional[torch.Tensor], dtype=None):
+def check_ptr(t: Optional[torch.Tensor], dtype=None):
     if t is None:
         return None
     if not t.is_cuda:
@@ -192,7 +197,12 @@ def _ptr(t: Optional[torch.Tensor], dtype=None):
         raise TypeError("expected a contiguous tensor")
     if dtype is not None and t.dtype != dtype:
         raise TypeError("expected dtype %s, got %s" % (dtype, t.dtype))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+# the same in native code (csrc/marshal.cpp), which comes back to check_ptr for what does not pass
+_marshal.set_slow_path(check_ptr)
+_ptr = _marshal.ptr
 
 
 def sf_workspace_bytes(max_flows: int, n_trees: int = 0, tree_depth: int = 0, n_in: int = 0, n_h1: int = 0,
@@ -265,16 +275,13 @@ class DevicePackets:
 
     def c_struct(self) -> SfPackets:
         # uint16/uint32 tensors are carried as int16/int32 storage of the same bits
-        s = SfPackets()
-        s.n_flows, s.n_pkts = self.n_flows, self.n_pkts
-        s.flow_off = _ptr(self.flow_off, torch.int32).value
-        s.pkt_size = _ptr(self.pkt_size, torch.int16).value if self.n_pkts else None
-        s.pkt_iat = _ptr(self.pkt_iat, torch.float32).value if self.n_pkts else None
-        s.pkt_dir = _ptr(self.pkt_dir, torch.uint8).value if self.n_pkts else None
-        if self.pkt_hdr is not None:
-            s.pkt_hdr = _ptr(self.pkt_hdr, torch.int32).value
-            s.hdr_words = int(self.pkt_hdr.shape[1])
-        return s
+        off = _ptr(self.flow_off, torch.int32)
+        size = iat = way = None
+        if self.n_pkts:
+            size, iat, way = _ptr(self.pkt_size, torch.int16), _ptr(self.pkt_iat, torch.float32), _ptr(self.pkt_dir, torch.uint8)
+        if self.pkt_hdr is None:
+            return SfPackets(self.n_flows, self.n_pkts, off, size, iat, way)
+        return SfPackets(self.n_flows, self.n_pkts, off, size, iat, way, _ptr(self.pkt_hdr, torch.int32), int(self.pkt_hdr.shape[1]))
 
 
 class DeviceForest:
@@ -284,13 +291,9 @@ class DeviceForest:
         self.packed = None   # set by ServeFlow.sf_forest_pack
 
     def c_struct(self) -> SfForest:
-        s = SfForest()
-        s.n_trees, s.depth, s.n_classes, s.n_features = self.n_trees, self.depth, self.n_classes, self.n_features
-        s.node_feat = _ptr(self.node_feat, torch.int16).value
-        s.node_thr = _ptr(self.node_thr, torch.float32).value
-        s.leaf_label = _ptr(self.leaf_label, torch.uint8).value
-        s.packed = self.packed.data_ptr() if self.packed is not None else None
-        return s
+        return SfForest(self.n_trees, self.depth, self.n_classes, self.n_features, _ptr(self.node_feat, torch.int16),
+                        _ptr(self.node_thr, torch.float32), _ptr(self.leaf_label, torch.uint8),
+                        self.packed.data_ptr() if self.packed is not None else None)
 
 
 class DeviceTree:
@@ -299,12 +302,8 @@ class DeviceTree:
         self.node_feat, self.node_thr, self.leaf_count = node_feat, node_thr, leaf_count
 
     def c_struct(self) -> SfTree:
-        s = SfTree()
-        s.depth, s.n_classes, s.n_features = self.depth, self.n_classes, self.n_features
-        s.node_feat = _ptr(self.node_feat, torch.int16).value
-        s.node_thr = _ptr(self.node_thr, torch.float32).value
-        s.leaf_count = _ptr(self.leaf_count, torch.int16).value
-        return s
+        return SfTree(self.depth, self.n_classes, self.n_features, _ptr(self.node_feat, torch.int16),
+                      _ptr(self.node_thr, torch.float32), _ptr(self.leaf_count, torch.int16))
 
 
 class DeviceGbdt:
@@ -314,14 +313,9 @@ class DeviceGbdt:
         self.packed = None   # set by ServeFlow.sf_gbdt_pack
 
     def c_struct(self) -> SfGbdt:
-        s = SfGbdt()
-        s.n_trees, s.depth, s.n_classes, s.n_features = self.n_trees, self.depth, self.n_classes, self.n_features
-        s.node_feat = _ptr(self.node_feat, torch.int16).value
-        s.node_thr = _ptr(self.node_thr, torch.float32).value
-        s.leaf_value = _ptr(self.leaf_value, torch.float32).value
-        s.base = _ptr(self.base, torch.float32).value if self.base is not None else None
-        s.packed = self.packed.data_ptr() if self.packed is not None else None
-        return s
+        return SfGbdt(self.n_trees, self.depth, self.n_classes, self.n_features, _ptr(self.node_feat, torch.int16),
+                      _ptr(self.node_thr, torch.float32), _ptr(self.leaf_value, torch.float32), _ptr(self.base, torch.float32),
+                      self.packed.data_ptr() if self.packed is not None else None)
 
 
 class DeviceMlp:
@@ -334,17 +328,12 @@ class DeviceMlp:
         self.ordered = None  # set by ServeFlow.sf_mlp_order
 
     def c_struct(self) -> SfMlp:
-        s = SfMlp()
-        s.n_in, s.n_h1, s.n_h2, s.n_classes = self.dims
-        s.dtype = self.dtype
-        wd = torch.float32 if self.dtype == SF_F32 else torch.bfloat16
-        s.mu = _ptr(self.mu, torch.float32).value if self.mu is not None else None
-        s.inv_sigma = _ptr(self.inv_sigma, torch.float32).value if self.inv_sigma is not None else None
-        s.clamp = self.clamp
-        s.w1, s.w2, s.w3 = (_ptr(w, wd).value for w in (self.w1, self.w2, self.w3))
-        s.b1, s.b2, s.b3 = (_ptr(b, torch.float32).value for b in (self.b1, self.b2, self.b3))
-        s.ordered = self.ordered.data_ptr() if self.ordered is not None else None
-        return s
+        n_in, n_h1, n_h2, n_classes = self.dims
+        f32 = torch.float32
+        wd = f32 if self.dtype == SF_F32 else torch.bfloat16
+        return SfMlp(n_in, n_h1, n_h2, n_classes, self.dtype, _ptr(self.mu, f32), _ptr(self.inv_sigma, f32), self.clamp,
+                     _ptr(self.w1, wd), _ptr(self.w2, wd), _ptr(self.w3, wd), _ptr(self.b1, f32), _ptr(self.b2, f32), _ptr(self.b3, f32),
+                     self.ordered.data_ptr() if self.ordered is not None else None)
 
 
 def _feat_cfg(depths: Sequence[int], raw_pkts: int = 0, raw_bits: int = 0) -> SfFeatCfg:

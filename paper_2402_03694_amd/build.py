@@ -1,12 +1,14 @@
-"""Builds the HIP library in-tree with hipcc for gfx950 (cross-compiles without a GPU)."""
+"""Builds the HIP library in-tree with hipcc for gfx950 (cross-compiles without a GPU) and the binding's tensor check with g++."""
 import glob
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libserveflow_hip.so")
+MARSHAL_SRC, MARSHAL = os.path.join(CSRC, "marshal.cpp"), os.path.join(HERE, "_marshal.so")
 
 # -ffp-contract=off: the feature statistics are defined with one rounding per operation.
 # The packed-fp32 feature is switched off for device code (hipcc's host pass does not know
@@ -26,17 +28,36 @@ def sources():
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(MARSHAL) or os.path.getmtime(MARSHAL_SRC) > os.path.getmtime(MARSHAL):
         return True
     t = os.path.getmtime(LIB)
     deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
     return any(os.path.getmtime(p) > t for p in deps)
 
 
+def build_marshal() -> str:
+    """Compile the tensor check (csrc/marshal.cpp) against the installed torch; returns its path."""
+    import torch
+    from torch.utils import cpp_extension
+    tmp = MARSHAL + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I" + sysconfig.get_paths()["include"],
+           *["-I" + p for p in cpp_extension.include_paths()], MARSHAL_SRC, "-o", tmp,
+           *["-L" + p for p in cpp_extension.library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        if os.path.exists(tmp):
+            os.remove(tmp)
+        raise RuntimeError("%s failed:\n%s" % (cmd[0], res.stdout))
+    os.replace(tmp, MARSHAL)
+    return MARSHAL
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile every kernel file into one shared library; returns its path."""
+    """Compile every kernel file into one shared library, and the tensor check; returns the library's path."""
     if not force and not is_stale():
         return LIB
+    build_marshal()
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIB + ".tmp.%d" % os.getpid()
     cmd = [hipcc, *HIPCC_FLAGS, "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, *sources(), "-o", tmp]
