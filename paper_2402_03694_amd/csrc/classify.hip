@@ -21,10 +21,14 @@
 #include "featurize_core.h"
 #include "forest_core.h"
 #include "forest_wave.h"
+#include "small_batch.h"
 
 namespace sf {
 int forest_setup(sf_ctx* ctx, const char* who, const sf_forest* f, uint32_t feat_ld, sfforest::FastArgs& a, uint32_t* result_words);
 sfforest::TileShape forest_shape(sfforest::FastArgs& a, uint32_t result_words, uint32_t n_rows, uint32_t n_cu, uint32_t dmax, size_t* lds);
+bool slow_gates(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n, const sf_mlp* mlp); // slow_infer.hip
+int slow_infer_gated(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n, const sf_mlp* mlp, const sfsmall::GateRows& gate, const uint16_t* pred,
+                     float* logits, uint16_t* labels);
 }
 
 namespace {
@@ -398,6 +402,11 @@ extern "C" int sf_classify(sf_ctx* ctx, const sf_packets* pk, const sf_feat_cfg*
     int rc = run_features_and_forest(ctx, "sf_classify", pk, cfg, forest, host_vmin, n_vmin, !raw, feat, feat_ld, pred, top_votes,
                                      labels, &labels_done);
     if (rc != SF_OK) return rc;
+    if (!raw && sf::slow_gates(ctx, feat, feat_ld, n, mlp)) {
+        sfsmall::GateRows gate = {top_votes, pred, n, n_vmin, esc_idx, esc_count, {}};
+        for (uint32_t c = 0; c < SF_MAX_CLASSES; ++c) gate.vmin[c] = host_vmin[c < n_vmin ? c : n_vmin - 1u];
+        return sf::slow_infer_gated(ctx, feat, feat_ld, n, mlp, gate, labels_done ? nullptr : pred, logits, labels);
+    }
     rc = sf_route(ctx, top_votes, pred, n, host_vmin, n_vmin, esc_idx, esc_count);
     if (rc != SF_OK || n == 0) return rc;
     return sf_slow_infer(ctx, raw ? nullptr : feat, raw ? 0u : feat_ld, raw ? pk : nullptr, raw ? cfg : nullptr, esc_idx, esc_count, n,

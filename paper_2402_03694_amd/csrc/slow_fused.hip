@@ -22,13 +22,16 @@
 #include "slow_few.h"
 #include "slow_rows.h"
 #include "slow_tiles.h"
+#include "small_batch.h"
 
 namespace sf {
 bool slow_fused_ok(const sf_mlp* mlp, bool raw_input);
 size_t slow_fused_ws_bytes(const sf_mlp* mlp);
 int slow_fused(sf_ctx* ctx, void* ws, bool ws_is_ordered, const float* feat, uint32_t feat_ld, uint32_t n_rows,
                const uint32_t* esc_idx, const uint32_t* scatter, const uint32_t* esc_count, uint32_t esc_cap,
-               uint32_t n_labels, const sf_mlp* mlp, float* logits, uint16_t* labels);
+               uint32_t n_labels, const sf_mlp* mlp, const uint16_t* pred, const sfsmall::GateRows* gate, float* logits, uint16_t* labels);
+bool slow_fused_gates(sf_ctx* ctx, const sf_mlp* mlp, uint32_t n);
+int copy_labels_async(sf_ctx* ctx, const uint16_t* pred, uint16_t* labels, uint32_t n); // slow_infer.hip
 int order_all(sf_ctx* ctx, const sf_mlp* mlp, void* out);
 } // namespace sf
 
@@ -37,6 +40,7 @@ namespace {
 using namespace sftiles;
 
 constexpr int kWaves = 8; // waves per block
+constexpr uint32_t kRowsLine = 128; // rows a compute unit from which the register form may take a list
 constexpr int kNI = 2;    // 32-column blocks per wave
 
 // W[N][K] (row-major, bfloat16 bits) -> out[(nb * KS + ks) * 64 + lane] = the 8 values
@@ -82,17 +86,37 @@ __device__ __forceinline__ FusedSmem fused_smem(unsigned char* smem)
     return m;
 }
 
-// One row block a block goes through few(row, end of the rows), more through the tiles.
-template <class Few>
-__device__ __forceinline__ void fused_rows(const FusedArgs& a, const FusedSmem& m, uint32_t wave, Few few)
+// One row block a block goes through few(row, end of the rows), more through the tiles.  The gate, if there is one, makes the list.
+template <class Gate, class Few>
+__device__ __forceinline__ void fused_rows(const FusedArgs& a, const FusedSmem& m, uint32_t wave, const Gate& gate, Few few)
 {
-    uint32_t total = *a.esc_count;
-    total = total < a.esc_cap ? total : a.esc_cap;
     // this block's run of row blocks: the runs of the grid differ by at most one row block
-    const uint32_t rb_total = (total + 31u) / 32u;
-    const uint32_t rb_lo = rb_total / gridDim.x, rb_rem = rb_total % gridDim.x;
-    const uint32_t rb_first = blockIdx.x * rb_lo + (blockIdx.x < rb_rem ? blockIdx.x : rb_rem);
-    const uint32_t rb_count = rb_lo + (blockIdx.x < rb_rem ? 1u : 0u);
+    const uint32_t block = blockIdx.x - a.n_copy, blocks = gridDim.x - a.n_copy;
+    struct Run {
+        uint32_t first, count;
+    };
+    auto run_of = [&](uint32_t total) {
+        const uint32_t all = (total + 31u) / 32u, lo = all / blocks, rem = all % blocks;
+        return Run{block * lo + (block < rem ? block : rem), lo + (block < rem ? 1u : 0u)};
+    };
+    uint32_t total;
+    if constexpr (std::is_same<Gate, sfsmall::GateRows>::value) {
+        total = sfsmall::gate_rows<kWaves * 64>(gate, m.H, [&](uint32_t n) {
+            const Run r = run_of(n);
+            return [=](uint32_t p) { return p / 32u - r.first < r.count; };
+        });
+        if (block == 0 && threadIdx.x == 0) *gate.esc_count = total;
+        __syncthreads();
+    } else {
+        total = *a.esc_count;
+        total = total < a.esc_cap ? total : a.esc_cap;
+        if (blockIdx.x < a.n_copy) {
+            sfsmall::copy_unlisted<kWaves * 64, true>(a.pred, a.labels, a.n_labels, a.esc_idx, total, blockIdx.x * sfsmall::kCopySlice, m.s_flow);
+            return;
+        }
+    }
+    const Run run = run_of(total);
+    const uint32_t rb_first = run.first, rb_count = run.count;
     if (rb_count == 0) return;
     const uint32_t row_begin = rb_first * 32u;
     uint32_t row_end = (rb_first + rb_count) * 32u;
@@ -120,18 +144,18 @@ __global__ __launch_bounds__(kWaves * 64) void mlp_fused(FusedArgs a)
     // the wave index is the same in every lane: say so, and everything derived from it (column
     // block, weight pointers) lives in scalar registers
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    fused_rows(a, fused_smem(smem), wave, [](uint32_t, uint32_t) { return false; });
+    fused_rows(a, fused_smem(smem), wave, sfsmall::NoGate{}, [](uint32_t, uint32_t) { return false; });
 }
 
 // ... with few rows a block in the form of slow_few.h (a kernel for each of its shapes: code that a short list never runs costs it
 // time all the same, 0.7 us with all eight in one kernel)
-template <int KS1, int N1, int N2>
-__global__ __launch_bounds__(kWaves * 64) void mlp_few(FusedArgs a)
+template <int KS1, int N1, int N2, class Gate>
+__global__ __launch_bounds__(kWaves * 64) void mlp_few(FusedArgs a, Gate gate)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const FusedSmem m = fused_smem(smem);
-    fused_rows(a, m, wave, [&](uint32_t row0, uint32_t row_end) {
+    fused_rows(a, m, wave, gate, [&](uint32_t row0, uint32_t row_end) {
         few_tile<kWaves, KS1, N1, N2>(a, m, wave, row0, row_end);
         return true;
     });
@@ -141,20 +165,27 @@ __global__ __launch_bounds__(kWaves * 64) void mlp_few(FusedArgs a)
 constexpr size_t kFusedLds = (size_t)FBM * LDH * 2 + 2 * FBM * 4 + (4 * HMAX + 32) * 4;
 static_assert(kFewH <= FBM * LDH, "the few rows' activations in the tile's place");
 
-template <int KS1, int N1, int N2>
-int launch_few(sf_ctx* ctx, const FusedArgs& a, uint32_t grid)
+template <int KS1, int N1, int N2, class Gate>
+int launch_few(sf_ctx* ctx, const FusedArgs& a, const Gate& gate, uint32_t grid)
 {
-    SF_ALLOW_LDS(ctx, sf::kLdsFew + (KS1 == 8 ? 4 : 0) + (N1 - 1) * 2 + (N2 - 1), (mlp_few<KS1, N1, N2>));
-    mlp_few<KS1, N1, N2><<<grid, kWaves * 64, kFusedLds, ctx->stream>>>(a);
+    SF_ALLOW_LDS(ctx, sf::kLdsFew + (std::is_same<Gate, sfsmall::NoGate>::value ? 0 : 8) + (KS1 == 8 ? 4 : 0) + (N1 - 1) * 2 + (N2 - 1),
+                 (mlp_few<KS1, N1, N2, Gate>));
+    mlp_few<KS1, N1, N2, Gate><<<grid, kWaves * 64, kFusedLds, ctx->stream>>>(a, gate);
     SF_LAUNCH_CHECK(ctx, "mlp_few");
     return SF_OK;
 }
 
-template <int KS1>
-int launch_few(sf_ctx* ctx, const FusedArgs& a, uint32_t grid)
+template <int KS1, class Gate>
+int launch_few(sf_ctx* ctx, const FusedArgs& a, const Gate& gate, uint32_t grid)
 {
-    if (a.h1 > 32u * kWaves) return a.h2 > 32u * kWaves ? launch_few<KS1, 2, 2>(ctx, a, grid) : launch_few<KS1, 2, 1>(ctx, a, grid);
-    return a.h2 > 32u * kWaves ? launch_few<KS1, 1, 2>(ctx, a, grid) : launch_few<KS1, 1, 1>(ctx, a, grid);
+    if (a.h1 > 32u * kWaves) return a.h2 > 32u * kWaves ? launch_few<KS1, 2, 2>(ctx, a, gate, grid) : launch_few<KS1, 2, 1>(ctx, a, gate, grid);
+    return a.h2 > 32u * kWaves ? launch_few<KS1, 1, 2>(ctx, a, gate, grid) : launch_few<KS1, 1, 1>(ctx, a, gate, grid);
+}
+
+template <class Gate>
+int launch_few(sf_ctx* ctx, const FusedArgs& a, const Gate& gate, uint32_t grid)
+{
+    return a.n_in <= 64u ? launch_few<4>(ctx, a, gate, grid) : launch_few<8>(ctx, a, gate, grid);
 }
 
 } // namespace
@@ -164,6 +195,12 @@ namespace sf {
 bool slow_fused_ok(const sf_mlp* m, bool raw_input)
 {
     return m->dtype == SF_BF16 && !raw_input && m->n_in <= HMAX && m->n_h1 <= HMAX && m->n_h2 <= HMAX && m->n_classes <= 32;
+}
+
+// the gate goes with the form for few rows a block (a list that the register form may take has the gate's own launches)
+bool slow_fused_gates(sf_ctx* ctx, const sf_mlp* m, uint32_t n)
+{
+    return slow_fused_ok(m, false) && m->n_in <= kFewInput && n <= kRowsLine * (uint32_t)ctx->n_cu;
 }
 
 // the kernel reads kRing k-steps past the end of a column block: keep that much padding behind the last one
@@ -216,7 +253,7 @@ int order_all(sf_ctx* ctx, const sf_mlp* m, void* out)
 
 int slow_fused(sf_ctx* ctx, void* ws, bool ws_is_ordered, const float* feat, uint32_t feat_ld, uint32_t n_rows,
                const uint32_t* esc_idx, const uint32_t* scatter, const uint32_t* esc_count, uint32_t esc_cap,
-               uint32_t n_labels, const sf_mlp* m, float* logits, uint16_t* labels)
+               uint32_t n_labels, const sf_mlp* m, const uint16_t* pred, const sfsmall::GateRows* gate, float* logits, uint16_t* labels)
 {
     char* p = (char*)ws;
     uint4* w1s = (uint4*)p;
@@ -252,6 +289,8 @@ int slow_fused(sf_ctx* ctx, void* ws, bool ws_is_ordered, const float* feat, uin
     a.b3 = m->b3;
     a.logits = logits;
     a.labels = labels;
+    a.pred = pred;
+    a.n_copy = 0;
     // Register form: lists that may give a compute unit more than 128 rows (192 where the passes have no
     // registers left to run ahead, more than 64 inputs and 384 columns in the first layer, unless their pieces are whole and the second layer
     // small: tiles : this form, 128-455-469-17 33,000 rows 39.3 : 46.6 us, 49,152 38.9 : 47, 60,000 about equal; 128-512-512-10 36.2 : 39.4; but
@@ -264,9 +303,13 @@ int slow_fused(sf_ctx* ctx, void* ws, bool ws_is_ordered, const float* feat, uin
     // further up would lose more on full lists than it gave on sparse ones.
     const uint32_t nb1 = up(a.h1, 32) / 32u, nb2 = up(a.h2, 32) / 32u;
     const bool tight = a.n_in > 64u && nb1 > 12u && (nb1 < 16u || nb2 > 12u || nb2 % 2u != 0);
-    const uint32_t line = tight ? 192u : 128u;
+    const uint32_t line = tight ? 192u : kRowsLine;
     if (esc_cap > line * (uint32_t)ctx->n_cu && nb2 <= 2u * nb1 && a.n_in <= 128 && (a.n_in & 3u) == 0 && (feat_ld & 3u) == 0 &&
         ((uintptr_t)feat & 15u) == 0) {
+        if (pred) {
+            const int rc = copy_labels_async(ctx, pred, labels, n_labels);
+            if (rc != SF_OK) return rc;
+        }
         sfrows::RowsArgs r;
         static_cast<FusedArgs&>(r) = a;
         r.clamp_z = a.mu ? a.clamp : __builtin_inff();
@@ -280,7 +323,15 @@ int slow_fused(sf_ctx* ctx, void* ws, bool ws_is_ordered, const float* feat, uin
     uint32_t grid = (uint32_t)ctx->n_cu; // one block per compute unit (its shared memory fills the unit)
     if (grid > rb_cap) grid = rb_cap;
     if (grid == 0) grid = 1;
-    if (a.n_in <= kFewInput) return a.n_in <= 64u ? launch_few<4>(ctx, a, grid) : launch_few<8>(ctx, a, grid);
+    if (gate) return launch_few(ctx, a, *gate, grid);
+    if (pred && n_labels <= sfsmall::kCopyRows) {
+        a.n_copy = (n_labels + sfsmall::kCopySlice - 1u) / sfsmall::kCopySlice;
+        grid += a.n_copy;
+    } else if (pred) {
+        const int rc = copy_labels_async(ctx, pred, labels, n_labels);
+        if (rc != SF_OK) return rc;
+    }
+    if (a.n_in <= kFewInput) return launch_few(ctx, a, sfsmall::NoGate{}, grid);
     SF_ALLOW_LDS(ctx, sf::kLdsFused, mlp_fused);
     mlp_fused<<<grid, kWaves * 64, kFusedLds, ctx->stream>>>(a);
     SF_LAUNCH_CHECK(ctx, "mlp_fused");

@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "mlp_common.h"
+#include "small_batch.h"
 
 namespace sf {
 // fused single-kernel form for narrow hidden layers (slow_fused.hip)
@@ -21,7 +22,9 @@ bool slow_fused_ok(const sf_mlp* mlp, bool raw_input);
 size_t slow_fused_ws_bytes(const sf_mlp* mlp);
 int slow_fused(sf_ctx* ctx, void* ws, bool ws_is_ordered, const float* feat, uint32_t feat_ld, uint32_t n_rows,
                const uint32_t* esc_idx, const uint32_t* scatter, const uint32_t* esc_count, uint32_t esc_cap,
-               uint32_t n_labels, const sf_mlp* mlp, float* logits, uint16_t* labels);
+               uint32_t n_labels, const sf_mlp* mlp, const uint16_t* pred, const sfsmall::GateRows* gate, float* logits, uint16_t* labels);
+bool slow_fused_gates(sf_ctx* ctx, const sf_mlp* mlp, uint32_t n);
+int copy_labels_async(sf_ctx* ctx, const uint16_t* pred, uint16_t* labels, uint32_t n);
 int order_all(sf_ctx* ctx, const sf_mlp* mlp, void* out);
 // one hidden layer of any width on operand-ordered weights (slow_wide.hip)
 int wide_layer(sf_ctx* ctx, int amode, const sfmlp::LayerArgs& a, const void* w_ordered, uint32_t rows_cap);
@@ -242,6 +245,8 @@ struct F32Model {
     float* logits;
     uint16_t* labels;
     uint32_t n_labels;
+    const uint16_t* pred; // as in FusedArgs
+    uint32_t n_copy;
 };
 
 // x of lane L of the R this lane belongs to
@@ -380,7 +385,7 @@ __device__ __forceinline__ void f32_columns(const F32Layer& l, const float* in, 
 }
 
 template <uint32_t R>
-__device__ __forceinline__ void f32_rows(const F32Args& a, const F32Model& m, uint32_t total, float* sm)
+__device__ __forceinline__ void f32_rows(const F32Args& a, const F32Model& m, uint32_t block, uint32_t blocks, uint32_t total, float* sm)
 {
     constexpr uint32_t kThreads = kF32Waves * 64;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -398,7 +403,7 @@ __device__ __forceinline__ void f32_rows(const F32Args& a, const F32Model& m, ui
     // the first weights of a layer are requested ahead of what the layer waits for
     F32Weights<R> w;
     f32_first_weights<R>(layer_at(0), wave, lane, w);
-    for (uint32_t row0 = blockIdx.x * R; row0 < total; row0 += gridDim.x * R) {
+    for (uint32_t row0 = block * R; row0 < total; row0 += blocks * R) {
         const uint32_t k_in = up16(a.n_in);
         for (uint32_t e = tid; e < R * k_in; e += kThreads) {
             const uint32_t r = e / k_in, k = e - r * k_in;
@@ -444,15 +449,33 @@ __device__ __forceinline__ void f32_rows(const F32Args& a, const F32Model& m, ui
     }
 }
 
-__global__ __launch_bounds__(kF32Waves * 64, 4) void f32_mlp(F32Args a, F32Model m, uint32_t few)
+// few: the most rows that go four to a block.  The gate, if there is one, makes the list.
+template <class Gate>
+__global__ __launch_bounds__(kF32Waves * 64, 4) void f32_mlp(F32Args a, F32Model m, uint32_t few, Gate gate)
 {
     extern __shared__ __attribute__((aligned(16))) float sm[];
-    uint32_t total = *a.esc_count;
-    total = total < a.esc_cap ? total : a.esc_cap;
+    const uint32_t block = blockIdx.x - m.n_copy, blocks = gridDim.x - m.n_copy;
+    uint32_t total;
+    if constexpr (std::is_same<Gate, sfsmall::GateRows>::value) {
+        total = sfsmall::gate_rows<kF32Waves * 64>(gate, sm, [&](uint32_t n) {
+            const uint32_t rows = n <= few ? kF32FewRows : kF32Rows;
+            return [=](uint32_t p) { return p / rows % blocks == block; };
+        });
+        if (block == 0 && threadIdx.x == 0) *gate.esc_count = total;
+        __syncthreads();
+    } else {
+        total = *a.esc_count;
+        total = total < a.esc_cap ? total : a.esc_cap;
+        if (blockIdx.x < m.n_copy) {
+            sfsmall::copy_unlisted<kF32Waves * 64, false>(m.pred, m.labels, m.n_labels, a.esc_idx, total, blockIdx.x * sfsmall::kCopySlice,
+                                                   reinterpret_cast<uint32_t*>(sm));
+            return;
+        }
+    }
     if (total <= few)
-        f32_rows<kF32FewRows>(a, m, total, sm);
+        f32_rows<kF32FewRows>(a, m, block, blocks, total, sm);
     else
-        f32_rows<kF32Rows>(a, m, total, sm);
+        f32_rows<kF32Rows>(a, m, block, blocks, total, sm);
 }
 
 __global__ __launch_bounds__(256) void f32_input(F32Args a, float* __restrict__ z)
@@ -584,13 +607,18 @@ uint32_t pad64(uint32_t x) { return (x + 63u) / 64u * 64u; }
 
 } // namespace
 
+namespace sf {
+int copy_labels_async(sf_ctx* ctx, const uint16_t* pred, uint16_t* labels, uint32_t n)
+{
+    copy_labels<<<(n + 2047u) / 2048u, 256, 0, ctx->stream>>>(pred, labels, n);
+    SF_LAUNCH_CHECK(ctx, "copy_labels");
+    return SF_OK;
+}
+} // namespace sf
+
 namespace {
 
-// Both entry points.  esc_idx: input rows (of feat, n_rows of them, or flows of raw_src); scatter: where the
-// labels go (NULL = esc_idx); n_flows: entries of labels.
-int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, const sf_packets* raw_src,
-             const sf_feat_cfg* raw_cfg, const uint32_t* esc_idx, const uint32_t* scatter, const uint32_t* esc_count,
-             uint32_t esc_cap, uint32_t n_flows, const sf_mlp* mlp, const uint16_t* pred, float* logits, uint16_t* labels)
+int check_model(sf_ctx* ctx, const sf_mlp* mlp)
 {
     if (!mlp) return sf::fail(ctx, SF_EINVAL, "sf_slow_infer: mlp is NULL");
     if (mlp->dtype != SF_F32 && mlp->dtype != SF_BF16) return sf::fail(ctx, SF_EINVAL, "sf_slow_infer: unknown dtype %d", mlp->dtype);
@@ -602,14 +630,44 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
         return sf::fail(ctx, SF_EINVAL, "sf_slow_infer: weights or biases missing");
     if ((mlp->mu == nullptr) != (mlp->inv_sigma == nullptr))
         return sf::fail(ctx, SF_EINVAL, "sf_slow_infer: mu and inv_sigma come together");
+    return SF_OK;
+}
+
+// the binary32 model in one launch; the rule is at run_slow()
+bool f32_in_one(const sf_mlp* mlp, uint32_t esc_cap)
+{
+    return f32_fused_lds(mlp->n_in, mlp->n_h1, mlp->n_h2, mlp->n_classes) <= kF32FusedLds &&
+           esc_cap * f32_terms(mlp->n_in, mlp->n_h1, mlp->n_h2, mlp->n_classes) <= kF32FusedTerms;
+}
+
+size_t row_bytes_of(const sf_mlp* mlp)
+{
+    return mlp->dtype == SF_BF16 ? ((size_t)pad64(mlp->n_h1) + pad64(mlp->n_h2)) * 2
+                                 : ((size_t)mlp->n_in + mlp->n_h1 + mlp->n_h2 + mlp->n_classes) * 4;
+}
+uint64_t rows_in(const sf::Carve& ws, size_t row_bytes)
+{
+    const size_t avail = ws.left() > 4 * sf::kAlign ? ws.left() - 4 * sf::kAlign : 0;
+    return avail / row_bytes / BM * BM;
+}
+
+// All entry points.  esc_idx: input rows (of feat, n_rows of them, or flows of raw_src); scatter: where the
+// labels go (NULL = esc_idx); n_flows: entries of labels; gate: makes the list first (only where sf::slow_gates()).
+int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, const sf_packets* raw_src,
+             const sf_feat_cfg* raw_cfg, const uint32_t* esc_idx, const uint32_t* scatter, const uint32_t* esc_count,
+             uint32_t esc_cap, uint32_t n_flows, const sf_mlp* mlp, const uint16_t* pred, const sfsmall::GateRows* gate, float* logits,
+             uint16_t* labels)
+{
+    if (const int rc = check_model(ctx, mlp); rc != SF_OK) return rc;
     if (n_flows == 0) return SF_OK;
-    if (pred && pred != labels) {
-        // labels = the fast prediction for every flow, also when nothing escalates (Section 4.4: the fast
-        // label stands unless the slow model replaces it)
-        if (!labels) return sf::fail(ctx, SF_EINVAL, "sf_slow_infer: labels is NULL");
-        uint32_t blocks = (n_flows + 2047) / 2048;
-        copy_labels<<<blocks, 256, 0, ctx->stream>>>(pred, labels, n_flows);
-        SF_LAUNCH_CHECK(ctx, "copy_labels");
+    if (pred == labels) pred = nullptr;
+    if (pred && !labels) return sf::fail(ctx, SF_EINVAL, "sf_slow_infer: labels is NULL");
+    // labels = the fast prediction for every flow, also when nothing escalates (Section 4.4: the fast label stands unless the
+    // slow model replaces it): by the launch that writes the slow labels where it can, else by one before it
+    const bool bf = mlp->dtype == SF_BF16, in_one = bf ? sf::slow_fused_ok(mlp, raw_src != nullptr) : f32_in_one(mlp, esc_cap) && n_flows <= sfsmall::kCopyRows;
+    if (pred && (!in_one || esc_cap == 0 || n_rows == 0)) {
+        if (const int rc = sf::copy_labels_async(ctx, pred, labels, n_flows); rc != SF_OK) return rc;
+        pred = nullptr;
     }
     if (esc_cap == 0 || n_rows == 0) return SF_OK;
     if ((feat == nullptr) == (raw_src == nullptr))
@@ -628,16 +686,15 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
     if (!scatter && esc_cap > n_flows) esc_cap = n_flows;
 
     sf::Carve ws(ctx);
-    const bool bf = mlp->dtype == SF_BF16;
-    if (sf::slow_fused_ok(mlp, raw_src != nullptr)) {
+    if (bf && in_one) {
         if (mlp->ordered)
             return sf::slow_fused(ctx, const_cast<void*>(mlp->ordered), true, feat, feat_ld, n_rows, esc_idx, scatter, esc_count,
-                                  esc_cap, n_flows, mlp, logits, labels);
+                                  esc_cap, n_flows, mlp, pred, gate, logits, labels);
         const size_t need = sf::slow_fused_ws_bytes(mlp);
         void* w = ws.take(need);
         if (!w) return sf::fail(ctx, SF_ENOMEM, "sf_slow_infer: workspace too small for %zu bytes of re-ordered weights", need);
-        return sf::slow_fused(ctx, w, false, feat, feat_ld, n_rows, esc_idx, scatter, esc_count, esc_cap, n_flows, mlp, logits,
-                              labels);
+        return sf::slow_fused(ctx, w, false, feat, feat_ld, n_rows, esc_idx, scatter, esc_count, esc_cap, n_flows, mlp, pred, gate,
+                              logits, labels);
     }
     const void *w1o = nullptr, *w2o = nullptr;
     if (bf && mlp->ordered) {
@@ -655,9 +712,7 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
         w2o = o2;
     }
     const uint32_t ld1 = bf ? pad64(mlp->n_h1) : mlp->n_h1, ld2 = bf ? pad64(mlp->n_h2) : mlp->n_h2;
-    const size_t row_bytes = bf ? ((size_t)ld1 + ld2) * 2 : ((size_t)mlp->n_in + ld1 + ld2 + mlp->n_classes) * 4;
-    const size_t avail = ws.left() > 4 * sf::kAlign ? ws.left() - 4 * sf::kAlign : 0;
-    uint64_t rows_cap = avail / row_bytes / BM * BM;
+    uint64_t rows_cap = rows_in(ws, row_bytes_of(mlp));
     if (rows_cap < sf::kSlowMinRows)
         return sf::fail(ctx, SF_ENOMEM, "sf_slow_infer: workspace holds %llu rows of hidden activations, need at least %u",
                         (unsigned long long)rows_cap, sf::kSlowMinRows);
@@ -758,15 +813,21 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
     // (23e9) 1,274 : 1,377, 32,768 through 128-650-650-10 (19e9) 1,224 : 1,307.
     // Four rows a block while that gives a compute unit at most two: 2,000 rows through 32-128-128-4 12.9 : 10.4, 1,500 through
     // 64-200-256-10 28.7 : 21.7; four of them against one of 16 rows, 4,096 rows, 18.6 : 13.4.  (Rows that exist: the kernel deals them out.)
-    const size_t lds = f32_fused_lds(mlp->n_in, mlp->n_h1, mlp->n_h2, mlp->n_classes);
-    const double terms = esc_cap * f32_terms(mlp->n_in, mlp->n_h1, mlp->n_h2, mlp->n_classes);
-    if (lds <= kF32FusedLds && terms <= kF32FusedTerms) {
-        const F32Model m = {(const float*)mlp->w1, mlp->b1, (const float*)mlp->w2, mlp->b2, (const float*)mlp->w3, mlp->b3, mlp->n_h1,
-                            mlp->n_h2, mlp->n_classes, scatter ? scatter : esc_idx, logits, labels, n_flows};
-        SF_ALLOW_LDS(ctx, sf::kLdsF32, f32_mlp);
+    if (f32_in_one(mlp, esc_cap)) {
+        F32Model m = {(const float*)mlp->w1, mlp->b1, (const float*)mlp->w2, mlp->b2, (const float*)mlp->w3, mlp->b3, mlp->n_h1, mlp->n_h2,
+                      mlp->n_classes, scatter ? scatter : esc_idx, logits, labels, n_flows, pred, 0};
+        if (pred) m.n_copy = (n_flows + sfsmall::kCopySlice - 1u) / sfsmall::kCopySlice;
+        const size_t lds = f32_fused_lds(mlp->n_in, mlp->n_h1, mlp->n_h2, mlp->n_classes);
         const uint32_t few = 2u * kF32FewRows * (uint32_t)ctx->n_cu;
         const uint32_t tiles = (esc_cap + kF32FewRows - 1u) / kF32FewRows, most = 4u * (uint32_t)ctx->n_cu;
-        f32_mlp<<<tiles < most ? tiles : most, kF32Waves * 64, lds, ctx->stream>>>(f, m, few);
+        const uint32_t grid = (tiles < most ? tiles : most) + m.n_copy;
+        if (gate) {
+            SF_ALLOW_LDS(ctx, sf::kLdsF32 + 1, f32_mlp<sfsmall::GateRows>);
+            f32_mlp<<<grid, kF32Waves * 64, lds, ctx->stream>>>(f, m, few, *gate);
+        } else {
+            SF_ALLOW_LDS(ctx, sf::kLdsF32, f32_mlp<sfsmall::NoGate>);
+            f32_mlp<<<grid, kF32Waves * 64, lds, ctx->stream>>>(f, m, few, sfsmall::NoGate{});
+        }
         SF_LAUNCH_CHECK(ctx, "f32_mlp");
         return SF_OK;
     }
@@ -800,6 +861,31 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
 
 } // namespace
 
+namespace sf {
+
+// Whether the slow model's launch can make the list too, on a feature matrix of n rows: small batches, a model that goes through one
+// launch, and nothing that the gate or the slow model would refuse (their own calls then say what).  One launch less: the whole call
+// on 97 flows with a 64-512-512-10 model 27.1 -> 25.9 us, on 4,096 with a binary32 one 23.4 -> 21.4.
+bool slow_gates(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n, const sf_mlp* mlp)
+{
+    if (n == 0 || n > sfsmall::kGateRows || !feat || check_model(ctx, mlp) != SF_OK || mlp->n_in > feat_ld) return false;
+    if (Carve ws(ctx); !ws.take(route_scratch_bytes(n))) return false;
+    Carve ws(ctx);
+    if (mlp->dtype == SF_F32) return f32_in_one(mlp, n) && rows_in(ws, row_bytes_of(mlp)) >= kSlowMinRows;
+    return slow_fused_gates(ctx, mlp, n) && (mlp->ordered || ws.take(slow_fused_ws_bytes(mlp)));
+}
+
+int slow_infer_gated(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n, const sf_mlp* mlp, const sfsmall::GateRows& gate, const uint16_t* pred,
+                     float* logits, uint16_t* labels)
+{
+    if (pred && pred != labels) {
+        if (const int rc = copy_labels_async(ctx, pred, labels, n); rc != SF_OK) return rc;
+    }
+    return run_slow(ctx, feat, feat_ld, n, nullptr, nullptr, gate.esc_idx, nullptr, gate.esc_count, n, n, mlp, nullptr, &gate, logits, labels);
+}
+
+} // namespace sf
+
 extern "C" int sf_slow_infer(sf_ctx* ctx, const float* feat, uint32_t feat_ld, const sf_packets* raw_src,
                              const sf_feat_cfg* raw_cfg, const uint32_t* esc_idx, const uint32_t* esc_count,
                              uint32_t esc_cap, uint32_t n_flows, const sf_mlp* mlp, const uint16_t* pred, float* logits,
@@ -807,7 +893,7 @@ extern "C" int sf_slow_infer(sf_ctx* ctx, const float* feat, uint32_t feat_ld, c
 {
     if (!ctx) return sf::fail(nullptr, SF_EINVAL, "sf_slow_infer: ctx is NULL");
     return run_slow(ctx, feat, feat_ld, n_flows, raw_src, raw_cfg, esc_idx, nullptr, esc_count, esc_cap, n_flows, mlp, pred,
-                    logits, labels);
+                    nullptr, logits, labels);
 }
 
 extern "C" int sf_slow_infer_pairs(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows,
@@ -818,7 +904,7 @@ extern "C" int sf_slow_infer_pairs(sf_ctx* ctx, const float* feat, uint32_t feat
     if (!feat) return sf::fail(ctx, SF_EINVAL, "sf_slow_infer_pairs: feat is NULL");
     if (pair_cap && n_flows && n_rows && !pair_flow) return sf::fail(ctx, SF_EINVAL, "sf_slow_infer_pairs: pair_flow is NULL");
     return run_slow(ctx, feat, feat_ld, n_rows, nullptr, nullptr, pair_row, pair_flow, n_pairs, pair_cap, n_flows, mlp,
-                    nullptr, logits, labels);
+                    nullptr, nullptr, logits, labels);
 }
 
 extern "C" size_t sf_mlp_ordered_bytes(const sf_mlp* mlp)

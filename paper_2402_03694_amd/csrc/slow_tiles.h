@@ -37,6 +37,8 @@ struct FusedArgs {
     const float *b1, *b2, *b3;
     float* logits;
     uint16_t* labels;
+    const uint16_t* pred; // labels of the flows that are not on the list, copied by the grid's first blocks; NULL = they stay
+    uint32_t n_copy;      // blocks that copy
 };
 
 __device__ __forceinline__ bf16x8 as_frag(uint4 u)

@@ -1,0 +1,93 @@
+"""Small batches whose gate and label copy go with the slow model's launch, at the edges of what that launch takes (16,384 rows for
+the gate, 65,536 for the copy, slices of 2,048): sf_classify against the four separate calls, and sf_slow_infer's labels against
+what the header says, for lists in any order with entries outside the batch."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _model(dims, f32, seed):
+    import torch
+    import paper_2402_03694_amd as sf
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    par = []
+    for o, k in zip(dims[1:], dims[:-1]):
+        w = torch.randn((o, k), device=DEV, generator=g) / k ** 0.5
+        par += [w if f32 else w.to(torch.bfloat16), torch.randn(o, device=DEV, generator=g) * 0.1]
+    return sf.DeviceMlp(dims, sf.SF_F32 if f32 else sf.SF_BF16, *par)
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("per_class,shift", [(False, 0), (True, 0), (True, 1)])
+def test_gate(f32, per_class, shift):
+    import torch
+    import paper_2402_03694_amd as sf
+    t, d, c, f = 40, 6, 5, 32
+    for n in (1, 7, 31, 97, 511, 4096, 4097, 12289, 16384, 16385):
+        g = torch.Generator(device=DEV)
+        g.manual_seed(n)
+        m = n * 8
+        pk = sf.DevicePackets(torch.arange(0, m + 1, 8, dtype=torch.int32, device=DEV), torch.randint(40, 1500, (m,), device=DEV, generator=g).to(torch.int16),
+                              torch.rand(m, device=DEV, generator=g), (torch.rand(m, device=DEV, generator=g) < 0.5).to(torch.uint8))
+        nf = torch.randint(0, f, (t, 2 ** d - 1), device=DEV, generator=g).to(torch.int16)
+        nt = torch.rand((t, 2 ** d - 1), device=DEV, generator=g) * 500
+        leaf = torch.randint(0, c, (t, 2 ** d), device=DEV, generator=g).to(torch.uint8)
+        forest = sf.DeviceForest(t, d, c, f, nf, nt, leaf)
+        mlp = _model((f, 100, 60, c), f32, n)
+        ctx = sf.ServeFlow(sf.sf_workspace_bytes(n, t, d, f, 100, 60))
+        ctx.sf_forest_pack(forest)
+        vmin = [12, 14, 0, 13, 15] if per_class else 13
+        i16 = lambda: torch.full((n + shift,), -1, dtype=torch.int16, device=DEV)[shift:]
+        i32 = lambda k: torch.full((k,), -1, dtype=torch.int32, device=DEV)
+        out = []
+        for whole in (True, False):
+            feat = torch.zeros((n, f), device=DEV)
+            pred, top, labels, idx, count, logits = i16(), i16(), i16(), i32(n), i32(1), torch.full((n, c), -7.0, device=DEV)
+            if whole:
+                ctx.sf_classify(pk, [8], forest, vmin, mlp, feat, pred, top, idx, count, labels, logits=logits)
+            else:
+                ctx.sf_featurize(pk, [8], feat)
+                ctx.sf_fast_infer(feat, forest, pred, top)
+                ctx.sf_route(top, pred, vmin, idx, count)
+                ctx.sf_slow_infer(mlp, idx, count, labels, feat=feat, logits=logits, pred=pred)
+            out.append((pred, top, labels, idx, count, logits))
+        assert 0 <= int(count) <= n and (n < 97 or 0 < int(count) < n)
+        for a, b in zip(*out):
+            assert torch.equal(a, b), n
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("n", [1, 2047, 2049, 9001, 65536, 65537])
+def test_copied_labels(f32, n):
+    import torch
+    import paper_2402_03694_amd as sf
+    rng = np.random.default_rng(n)
+    dims = (16, 40, 50, 6)
+    mlp = _model(dims, f32, n)
+    feat = torch.from_numpy(rng.standard_normal((n, 16)).astype(np.float32)).to(DEV)
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(n, 0, 0, *dims[:3]))
+    pred = torch.from_numpy(rng.integers(0, 6, n).astype(np.int16)).to(DEV)
+    # the label of every row, from a list of all
+    every = torch.arange(n, dtype=torch.int32, device=DEV)
+    slow = torch.full((n,), -1, dtype=torch.int16, device=DEV)
+    ctx.sf_slow_infer(mlp, every, torch.tensor([n], dtype=torch.int32, device=DEV), slow, feat=feat)
+    for rows in (0, 1, n // 3):
+        list_ = rng.permutation(n)[:rows].astype(np.int64)
+        if rows > 4:
+            list_[2], list_[3] = n + 5, 2 ** 31 - 1  # outside the batch: the row read is the last one's
+            list_ = list_[list_ != n - 1]
+        idx = np.full(n, 7, np.int32)
+        idx[:len(list_)] = list_
+        count = torch.tensor([len(list_)], dtype=torch.int32, device=DEV)
+        labels = torch.full((n,), -1, dtype=torch.int16, device=DEV)
+        ctx.sf_slow_infer(mlp, torch.from_numpy(idx).to(DEV), count, labels, feat=feat, pred=pred)
+        want, got, s = pred.cpu().numpy().copy(), labels.cpu().numpy(), slow.cpu().numpy()
+        inside = list_[list_ < n]
+        want[inside] = s[inside]
+        if len(inside) < len(list_) and not f32:
+            want[n - 1] = s[n - 1]  # (bfloat16 models in one launch label it, binary32 models label nothing)
+        assert np.array_equal(got, want), rows
