@@ -42,8 +42,15 @@ struct LayerArgs {
     // output
     uint16_t* h_out; // [rows_in_chunk][ldh] bfloat16
     uint32_t ldh;
-    float* logits;   // [esc_cap][N] or NULL
+    float* logits;   // [esc_cap][classes] or NULL
     uint16_t* labels;
+    // The second hidden layer may take the last one along (wide_takes_last): its weights [n_last][N], biases and classes (0: it may not)
+    const uint16_t* w_last;
+    const uint4* wo_last; // operand-ordered copy, or NULL
+    const float* b_last;
+    uint32_t n_last;
+    // ... and for the last layer's own launch: blocks of the second hidden layer's (0: that one took nothing along) and its K
+    uint32_t units_before, k_before;
 };
 
 static __device__ __forceinline__ uint16_t f32_to_bf16_bits(float x)
@@ -55,6 +62,40 @@ static __device__ __forceinline__ uint16_t f32_to_bf16_bits(float x)
 }
 
 static __device__ __forceinline__ uint32_t pack2(uint16_t lo, uint16_t hi) { return (uint32_t)lo | ((uint32_t)hi << 16); }
+
+// 8 consecutive K values [k, k+8) of weight row n (row-major [N][K] bfloat16 bits), zero outside
+static __device__ __forceinline__ uint4 weight_chunk(const uint16_t* w, uint32_t N, uint32_t K, uint32_t n, uint32_t k)
+{
+    if (n >= N || k >= K) return make_uint4(0, 0, 0, 0);
+    const uint16_t* p = w + (size_t)n * K + k;
+    if (k + 8 <= K && (K & 7u) == 0 && (reinterpret_cast<uintptr_t>(w) & 15u) == 0) return *reinterpret_cast<const uint4*>(p);
+    uint16_t v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = k + q < K ? p[q] : (uint16_t)0;
+    return make_uint4(pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7]));
+}
+
+// the last layer's operand of one k-step (32 classes from 32 j on): from the ordered copy, which a wave reads as it lies, if there is one
+// (up to 32 classes; 200,000 rows through 2048-32, rows of weights one by one: as long again in the address path)
+static __device__ __forceinline__ uint4 last_weights(const LayerArgs& a, uint32_t N, uint32_t K, uint32_t j, uint32_t ks, uint32_t lane)
+{
+    if (a.wo_last) return a.wo_last[ks * 64u + lane];
+    return weight_chunk(a.w_last, N, K, j * 32u + (lane & 31u), ks * 16u + 8u * (lane >> 5));
+}
+
+// How a hidden layer's tiles of 128 rows x 512 columns are dealt out to `units` blocks: a row block with all its n_cb column blocks
+// (walk), where that costs no block a tile more than 1 in 16 or the input stays (resident), else tile by tile.
+static __device__ __forceinline__ bool wide_walks(uint32_t row_blocks, uint32_t n_cb, uint32_t units, bool resident)
+{
+    const uint32_t t_walk = (row_blocks + units - 1u) / units * n_cb, t_split = (row_blocks * n_cb + units - 1u) / units; // tiles, longest block
+    return n_cb > 1u && row_blocks >= units && (resident || t_walk - t_split <= t_split / 16u);
+}
+// A block that holds all columns of a row takes the last layer along.
+static __device__ __forceinline__ bool wide_takes_last(uint32_t row_blocks, uint32_t n_cb, uint32_t units, bool resident)
+{
+    return n_cb == 1u || wide_walks(row_blocks, n_cb, units, resident);
+}
+constexpr uint32_t kWideCols = 512, kWideSlab = 64, kWideSlabs = 3; // columns of a tile, K values of a slab, slabs that stay
 
 // the packets of a flow for the raw-bit input: first packet and count, clamped into the packet arrays
 static __device__ __forceinline__ void raw_flow_range(const LayerArgs& a, uint32_t flow, uint32_t& b0, uint32_t& n)

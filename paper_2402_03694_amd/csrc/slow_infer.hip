@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "mlp_common.h"
+#include "slow_label.h"
 #include "small_batch.h"
 
 namespace sf {
@@ -28,140 +29,216 @@ int copy_labels_async(sf_ctx* ctx, const uint16_t* pred, uint16_t* labels, uint3
 int order_all(sf_ctx* ctx, const sf_mlp* mlp, void* out);
 // one hidden layer of any width on operand-ordered weights (slow_wide.hip)
 int wide_layer(sf_ctx* ctx, int amode, const sfmlp::LayerArgs& a, const void* w_ordered, uint32_t rows_cap);
+uint32_t wide_blocks(const sf_ctx* ctx, uint32_t ldh, uint32_t rows_cap); // blocks of its launch
 } // namespace sf
 
 namespace {
 
 using namespace sfmlp;
 
-// 8 consecutive K values [k, k+8) of weight row n (row-major [N][K] bfloat16 bits), zero outside
-__device__ __forceinline__ uint4 load_w_chunk(const LayerArgs& a, uint32_t n, uint32_t k)
+// The last layer of a wide model: logits = A * W3^T + b3 on bfloat16 activations (at most 64 classes), then the arg-max per row
+// and the scatter of the label.  K is cut into pieces of 64, and a logit is its bias plus the pieces' sums in order, whatever form
+// makes them: mlp_wide_last (slow_wide.hip), which takes this layer along where it can, or one of the two here.
+//   - Long lists: 256 rows a block, a wave 32 of them, K walked by all waves together through shared memory in steps of two pieces,
+//     the next step requested ahead of the MFMAs.  What bounds it is HBM (200,000 rows of 2,048 values 216 us, 3.8 TB/s; straight
+//     from the cache into registers, a row's operands are 32 lines to the address path, 270).
+//   - Short ones (up to six blocks of 32 rows a unit): the waves of a block split the pieces of 32 rows, whose operands are all
+//     requested before the first MFMA; the pieces' sums meet in shared memory.  What bounds it is the chain of latencies.
+//     500 rows of 1,024 values 11.4 -> 6.2 us, 19,600 14.
+constexpr int LROWS = 32, LWAVES = 8, LPIECE = 64;
+constexpr int LTILE = LWAVES * 32, LSTEP = 2 * LPIECE, LLDT = LSTEP + 8; // long lists: rows of a block, K of a step, row stride in shared memory
+template <int NI> // 32-class blocks
+struct LastShape {
+    static constexpr int kLd = NI * 32 + 4;            // row stride of a piece's sums (16-byte writes of 8 rows on distinct banks)
+    static constexpr int kHeld = LWAVES * (NI == 1 ? 2 : 1); // pieces whose sums are held at a time
+    static constexpr size_t kShort = (size_t)(kHeld + 1) * LROWS * kLd * 4, kLong = (size_t)(LTILE + NI * 32) * LLDT * 2;
+    static constexpr size_t kLds = kShort > kLong ? kShort : kLong;
+};
+
+// Rows [r0, r0 + 256) of the chunk by the whole block, K in steps of two pieces
+template <int NI>
+__device__ __forceinline__ void last_tile(const LayerArgs& a, uint32_t r0, uint32_t rows, unsigned char* smem, uint32_t tid, uint32_t lane, uint32_t wave)
 {
-    if (n >= a.N || k >= a.K) return make_uint4(0, 0, 0, 0);
-    const uint16_t* p = a.w + (size_t)n * a.K + k;
-    if (k + 8 <= a.K && (a.K & 7u) == 0 && (reinterpret_cast<uintptr_t>(a.w) & 15u) == 0)
-        return *reinterpret_cast<const uint4*>(p);
-    uint16_t v[8];
+    constexpr int kA = LTILE * LSTEP / 8 / (LWAVES * 64), kB = NI * 32 * LSTEP / 8 / (LWAVES * 64); // 16-byte pieces of a thread per step
+    uint16_t *As = reinterpret_cast<uint16_t*>(smem), *Bs = As + LTILE * LLDT;
+    const uint32_t half = lane >> 5, r = wave * 32u + (lane & 31u); // this lane's row of the tile
+    const uint32_t row = r0 + r < rows ? r0 + r : rows - 1u, dst = (a.scatter ? a.scatter : a.esc_idx)[a.row_begin + row];
+    float y[NI][16]; // class 32 j + 8 * (v / 4) + 4 * half + v % 4
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = k + q < a.K ? p[q] : (uint16_t)0;
-    return make_uint4(pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7]));
-}
-
-// The last layer of a wide model: logits = A * W3^T + b3 on bfloat16 activations (at most BN classes), then the
-// arg-max per row and the scatter of the label.  128 rows per block, four waves of 32 rows each.  K is walked
-// in steps of 128; the operands of the next step are requested before the MFMAs of the current one, so that
-// a launch with few blocks (a small batch) does not wait a whole memory latency per step.
-constexpr int LBK = 128;      // K per step of the last layer
-constexpr int LLDT = LBK + 8; // shared-memory row stride (elements): 272 bytes, 16-byte reads of 8 consecutive rows on distinct banks
-
-template <int BN>
-__global__ __launch_bounds__(256) void mlp_last_layer(LayerArgs a)
-{
-    constexpr int MI = 1, NI = BN / 32;   // a wave owns 32 rows x BN columns
-    constexpr int WM = BM / 4;
-    constexpr int A_CHUNKS = BM * LBK / 8 / 256; // 16-byte chunks per thread per step
-    constexpr int B_CHUNKS = (BN * LBK / 8 + 255) / 256;
-    constexpr int SM_AB = (BM + BN) * LLDT * 2;
-    constexpr int SM_EPI = BM * (BN + 1) * 4;
-    constexpr int SM_BYTES = SM_AB > SM_EPI ? SM_AB : SM_EPI;
-    __shared__ __attribute__((aligned(16))) unsigned char smem[SM_BYTES];
-    __shared__ uint32_t s_flow[BM];
-    uint16_t* As = reinterpret_cast<uint16_t*>(smem);
-    uint16_t* Bs = As + BM * LLDT;
-
-    uint32_t total = *a.esc_count;
-    total = total < a.esc_cap ? total : a.esc_cap;
-    const uint32_t row0 = a.row_begin + blockIdx.x * BM; // first escalated row of this block
-    if (row0 >= total) return;
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wm = tid >> 6;
-
-    if (tid < BM) // the index the row's label goes to
-        s_flow[tid] = row0 + tid < total ? (a.scatter ? a.scatter[row0 + tid] : a.esc_idx[row0 + tid]) : 0u;
-
-    f32x16 acc[MI][NI];
+    for (int j = 0; j < NI; ++j)
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    uint4 ra[A_CHUNKS], rb[B_CHUNKS];
+        for (int v = 0; v < 16; ++v) {
+            const uint32_t c = j * 32u + 8u * (v >> 2) + 4u * half + (v & 3);
+            y[j][v] = c < a.N ? a.bias[c] : 0.f;
+        }
+    uint4 ra[kA], rb[kB];
+    const uint32_t ck = tid % (LSTEP / 8) * 8u, cr = tid / (LSTEP / 8); // (rows of As: every 32nd from cr on)
     auto fetch = [&](uint32_t k0) {
 #pragma unroll
-        for (int u = 0; u < A_CHUNKS; ++u) {
-            const uint32_t c = tid + 256 * u, r = c / (LBK / 8), kq = c % (LBK / 8);
-            ra[u] = load_a_chunk<A_BF16>(a, row0 + r < total, blockIdx.x * BM + r, 0u, k0 + kq * 8);
+        for (int u = 0; u < kA; ++u) { // (lda: whole pieces, zeros behind K; a row past the end: the last one again)
+            const uint32_t q = r0 + cr + 32u * u;
+            ra[u] = k0 + ck < a.lda ? *reinterpret_cast<const uint4*>(a.a_bf16 + (size_t)(q < rows ? q : rows - 1u) * a.lda + k0 + ck) : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
-        for (int u = 0; u < B_CHUNKS; ++u) {
-            const uint32_t c = tid + 256 * u, r = c / (LBK / 8), kq = c % (LBK / 8);
-            rb[u] = (r < (uint32_t)BN) ? load_w_chunk(a, r, k0 + kq * 8) : make_uint4(0, 0, 0, 0);
-        }
+        for (int u = 0; u < kB; ++u) rb[u] = weight_chunk(a.w, a.N, a.K, cr + 32u * u, k0 + ck);
     };
     fetch(0);
-    for (uint32_t k0 = 0; k0 < a.K; k0 += LBK) {
-        __syncthreads(); // previous step's fragment reads are done (first step: s_flow is in place)
+    for (uint32_t k0 = 0; k0 < a.K; k0 += LSTEP) {
+        __syncthreads(); // the step before has been read
 #pragma unroll
-        for (int u = 0; u < A_CHUNKS; ++u) {
-            const uint32_t c = tid + 256 * u, r = c / (LBK / 8), kq = c % (LBK / 8);
-            *reinterpret_cast<uint4*>(As + r * LLDT + kq * 8) = ra[u];
-        }
+        for (int u = 0; u < kA; ++u) *reinterpret_cast<uint4*>(As + (cr + 32u * u) * LLDT + ck) = ra[u];
 #pragma unroll
-        for (int u = 0; u < B_CHUNKS; ++u) {
-            const uint32_t c = tid + 256 * u, r = c / (LBK / 8), kq = c % (LBK / 8);
-            if (r < (uint32_t)BN) *reinterpret_cast<uint4*>(Bs + r * LLDT + kq * 8) = rb[u];
-        }
+        for (int u = 0; u < kB; ++u) *reinterpret_cast<uint4*>(Bs + (cr + 32u * u) * LLDT + ck) = rb[u];
         __syncthreads();
-        if (k0 + LBK < a.K) fetch(k0 + LBK); // chunks past K read as zeros
-        __builtin_amdgcn_sched_barrier(0);   // keep the requests ahead of the MFMAs
+        if (k0 + LSTEP < a.K) fetch(k0 + LSTEP);
+        __builtin_amdgcn_sched_barrier(0); // keep the requests ahead of the MFMAs
 #pragma unroll
-        for (int ks = 0; ks < LBK / 16; ++ks) {
-            bf16x8 fa[MI], fb[NI];
-            const uint32_t kofs = ks * 16 + (lane >> 5) * 8;
+        for (int p = 0; p < LSTEP / LPIECE; ++p) {
+            if (k0 + p * LPIECE >= a.K) continue;
 #pragma unroll
-            for (int i = 0; i < MI; ++i)
-                fa[i] = as_bf16x8(*reinterpret_cast<const uint4*>(As + (wm * WM + i * 32 + (lane & 31)) * LLDT + kofs));
+            for (int j = 0; j < NI; ++j) {
+                f32x16 c3;
 #pragma unroll
-            for (int j = 0; j < NI; ++j)
-                fb[j] = as_bf16x8(*reinterpret_cast<const uint4*>(Bs + (j * 32 + (lane & 31)) * LLDT + kofs));
+                for (int v = 0; v < 16; ++v) c3[v] = 0.f;
 #pragma unroll
-            for (int i = 0; i < MI; ++i)
+                for (int s = 0; s < 4; ++s) {
+                    const uint32_t at = p * LPIECE + s * 16u + 8u * half;
+                    c3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*reinterpret_cast<const uint4*>(Bs + (j * 32u + (lane & 31u)) * LLDT + at)),
+                                                                 as_bf16x8(*reinterpret_cast<const uint4*>(As + r * LLDT + at)), c3, 0, 0, 0);
+                }
 #pragma unroll
-                for (int j = 0; j < NI; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+                for (int v = 0; v < 16; ++v) y[j][v] += c3[v];
+            }
         }
     }
+    // class 0 first, then every class that is strictly larger than all before it (label_start, label_of)
+    uint32_t best = 4u * half;
+    float bv = label_start(half, y[0][0]);
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const uint32_t c = j * 32u + 8u * (v >> 2) + 4u * half + (v & 3); // ascending in v
+            if (c < a.N) {
+                if (a.logits && r0 + r < rows) a.logits[(size_t)(a.row_begin + r0 + r) * a.N + c] = y[j][v];
+                if (y[j][v] > bv) {
+                    bv = y[j][v];
+                    best = c;
+                }
+            }
+        }
+    best = label_of(best, bv);
+    if (half == 0 && r0 + r < rows && dst < a.n_labels) a.labels[dst] = (uint16_t)best;
+}
 
-    // accumulator element v of lane l in a 32x32 block: row 8*(v/4) + 4*(l/32) + v%4, column l%32
-    __syncthreads(); // operand tiles are dead; reuse the space for the logits tile
-    float* Ls = reinterpret_cast<float*>(smem);
+template <int NI>
+__global__ __launch_bounds__(LWAVES * 64, 4) void mlp_last_layer(LayerArgs a, uint32_t short_tiles)
+{
+    typedef LastShape<NI> S;
+    constexpr int kMine = S::kHeld / LWAVES;               // pieces a wave has at a time
+    constexpr int kOut = LROWS * NI * 32 / (LWAVES * 64);  // logits of a thread
+    extern __shared__ __attribute__((aligned(16))) float sums[]; // [kHeld][32][kLd]
+    float* s_logits = sums + S::kHeld * LROWS * S::kLd;          // [32][kLd]
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint32_t total = *a.esc_count;
+    total = total < a.esc_cap ? total : a.esc_cap;
+    if (a.row_begin >= total) return;
+    const uint32_t left = total - a.row_begin, rows = left < a.rows_cap ? left : a.rows_cap; // of this chunk
+    if (a.units_before && wide_takes_last((rows + BM - 1u) / BM, (a.lda + kWideCols - 1u) / kWideCols, a.units_before, a.k_before <= kWideSlab * kWideSlabs))
+        return; // the layer before has taken this one along
+    const uint32_t pieces = (a.K + LPIECE - 1u) / LPIECE, tiles = (rows + LROWS - 1u) / LROWS;
+    if (tiles > short_tiles) {
+        for (uint32_t r0 = blockIdx.x * LTILE; r0 < rows; r0 += gridDim.x * LTILE)
+            last_tile<NI>(a, r0, rows, reinterpret_cast<unsigned char*>(sums), tid, lane, wave);
+        return;
+    }
+    uint4 fa[kMine][4], fw[kMine][4][NI];
+    // operands of this wave's pieces from p0 on for the rows from r0 on (a row, piece or class past the last one: that one again)
+    auto request = [&](uint32_t r0, uint32_t p0) {
+        const uint32_t r = r0 + (lane & 31u);
+        const uint16_t* arow = a.a_bf16 + (size_t)(r < rows ? r : rows - 1u) * a.lda; // (lda: whole pieces, zeros behind K)
+        auto each = [&](auto ordered) {
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+            for (int m = 0; m < kMine; ++m) {
+                const uint32_t p = p0 + wave + LWAVES * m, ks = (p < pieces ? p : pieces - 1u) * (LPIECE / 16u);
 #pragma unroll
-        for (int j = 0; j < NI; ++j) {
-            const uint32_t cl = j * 32 + (lane & 31);
-            const float b = cl < a.N ? a.bias[cl] : 0.f;
+                for (int s = 0; s < 4; ++s) {
+                    fa[m][s] = *reinterpret_cast<const uint4*>(arow + (ks + s) * 16u + 8u * (lane >> 5));
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const uint32_t r = wm * WM + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                Ls[r * (BN + 1) + cl] = acc[i][j][v] + b;
+                    for (int j = 0; j < NI; ++j)
+                        fw[m][s][j] = decltype(ordered)::value ? a.wo_last[(ks + s) * 64u + lane] : last_weights(a, a.N, a.K, j, ks + s, lane);
+                }
             }
+        };
+        if (NI == 1 && a.wo_last)
+            each(std::true_type{});
+        else
+            each(std::false_type{});
+    };
+    const uint32_t first = blockIdx.x * LROWS, step = gridDim.x * LROWS;
+    if (first >= rows) return;
+    request(first, 0);
+    for (uint32_t r0 = first; r0 < rows; r0 += step) {
+        uint32_t dst = 0;
+        if (tid < LROWS && r0 + tid < rows) dst = (a.scatter ? a.scatter : a.esc_idx)[a.row_begin + r0 + tid];
+        float y[kOut];
+#pragma unroll
+        for (int q = 0; q < kOut; ++q) {
+            const uint32_t c = (tid + q * LWAVES * 64u) % (NI * 32u);
+            y[q] = c < a.N ? a.bias[c] : 0.f;
         }
-    __syncthreads();
-    if (tid < BM && row0 + tid < total) {
-        const float* lr = Ls + tid * (BN + 1);
-        uint32_t best = 0;
-        float bv = lr[0];
-        for (uint32_t c = 0; c < a.N; ++c) {
-            const float v = lr[c];
-            if (a.logits) a.logits[(size_t)(row0 + tid) * a.N + c] = v;
-            if (v > bv) {
-                bv = v;
-                best = c;
+        for (uint32_t p0 = 0; p0 < pieces; p0 += S::kHeld) {
+#pragma unroll
+            for (int m = 0; m < kMine; ++m) {
+                if (p0 + wave + LWAVES * m >= pieces) continue;
+#pragma unroll
+                for (int j = 0; j < NI; ++j) {
+                    f32x16 c3;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) c3[v] = 0.f;
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) c3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fw[m][s][j]), as_bf16x8(fa[m][s]), c3, 0, 0, 0);
+                    // the weights first: element v of lane l is row l % 32, class 8 * (v / 4) + 4 * (l / 32) + v % 4
+                    float* to = sums + ((size_t)(wave + LWAVES * m) * LROWS + (lane & 31u)) * S::kLd + j * 32u + 4u * (lane >> 5);
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        *reinterpret_cast<float4*>(to + 8 * g) = make_float4(c3[4 * g], c3[4 * g + 1], c3[4 * g + 2], c3[4 * g + 3]);
+                }
             }
+            // the next operands are on their way while the sums meet
+            const bool more = p0 + S::kHeld < pieces;
+            if (more || r0 + step < rows) request(more ? r0 : r0 + step, more ? p0 + S::kHeld : 0u);
+            __syncthreads();
+            const uint32_t held = pieces - p0 < (uint32_t)S::kHeld ? pieces - p0 : S::kHeld;
+            for (uint32_t p = 0; p < held; ++p)
+#pragma unroll
+                for (int q = 0; q < kOut; ++q) {
+                    const uint32_t e = tid + q * LWAVES * 64u;
+                    y[q] += sums[((size_t)p * LROWS + e / (NI * 32u)) * S::kLd + e % (NI * 32u)];
+                }
+            __syncthreads(); // the sums have been read
         }
-        if (s_flow[tid] < a.n_labels) a.labels[s_flow[tid]] = (uint16_t)best;
+#pragma unroll
+        for (int q = 0; q < kOut; ++q) {
+            const uint32_t e = tid + q * LWAVES * 64u, row = e / (NI * 32u), c = e % (NI * 32u);
+            s_logits[row * S::kLd + c] = y[q];
+            if (a.logits && c < a.N && r0 + row < rows) a.logits[(size_t)(a.row_begin + r0 + row) * a.N + c] = y[q];
+        }
+        __syncthreads();
+        if (tid < LROWS && r0 + tid < rows) {
+            const float* lr = s_logits + tid * S::kLd;
+            uint32_t best = 0;
+            float bv = lr[0];
+#pragma unroll 8
+            for (uint32_t c = 1; c < a.N; ++c) {
+                const float v = lr[c];
+                if (v > bv) {
+                    bv = v;
+                    best = c;
+                }
+            }
+            if (dst < a.n_labels) a.labels[dst] = (uint16_t)best;
+        } // (the next rows' logits are written two barriers on)
     }
 }
 
@@ -583,13 +660,14 @@ __global__ __launch_bounds__(256) void f32_argmax(const uint32_t* label_idx, con
     }
 }
 
-void launch_final(sf_ctx* ctx, const LayerArgs& a, uint32_t rows_cap)
+template <int NI>
+int launch_last(sf_ctx* ctx, const LayerArgs& a, uint32_t rows_cap)
 {
-    dim3 grid((rows_cap + BM - 1) / BM, 1);
-    if (a.N <= 32)
-        mlp_last_layer<32><<<grid, 256, 0, ctx->stream>>>(a);
-    else
-        mlp_last_layer<64><<<grid, 256, 0, ctx->stream>>>(a);
+    SF_ALLOW_LDS(ctx, sf::kLdsLast + NI - 1, mlp_last_layer<NI>);
+    const uint32_t tiles = (rows_cap + LROWS - 1u) / LROWS, most = 4u * (uint32_t)ctx->n_cu; // (rows that exist are dealt out in the kernel)
+    mlp_last_layer<NI><<<tiles < most ? tiles : most, LWAVES * 64, LastShape<NI>::kLds, ctx->stream>>>(a, 6u * (uint32_t)ctx->n_cu);
+    SF_LAUNCH_CHECK(ctx, "mlp_last_layer");
+    return SF_OK;
 }
 
 // labels = pred for every flow; the slow labels are scattered over it afterwards
@@ -696,10 +774,11 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
         return sf::slow_fused(ctx, w, false, feat, feat_ld, n_rows, esc_idx, scatter, esc_count, esc_cap, n_flows, mlp, pred, gate,
                               logits, labels);
     }
-    const void *w1o = nullptr, *w2o = nullptr;
+    const void *w1o = nullptr, *w2o = nullptr, *w3o = nullptr;
     if (bf && mlp->ordered) {
         w1o = mlp->ordered;
         w2o = (const char*)mlp->ordered + sf::reordered_bytes(mlp->n_h1, mlp->n_in);
+        if (mlp->n_classes <= 32u) w3o = (const char*)w2o + sf::reordered_bytes(mlp->n_h2, mlp->n_h1);
     } else if (bf) {
         // operand-ordered copies of the two hidden layers' weights
         void* o1 = ws.take(sf::reordered_bytes(mlp->n_h1, mlp->n_in));
@@ -766,11 +845,18 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
             a.K = mlp->n_h1;
             a.h_out = h2;
             a.ldh = ld2;
+            a.w_last = (const uint16_t*)mlp->w3;
+            a.wo_last = (const uint4*)w3o;
+            a.b_last = mlp->b3;
+            a.n_last = mlp->n_classes <= 32u ? mlp->n_classes : 0u;
+            a.logits = logits;
             {
                 const int rc = sf::wide_layer(ctx, A_BF16, a, w2o, R);
                 if (rc != SF_OK) return rc;
             }
             // layer 3
+            a.units_before = a.n_last ? sf::wide_blocks(ctx, ld2, R) : 0u;
+            a.k_before = mlp->n_h1;
             a.a_bf16 = h2;
             a.lda = ld2;
             a.w = (const uint16_t*)mlp->w3;
@@ -779,9 +865,11 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
             a.K = mlp->n_h2;
             a.h_out = nullptr;
             a.ldh = 0;
-            a.logits = logits;
-            launch_final(ctx, a, R);
-            SF_LAUNCH_CHECK(ctx, "mlp_last_layer");
+            a.rows_cap = R;
+            {
+                const int rc = a.N <= 32u ? launch_last<1>(ctx, a, R) : launch_last<2>(ctx, a, R);
+                if (rc != SF_OK) return rc;
+            }
         }
         return SF_OK;
     }

@@ -337,7 +337,7 @@ struct Rows {
             float* lg = a.logits + (size_t)row * a.c;
             const bool write = a.logits && row < row_end;
             uint32_t best = 8u * half;
-            float bv = sftiles::label_start(half, out[i][0]);
+            float bv = label_start(half, out[i][0]);
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 if (16u * e >= a.c) break;
@@ -352,7 +352,7 @@ struct Rows {
                     best = take ? c : best;
                 }
             }
-            best = sftiles::label_of(best, bv);
+            best = label_of(best, bv);
             if (i == 0 || half) label = best;
         }
         if (own_ok && dst < a.n_labels) a.labels[dst] = (uint16_t)label;

@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "mlp_common.h"
+#include "slow_label.h"
 
 namespace sftiles {
 
@@ -71,18 +72,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 __device__ __forceinline__ uint32_t relu_pair(float lo, float hi)
 {
     return pack_bf16(__builtin_amdgcn_fmed3f(lo, 0.f, 3.402823466e38f), __builtin_amdgcn_fmed3f(hi, 0.f, 3.402823466e38f));
-}
-
-// The label of a row whose classes two lanes hold, lane l and lane l ^ 32: class 0 first, then every class that is strictly larger
-// than all before it.  A NaN is larger than nothing, and nothing than a NaN in class 0, which counts as infinity here; so what a
-// lane holds is never NaN, and the two lanes come to the same label.
-// A lane starts before its first class (the lower lane's is class 0, whose logit is y0) and takes c where y > bv.
-__device__ __forceinline__ float label_start(uint32_t half, float y0) { return half ? -__builtin_inff() : y0 == y0 ? y0 : __builtin_inff(); }
-__device__ __forceinline__ uint32_t label_of(uint32_t best, float bv)
-{
-    const float ov = __shfl_xor(bv, 32, 64);
-    const uint32_t ob = (uint32_t)__shfl_xor((int)best, 32, 64);
-    return ov > bv || (ov == bv && ob < best) ? ob : best; // (a lane without classes holds -infinity and a number past the last)
 }
 
 constexpr int kMI = 4;     // 32-row blocks of the tallest tile (128 rows)

@@ -28,6 +28,7 @@
 
 namespace sf {
 int wide_layer(sf_ctx* ctx, int amode, const sfmlp::LayerArgs& a, const void* w_ordered, uint32_t rows_cap);
+uint32_t wide_blocks(const sf_ctx* ctx, uint32_t ldh, uint32_t rows_cap);
 }
 
 namespace {
@@ -51,6 +52,10 @@ constexpr int WSTAGE = WBM / 2;   // rows of a wave's output staged at a time
 constexpr size_t kSlabBytes = (size_t)WBUF * WBM * WLDS * 2;
 constexpr size_t kStageBytes = (size_t)WSTAGE * WLDO * 2 + WCOLS * 4; // a wave's staged output rows and bias
 constexpr size_t kWideLds = kSlabBytes + WWAVES * kStageBytes + WBM * 4; // slabs, waves' own space, flow ids
+constexpr int WLDP = 36;          // row stride of the last layer's sums (floats): a wave's 64 rows of them take the place of its staged output
+static_assert(WLDP * 4 == WLDO * 2, "the sums in the staged rows' place");
+constexpr size_t kLastLds = (size_t)WBM * WLDP * 4; // a tile's logits, between column blocks
+static_assert(WBN == kWideCols && WSLAB == kWideSlab && WBUF == kWideSlabs, "as the last layer's launch assumes");
 
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {
@@ -81,10 +86,13 @@ __device__ __forceinline__ void wave_sync()
 
 // RESIDENT: every slab of a row block has a buffer of its own (K up to WBUF slabs).
 // FORM: how header bits lie (A_RAW).
-template <int AMODE, bool RESIDENT, int FORM>
-__global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const uint4* __restrict__ ws, uint32_t n_cb)
+// LAST: the last layer goes along (a block holds all columns of a row, wide_takes_last): a wave multiplies the 64 columns it has
+// staged with their weights, the eight waves' sums meet in shared memory, and the activations are neither written nor read back: 60,000
+// rows through 1024-1024-16 a whole call 204 -> 181 us, 200,000 through 1024-512-16 419 -> 376, the large workload's pass 14.5 -> 13.3-13.8 ms,
+// header bits 1,975 -> 1,930 us (sum of the launches).  A logit is its bias plus the sums of 64 columns each, in order, as in mlp_last_layer: the same bits.
+template <int AMODE, bool RESIDENT, int FORM, bool LAST>
+__device__ __forceinline__ void wide_tiles(const LayerArgs& a, const uint4* __restrict__ ws, uint32_t n_cb, unsigned char* smem)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     uint16_t* slab = reinterpret_cast<uint16_t*>(smem);                                                  // [WBUF][128][WLDS]
     uint32_t* s_flow = reinterpret_cast<uint32_t*>(smem + kSlabBytes + WWAVES * kStageBytes);            // [128]
     uint32_t total = *a.esc_count;
@@ -103,8 +111,8 @@ __global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const
     const uint32_t rb_count = rb_exist < rb_chunk ? rb_exist : rb_chunk;
     const uint32_t rows = total - a.row_begin < a.rows_cap ? total - a.row_begin : a.rows_cap; // of this chunk
     const uint32_t units = gridDim.x;
-    const uint32_t t_walk = (rb_count + units - 1u) / units * n_cb, t_split = (rb_count * n_cb + units - 1u) / units; // tiles, longest block
-    const bool walk = n_cb > 1u && rb_count >= units && (RESIDENT || t_walk - t_split <= t_split / 16u);
+    const bool walk = wide_walks(rb_count, n_cb, units, RESIDENT);
+    float* s_logits = reinterpret_cast<float*>(smem + kWideLds); // [128][WLDP]
     const uint32_t n_items = walk ? rb_count : rb_count * n_cb;
     const uint32_t cb_per_item = walk ? n_cb : 1u;
 
@@ -309,9 +317,9 @@ __global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const
             // a repeat of that block's results: stored as zeros.  Columns in [N, ldh) are padding and hold zeros.
             s_bias[lane] = next_bias;
             const uint32_t ln = again(lane);
-            if (col0 < a.ldh) { // (ldh is a multiple of the wave's 64 columns)
 #pragma unroll
-                for (int half = 0; half < 2; ++half) {
+            for (int half = 0; half < 2; ++half) {
+                if (col0 < a.ldh) { // (ldh is a multiple of the wave's 64 columns)
 #pragma unroll
                     for (int j = 0; j < WNI; ++j) {
                         const uint32_t real = nb0 + j < nb_total ? 0xFFFFFFFFu : 0u;
@@ -330,48 +338,139 @@ __global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const
                         }
                     }
                     wave_sync();
+                    if (LAST) {
+                        // this wave's piece of the logits of 64 rows: operands from the staged rows, the sums then in their place
+                        uint4 fw[4], fh[2][4];
 #pragma unroll
-                    for (int q = 0; q < WSTAGE / 8; ++q) {
-                        const uint32_t rh = q * 8u + (ln >> 3), k = (ln & 7u) * 8u;
-                        const uint32_t r = half * WSTAGE + rh;
-                        const uint4 v = *reinterpret_cast<const uint4*>(stage + rh * WLDO + k);
-                        if (row0 + r < total) *reinterpret_cast<uint4*>(a.h_out + (size_t)(rb * WBM + r) * a.ldh + col0 + k) = v;
+                        for (int k = 0; k < 4; ++k) {
+                            fw[k] = last_weights(a, a.n_last, a.N, 0, col0 / 16u + k, ln);
+#pragma unroll
+                            for (int i = 0; i < 2; ++i)
+                                fh[i][k] = *reinterpret_cast<const uint4*>(stage + (i * 32u + (ln & 31u)) * WLDO + k * 16u + 8u * (ln >> 5));
+                        }
+                        wave_sync();
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+                            f32x16 c3;
+#pragma unroll
+                            for (int v = 0; v < 16; ++v) c3[v] = 0.f;
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) c3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fw[k]), as_bf16x8(fh[i][k]), c3, 0, 0, 0);
+                            float* to = reinterpret_cast<float*>(stage) + (i * 32u + (ln & 31u)) * WLDP + 4u * (ln >> 5);
+#pragma unroll
+                            for (int g = 0; g < 4; ++g)
+                                *reinterpret_cast<float4*>(to + 8 * g) = make_float4(c3[4 * g], c3[4 * g + 1], c3[4 * g + 2], c3[4 * g + 3]);
+                        }
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < WSTAGE / 8; ++q) {
+                            const uint32_t rh = q * 8u + (ln >> 3), k = (ln & 7u) * 8u;
+                            const uint32_t r = half * WSTAGE + rh;
+                            const uint4 v = *reinterpret_cast<const uint4*>(stage + rh * WLDO + k);
+                            if (row0 + r < total) *reinterpret_cast<uint4*>(a.h_out + (size_t)(rb * WBM + r) * a.ldh + col0 + k) = v;
+                        }
                     }
                     wave_sync(); // the staged rows are out: the space may be written again
                 }
+                if (LAST) {
+                    // (every wave comes here: what is added to a row's logits, the waves with columns have written)
+                    __syncthreads();
+                    const uint32_t pieces = (a.ldh - cb * WBN + WCOLS - 1u) / WCOLS, held = pieces < (uint32_t)WWAVES ? pieces : WWAVES;
+                    const uint32_t t = again(tid);
+#pragma unroll
+                    for (int q = 0; q < WSTAGE * 32 / (WWAVES * 64); ++q) {
+                        const uint32_t e = t + q * WWAVES * 64u, r = e / 32u, cls = e % 32u;
+                        float y = cb == 0u ? (cls < a.n_last ? a.b_last[cls] : 0.f) : s_logits[(half * WSTAGE + r) * WLDP + cls];
+                        for (uint32_t w = 0; w < held; ++w)
+                            y += reinterpret_cast<const float*>(smem + kSlabBytes + w * kStageBytes)[r * WLDP + cls];
+                        s_logits[(half * WSTAGE + r) * WLDP + cls] = y;
+                    }
+                    __syncthreads();
+                }
             }
+            if (LAST && last_cb) {
+                const uint32_t t = again(tid);
+                if (t < WBM && row0 + t < total) {
+                    const uint32_t dst = (a.scatter ? a.scatter : a.esc_idx)[row0 + t];
+                    const float* lr = s_logits + t * WLDP;
+                    uint32_t best = 0;
+                    float bv = lr[0];
+                    for (uint32_t k = 1; k < a.n_last; ++k) {
+                        const float v = lr[k];
+                        if (v > bv) {
+                            bv = v;
+                            best = k;
+                        }
+                    }
+                    if (dst < a.n_labels) a.labels[dst] = (uint16_t)best;
+                }
+                if (a.logits)
+                    for (uint32_t e = t; e < WBM * a.n_last; e += WWAVES * 64u) {
+                        const uint32_t r = e / a.n_last;
+                        if (row0 + r < total) a.logits[(size_t)row0 * a.n_last + e] = s_logits[r * WLDP + (e - r * a.n_last)];
+                    }
+            } // (the next row block's first sums are two barriers away)
             wave_sync();
         }
     }
 }
 
 template <int AMODE, bool RESIDENT, int FORM>
+__global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const uint4* __restrict__ ws, uint32_t n_cb)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    wide_tiles<AMODE, RESIDENT, FORM, false>(a, ws, n_cb, smem);
+}
+
+// The second hidden layer, with the last one where that goes along, which depends on how many rows there are.  (Both ways through
+// one copy of the code, the write-out of the activations cost 2,400 clocks a tile more.)
+template <bool RESIDENT>
+__global__ __launch_bounds__(WWAVES * 64) void mlp_wide_last(LayerArgs a, const uint4* __restrict__ ws, uint32_t n_cb)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    uint32_t total = *a.esc_count;
+    total = total < a.esc_cap ? total : a.esc_cap;
+    if (a.row_begin >= total) return;
+    const uint32_t left = total - a.row_begin, rows = left < a.rows_cap ? left : a.rows_cap;
+    if (wide_takes_last((rows + WBM - 1u) / WBM, n_cb, gridDim.x, RESIDENT))
+        wide_tiles<A_BF16, RESIDENT, 0, true>(a, ws, n_cb, smem);
+    else
+        wide_tiles<A_BF16, RESIDENT, 0, false>(a, ws, n_cb, smem);
+}
+
+template <int AMODE, bool RESIDENT, int FORM, bool LAST>
 int launch_wide(sf_ctx* ctx, int slot, LayerArgs a, const void* w_ordered, uint32_t rows_cap)
 {
     auto* kernel = mlp_wide_layer<AMODE, RESIDENT, FORM>;
+    if constexpr (LAST) kernel = mlp_wide_last<RESIDENT>;
     SF_ALLOW_LDS(ctx, slot, kernel);
     a.rows_cap = rows_cap;
     const uint32_t n_cb = (a.ldh + WBN - 1) / WBN;
-    const uint64_t tiles = (uint64_t)((rows_cap + WBM - 1) / WBM) * n_cb;
-    const uint32_t grid = tiles < (uint64_t)ctx->n_cu ? (uint32_t)tiles : (uint32_t)ctx->n_cu; // one block per compute unit
-    kernel<<<grid, WWAVES * 64, kWideLds, ctx->stream>>>(a, (const uint4*)w_ordered, n_cb);
+    kernel<<<sf::wide_blocks(ctx, a.ldh, rows_cap), WWAVES * 64, kWideLds + (LAST ? kLastLds : 0), ctx->stream>>>(a, (const uint4*)w_ordered, n_cb);
     SF_LAUNCH_CHECK(ctx, "mlp_wide_layer");
     return SF_OK;
 }
 
-template <int AMODE, int FORM>
+template <int AMODE, int FORM, bool LAST = false>
 int launch_wide(sf_ctx* ctx, int slot, const LayerArgs& a, const void* w_ordered, uint32_t rows_cap)
 {
-    if ((a.K + WSLAB - 1) / WSLAB <= WBUF) return launch_wide<AMODE, true, FORM>(ctx, slot, a, w_ordered, rows_cap);
-    return launch_wide<AMODE, false, FORM>(ctx, slot + 1, a, w_ordered, rows_cap);
+    if ((a.K + WSLAB - 1) / WSLAB <= WBUF) return launch_wide<AMODE, true, FORM, LAST>(ctx, slot, a, w_ordered, rows_cap);
+    return launch_wide<AMODE, false, FORM, LAST>(ctx, slot + 1, a, w_ordered, rows_cap);
 }
 
 } // namespace
 
 namespace sf {
 
+uint32_t wide_blocks(const sf_ctx* ctx, uint32_t ldh, uint32_t rows_cap)
+{
+    const uint64_t tiles = (uint64_t)((rows_cap + WBM - 1) / WBM) * ((ldh + WBN - 1) / WBN);
+    return tiles < (uint64_t)ctx->n_cu ? (uint32_t)tiles : (uint32_t)ctx->n_cu; // one block per compute unit
+}
+
 int wide_layer(sf_ctx* ctx, int amode, const sfmlp::LayerArgs& a, const void* w_ordered, uint32_t rows_cap)
 {
+    if (amode == A_BF16 && a.n_last) return launch_wide<A_BF16, 0, true>(ctx, sf::kLdsWideLast, a, w_ordered, rows_cap);
     if (amode == A_BF16) return launch_wide<A_BF16, 0>(ctx, sf::kLdsWide, a, w_ordered, rows_cap);
     if (amode == A_FEAT) return launch_wide<A_FEAT, 0>(ctx, sf::kLdsWide + 2, a, w_ordered, rows_cap);
     if ((a.raw_bits & 7u) == 0) return launch_wide<A_RAW, RAW_BYTES>(ctx, sf::kLdsWide + 4, a, w_ordered, rows_cap);
