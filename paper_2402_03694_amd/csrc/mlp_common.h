@@ -90,12 +90,19 @@ static __device__ __forceinline__ bool wide_walks(uint32_t row_blocks, uint32_t 
     const uint32_t t_walk = (row_blocks + units - 1u) / units * n_cb, t_split = (row_blocks * n_cb + units - 1u) / units; // tiles, longest block
     return n_cb > 1u && row_blocks >= units && (resident || t_walk - t_split <= t_split / 16u);
 }
-// A block that holds all columns of a row takes the last layer along.
-static __device__ __forceinline__ bool wide_takes_last(uint32_t row_blocks, uint32_t n_cb, uint32_t units, bool resident)
+constexpr uint32_t kFewTileRows = 32, kFewTileCols = 256;
+// So few rows that tiles of 32 rows x 256 columns (ldh columns in all) give a block at most one: they go that way (wide_few).
+static __host__ __device__ __forceinline__ uint64_t wide_few_tiles(uint32_t rows, uint32_t ldh)
 {
-    return n_cb == 1u || wide_walks(row_blocks, n_cb, units, resident);
+    return (uint64_t)((rows + kFewTileRows - 1u) / kFewTileRows) * ((ldh + kFewTileCols - 1u) / kFewTileCols);
 }
-constexpr uint32_t kWideCols = 512, kWideSlab = 64, kWideSlabs = 3; // columns of a tile, K values of a slab, slabs that stay
+// A block that holds all columns of a row takes the last layer along.
+static __device__ __forceinline__ bool wide_takes_last(uint32_t rows, uint32_t ldh, uint32_t units, bool resident)
+{
+    const uint32_t n_cb = (ldh + 511u) / 512u;
+    return wide_few_tiles(rows, ldh) > units && (n_cb == 1u || wide_walks((rows + BM - 1u) / BM, n_cb, units, resident));
+}
+constexpr uint32_t kWideSlab = 64, kWideSlabs = 3; // K values of a slab, slabs that stay
 
 // the packets of a flow for the raw-bit input: first packet and count, clamped into the packet arrays
 static __device__ __forceinline__ void raw_flow_range(const LayerArgs& a, uint32_t flow, uint32_t& b0, uint32_t& n)

@@ -42,7 +42,7 @@ using namespace sfmlp;
 //   - Long lists: 256 rows a block, a wave 32 of them, K walked by all waves together through shared memory in steps of two pieces,
 //     the next step requested ahead of the MFMAs.  What bounds it is HBM (200,000 rows of 2,048 values 216 us, 3.8 TB/s; straight
 //     from the cache into registers, a row's operands are 32 lines to the address path, 270).
-//   - Short ones (up to six blocks of 32 rows a unit): the waves of a block split the pieces of 32 rows, whose operands are all
+//   - Short ones (up to four blocks of 32 rows a unit, two with more than 16 pieces): the waves of a block split the pieces of 32 rows, whose operands are all
 //     requested before the first MFMA; the pieces' sums meet in shared memory.  What bounds it is the chain of latencies.
 //     500 rows of 1,024 values 11.4 -> 6.2 us, 19,600 14.
 constexpr int LROWS = 32, LWAVES = 8, LPIECE = 64;
@@ -144,10 +144,10 @@ __global__ __launch_bounds__(LWAVES * 64, 4) void mlp_last_layer(LayerArgs a, ui
     total = total < a.esc_cap ? total : a.esc_cap;
     if (a.row_begin >= total) return;
     const uint32_t left = total - a.row_begin, rows = left < a.rows_cap ? left : a.rows_cap; // of this chunk
-    if (a.units_before && wide_takes_last((rows + BM - 1u) / BM, (a.lda + kWideCols - 1u) / kWideCols, a.units_before, a.k_before <= kWideSlab * kWideSlabs))
+    if (a.units_before && wide_takes_last(rows, a.lda, a.units_before, a.k_before <= kWideSlab * kWideSlabs))
         return; // the layer before has taken this one along
     const uint32_t pieces = (a.K + LPIECE - 1u) / LPIECE, tiles = (rows + LROWS - 1u) / LROWS;
-    if (tiles > short_tiles) {
+    if (tiles * ((pieces + S::kHeld - 1u) / S::kHeld) > short_tiles) {
         for (uint32_t r0 = blockIdx.x * LTILE; r0 < rows; r0 += gridDim.x * LTILE)
             last_tile<NI>(a, r0, rows, reinterpret_cast<unsigned char*>(sums), tid, lane, wave);
         return;
@@ -665,7 +665,7 @@ int launch_last(sf_ctx* ctx, const LayerArgs& a, uint32_t rows_cap)
 {
     SF_ALLOW_LDS(ctx, sf::kLdsLast + NI - 1, mlp_last_layer<NI>);
     const uint32_t tiles = (rows_cap + LROWS - 1u) / LROWS, most = 4u * (uint32_t)ctx->n_cu; // (rows that exist are dealt out in the kernel)
-    mlp_last_layer<NI><<<tiles < most ? tiles : most, LWAVES * 64, LastShape<NI>::kLds, ctx->stream>>>(a, 6u * (uint32_t)ctx->n_cu);
+    mlp_last_layer<NI><<<tiles < most ? tiles : most, LWAVES * 64, LastShape<NI>::kLds, ctx->stream>>>(a, 4u * (uint32_t)ctx->n_cu);
     SF_LAUNCH_CHECK(ctx, "mlp_last_layer");
     return SF_OK;
 }

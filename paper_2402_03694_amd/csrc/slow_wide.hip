@@ -55,7 +55,9 @@ constexpr size_t kWideLds = kSlabBytes + WWAVES * kStageBytes + WBM * 4; // slab
 constexpr int WLDP = 36;          // row stride of the last layer's sums (floats): a wave's 64 rows of them take the place of its staged output
 static_assert(WLDP * 4 == WLDO * 2, "the sums in the staged rows' place");
 constexpr size_t kLastLds = (size_t)WBM * WLDP * 4; // a tile's logits, between column blocks
-static_assert(WBN == kWideCols && WSLAB == kWideSlab && WBUF == kWideSlabs, "as the last layer's launch assumes");
+static_assert(WBN == 512 && WSLAB == kWideSlab && WBUF == kWideSlabs, "as the last layer's launch assumes");
+constexpr int FCHUNK = 1024, FLD = FCHUNK + 8, FRING = 16; // few rows: K values in shared memory at a time, their row stride, k-steps of weights in flight
+constexpr size_t kFewLds = (size_t)2 * kFewTileRows * FLD * 2 + kFewTileRows * 4;
 
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {
@@ -415,27 +417,135 @@ __device__ __forceinline__ void wide_tiles(const LayerArgs& a, const uint4* __re
     }
 }
 
-template <int AMODE, bool RESIDENT, int FORM>
-__global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const uint4* __restrict__ ws, uint32_t n_cb)
+// Few rows: a tile of 32 rows x 256 columns a block, a wave 32 columns.  What counts is the chain of latencies and the weights' way
+// through one unit's path to the cache (half a megabyte for K = 1,024), so the weights are requested first, 16 k-steps ahead, and the
+// rows' values come to shared memory 1,024 at a time, so that waves meet once in as many k-steps.  A sum starts at its bias and runs in
+// order of K, as in the tiles: the same bits.  Tiles of 128 x 512 : these, whole call in us: one
+// row through 64-1024-1024-10 40.7 : 20.2, 500 46.8 : 24.5, 2,000 47.8 : 32.3, 500 through 96-300-900-20 46.8 : 22.9.
+template <int AMODE, int FORM>
+__device__ __forceinline__ void wide_few(const LayerArgs& a, const uint4* __restrict__ ws, uint32_t rows, uint32_t total, unsigned char* smem)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    wide_tiles<AMODE, RESIDENT, FORM, false>(a, ws, n_cb, smem);
+    uint16_t* A = reinterpret_cast<uint16_t*>(smem); // [2][32][FLD]
+    uint32_t* s_flow = reinterpret_cast<uint32_t*>(smem + (size_t)2 * kFewTileRows * FLD * 2);
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t n_cb = (a.ldh + kFewTileCols - 1u) / kFewTileCols, cb = blockIdx.x % n_cb, row0 = blockIdx.x / n_cb * kFewTileRows;
+    if (row0 >= rows) return;
+    const uint32_t nb_total = (a.N + 31u) / 32u, nb = cb * (kFewTileCols / 32u) + wave, KS = (a.K + WSLAB - 1u) / WSLAB * (WSLAB / 16u);
+    const uint4* w = ws + (size_t)(nb < nb_total ? nb : nb_total - 1u) * KS * 64u + lane;
+    uint4 fb[FRING];
+#pragma unroll
+    for (int s = 0; s < FRING; ++s) fb[s] = w[((uint32_t)s < KS ? s : KS - 1u) * 64u];
+    __builtin_amdgcn_sched_barrier(0);
+    const uint32_t r = tid >> 4, k8 = (tid & 15u) * 8u; // this thread's row and its first values of 128
+    const uint32_t left = rows - row0 - 1u, mine = r < left ? r : left; // (a row past the end: the last one again, not stored)
+    uint32_t flow = 0, raw_b0 = 0, raw_n = 0;
+    if (AMODE != A_BF16) {
+        flow = a.esc_idx[a.row_begin + row0 + mine];
+        flow = flow < a.n_rows ? flow : a.n_rows - 1u; // a bad list entry must not leave the input
+        if (AMODE == A_RAW) raw_flow_range(a, flow, raw_b0, raw_n);
+    }
+    constexpr int kMine = FCHUNK / 128; // 16-byte pieces of a thread
+    uint4 ra[kMine];
+    auto fetch = [&](uint32_t k0) {
+#pragma unroll
+        for (int u = 0; u < kMine; ++u) {
+            const uint32_t k = k0 + u * 128u + k8;
+            if (AMODE == A_RAW) {
+                const uint32_t j = k / a.raw_bits, b = k - j * a.raw_bits;
+                const uint4 words = raw_words_at<FORM>(a, raw_b0, raw_n, j, b); // (past K: packets that raw_pkts leaves out)
+                ra[u] = raw_bits_of<FORM>(a, words, b);
+            } else if (AMODE == A_FEAT) {
+                ra[u] = load_a_chunk<AMODE>(a, true, 0u, flow, k);
+            } else { // (lda is K rounded up to whole slabs and the padding holds zeros)
+                const uint32_t at = k < a.lda ? k : 0u;
+                ra[u] = *reinterpret_cast<const uint4*>(a.a_bf16 + (size_t)(row0 + mine) * a.lda + at);
+            }
+        }
+    };
+    auto store = [&](uint32_t buf) {
+#pragma unroll
+        for (int u = 0; u < kMine; ++u) *reinterpret_cast<uint4*>(A + ((size_t)buf * kFewTileRows + r) * FLD + u * 128 + k8) = ra[u];
+    };
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const uint32_t col = nb * 32u + 8u * (v >> 2) + 4u * (lane >> 5) + (v & 3);
+        acc[v] = a.bias[col < a.N ? col : a.N - 1u];
+    }
+    fetch(0);
+    store(0);
+    __syncthreads();
+    uint32_t buf = 0;
+    for (uint32_t c0 = 0; c0 < KS; c0 += FCHUNK / 16) {
+        const bool more = c0 + FCHUNK / 16 < KS;
+        if (more) fetch((c0 + FCHUNK / 16) * 16u);
+        const uint32_t end = more ? c0 + FCHUNK / 16 : KS;
+        const uint16_t* arow = A + ((size_t)buf * kFewTileRows + (lane & 31u)) * FLD + 8u * (lane >> 5);
+        for (uint32_t k0 = c0; k0 < end; k0 += FRING) { // (KS is a multiple of 4)
+#pragma unroll
+            for (int s0 = 0; s0 < FRING; s0 += 4) {
+                if (k0 + s0 < end) {
+                    uint4 fa[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) fa[q] = *reinterpret_cast<const uint4*>(arow + (k0 - c0 + s0 + q) * 16u);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fb[s0 + q]), as_bf16x8(fa[q]), acc, 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = s0; s < s0 + 4; ++s) {
+                    const uint32_t ks = k0 + s + FRING;
+                    fb[s] = w[(ks < KS ? ks : KS - 1u) * 64u];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (more) {
+            store(buf ^ 1u);
+            __syncthreads(); // the next values are in place; the buffer before is written again a chunk further on
+            buf ^= 1u;
+        }
+    }
+    // relu, bfloat16; a column block past the last real one holds zeros, as the padding does
+    const uint32_t real = nb < nb_total ? 0xFFFFFFFFu : 0u;
+    if (nb * 32u < a.ldh && (lane & 31u) <= left) {
+        uint16_t* out = a.h_out + (size_t)(row0 + (lane & 31u)) * a.ldh + nb * 32u + 4u * (lane >> 5);
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<uint2*>(out + 8 * g) = make_uint2(pack_bf16(fmaxf(acc[4 * g], 0.f), fmaxf(acc[4 * g + 1], 0.f)) & real,
+                                                                pack_bf16(fmaxf(acc[4 * g + 2], 0.f), fmaxf(acc[4 * g + 3], 0.f)) & real);
+    }
 }
 
-// The second hidden layer, with the last one where that goes along, which depends on how many rows there are.  (Both ways through
-// one copy of the code, the write-out of the activations cost 2,400 clocks a tile more.)
-template <bool RESIDENT>
-__global__ __launch_bounds__(WWAVES * 64) void mlp_wide_last(LayerArgs a, const uint4* __restrict__ ws, uint32_t n_cb)
+// The form for the rows that there are.  (A copy of the code for each: with and without the last layer through one, the write-out
+// of the activations cost 2,400 clocks a tile more.)
+template <int AMODE, bool RESIDENT, int FORM, bool LAST>
+__device__ __forceinline__ void wide_any(const LayerArgs& a, const uint4* __restrict__ ws, uint32_t n_cb, unsigned char* smem)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     uint32_t total = *a.esc_count;
     total = total < a.esc_cap ? total : a.esc_cap;
     if (a.row_begin >= total) return;
     const uint32_t left = total - a.row_begin, rows = left < a.rows_cap ? left : a.rows_cap;
-    if (wide_takes_last((rows + WBM - 1u) / WBM, n_cb, gridDim.x, RESIDENT))
-        wide_tiles<A_BF16, RESIDENT, 0, true>(a, ws, n_cb, smem);
+    if (wide_few_tiles(rows, a.ldh) <= gridDim.x)
+        wide_few<AMODE, FORM>(a, ws, rows, total, smem);
+    else if (LAST && wide_takes_last(rows, a.ldh, gridDim.x, RESIDENT))
+        wide_tiles<AMODE, RESIDENT, FORM, LAST>(a, ws, n_cb, smem);
     else
-        wide_tiles<A_BF16, RESIDENT, 0, false>(a, ws, n_cb, smem);
+        wide_tiles<AMODE, RESIDENT, FORM, false>(a, ws, n_cb, smem);
+}
+
+template <int AMODE, bool RESIDENT, int FORM>
+__global__ __launch_bounds__(WWAVES * 64) void mlp_wide_layer(LayerArgs a, const uint4* __restrict__ ws, uint32_t n_cb)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    wide_any<AMODE, RESIDENT, FORM, false>(a, ws, n_cb, smem);
+}
+
+template <bool RESIDENT>
+__global__ __launch_bounds__(WWAVES * 64) void mlp_wide_last(LayerArgs a, const uint4* __restrict__ ws, uint32_t n_cb)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    wide_any<A_BF16, RESIDENT, 0, true>(a, ws, n_cb, smem);
 }
 
 template <int AMODE, bool RESIDENT, int FORM, bool LAST>
@@ -446,7 +556,7 @@ int launch_wide(sf_ctx* ctx, int slot, LayerArgs a, const void* w_ordered, uint3
     SF_ALLOW_LDS(ctx, slot, kernel);
     a.rows_cap = rows_cap;
     const uint32_t n_cb = (a.ldh + WBN - 1) / WBN;
-    kernel<<<sf::wide_blocks(ctx, a.ldh, rows_cap), WWAVES * 64, kWideLds + (LAST ? kLastLds : 0), ctx->stream>>>(a, (const uint4*)w_ordered, n_cb);
+    kernel<<<sf::wide_blocks(ctx, a.ldh, rows_cap), WWAVES * 64, (kWideLds > kFewLds ? kWideLds : kFewLds) + (LAST ? kLastLds : 0), ctx->stream>>>(a, (const uint4*)w_ordered, n_cb);
     SF_LAUNCH_CHECK(ctx, "mlp_wide_layer");
     return SF_OK;
 }
@@ -464,7 +574,7 @@ namespace sf {
 
 uint32_t wide_blocks(const sf_ctx* ctx, uint32_t ldh, uint32_t rows_cap)
 {
-    const uint64_t tiles = (uint64_t)((rows_cap + WBM - 1) / WBM) * ((ldh + WBN - 1) / WBN);
+    const uint64_t tiles = wide_few_tiles(rows_cap, ldh);
     return tiles < (uint64_t)ctx->n_cu ? (uint32_t)tiles : (uint32_t)ctx->n_cu; // one block per compute unit
 }
 

@@ -1,4 +1,5 @@
-"""The last layer of a wide model in each of its forms: along with the second hidden layer (all columns of a row in one block),
+"""The layers of a wide model in each of their forms.  The hidden layers: 32 rows x 256 columns a block while that gives a block one
+tile (1,024 columns: 2,048 rows), 128 rows x 512 columns past it.  The last layer: along with the second hidden layer (all columns of a row in one block),
 split by pieces of K over a block's waves (short lists), 256 rows a block (long ones).  A row's logits and label are the same bits in
 all of them, with and without operand-ordered weights, and agree with binary64 on the same activations' layers."""
 import pytest
@@ -9,7 +10,8 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("dims", [(64, 1024, 1024, 16), (64, 150, 1000, 31), (40, 600, 500, 7), (64, 530, 577, 32), (33, 520, 520, 1),
-                                  (64, 600, 1100, 33), (32, 520, 96, 64)])
+                                  (64, 600, 1100, 33), (32, 520, 96, 64),
+                                  (600, 1100, 64, 5), (40, 2100, 530, 9)])
 def test_same_bits(dims):
     import torch
     import paper_2402_03694_amd as sf
@@ -30,7 +32,7 @@ def test_same_bits(dims):
         ctx = sf.ServeFlow(sf.sf_workspace_bytes(most, 0, 0, *dims[:3]))
         if ordered:
             ctx.sf_mlp_order(mlp)
-        for rows in (most, 1, 33, 5000, 49153, most - 31):   # (256 compute units: the second hidden layer takes the last one along for `most`)
+        for rows in (most, 1, 33, 1023, 2048, 2049, 5000, 32769, 49153, most - 31):   # (256 compute units: the second hidden layer takes the last one along for `most`)
             logits = torch.full((most, dims[3]), float("nan"), device=DEV)
             labels = torch.full((most,), -1, dtype=torch.int16, device=DEV)
             ctx.sf_slow_infer(mlp, idx, torch.tensor([rows], dtype=torch.int32, device=DEV), labels, feat=feat, logits=logits)
