@@ -44,6 +44,7 @@ struct LayerArgs {
     uint32_t ldh;
     float* logits;   // [esc_cap][classes] or NULL
     uint16_t* labels;
+    const uint16_t* pred; // labels = pred for all n_labels flows first, by the first hidden layer's launch; NULL = they stay
     // The second hidden layer may take the last one along (wide_takes_last): its weights [n_last][N], biases and classes (0: it may not)
     const uint16_t* w_last;
     const uint4* wo_last; // operand-ordered copy, or NULL

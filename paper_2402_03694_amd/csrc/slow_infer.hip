@@ -42,7 +42,7 @@ using namespace sfmlp;
 //   - Long lists: 256 rows a block, a wave 32 of them, K walked by all waves together through shared memory in steps of two pieces,
 //     the next step requested ahead of the MFMAs.  What bounds it is HBM (200,000 rows of 2,048 values 216 us, 3.8 TB/s; straight
 //     from the cache into registers, a row's operands are 32 lines to the address path, 270).
-//   - Short ones (up to four blocks of 32 rows a unit, two with more than 16 pieces): the waves of a block split the pieces of 32 rows, whose operands are all
+//   - Short ones (up to six blocks of 32 rows a unit, three with more than 16 pieces): the waves of a block split the pieces of 32 rows, whose operands are all
 //     requested before the first MFMA; the pieces' sums meet in shared memory.  What bounds it is the chain of latencies.
 //     500 rows of 1,024 values 11.4 -> 6.2 us, 19,600 14.
 constexpr int LROWS = 32, LWAVES = 8, LPIECE = 64;
@@ -665,7 +665,7 @@ int launch_last(sf_ctx* ctx, const LayerArgs& a, uint32_t rows_cap)
 {
     SF_ALLOW_LDS(ctx, sf::kLdsLast + NI - 1, mlp_last_layer<NI>);
     const uint32_t tiles = (rows_cap + LROWS - 1u) / LROWS, most = 4u * (uint32_t)ctx->n_cu; // (rows that exist are dealt out in the kernel)
-    mlp_last_layer<NI><<<tiles < most ? tiles : most, LWAVES * 64, LastShape<NI>::kLds, ctx->stream>>>(a, 4u * (uint32_t)ctx->n_cu);
+    mlp_last_layer<NI><<<tiles < most ? tiles : most, LWAVES * 64, LastShape<NI>::kLds, ctx->stream>>>(a, 6u * (uint32_t)ctx->n_cu);
     SF_LAUNCH_CHECK(ctx, "mlp_last_layer");
     return SF_OK;
 }
@@ -741,9 +741,9 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
     if (pred == labels) pred = nullptr;
     if (pred && !labels) return sf::fail(ctx, SF_EINVAL, "sf_slow_infer: labels is NULL");
     // labels = the fast prediction for every flow, also when nothing escalates (Section 4.4: the fast label stands unless the
-    // slow model replaces it): by the launch that writes the slow labels where it can, else by one before it
+    // slow model replaces it): by the slow model's (first) launch where it can, else by one before it
     const bool bf = mlp->dtype == SF_BF16, in_one = bf ? sf::slow_fused_ok(mlp, raw_src != nullptr) : f32_in_one(mlp, esc_cap) && n_flows <= sfsmall::kCopyRows;
-    if (pred && (!in_one || esc_cap == 0 || n_rows == 0)) {
+    if (pred && ((!bf && !in_one) || esc_cap == 0 || n_rows == 0)) {
         if (const int rc = sf::copy_labels_async(ctx, pred, labels, n_flows); rc != SF_OK) return rc;
         pred = nullptr;
     }
@@ -812,6 +812,7 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
             a.n_rows = n_rows;
             a.n_labels = n_flows;
             a.labels = labels;
+            a.pred = begin == 0 ? pred : nullptr;
             // layer 1
             a.feat = feat;
             a.feat_ld = feat_ld;
@@ -837,6 +838,7 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
                 if (rc != SF_OK) return rc;
             }
             // layer 2
+            a.pred = nullptr;
             a.a_bf16 = h1;
             a.lda = ld1;
             a.w = (const uint16_t*)mlp->w2;
