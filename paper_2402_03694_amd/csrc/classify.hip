@@ -233,7 +233,7 @@ __device__ __forceinline__ void features_by_lanes(const ClassifyArgs& c, float* 
 // gathers (forest_core.h) and about 80 us of vector arithmetic for the statistics.  With a wave to a tree behind the same
 // features (forest_wave.h; 128 flows, eight lanes a flow for the statistics): 500 -> 439 us and 367 -> 336.
 template <int FPB_, int W, int ILP, int TAIL, int KMAX, bool KEEP_ROWS>
-__global__ __launch_bounds__(FPB_ * W, W == 1 ? 2 : 8) void featurize_forest(ClassifyArgs c)
+__global__ __launch_bounds__(FPB_ * W, W == 1 ? 2 : FPB_ == 16 ? 4 : 8) void featurize_forest(ClassifyArgs c)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const FastArgs& a = c.fa;
