@@ -427,12 +427,17 @@ __device__ __forceinline__ void stage_packets(const FeatArgs& c, uint32_t flow0,
 // windows 8, 16: 37-40 -> 32.6 us; 1,048,576 of those 138 -> 133 us.  (A second tile instead of the second barrier per
 // window: 13.4 -> 12.8 us and 133 -> 141; 64 registers per lane for 16 packets, eight waves per SIMD with 20 spilled:
 // 133 -> 190.)
-template <int KMAX>
-__global__ __launch_bounds__(4 * kWave, KMAX == 8 ? 8 : KMAX == 16 ? 6 : 4) void featurize_parts(FeatArgs a)
+// LONG: windows may be deeper than KMAX = 32 (up to 64 packets); a flow that has more is worked on by a whole wave, see above, the
+// long flows of the 64 dealt out to the four waves.  One lane per flow : this, windows 8 and 64: 97 ragged flows 25.6 : 15.6 us, 65,536 36.1 :
+// 30.7; 65,536 of 64 packets 149 : 91; the rest at long_lanes_pay.
+template <int KMAX, bool LONG>
+__device__ __forceinline__ void feature_parts(const FeatArgs& a)
 {
+    static_assert(!LONG || KMAX == 32, "the whole-wave path takes over above 32 packets");
     constexpr uint32_t SS = stage_stride(kWave);
     constexpr uint32_t kStage = stage_words(KMAX, kWave), kSort = 2u * KMAX * kWave; // two of the waves sort
-    __shared__ uint32_t space[kStage > kSort ? kStage : kSort];
+    constexpr uint32_t kPark = LONG ? 4u * kSlots * kSlotWords : 0u, kMost = kStage > kSort ? kStage : kSort;
+    __shared__ uint32_t space[kMost > kPark ? kMost : kPark];
     __shared__ float tile[kWave * kRow]; // [lane][33]
     const uint32_t tid = threadIdx.x, slot = tid % kWave, flow0 = blockIdx.x * kWave;
     const uint32_t kind = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -445,6 +450,11 @@ __global__ __launch_bounds__(4 * kWave, KMAX == 8 ? 8 : KMAX == 16 ? 6 : 4) void
     const uint32_t dmask = space[2u * KMAX * SS + slot];
     const int avail = (int)space[(2u * KMAX + 1u) * SS + slot];
     __syncthreads(); // the staged packets are in registers: their space is scratch now
+    uint32_t o = 0; // where a long flow's packets start
+    if (LONG && flow0 + slot < a.n_flows) {
+        uint32_t n;
+        flow_range(a, flow0 + slot, o, n);
+    }
     uint32_t* col = space + (kind >> 1) * (KMAX * kWave) + slot; // the lane's own column
     float* row = tile + slot * kRow;
     uint32_t rows = a.n_flows - flow0;
@@ -455,7 +465,9 @@ __global__ __launch_bounds__(4 * kWave, KMAX == 8 ? 8 : KMAX == 16 ? 6 : 4) void
 #pragma unroll
         for (int j = 0; j < KMAX; ++j) asm volatile("" : "+v"(x[j]));
         const int dw = (int)a.depth[w];
-        const int m = avail < dw ? avail : dw;
+        const int m_w = avail < dw ? avail : dw;
+        const bool long_flow = LONG && m_w > KMAX && flow0 + slot < a.n_flows;
+        const int m = LONG && m_w > KMAX ? 0 : m_w; // (what the lane makes of such a flow is overwritten below)
         // the smallest network that covers every lane's window (wave-uniform choice)
         if (KMAX >= 32 && __any(m > 16))
             window_part<KMAX, KMAX>(kind, x, dmask, m, col, kWave, row, 1u);
@@ -464,6 +476,46 @@ __global__ __launch_bounds__(4 * kWave, KMAX == 8 ? 8 : KMAX == 16 ? 6 : 4) void
         else
             window_part<8, KMAX>(kind, x, dmask, m, col, kWave, row, 1u);
         __syncthreads();
+        if (LONG && __ballot(long_flow) != 0ull) { // (the same flows in all four waves)
+            // (the sort columns are free by now: the long flows' values are parked there)
+            uint32_t* park = space + kind * (kSlots * kSlotWords);
+            uint64_t todo = __ballot(long_flow), mine = 0;
+            for (uint32_t q = 0; todo; ++q) { // every fourth is this wave's
+                const uint64_t low = todo & (0ull - todo);
+                todo ^= low;
+                if ((q & 3u) == kind) mine |= low;
+            }
+            if (mine) {
+                const uint32_t lane = slot;
+                // the packets of the next long flow are requested while the current one is sorted
+                int l = __ffsll((unsigned long long)mine) - 1;
+                int m_l = (int)lane_value((uint32_t)m_w, l);
+                LanePacket cur = long_flow_load(a, lane_value(o, l), m_l, lane);
+                while (mine) {
+                    uint32_t n_slots = 0;
+                    while (mine && n_slots < kSlots) {
+                        mine &= mine - 1ull;
+                        const int l_next = mine ? __ffsll((unsigned long long)mine) - 1 : 0;
+                        const int m_next = mine ? (int)lane_value((uint32_t)m_w, l_next) : 0;
+                        uint32_t key[6];
+                        int c0, c1;
+                        long_flow_keys(cur, m_l, (uint32_t)l, lane, park + n_slots * kSlotWords, key, c0, c1);
+                        // (requested only now, behind the wait for the current flow's packets, and pinned here: the
+                        // request then flies while the current flow is sorted)
+                        __builtin_amdgcn_sched_barrier(0);
+                        const LanePacket next = long_flow_load(a, lane_value(o, l_next), m_next, lane);
+                        __builtin_amdgcn_sched_barrier(0);
+                        long_flow_order_stats(key, m_l, c0, c1, lane, tile + l * kRow);
+                        ++n_slots;
+                        cur = next;
+                        l = l_next;
+                        m_l = m_next;
+                    }
+                    long_flow_chains(park, n_slots, lane, tile);
+                }
+            }
+            __syncthreads();
+        }
         if (a.store16) {
             // eight lanes write one staged row (32 consecutive floats = one 128-byte run) as 16-byte pieces
             const uint32_t c4 = (tid & 7u) * 4u;
@@ -480,6 +532,13 @@ __global__ __launch_bounds__(4 * kWave, KMAX == 8 ? 8 : KMAX == 16 ? 6 : 4) void
         __syncthreads();
     }
 }
+
+template <int KMAX>
+__global__ __launch_bounds__(4 * kWave, KMAX == 8 ? 8 : KMAX == 16 ? 6 : 4) void featurize_parts(FeatArgs a)
+{
+    feature_parts<KMAX, false>(a);
+}
+__global__ __launch_bounds__(4 * kWave, 4) void featurize_long(FeatArgs a) { feature_parts<32, true>(a); }
 
 // Raw header bits -> one byte per bit.  A thread unpacks one header word (32 features).
 __global__ __launch_bounds__(256) void unpack_raw(uint32_t n_flows, uint32_t n_pkts, const uint32_t* __restrict__ off,
@@ -532,6 +591,12 @@ bool one_lane_pays(uint32_t dmax, uint32_t per_unit, uint32_t n_flows, uint64_t 
     return per_unit >= 1536u && (dmax <= 12 || (dmax < 16 && n_pkts <= 12ull * n_flows));
 }
 
+// The same for windows deeper than 32 packets, windows 8 and 64 unless said otherwise: lanes only where most waves have no long flow and the
+// batch is large.  Lanes : parts, ragged with a mean of 10 packets: 131,072 flows 50.0 : 54.7 us, 262,144 79.5 : 92.8, 1,000,000 239 : 349; 400,000 of 12
+// packets 56.4 : 71.2; but a mean of 17 packets 131,072 flows 82.9 : 69.3, 400,000 181 : 169, of 25 267 : 213; 400,000 of 24 packets 100.7 : 88.9;
+// 262,144 of 64 packets, window 64, 387 : 287; 300,000 of 50, windows 20 and 50, 565 : 358.
+bool long_lanes_pay(uint32_t per_unit, uint32_t n_flows, uint64_t n_pkts) { return per_unit >= 2u * 4u * kWave && n_pkts <= 16ull * n_flows; }
+
 } // namespace
 
 extern "C" int sf_featurize(sf_ctx* ctx, const sf_packets* pk, const sf_feat_cfg* cfg, float* feat,
@@ -580,8 +645,10 @@ extern "C" int sf_featurize(sf_ctx* ctx, const sf_packets* pk, const sf_feat_cfg
     const uint32_t grid = (a.n_flows + kWave - 1) / kWave;
     const uint32_t per_unit = a.n_flows / (uint32_t)ctx->n_cu;
     const bool lanes = one_lane_pays(dmax, per_unit, a.n_flows, pk->n_pkts);
-    if (dmax > 32)
+    if (dmax > 32 && long_lanes_pay(per_unit, a.n_flows, pk->n_pkts))
         featurize_wave<32, true><<<grid, kWave, 0, ctx->stream>>>(a);
+    else if (dmax > 32)
+        featurize_long<<<grid, 4 * kWave, 0, ctx->stream>>>(a);
     else if (dmax > 16 && lanes)
         featurize_wave<32, false><<<grid, kWave, 0, ctx->stream>>>(a);
     else if (dmax > 16)
