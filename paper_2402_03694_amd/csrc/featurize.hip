@@ -579,13 +579,16 @@ __global__ __launch_bounds__(256) void unpack_raw(uint32_t n_flows, uint32_t n_p
 //     way, 53 : 49);
 //     up to 12 packets, or short flows, from 1,536 flows per unit (1,048,576 ragged, windows 5, 10, 120 : 133; but
 //     180,000 25.1 : 24.3, and windows 8, 16, 1,048,576, 139 : 134).
-//   windows of 17 to 32 packets: lanes (4,194,304 x 32 packets, four windows: 1.11 ms against 1.22; ragged 1,048,576: 321
-//     us against 351).
+//   windows of 17 to 32 packets: flows of one length that fill 32 (wide loads; 4,194,304 x 32 packets, four windows: 1.11 ms against 1.22;
+//     1,000,000, windows 8, 32, 150 : 169), and short flows, up to 18 packets on average, 22 in the largest batches (1,000,000 ragged with a mean
+//     of 10, windows 8, 20, 170 : 210; of 17 191 : 222, with windows 8, 16, 24, 32 341 : 340; 2,000,000 of 20 packets 338 : 345).  The others read
+//     packet by packet past the first-level cache: 1,000,000 of 20 packets, windows 8, 20, 186 : 178, of 24, windows 8, 24, 214 : 178, of 50,
+//     windows 10, 30, 484 : 194; ragged with a mean of 25, windows 8, 32, 265 : 228; 131,072 of them 42.5 : 32.5.
 bool one_lane_pays(uint32_t dmax, uint32_t per_unit, uint32_t n_flows, uint64_t n_pkts)
 {
     if (per_unit < 2u * 4u * kWave) return false;
-    if (dmax > 16) return true;
     const uint64_t len = n_pkts / n_flows;
+    if (dmax > 16) return n_pkts <= (per_unit >= 6000u ? 22ull : 18ull) * n_flows || (dmax == 32 && n_pkts % n_flows == 0 && len % 8u == 0 && len >= 32);
     if (dmax % 8u == 0 && n_pkts % n_flows == 0 && len % 8u == 0 && len >= dmax) return true;
     if (dmax <= 8) return dmax <= 4 || (dmax <= 6 && per_unit >= 2048u);
     return per_unit >= 1536u && (dmax <= 12 || (dmax < 16 && n_pkts <= 12ull * n_flows));
