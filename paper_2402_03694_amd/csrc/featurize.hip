@@ -538,7 +538,14 @@ __global__ __launch_bounds__(4 * kWave, KMAX == 8 ? 8 : KMAX == 16 ? 6 : 4) void
 {
     feature_parts<KMAX, false>(a);
 }
-__global__ __launch_bounds__(4 * kWave, 4) void featurize_long(FeatArgs a) { feature_parts<32, true>(a); }
+// WAVES per SIMD asked of the compiler: 4 leave 128 registers, 13 spilled; 2 take 144 (three blocks a unit) and spill none, which pays while
+// the blocks are no more than that: windows 8 and 64, 97 ragged flows 15.9 -> 14.2 us, 16,384 17.4 -> 15.7, 49,152 24.7 -> 23.5, 41,000 of 40 packets
+// 73.8 -> 72.7; with four blocks a unit it is the other way, 65,536 30.1 : 31.5, 300,000 of 40 packets 358 : 389.
+template <int WAVES>
+__global__ __launch_bounds__(4 * kWave, WAVES) void featurize_long(FeatArgs a)
+{
+    feature_parts<32, true>(a);
+}
 
 // Raw header bits -> one byte per bit.  A thread unpacks one header word (32 features).
 __global__ __launch_bounds__(256) void unpack_raw(uint32_t n_flows, uint32_t n_pkts, const uint32_t* __restrict__ off,
@@ -650,8 +657,10 @@ extern "C" int sf_featurize(sf_ctx* ctx, const sf_packets* pk, const sf_feat_cfg
     const bool lanes = one_lane_pays(dmax, per_unit, a.n_flows, pk->n_pkts);
     if (dmax > 32 && long_lanes_pay(per_unit, a.n_flows, pk->n_pkts))
         featurize_wave<32, true><<<grid, kWave, 0, ctx->stream>>>(a);
+    else if (dmax > 32 && grid <= 3u * (uint32_t)ctx->n_cu)
+        featurize_long<2><<<grid, 4 * kWave, 0, ctx->stream>>>(a);
     else if (dmax > 32)
-        featurize_long<<<grid, 4 * kWave, 0, ctx->stream>>>(a);
+        featurize_long<4><<<grid, 4 * kWave, 0, ctx->stream>>>(a);
     else if (dmax > 16 && lanes)
         featurize_wave<32, false><<<grid, kWave, 0, ctx->stream>>>(a);
     else if (dmax > 16)
