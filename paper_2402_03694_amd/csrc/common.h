@@ -68,7 +68,8 @@ constexpr int kLdsLimitBytes = 160 * 1024;
 enum LdsSlot { kLdsForest = 0 /* 10 block shapes, leaf numbers wanted or not */, kLdsTreeWalk = 20, kLdsWide = 21 /* 5 operand forms, K resident or streamed */,
                kLdsFused = 31, kLdsClassify = 32 /* 5 block shapes x 2 window depths x rows kept or not */,
                kLdsRows = 52 /* input up to 64 or 128 x 5 widths */, kLdsTrees = 62 /* 5 block shapes, voting or boosted */, kLdsF32 = 72 /* without and with the gate */, kLdsFew = 74 /* input up to 64 or 128 x one or two column blocks a wave in each hidden layer,
-               without and with the gate */, kLdsLast = 90 /* up to 32 or 64 classes */, kLdsWideLast = 92 /* K resident or streamed */ };
+               without and with the gate */, kLdsLast = 90 /* up to 32 or 64 classes */, kLdsWideLast = 92 /* K resident or streamed */,
+               kLdsClassifyFew = 94 /* 3 block shapes x rows kept or not */ };
 #define SF_ALLOW_LDS(ctx, slot, func)                                                                         \
     do {                                                                                                      \
         if (!((ctx)->lds_ready[(slot) >> 6] & (1ull << ((slot) & 63)))) {                                     \
