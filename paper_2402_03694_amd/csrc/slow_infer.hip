@@ -39,29 +39,33 @@ using namespace sfmlp;
 // The last layer of a wide model: logits = A * W3^T + b3 on bfloat16 activations (at most 64 classes), then the arg-max per row
 // and the scatter of the label.  K is cut into pieces of 64, and a logit is its bias plus the pieces' sums in order, whatever form
 // makes them: mlp_wide_last (slow_wide.hip), which takes this layer along where it can, or one of the two here.
-//   - Long lists: 256 rows a block, a wave 32 of them, K walked by all waves together through shared memory in steps of two pieces,
+//   - Long lists: 256 rows a block (128 with more than 32 classes), a wave 32 of them, K walked by all waves together through shared memory in steps of two pieces,
 //     the next step requested ahead of the MFMAs.  What bounds it is HBM (200,000 rows of 2,048 values 216 us, 3.8 TB/s; straight
 //     from the cache into registers, a row's operands are 32 lines to the address path, 270).
-//   - Short ones (up to six blocks of 32 rows a unit, three with more than 16 pieces): the waves of a block split the pieces of 32 rows, whose operands are all
+//   - Short ones (up to six blocks of 32 rows a unit, three with more than 16 pieces; with more than 32 classes two, one with more than 8 pieces: 10,000 rows of 900 values,
+//     64 classes, 84.5 this way, 66.8 as a long list, whole call; 7,000 63.6 : 77): the waves of a block split the pieces of 32 rows, whose operands are all
 //     requested before the first MFMA; the pieces' sums meet in shared memory.  What bounds it is the chain of latencies.
 //     500 rows of 1,024 values 11.4 -> 6.2 us, 19,600 14.
 constexpr int LROWS = 32, LWAVES = 8, LPIECE = 64;
-constexpr int LTILE = LWAVES * 32, LSTEP = 2 * LPIECE, LLDT = LSTEP + 8; // long lists: rows of a block, K of a step, row stride in shared memory
+constexpr int LSTEP = 2 * LPIECE, LLDT = LSTEP + 8; // long lists: K of a step, row stride in shared memory
 template <int NI> // 32-class blocks
 struct LastShape {
+    static constexpr int kTile = LWAVES * 32 / NI;     // long lists: rows of a block (33 to 64 classes: half the waves only load)
     static constexpr int kLd = NI * 32 + 4;            // row stride of a piece's sums (16-byte writes of 8 rows on distinct banks)
     static constexpr int kHeld = LWAVES * (NI == 1 ? 2 : 1); // pieces whose sums are held at a time
-    static constexpr size_t kShort = (size_t)(kHeld + 1) * LROWS * kLd * 4, kLong = (size_t)(LTILE + NI * 32) * LLDT * 2;
+    static constexpr size_t kShort = (size_t)(kHeld + 1) * LROWS * kLd * 4, kLong = (size_t)(kTile + NI * 32) * LLDT * 2;
     static constexpr size_t kLds = kShort > kLong ? kShort : kLong;
 };
 
-// Rows [r0, r0 + 256) of the chunk by the whole block, K in steps of two pieces
+// Rows [r0, r0 + kTile) of the chunk by the whole block, K in steps of two pieces
 template <int NI>
 __device__ __forceinline__ void last_tile(const LayerArgs& a, uint32_t r0, uint32_t rows, unsigned char* smem, uint32_t tid, uint32_t lane, uint32_t wave)
 {
+    constexpr int LTILE = LastShape<NI>::kTile;
     constexpr int kA = LTILE * LSTEP / 8 / (LWAVES * 64), kB = NI * 32 * LSTEP / 8 / (LWAVES * 64); // 16-byte pieces of a thread per step
     uint16_t *As = reinterpret_cast<uint16_t*>(smem), *Bs = As + LTILE * LLDT;
-    const uint32_t half = lane >> 5, r = wave * 32u + (lane & 31u); // this lane's row of the tile
+    const bool idle = NI > 1 && wave * 32u >= (uint32_t)LTILE; // (uniform)
+    const uint32_t half = lane >> 5, r = (idle ? 0u : wave * 32u) + (lane & 31u); // this lane's row of the tile
     const uint32_t row = r0 + r < rows ? r0 + r : rows - 1u, dst = (a.scatter ? a.scatter : a.esc_idx)[a.row_begin + row];
     float y[NI][16]; // class 32 j + 8 * (v / 4) + 4 * half + v % 4
 #pragma unroll
@@ -94,7 +98,7 @@ __device__ __forceinline__ void last_tile(const LayerArgs& a, uint32_t r0, uint3
         __builtin_amdgcn_sched_barrier(0); // keep the requests ahead of the MFMAs
 #pragma unroll
         for (int p = 0; p < LSTEP / LPIECE; ++p) {
-            if (k0 + p * LPIECE >= a.K) continue;
+            if (idle || k0 + p * LPIECE >= a.K) continue;
 #pragma unroll
             for (int j = 0; j < NI; ++j) {
                 f32x16 c3;
@@ -111,6 +115,7 @@ __device__ __forceinline__ void last_tile(const LayerArgs& a, uint32_t r0, uint3
             }
         }
     }
+    if (idle) return; // (the next tile's first barrier stands before anything this one wrote is used)
     // class 0 first, then every class that is strictly larger than all before it (label_start, label_of)
     uint32_t best = 4u * half;
     float bv = label_start(half, y[0][0]);
@@ -148,7 +153,7 @@ __global__ __launch_bounds__(LWAVES * 64, 4) void mlp_last_layer(LayerArgs a, ui
         return; // the layer before has taken this one along
     const uint32_t pieces = (a.K + LPIECE - 1u) / LPIECE, tiles = (rows + LROWS - 1u) / LROWS;
     if (tiles * ((pieces + S::kHeld - 1u) / S::kHeld) > short_tiles) {
-        for (uint32_t r0 = blockIdx.x * LTILE; r0 < rows; r0 += gridDim.x * LTILE)
+        for (uint32_t r0 = blockIdx.x * S::kTile; r0 < rows; r0 += gridDim.x * S::kTile)
             last_tile<NI>(a, r0, rows, reinterpret_cast<unsigned char*>(sums), tid, lane, wave);
         return;
     }
@@ -665,7 +670,7 @@ int launch_last(sf_ctx* ctx, const LayerArgs& a, uint32_t rows_cap)
 {
     SF_ALLOW_LDS(ctx, sf::kLdsLast + NI - 1, mlp_last_layer<NI>);
     const uint32_t tiles = (rows_cap + LROWS - 1u) / LROWS, most = 4u * (uint32_t)ctx->n_cu; // (rows that exist are dealt out in the kernel)
-    mlp_last_layer<NI><<<tiles < most ? tiles : most, LWAVES * 64, LastShape<NI>::kLds, ctx->stream>>>(a, 6u * (uint32_t)ctx->n_cu);
+    mlp_last_layer<NI><<<tiles < most ? tiles : most, LWAVES * 64, LastShape<NI>::kLds, ctx->stream>>>(a, (NI == 1 ? 6u : 2u) * (uint32_t)ctx->n_cu);
     SF_LAUNCH_CHECK(ctx, "mlp_last_layer");
     return SF_OK;
 }
