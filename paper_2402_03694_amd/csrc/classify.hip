@@ -232,9 +232,8 @@ __device__ __forceinline__ void features_by_lanes(const ClassifyArgs& c, float* 
 // windows of 5 and 10, depth 10, no rows: 468 -> 385 us; 97 ragged flows: 51 -> 11 us.  What bounds it: the walk's
 // gathers (forest_core.h) and about 80 us of vector arithmetic for the statistics.  With a wave to a tree behind the same
 // features (forest_wave.h; 128 flows, eight lanes a flow for the statistics): 500 -> 439 us and 367 -> 336.
-// ROOMY: for batches whose blocks are all resident with more than 64 registers a lane (see launch_fused).
-template <int FPB_, int W, int ILP, int TAIL, int KMAX, bool KEEP_ROWS, bool ROOMY>
-__global__ __launch_bounds__(FPB_ * W, W == 1 ? 2 : FPB_ == 16 || (ROOMY && FPB_ * W == 1024) ? 4 : ROOMY ? 6 : 8) void featurize_forest(ClassifyArgs c)
+template <int FPB_, int W, int ILP, int TAIL, int KMAX, bool KEEP_ROWS>
+__device__ __forceinline__ void features_then_walk(const ClassifyArgs& c)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const FastArgs& a = c.fa;
@@ -252,24 +251,37 @@ __global__ __launch_bounds__(FPB_ * W, W == 1 ? 2 : FPB_ == 16 || (ROOMY && FPB_
         forest_walk<FPB_, W, ILP, TAIL, false, false, false, KEEP_ROWS>(a, xT, i, i, i < a.n_flows);
     }
 }
+template <int FPB_, int W, int ILP, int TAIL, int KMAX, bool KEEP_ROWS>
+__global__ __launch_bounds__(FPB_ * W, W == 1 ? 2 : FPB_ == 16 ? 4 : 8) void featurize_forest(ClassifyArgs c)
+{
+    features_then_walk<FPB_, W, ILP, TAIL, KMAX, KEEP_ROWS>(c);
+}
+// For batches whose blocks are all resident with more than 64 registers a lane (see launch_fused)
+template <int FPB_, int W, int ILP, int TAIL, int KMAX, bool KEEP_ROWS>
+__global__ __launch_bounds__(FPB_ * W, FPB_ * W == 1024 ? 4 : 6) void featurize_forest_few(ClassifyArgs c)
+{
+    features_then_walk<FPB_, W, ILP, TAIL, KMAX, KEEP_ROWS>(c);
+}
 
-template <int FPB, int W, int ILP, int TAIL, int KMAX, bool KEEP_ROWS, bool ROOMY = false>
+template <int FPB, int W, int ILP, int TAIL, int KMAX, bool KEEP_ROWS>
 int launch_fused(sf_ctx* ctx, const ClassifyArgs& c, size_t lds, int slot)
 {
-    const uint32_t grid = (c.fa.n_flows + FPB - 1u) / FPB;
-    // Windows up to 16 packets spill 13 to 17 of 64 registers in the feature phase, each a round trip when the blocks are few; 78 to 80 spill
-    // none and hold six waves a SIMD (one block of sixteen waves a unit, which has no more).  Before, with 64 -> with them: 16,384 ragged flows,
-    // windows 8 and 16, 100 trees of depth 10 16.5 -> 15.3 us, 40 trees 15.2 -> 13.8; 49,152, 100 trees of depth 2 17.1 -> 14.7; 60,000, 40 trees 21.5
-    // -> 18.7; 32,768 with a wave to a tree 18.8 -> 17.9.  Past the line the occupancy counts: 65,536, 300 trees of depth 4 37.0 with 64, 39.1 with 80.
-    if constexpr (KMAX == 16 && W > 1 && FPB > 16 && !ROOMY) {
-        if (grid <= (uint32_t)ctx->n_cu * (FPB * W == 1024 ? 1u : 3u))
-            return launch_fused<FPB, W, ILP, TAIL, KMAX, KEEP_ROWS, true>(ctx, c, lds, sf::kLdsClassifyFew + (KEEP_ROWS ? 3 : 0) + (ILP == 0 ? 0 : FPB == 128 ? 1 : 2));
-    }
     const size_t parts = stage_words(KMAX, FPB) > scratch_words(KMAX, FPB, W) ? stage_words(KMAX, FPB) : scratch_words(KMAX, FPB, W);
     const size_t behind = W == 1 ? (size_t)(c.depth[0] > 8u ? 16 : 8) * FPB : parts; // (one lane per flow: the first window's network)
     const size_t lds_feat = ((size_t)c.fa.n_features * FPB + behind) * 4;
     if (lds_feat > lds) lds = lds_feat;
-    auto* kernel = featurize_forest<FPB, W, ILP, TAIL, KMAX, KEEP_ROWS, ROOMY>;
+    const uint32_t grid = (c.fa.n_flows + FPB - 1u) / FPB;
+    auto* kernel = featurize_forest<FPB, W, ILP, TAIL, KMAX, KEEP_ROWS>;
+    // Windows up to 16 packets spill 13 to 17 of 64 registers in the feature phase, each a round trip when the blocks are few; 78 to 80 spill
+    // none and hold six waves a SIMD (one block of sixteen waves a unit, which has no more).  Before, with 64 -> with them: 16,384 ragged flows,
+    // windows 8 and 16, 100 trees of depth 10 16.5 -> 15.3 us, 40 trees 15.2 -> 13.8; 49,152, 100 trees of depth 2 17.1 -> 14.7; 60,000, 40 trees 21.5
+    // -> 18.7; 32,768 with a wave to a tree 18.8 -> 17.9.  Past the line the occupancy counts: 65,536, 300 trees of depth 4 37.0 with 64, 39.1 with 80.
+    if constexpr (KMAX == 16 && W > 1 && FPB > 16) {
+        if (grid <= (uint32_t)ctx->n_cu * (FPB * W == 1024 ? 1u : 3u)) {
+            kernel = featurize_forest_few<FPB, W, ILP, TAIL, KMAX, KEEP_ROWS>;
+            slot = sf::kLdsClassifyFew + (KEEP_ROWS ? 3 : 0) + (ILP == 0 ? 0 : FPB == 128 ? 1 : 2);
+        }
+    }
     SF_ALLOW_LDS(ctx, slot, kernel);
     kernel<<<grid, FPB * W, lds, ctx->stream>>>(c);
     SF_LAUNCH_CHECK(ctx, "featurize_forest");
