@@ -3,18 +3,14 @@
 Every step of the path (featurize, fast model, gate, slow model) runs in the library's HIP
 kernels; this module turns torch device tensors into the pointers and sizes of the C ABI
 declared in include/serveflow.h.  torch is used for device memory and the stream, nothing
-else.  There is no CPU fallback: if the library is missing the import fails.
+else.  There is no CPU fallback: the first call fails if the library is missing.  The import itself needs
+nothing that has to be built, since the module that builds it is imported through this package.
 """
 import ctypes
 import os
 from typing import Optional, Sequence
 
 import torch
-
-try:
-    from . import _marshal
-except ImportError as e:
-    raise ImportError("_marshal.so is missing or does not load (%s): build it with paper_2402_03694_amd.build.build()" % e) from e
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # SERVEFLOW_LIB names another build of the same library (the host-sanitized one of build.build_host_sanitized)
@@ -178,13 +174,28 @@ def load_library() -> ctypes.CDLL:
     return lib
 
 
+def load_marshal():
+    """The native form of check_ptr (csrc/marshal.cpp), which comes back to check_ptr for what does not pass."""
+    import importlib.util
+    from .build import marshal_path
+    path = marshal_path()
+    if not os.path.exists(path):
+        raise ImportError("%s is missing: build it with paper_2402_03694_amd.build.build()" % path)
+    spec = importlib.util.spec_from_file_location(__package__ + "._marshal", path)
+    native = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(native)
+    native.set_slow_path(check_ptr)
+    return native
+
+
 _lib = None
 
 
 def lib() -> ctypes.CDLL:
-    global _lib
+    global _lib, _ptr
     if _lib is None:
-        _lib = load_library()
+        loaded, native = load_library(), load_marshal()
+        _lib, _ptr = loaded, native.ptr
     return _lib
 
 
@@ -200,9 +211,7 @@ def check_ptr(t: Optional[torch.Tensor], dtype=None):
     return t.data_ptr()
 
 
-# the same in native code (csrc/marshal.cpp), which comes back to check_ptr for what does not pass
-_marshal.set_slow_path(check_ptr)
-_ptr = _marshal.ptr
+_ptr = check_ptr  # the native form once lib() has loaded it
 
 
 def sf_workspace_bytes(max_flows: int, n_trees: int = 0, tree_depth: int = 0, n_in: int = 0, n_h1: int = 0,

@@ -2,13 +2,14 @@
 import glob
 import os
 import subprocess
+import sys
 import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libserveflow_hip.so")
-MARSHAL_SRC, MARSHAL = os.path.join(CSRC, "marshal.cpp"), os.path.join(HERE, "_marshal.so")
+MARSHAL_SRC = os.path.join(CSRC, "marshal.cpp")
 
 # -ffp-contract=off: the feature statistics are defined with one rounding per operation.
 # The packed-fp32 feature is switched off for device code (hipcc's host pass does not know
@@ -27,8 +28,15 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def marshal_path() -> str:
+    """Where the tensor check for this Python and torch is, or would be: it holds for no other."""
+    import torch
+    return os.path.join(HERE, "_marshal.%s.torch-%s.so" % (sys.implementation.cache_tag, torch.__version__))
+
+
 def is_stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(MARSHAL) or os.path.getmtime(MARSHAL_SRC) > os.path.getmtime(MARSHAL):
+    marshal = marshal_path()
+    if not os.path.exists(LIB) or not os.path.exists(marshal) or os.path.getmtime(MARSHAL_SRC) > os.path.getmtime(marshal):
         return True
     t = os.path.getmtime(LIB)
     deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
@@ -39,7 +47,8 @@ def build_marshal() -> str:
     """Compile the tensor check (csrc/marshal.cpp) against the installed torch; returns its path."""
     import torch
     from torch.utils import cpp_extension
-    tmp = MARSHAL + ".tmp.%d" % os.getpid()
+    path = marshal_path()
+    tmp = path + ".tmp.%d" % os.getpid()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I" + sysconfig.get_paths()["include"],
            *["-I" + p for p in cpp_extension.include_paths()], MARSHAL_SRC, "-o", tmp,
@@ -49,8 +58,8 @@ def build_marshal() -> str:
         if os.path.exists(tmp):
             os.remove(tmp)
         raise RuntimeError("%s failed:\n%s" % (cmd[0], res.stdout))
-    os.replace(tmp, MARSHAL)
-    return MARSHAL
+    os.replace(tmp, path)
+    return path
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
