@@ -26,7 +26,8 @@
 namespace sf {
 int forest_setup(sf_ctx* ctx, const char* who, const sf_forest* f, uint32_t feat_ld, sfforest::FastArgs& a, uint32_t* result_words);
 sfforest::TileShape forest_shape(sfforest::FastArgs& a, uint32_t result_words, uint32_t n_rows, uint32_t n_cu, uint32_t dmax, size_t* lds);
-bool slow_gates(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n, const sf_mlp* mlp); // slow_infer.hip
+bool slow_gates(sf_ctx* ctx, const float* feat, uint32_t feat_ld, const sf_mlp* mlp, const sfsmall::GateRows& gate, const float* logits,
+                const uint16_t* labels); // slow_infer.hip
 int slow_infer_gated(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n, const sf_mlp* mlp, const sfsmall::GateRows& gate, const uint16_t* pred,
                      float* logits, uint16_t* labels);
 }
@@ -424,8 +425,8 @@ extern "C" int sf_classify(sf_ctx* ctx, const sf_packets* pk, const sf_feat_cfg*
     int rc = run_features_and_forest(ctx, "sf_classify", pk, cfg, forest, host_vmin, n_vmin, !raw, feat, feat_ld, pred, top_votes,
                                      labels, &labels_done);
     if (rc != SF_OK) return rc;
-    if (!raw && sf::slow_gates(ctx, feat, feat_ld, n, mlp)) {
-        sfsmall::GateRows gate = {top_votes, pred, n, n_vmin, esc_idx, esc_count, {}};
+    sfsmall::GateRows gate = {top_votes, pred, n, n_vmin, esc_idx, esc_count, {}};
+    if (!raw && sf::slow_gates(ctx, feat, feat_ld, mlp, gate, logits, labels)) {
         for (uint32_t c = 0; c < SF_MAX_CLASSES; ++c) gate.vmin[c] = host_vmin[c < n_vmin ? c : n_vmin - 1u];
         return sf::slow_infer_gated(ctx, feat, feat_ld, n, mlp, gate, labels_done ? nullptr : pred, logits, labels);
     }

@@ -748,7 +748,8 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
     // labels = the fast prediction for every flow, also when nothing escalates (Section 4.4: the fast label stands unless the
     // slow model replaces it): by the slow model's (first) launch where it can, else by one before it
     const bool bf = mlp->dtype == SF_BF16, in_one = bf ? sf::slow_fused_ok(mlp, raw_src != nullptr) : f32_in_one(mlp, esc_cap) && n_flows <= sfsmall::kCopyRows;
-    if (pred && ((!bf && !in_one) || esc_cap == 0 || n_rows == 0)) {
+    const bool reused = sfsmall::share(pred, (uint64_t)n_flows * 2u, logits, (uint64_t)esc_cap * mlp->n_classes * 4u);
+    if (pred && ((!bf && !in_one) || reused || esc_cap == 0 || n_rows == 0)) {
         if (const int rc = sf::copy_labels_async(ctx, pred, labels, n_flows); rc != SF_OK) return rc;
         pred = nullptr;
     }
@@ -959,11 +960,18 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
 namespace sf {
 
 // Whether the slow model's launch can make the list too, on a feature matrix of n rows: small batches, a model that goes through one
-// launch, and nothing that the gate or the slow model would refuse (their own calls then say what).  One launch less: the whole call
-// on 97 flows with a 64-512-512-10 model 27.1 -> 25.9 us, on 4,096 with a binary32 one 23.4 -> 21.4.
-bool slow_gates(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n, const sf_mlp* mlp)
+// launch, and nothing that the gate or the slow model would refuse (their own calls then say what).  Every block reads what the gate
+// looks at for all flows while others write labels and logits, so those are arrays of their own (labels may be pred if the gate does
+// not look at it).  One launch less: the whole call on 97 flows with a 64-512-512-10 model 27.1 -> 25.9 us, on 4,096 with a binary32
+// one 23.4 -> 21.4.
+bool slow_gates(sf_ctx* ctx, const float* feat, uint32_t feat_ld, const sf_mlp* mlp, const sfsmall::GateRows& gate, const float* logits,
+                const uint16_t* labels)
 {
+    const uint32_t n = gate.n;
     if (n == 0 || n > sfsmall::kGateRows || !feat || check_model(ctx, mlp) != SF_OK || mlp->n_in > feat_ld) return false;
+    const uint64_t flows = (uint64_t)n * 2u, rows = (uint64_t)n * mlp->n_classes * 4u;
+    for (const uint16_t* read : {gate.top, gate.n_vmin > 1u ? gate.pred : gate.top})
+        if (sfsmall::share(read, flows, labels, flows) || sfsmall::share(read, flows, logits, rows)) return false;
     if (Carve ws(ctx); !ws.take(route_scratch_bytes(n))) return false;
     Carve ws(ctx);
     if (mlp->dtype == SF_F32) return f32_in_one(mlp, n) && rows_in(ws, row_bytes_of(mlp)) >= kSlowMinRows;

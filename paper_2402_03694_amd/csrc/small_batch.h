@@ -23,6 +23,14 @@ struct GateRows {
 };
 struct NoGate {};
 
+// Whether two arrays share memory.  What these kernels do in one launch the separate calls do one after the other, so an array that
+// one of the steps reads and another writes is not for them.
+inline bool share(const void* a, uint64_t a_bytes, const void* b, uint64_t b_bytes)
+{
+    const uint64_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return a && b && (x < y ? y - x < a_bytes : x - y < b_bytes);
+}
+
 constexpr uint32_t kGateLds = 64 + SF_MAX_CLASSES * 2; // bytes of shared memory
 
 // The gate for all rows by a block of T threads (up to 32 rows a thread, in order): the number of rows that escalate, and with

@@ -60,6 +60,75 @@ def test_gate(f32, per_class, shift):
             assert torch.equal(a, b), n
 
 
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("alias,depths", [("labels are pred", [8]), ("labels are pred", [8, 20]), ("labels are top", [8, 20]), ("logits over top", [8])])
+def test_gate_on_shared_arrays(f32, alias, depths):
+    """What the gate reads (the votes, with per-class thresholds the predictions too) may be the array a later step writes, as in the
+    four calls, on both sides of the line of the gate's own launch."""
+    import torch
+    import paper_2402_03694_amd as sf
+    t, d, c, f = 40, 6, 5, 32 * len(depths)
+    for n in (97, 4096, 16384, 16385):
+        g = torch.Generator(device=DEV)
+        g.manual_seed(n)
+        m = n * 8
+        pk = sf.DevicePackets(torch.arange(0, m + 1, 8, dtype=torch.int32, device=DEV), torch.randint(40, 1500, (m,), device=DEV, generator=g).to(torch.int16),
+                              torch.rand(m, device=DEV, generator=g), (torch.rand(m, device=DEV, generator=g) < 0.5).to(torch.uint8))
+        forest = sf.DeviceForest(t, d, c, f, torch.randint(0, f, (t, 2 ** d - 1), device=DEV, generator=g).to(torch.int16),
+                                 torch.rand((t, 2 ** d - 1), device=DEV, generator=g) * 500,
+                                 torch.randint(0, c, (t, 2 ** d), device=DEV, generator=g).to(torch.uint8))
+        mlp = _model((f, 100, 60, c), f32, n)
+        ctx = sf.ServeFlow(sf.sf_workspace_bytes(n, t, d, f, 100, 60))
+        vmin = [12, 14, 0, 13, 15]
+        out = []
+        for whole in (True, False):
+            feat, logits = torch.zeros((n, f), device=DEV), torch.full((n, c), -7.0, device=DEV)
+            pred, top, labels = (torch.full((n,), -1, dtype=torch.int16, device=DEV) for _ in range(3))
+            idx, count = torch.full((n,), -1, dtype=torch.int32, device=DEV), torch.full((1,), -1, dtype=torch.int32, device=DEV)
+            if alias == "labels are pred":
+                labels = pred
+            elif alias == "labels are top":
+                labels = top
+            else:
+                top = logits.view(torch.int16).flatten()[:n]
+            if whole:
+                ctx.sf_classify(pk, depths, forest, vmin, mlp, feat, pred, top, idx, count, labels, logits=logits)
+            else:
+                ctx.sf_featurize(pk, depths, feat)
+                ctx.sf_fast_infer(feat, forest, pred, top)
+                ctx.sf_route(top, pred, vmin, idx, count)
+                ctx.sf_slow_infer(mlp, idx, count, labels, feat=feat, logits=logits, pred=pred)
+            out.append((pred, labels, idx, count, logits))
+        assert 0 < int(count) < n
+        for a, b in zip(*out):
+            assert torch.equal(a.view(torch.int32) if a.dtype == torch.float32 else a, b.view(torch.int32) if b.dtype == torch.float32 else b), n
+
+
+@pytest.mark.parametrize("f32,dims", [(False, (16, 40, 50, 6)), (True, (16, 40, 50, 6))])
+def test_copied_labels_under_the_logits(f32, dims):
+    """Predictions in the memory that the logits take are copied before it is written."""
+    import torch
+    import paper_2402_03694_amd as sf
+    n = 40000
+    mlp = _model(dims, f32, n)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    feat = torch.randn((n, 16), device=DEV, generator=g)
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(n, 0, 0, *dims[:3]))
+    fast = torch.randint(0, 6, (n,), device=DEV, generator=g).to(torch.int16)
+    idx = torch.arange(0, n, 2, dtype=torch.int32, device=DEV)
+    count = torch.tensor([len(idx)], dtype=torch.int32, device=DEV)
+    out = []
+    for shared in (False, True):
+        logits, labels = torch.zeros((n, 6), device=DEV), torch.full((n,), -1, dtype=torch.int16, device=DEV)
+        pred = logits.view(torch.int16).flatten()[:n] if shared else torch.empty(n, dtype=torch.int16, device=DEV)
+        pred.copy_(fast)
+        ctx.sf_slow_infer(mlp, idx, count, labels, feat=feat, logits=logits, pred=pred)
+        out.append((labels, logits[:len(idx)]))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert torch.equal(out[0][0][1::2], fast[1::2])
+
+
 @pytest.mark.parametrize("f32,dims", [(False, (16, 40, 50, 6)), (True, (16, 40, 50, 6)), (False, (16, 600, 40, 6))])
 @pytest.mark.parametrize("n", [1, 2047, 2049, 9001, 65536, 65537])
 def test_copied_labels(f32, dims, n):
