@@ -175,7 +175,7 @@ def load_library() -> ctypes.CDLL:
 
 
 def load_marshal():
-    """The native form of check_ptr (csrc/marshal.cpp), which comes back to check_ptr for what does not pass."""
+    """The native forms of check_ptr and check_need (csrc/marshal.cpp), which come back to check_ptr for what does not pass."""
     import importlib.util
     from .build import marshal_path
     path = marshal_path()
@@ -192,10 +192,10 @@ _lib = None
 
 
 def lib() -> ctypes.CDLL:
-    global _lib, _ptr
+    global _lib, _ptr, _need
     if _lib is None:
         loaded, native = load_library(), load_marshal()
-        _lib, _ptr = loaded, native.ptr
+        _lib, _ptr, _need = loaded, native.ptr, native.need
     return _lib
 
 
@@ -211,7 +211,14 @@ def check_ptr(t: Optional[torch.Tensor], dtype=None):
     return t.data_ptr()
 
 
-_ptr = check_ptr  # the native form once lib() has loaded it
+def check_need(t: torch.Tensor, dtype=None):
+    """check_ptr for a tensor that may not be missing (as a null pointer not every call would notice it)."""
+    if t is None:
+        raise TypeError("expected a tensor, got None")
+    return check_ptr(t, dtype)
+
+
+_ptr, _need = check_ptr, check_need  # the native forms once lib() has loaded them
 
 
 def sf_workspace_bytes(max_flows: int, n_trees: int = 0, tree_depth: int = 0, n_in: int = 0, n_h1: int = 0,
@@ -284,13 +291,13 @@ class DevicePackets:
 
     def c_struct(self) -> SfPackets:
         # uint16/uint32 tensors are carried as int16/int32 storage of the same bits
-        off = _ptr(self.flow_off, torch.int32)
+        off = _need(self.flow_off, torch.int32)
         size = iat = way = None
         if self.n_pkts:
-            size, iat, way = _ptr(self.pkt_size, torch.int16), _ptr(self.pkt_iat, torch.float32), _ptr(self.pkt_dir, torch.uint8)
+            size, iat, way = _need(self.pkt_size, torch.int16), _need(self.pkt_iat, torch.float32), _need(self.pkt_dir, torch.uint8)
         if self.pkt_hdr is None:
             return SfPackets(self.n_flows, self.n_pkts, off, size, iat, way)
-        return SfPackets(self.n_flows, self.n_pkts, off, size, iat, way, _ptr(self.pkt_hdr, torch.int32), int(self.pkt_hdr.shape[1]))
+        return SfPackets(self.n_flows, self.n_pkts, off, size, iat, way, _need(self.pkt_hdr, torch.int32), int(self.pkt_hdr.shape[1]))
 
 
 class DeviceForest:
@@ -300,8 +307,8 @@ class DeviceForest:
         self.packed = None   # set by ServeFlow.sf_forest_pack
 
     def c_struct(self) -> SfForest:
-        return SfForest(self.n_trees, self.depth, self.n_classes, self.n_features, _ptr(self.node_feat, torch.int16),
-                        _ptr(self.node_thr, torch.float32), _ptr(self.leaf_label, torch.uint8),
+        return SfForest(self.n_trees, self.depth, self.n_classes, self.n_features, _need(self.node_feat, torch.int16),
+                        _need(self.node_thr, torch.float32), _need(self.leaf_label, torch.uint8),
                         self.packed.data_ptr() if self.packed is not None else None)
 
 
@@ -311,8 +318,8 @@ class DeviceTree:
         self.node_feat, self.node_thr, self.leaf_count = node_feat, node_thr, leaf_count
 
     def c_struct(self) -> SfTree:
-        return SfTree(self.depth, self.n_classes, self.n_features, _ptr(self.node_feat, torch.int16),
-                      _ptr(self.node_thr, torch.float32), _ptr(self.leaf_count, torch.int16))
+        return SfTree(self.depth, self.n_classes, self.n_features, _need(self.node_feat, torch.int16),
+                      _need(self.node_thr, torch.float32), _need(self.leaf_count, torch.int16))
 
 
 class DeviceGbdt:
@@ -322,8 +329,8 @@ class DeviceGbdt:
         self.packed = None   # set by ServeFlow.sf_gbdt_pack
 
     def c_struct(self) -> SfGbdt:
-        return SfGbdt(self.n_trees, self.depth, self.n_classes, self.n_features, _ptr(self.node_feat, torch.int16),
-                      _ptr(self.node_thr, torch.float32), _ptr(self.leaf_value, torch.float32), _ptr(self.base, torch.float32),
+        return SfGbdt(self.n_trees, self.depth, self.n_classes, self.n_features, _need(self.node_feat, torch.int16),
+                      _need(self.node_thr, torch.float32), _need(self.leaf_value, torch.float32), _ptr(self.base, torch.float32),
                       self.packed.data_ptr() if self.packed is not None else None)
 
 
@@ -341,7 +348,7 @@ class DeviceMlp:
         f32 = torch.float32
         wd = f32 if self.dtype == SF_F32 else torch.bfloat16
         return SfMlp(n_in, n_h1, n_h2, n_classes, self.dtype, _ptr(self.mu, f32), _ptr(self.inv_sigma, f32), self.clamp,
-                     _ptr(self.w1, wd), _ptr(self.w2, wd), _ptr(self.w3, wd), _ptr(self.b1, f32), _ptr(self.b2, f32), _ptr(self.b3, f32),
+                     _need(self.w1, wd), _need(self.w2, wd), _need(self.w3, wd), _need(self.b1, f32), _need(self.b2, f32), _need(self.b3, f32),
                      self.ordered.data_ptr() if self.ordered is not None else None)
 
 

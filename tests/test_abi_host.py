@@ -112,3 +112,19 @@ def test_product_package_never_touches_the_oracle():
         if f.endswith((".py", ".c")):
             text = open(os.path.join(ROOT, "oracle", f)).read()
             assert "paper_2402_03694_amd" not in text and "serveflow.h" not in text, f
+
+
+def test_structs_refuse_missing_tensors(lib):
+    """A tensor that a struct has to have is asked for before any call, by the Python check and by the native one."""
+    from paper_2402_03694_amd import binding as b
+    made = [b.DeviceForest(1, 1, 2, 4, None, None, None), b.DeviceTree(1, 2, 4, None, None, None),
+            b.DeviceGbdt(2, 1, 2, 4, None, None, None, None), b.DeviceMlp((4, 4, 4, 2), b.SF_F32, *[None] * 6)]
+    kept = b._ptr, b._need
+    native = b.load_marshal()
+    try:
+        for b._ptr, b._need in ((b.check_ptr, b.check_need), (native.ptr, native.need)):
+            for s in made:
+                with pytest.raises(TypeError, match="got None"):
+                    s.c_struct()
+    finally:
+        b._ptr, b._need = kept
