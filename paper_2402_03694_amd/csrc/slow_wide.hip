@@ -470,7 +470,8 @@ __device__ __forceinline__ void wide_few(const LayerArgs& a, const uint4* __rest
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const uint32_t col = nb * 32u + 8u * (v >> 2) + 4u * (lane >> 5) + (v & 3);
-        acc[v] = a.bias[col < a.N ? col : a.N - 1u];
+        const float b = a.bias[col < a.N ? col : a.N - 1u];
+        acc[v] = col < a.N ? b : 0.f; // (padding holds zeros: an infinite value there would not vanish behind a zero weight)
     }
     fetch(0);
     store(0);
