@@ -41,6 +41,11 @@ using namespace sftiles;
 
 constexpr int kWaves = 8; // waves per block
 constexpr uint32_t kRowsLine = 128; // rows a compute unit from which the register form may take a list
+// Flows a compute unit whose labels the launch copies.  The blocks that copy read the whole list and, where it fills the units, the last
+// tiles wait for them.  Copy in a launch of its own : in this one, us: 5,076 rows of 20,305 flows 11.0 : 8.1, 24,211 of 24,211 16.4 : 16.7,
+// 14,317 of 20,454 15.8 : 16.1, the longest loss up to the line 16,045 of 22,922 11.5 : 11.9; past it 28,466 of 31,629 14.7 : 16.6, 45,116 of
+// 45,116 22.4 : 24.7 (and short lists would gain, 7,640 of 30,560 13.6 : 9.4; how long a list is only the device knows).
+constexpr uint32_t kCopyUnit = 96;
 constexpr int kNI = 2;    // 32-column blocks per wave
 
 // W[N][K] (row-major, bfloat16 bits) -> out[(nb * KS + ks) * 64 + lane] = the 8 values
@@ -324,7 +329,7 @@ int slow_fused(sf_ctx* ctx, void* ws, bool ws_is_ordered, const float* feat, uin
     if (grid > rb_cap) grid = rb_cap;
     if (grid == 0) grid = 1;
     if (gate) return launch_few(ctx, a, *gate, grid);
-    if (pred && n_labels <= sfsmall::kCopyRows) {
+    if (pred && n_labels <= sfsmall::kCopyRows && n_labels <= kCopyUnit * (uint32_t)ctx->n_cu) {
         a.n_copy = (n_labels + sfsmall::kCopySlice - 1u) / sfsmall::kCopySlice;
         grid += a.n_copy;
     } else if (pred) {

@@ -9,7 +9,7 @@
 namespace sfsmall {
 
 constexpr uint32_t kGateRows = 16384;   // rows the gate takes this way: a block evaluates it for all of them
-constexpr uint32_t kCopyRows = 65536;   // flows whose labels are copied this way: a copying block reads the whole list
+constexpr uint32_t kCopyRows = 65536;   // flows whose labels are copied this way at most: a copying block reads the whole list
 constexpr uint32_t kCopySlice = 2048;   // flows of a copying block
 
 // sf_route's gate: the list and its length are written for the caller as by that call
@@ -104,13 +104,25 @@ __device__ __forceinline__ void copy_unlisted(const uint16_t* __restrict__ pred,
     const uint32_t tid = threadIdx.x;
     if (tid < kCopySlice / 32u) bits[tid] = 0;
     __syncthreads();
-#pragma unroll 8
-    for (uint32_t e = tid; e < total; e += T) {
-        uint32_t f = list[e];
+    const auto mark = [&](uint32_t f) {
         if (CLAMP) f = f < n ? f : n - 1u;
         f -= lo;
         if (f < kCopySlice) atomicOr(bits + f / 32u, 1u << (f & 31u));
+    };
+    // (the list's whole 16-byte pieces, four of a thread at a time: tiles wait behind the blocks that copy.  25,848 of 28,720 flows, entry
+    // by entry : this 26.5 : 22.1 us)
+    const uint32_t pieces = (reinterpret_cast<uintptr_t>(list) & 15u) == 0 ? total / 4u : 0u;
+    for (uint32_t e = tid; e < pieces; e += 4u * T) {
+        uint4 v[4];
+#pragma unroll
+        for (uint32_t q = 0; q < 4u; ++q) {
+            const uint32_t at = e + q * T;
+            v[q] = reinterpret_cast<const uint4*>(list)[at < pieces ? at : e];
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < 4u; ++q) mark(v[q].x), mark(v[q].y), mark(v[q].z), mark(v[q].w);
     }
+    for (uint32_t e = 4u * pieces + tid; e < total; e += T) mark(list[e]);
     __syncthreads();
     for (uint32_t f = tid; f < kCopySlice && lo + f < n; f += T)
         if (!(bits[f / 32u] >> (f & 31u) & 1u)) labels[lo + f] = pred[lo + f];

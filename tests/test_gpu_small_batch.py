@@ -1,6 +1,7 @@
 """Small batches whose gate and label copy go with the slow model's launch, at the edges of what that launch takes (16,384 rows for
-the gate, 65,536 for the copy, slices of 2,048; a wide model's first layer copies any number): sf_classify against the four separate calls, and sf_slow_infer's labels against
-what the header says, for lists in any order with entries outside the batch."""
+the gate; 65,536 for the copy, with a bfloat16 model 96 a compute unit; slices of 2,048; a wide model's first layer copies any number):
+sf_classify against the four separate calls, and sf_slow_infer's labels against what the header says, for lists in any order with
+entries outside the batch."""
 import numpy as np
 import pytest
 
@@ -130,7 +131,7 @@ def test_copied_labels_under_the_logits(f32, dims):
 
 
 @pytest.mark.parametrize("f32,dims", [(False, (16, 40, 50, 6)), (True, (16, 40, 50, 6)), (False, (16, 600, 40, 6))])
-@pytest.mark.parametrize("n", [1, 2047, 2049, 9001, 65536, 65537])
+@pytest.mark.parametrize("n", [1, 2047, 2049, 9001, 24576, 24577, 65536, 65537])
 def test_copied_labels(f32, dims, n):
     import torch
     import paper_2402_03694_amd as sf
@@ -143,16 +144,16 @@ def test_copied_labels(f32, dims, n):
     every = torch.arange(n, dtype=torch.int32, device=DEV)
     slow = torch.full((n,), -1, dtype=torch.int16, device=DEV)
     ctx.sf_slow_infer(mlp, every, torch.tensor([n], dtype=torch.int32, device=DEV), slow, feat=feat)
-    for rows in (0, 1, n // 3):
+    for rows, shift in ((0, 0), (1, 1), (n // 3, 0), (n // 3, 1)):   # (the list on the 16-byte grid and off it)
         list_ = rng.permutation(n)[:rows].astype(np.int64)
         if rows > 4:
             list_[2], list_[3] = n + 5, 2 ** 31 - 1  # outside the batch: the row read is the last one's
             list_ = list_[list_ != n - 1]
-        idx = np.full(n, 7, np.int32)
-        idx[:len(list_)] = list_
+        idx = np.full(n + shift, 7, np.int32)
+        idx[shift:shift + len(list_)] = list_
         count = torch.tensor([len(list_)], dtype=torch.int32, device=DEV)
         labels = torch.full((n,), -1, dtype=torch.int16, device=DEV)
-        ctx.sf_slow_infer(mlp, torch.from_numpy(idx).to(DEV), count, labels, feat=feat, pred=pred)
+        ctx.sf_slow_infer(mlp, torch.from_numpy(idx).to(DEV)[shift:], count, labels, feat=feat, pred=pred)
         want, got, s = pred.cpu().numpy().copy(), labels.cpu().numpy(), slow.cpu().numpy()
         inside = list_[list_ < n]
         want[inside] = s[inside]
