@@ -968,7 +968,8 @@ bool slow_gates(sf_ctx* ctx, const float* feat, uint32_t feat_ld, const sf_mlp* 
                 const uint16_t* labels)
 {
     const uint32_t n = gate.n;
-    if (n == 0 || n > sfsmall::kGateRows || !feat || check_model(ctx, mlp) != SF_OK || mlp->n_in > feat_ld) return false;
+    if (n == 0 || !feat || check_model(ctx, mlp) != SF_OK || mlp->n_in > feat_ld) return false;
+    if (n > (mlp->dtype == SF_F32 ? sfsmall::kGateRowsF32 : sfsmall::kGateRows)) return false;
     const uint64_t flows = (uint64_t)n * 2u, rows = (uint64_t)n * mlp->n_classes * 4u;
     for (const uint16_t* read : {gate.top, gate.n_vmin > 1u ? gate.pred : gate.top})
         if (sfsmall::share(read, flows, labels, flows) || sfsmall::share(read, flows, logits, rows)) return false;

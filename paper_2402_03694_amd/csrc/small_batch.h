@@ -8,7 +8,11 @@
 
 namespace sfsmall {
 
-constexpr uint32_t kGateRows = 16384;   // rows the gate takes this way: a block evaluates it for all of them
+// Rows the gate takes this way: a block evaluates it for all of them, eight to a thread at a time.  Whole pass, the gate as a launch : in
+// this one, us.  bfloat16, 64-200-300-10: 200 rows 18.9 : 17.5, 8,000 25.1 : 23.7, 12,000 25.3 : 24.7, 16,384 25.9 : 25.8; 32-128-64-6
+// 15.1 : 13.6, 21.2 : 19.2, 23.5 : 23.3, 24.4 : 25.4.  binary32, whose blocks are more than are resident from 2,048 rows on,
+// 32-128-128-4: 4,096 rows 22.8 : 21.4, 5,000 27.0 : 29.3, 16,384 46.4 : 58.1; 32-64-48-10: 16.5 : 15.8, 17.3 : 20.5, 21.5 : 30.5.
+constexpr uint32_t kGateRows = 12288, kGateRowsF32 = 4096;
 constexpr uint32_t kCopyRows = 65536;   // flows whose labels are copied this way at most: a copying block reads the whole list
 constexpr uint32_t kCopySlice = 2048;   // flows of a copying block
 

@@ -1,7 +1,7 @@
-"""Small batches whose gate and label copy go with the slow model's launch, at the edges of what that launch takes (16,384 rows for
-the gate; 65,536 for the copy, with a bfloat16 model 96 a compute unit; slices of 2,048; a wide model's first layer copies any number):
-sf_classify against the four separate calls, and sf_slow_infer's labels against what the header says, for lists in any order with
-entries outside the batch."""
+"""Small batches whose gate and label copy go with the slow model's launch, at the edges of what that launch takes (the gate: 4,096 rows
+with a binary32 model, 12,288 with a bfloat16 one; the copy: 65,536, with a bfloat16 model 96 a compute unit; slices of 2,048; a wide
+model's first layer copies any number): sf_classify against the four separate calls, and sf_slow_infer's labels against what the header
+says, for lists in any order with entries outside the batch."""
 import numpy as np
 import pytest
 
@@ -28,7 +28,7 @@ def test_gate(f32, per_class, shift):
     import torch
     import paper_2402_03694_amd as sf
     t, d, c, f = 40, 6, 5, 32
-    for n in (1, 7, 31, 97, 511, 4096, 4097, 12289, 16384, 16385):
+    for n in (1, 7, 31, 97, 511, 4096, 4097, 12288, 12289, 16384, 16385):
         g = torch.Generator(device=DEV)
         g.manual_seed(n)
         m = n * 8
@@ -69,7 +69,7 @@ def test_gate_on_shared_arrays(f32, alias, depths):
     import torch
     import paper_2402_03694_amd as sf
     t, d, c, f = 40, 6, 5, 32 * len(depths)
-    for n in (97, 4096, 16384, 16385):
+    for n in (97, 4096, 4097, 12288, 12289):
         g = torch.Generator(device=DEV)
         g.manual_seed(n)
         m = n * 8
