@@ -42,10 +42,12 @@ using namespace sfmlp;
 //   - Long lists: 256 rows a block (128 with more than 32 classes), a wave 32 of them, K walked by all waves together through shared memory in steps of two pieces,
 //     the next step requested ahead of the MFMAs.  What bounds it is HBM (200,000 rows of 2,048 values 216 us, 3.8 TB/s; straight
 //     from the cache into registers, a row's operands are 32 lines to the address path, 270).
-//   - Short ones (up to six blocks of 32 rows a unit, three with more than 16 pieces; with more than 32 classes two, one with more than 8 pieces: 10,000 rows of 900 values,
-//     64 classes, 84.5 this way, 66.8 as a long list, whole call; 7,000 63.6 : 77): the waves of a block split the pieces of 32 rows, whose operands are all
-//     requested before the first MFMA; the pieces' sums meet in shared memory.  What bounds it is the chain of latencies.
-//     500 rows of 1,024 values 11.4 -> 6.2 us, 19,600 14.
+//   - Short ones: the waves of a block split the pieces of 32 rows, whose operands are all requested before the first MFMA; the
+//     pieces' sums meet in shared memory.  What bounds it is the chain of latencies: 500 rows of 1,024 values 11.4 -> 6.2 us, 19,600 14.
+//     Lists of up to four such blocks a unit go this way, two and a half where the weights lie in rows (a block then gathers them line by
+//     line), one with more than 32 classes; a block counts once for every 16 pieces (8 with more than 32 classes).  Short : long, whole call in
+//     us: 22,611 rows through 64-64-1536-10 41.5 : 48.2, rows of weights 13,663 through 32-256-1792-10 48.4 : 55.5; 34,672 through 128-448-576-10,
+//     4.2 blocks, 82.8 : 76.5, rows of weights 22,378 through 96-176-1042-16, 5.5, 76.7 : 66.1; 49 classes, 8,730 rows of 63 values, 46.8 : 37.7.
 constexpr int LROWS = 32, LWAVES = 8, LPIECE = 64;
 constexpr int LSTEP = 2 * LPIECE, LLDT = LSTEP + 8; // long lists: K of a step, row stride in shared memory
 template <int NI> // 32-class blocks
@@ -57,16 +59,28 @@ struct LastShape {
     static constexpr size_t kLds = kShort > kLong ? kShort : kLong;
 };
 
-// Rows [r0, r0 + kTile) of the chunk by the whole block, K in steps of two pieces
+// The hidden layer before writes 128 rows a block, and blocks go to the eight dies in turn, each with a cache of its own.  A row is read
+// on the die that wrote it: read on another, the next call's write of the same memory has that copy taken away first, and it is that
+// launch which takes longer (13,544 rows through 64-576-6: 9.2 us, behind 32-row blocks in plain order 12.7).
+constexpr uint32_t kDies = 8;
+// first row of the 32 that block i of a short list takes; 32 blocks stand for eight row blocks of the layer before
+__device__ __forceinline__ uint32_t short_rows(uint32_t i) { return (i / (kDies * 4u) * (kDies * 4u) + i % kDies * 4u + i / kDies % 4u) * LROWS; }
+// first row of tile i of a long list: 128 rows from there on and, with tiles of 256, the 128 of the row block eight further on
+template <int NI>
+__device__ __forceinline__ uint32_t long_rows(uint32_t i) { return (NI == 1 ? i / kDies * (kDies * 2u) + i % kDies : i) * BM; }
+
+// A tile of a long list (from r0 on, long_rows) by the whole block, K in steps of two pieces
 template <int NI>
 __device__ __forceinline__ void last_tile(const LayerArgs& a, uint32_t r0, uint32_t rows, unsigned char* smem, uint32_t tid, uint32_t lane, uint32_t wave)
 {
     constexpr int LTILE = LastShape<NI>::kTile;
+    static_assert(LTILE == (NI == 1 ? 2 : 1) * BM, "as long_rows has it");
+    auto row_of = [=](uint32_t r) { return r0 + r + (r < (uint32_t)BM ? 0u : (kDies - 1u) * BM); }; // row r of the tile
     constexpr int kA = LTILE * LSTEP / 8 / (LWAVES * 64), kB = NI * 32 * LSTEP / 8 / (LWAVES * 64); // 16-byte pieces of a thread per step
     uint16_t *As = reinterpret_cast<uint16_t*>(smem), *Bs = As + LTILE * LLDT;
     const bool idle = NI > 1 && wave * 32u >= (uint32_t)LTILE; // (uniform)
     const uint32_t half = lane >> 5, r = (idle ? 0u : wave * 32u) + (lane & 31u); // this lane's row of the tile
-    const uint32_t row = r0 + r < rows ? r0 + r : rows - 1u, dst = (a.scatter ? a.scatter : a.esc_idx)[a.row_begin + row];
+    const uint32_t my_row = row_of(r), row = my_row < rows ? my_row : rows - 1u, dst = (a.scatter ? a.scatter : a.esc_idx)[a.row_begin + row];
     float y[NI][16]; // class 32 j + 8 * (v / 4) + 4 * half + v % 4
 #pragma unroll
     for (int j = 0; j < NI; ++j)
@@ -80,7 +94,7 @@ __device__ __forceinline__ void last_tile(const LayerArgs& a, uint32_t r0, uint3
     auto fetch = [&](uint32_t k0) {
 #pragma unroll
         for (int u = 0; u < kA; ++u) { // (lda: whole pieces, zeros behind K; a row past the end: the last one again)
-            const uint32_t q = r0 + cr + 32u * u;
+            const uint32_t q = row_of(cr + 32u * u);
             ra[u] = k0 + ck < a.lda ? *reinterpret_cast<const uint4*>(a.a_bf16 + (size_t)(q < rows ? q : rows - 1u) * a.lda + k0 + ck) : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
@@ -125,7 +139,7 @@ __device__ __forceinline__ void last_tile(const LayerArgs& a, uint32_t r0, uint3
         for (int v = 0; v < 16; ++v) {
             const uint32_t c = j * 32u + 8u * (v >> 2) + 4u * half + (v & 3); // ascending in v
             if (c < a.N) {
-                if (a.logits && r0 + r < rows) a.logits[(size_t)(a.row_begin + r0 + r) * a.N + c] = y[j][v];
+                if (a.logits && my_row < rows) a.logits[(size_t)(a.row_begin + my_row) * a.N + c] = y[j][v];
                 if (y[j][v] > bv) {
                     bv = y[j][v];
                     best = c;
@@ -133,7 +147,7 @@ __device__ __forceinline__ void last_tile(const LayerArgs& a, uint32_t r0, uint3
             }
         }
     best = label_of(best, bv);
-    if (half == 0 && r0 + r < rows && dst < a.n_labels) a.labels[dst] = (uint16_t)best;
+    if (half == 0 && my_row < rows && dst < a.n_labels) a.labels[dst] = (uint16_t)best;
 }
 
 template <int NI>
@@ -153,8 +167,8 @@ __global__ __launch_bounds__(LWAVES * 64, 4) void mlp_last_layer(LayerArgs a, ui
         return; // the layer before has taken this one along
     const uint32_t pieces = (a.K + LPIECE - 1u) / LPIECE, tiles = (rows + LROWS - 1u) / LROWS;
     if (tiles * ((pieces + S::kHeld - 1u) / S::kHeld) > short_tiles) {
-        for (uint32_t r0 = blockIdx.x * S::kTile; r0 < rows; r0 += gridDim.x * S::kTile)
-            last_tile<NI>(a, r0, rows, reinterpret_cast<unsigned char*>(sums), tid, lane, wave);
+        for (uint32_t i = blockIdx.x; long_rows<NI>(i) < rows; i += gridDim.x)
+            last_tile<NI>(a, long_rows<NI>(i), rows, reinterpret_cast<unsigned char*>(sums), tid, lane, wave);
         return;
     }
     uint4 fa[kMine][4], fw[kMine][4][NI];
@@ -180,10 +194,17 @@ __global__ __launch_bounds__(LWAVES * 64, 4) void mlp_last_layer(LayerArgs a, ui
         else
             each(std::false_type{});
     };
-    const uint32_t first = blockIdx.x * LROWS, step = gridDim.x * LROWS;
-    if (first >= rows) return;
-    request(first, 0);
-    for (uint32_t r0 = first; r0 < rows; r0 += step) {
+    const uint32_t blocks = (tiles + kDies * 4u - 1u) / (kDies * 4u) * (kDies * 4u); // (some of the last 32 have no rows)
+    auto from = [&](uint32_t i) { // the next block from i on that has
+        while (i < blocks && short_rows(i) >= rows) i += gridDim.x;
+        return i;
+    };
+    uint32_t i = from(blockIdx.x);
+    if (i >= blocks) return;
+    request(short_rows(i), 0);
+    for (uint32_t next; i < blocks; i = next) {
+        const uint32_t r0 = short_rows(i);
+        next = from(i + gridDim.x);
         uint32_t dst = 0;
         if (tid < LROWS && r0 + tid < rows) dst = (a.scatter ? a.scatter : a.esc_idx)[a.row_begin + r0 + tid];
         float y[kOut];
@@ -212,7 +233,7 @@ __global__ __launch_bounds__(LWAVES * 64, 4) void mlp_last_layer(LayerArgs a, ui
             }
             // the next operands are on their way while the sums meet
             const bool more = p0 + S::kHeld < pieces;
-            if (more || r0 + step < rows) request(more ? r0 : r0 + step, more ? p0 + S::kHeld : 0u);
+            if (more || next < blocks) request(more ? r0 : short_rows(next), more ? p0 + S::kHeld : 0u);
             __syncthreads();
             const uint32_t held = pieces - p0 < (uint32_t)S::kHeld ? pieces - p0 : S::kHeld;
             for (uint32_t p = 0; p < held; ++p)
@@ -669,8 +690,8 @@ template <int NI>
 int launch_last(sf_ctx* ctx, const LayerArgs& a, uint32_t rows_cap)
 {
     SF_ALLOW_LDS(ctx, sf::kLdsLast + NI - 1, mlp_last_layer<NI>);
-    const uint32_t tiles = (rows_cap + LROWS - 1u) / LROWS, most = 4u * (uint32_t)ctx->n_cu; // (rows that exist are dealt out in the kernel)
-    mlp_last_layer<NI><<<tiles < most ? tiles : most, LWAVES * 64, LastShape<NI>::kLds, ctx->stream>>>(a, (NI == 1 ? 6u : 2u) * (uint32_t)ctx->n_cu);
+    const uint32_t tiles = (rows_cap + LROWS * 4u * kDies - 1u) / (LROWS * 4u * kDies) * (4u * kDies), most = 4u * (uint32_t)ctx->n_cu; // (rows that exist are dealt out in the kernel)
+    mlp_last_layer<NI><<<tiles < most ? tiles : most, LWAVES * 64, LastShape<NI>::kLds, ctx->stream>>>(a, (NI > 1 ? 2u : a.wo_last ? 8u : 5u) * (uint32_t)ctx->n_cu / 2u);
     SF_LAUNCH_CHECK(ctx, "mlp_last_layer");
     return SF_OK;
 }
@@ -856,7 +877,9 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
             a.w_last = (const uint16_t*)mlp->w3;
             a.wo_last = (const uint4*)w3o;
             a.b_last = mlp->b3;
-            a.n_last = mlp->n_classes <= 32u ? mlp->n_classes : 0u;
+            // (not where its weights lie in rows that are no whole 16-byte pieces: every tile would read them value by value.  74,148 rows through
+            // 48-76-1636-30: its own launch 156 us, along with the second hidden layer 191)
+            a.n_last = mlp->n_classes <= 32u && (w3o || ((mlp->n_h2 & 7u) == 0 && ((uintptr_t)mlp->w3 & 15u) == 0)) ? mlp->n_classes : 0u;
             a.logits = logits;
             {
                 const int rc = sf::wide_layer(ctx, A_BF16, a, w2o, R);
