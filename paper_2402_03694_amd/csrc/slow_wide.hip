@@ -445,26 +445,28 @@ __device__ __forceinline__ void wide_few(const LayerArgs& a, const uint4* __rest
         if (AMODE == A_RAW) raw_flow_range(a, flow, raw_b0, raw_n);
     }
     constexpr int kMine = FCHUNK / 128; // 16-byte pieces of a thread
-    uint4 ra[kMine];
+    uint32_t __attribute__((ext_vector_type(4))) ra[kMine]; // (as uint4 the compiler keeps the array in memory)
     auto fetch = [&](uint32_t k0) {
 #pragma unroll
         for (int u = 0; u < kMine; ++u) {
+            uint4 v;
             const uint32_t k = k0 + u * 128u + k8;
             if (AMODE == A_RAW) {
                 const uint32_t j = k / a.raw_bits, b = k - j * a.raw_bits;
                 const uint4 words = raw_words_at<FORM>(a, raw_b0, raw_n, j, b); // (past K: packets that raw_pkts leaves out)
-                ra[u] = raw_bits_of<FORM>(a, words, b);
+                v = raw_bits_of<FORM>(a, words, b);
             } else if (AMODE == A_FEAT) {
-                ra[u] = load_a_chunk<AMODE>(a, true, 0u, flow, k);
+                v = load_a_chunk<AMODE>(a, true, 0u, flow, k);
             } else { // (lda is K rounded up to whole slabs and the padding holds zeros)
                 const uint32_t at = k < a.lda ? k : 0u;
-                ra[u] = *reinterpret_cast<const uint4*>(a.a_bf16 + (size_t)(row0 + mine) * a.lda + at);
+                v = *reinterpret_cast<const uint4*>(a.a_bf16 + (size_t)(row0 + mine) * a.lda + at);
             }
+            ra[u] = {v.x, v.y, v.z, v.w};
         }
     };
     auto store = [&](uint32_t buf) {
 #pragma unroll
-        for (int u = 0; u < kMine; ++u) *reinterpret_cast<uint4*>(A + ((size_t)buf * kFewTileRows + r) * FLD + u * 128 + k8) = ra[u];
+        for (int u = 0; u < kMine; ++u) *reinterpret_cast<uint4*>(A + ((size_t)buf * kFewTileRows + r) * FLD + u * 128 + k8) = make_uint4(ra[u].x, ra[u].y, ra[u].z, ra[u].w);
     };
     f32x16 acc;
 #pragma unroll
