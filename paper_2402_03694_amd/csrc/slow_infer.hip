@@ -503,6 +503,7 @@ __device__ __forceinline__ void f32_rows(const F32Args& a, const F32Model& m, ui
         l.wide = (l.K & 3u) == 0 && (reinterpret_cast<uintptr_t>(l.w) & 15u) == 0;
         return l;
     };
+    if (block * R >= total) return; // (nothing to request weights for: no rows of 16,850, 75-204-59-53, 9.7 us with the requests, 7.7 without)
     // the first weights of a layer are requested ahead of what the layer waits for
     F32Weights<R> w;
     f32_first_weights<R>(layer_at(0), wave, lane, w);
@@ -931,13 +932,16 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
     // through 20-600-600-10 (12.6e9 terms) 955 : 794, 500,000 through 64-128-128-4 (16e9) 913 : 995, 200,000 through 128-256-256-32
     // (23e9) 1,274 : 1,377, 32,768 through 128-650-650-10 (19e9) 1,224 : 1,307.
     // Four rows a block while that gives a compute unit at most two: 2,000 rows through 32-128-128-4 12.9 : 10.4, 1,500 through
-    // 64-200-256-10 28.7 : 21.7; four of them against one of 16 rows, 4,096 rows, 18.6 : 13.4.  (Rows that exist: the kernel deals them out.)
+    // 64-200-256-10 28.7 : 21.7; four of them against one of 16 rows, 4,096 rows, 18.6 : 13.4.  At most one where the second layer's weights
+    // come in single values (no whole 16-byte pieces a row), whose requests two blocks pay twice: 1,183 rows through 32-683-364-47 two blocks of
+    // four 153, one of 16 96; 1,902 through 154-551-315-27 153 : 88.  (Rows that exist: the kernel deals them out.)
     if (f32_in_one(mlp, esc_cap)) {
         F32Model m = {(const float*)mlp->w1, mlp->b1, (const float*)mlp->w2, mlp->b2, (const float*)mlp->w3, mlp->b3, mlp->n_h1, mlp->n_h2,
                       mlp->n_classes, scatter ? scatter : esc_idx, logits, labels, n_flows, pred, 0};
         if (pred) m.n_copy = (n_flows + sfsmall::kCopySlice - 1u) / sfsmall::kCopySlice;
         const size_t lds = f32_fused_lds(mlp->n_in, mlp->n_h1, mlp->n_h2, mlp->n_classes);
-        const uint32_t few = 2u * kF32FewRows * (uint32_t)ctx->n_cu;
+        const bool whole = (mlp->n_h1 & 3u) == 0 && ((uintptr_t)mlp->w2 & 15u) == 0;
+        const uint32_t few = (whole ? 2u : 1u) * kF32FewRows * (uint32_t)ctx->n_cu;
         const uint32_t tiles = (esc_cap + kF32FewRows - 1u) / kF32FewRows, most = 4u * (uint32_t)ctx->n_cu;
         const uint32_t grid = (tiles < most ? tiles : most) + m.n_copy;
         if (gate) {
