@@ -601,11 +601,22 @@ bool one_lane_pays(uint32_t dmax, uint32_t per_unit, uint32_t n_flows, uint64_t 
     return per_unit >= 1536u && (dmax <= 12 || (dmax < 16 && n_pkts <= 12ull * n_flows));
 }
 
-// The same for windows deeper than 32 packets, windows 8 and 64 unless said otherwise: lanes only where most waves have no long flow and the
-// batch is large.  Lanes : parts, ragged with a mean of 10 packets: 131,072 flows 50.0 : 54.7 us, 262,144 79.5 : 92.8, 1,000,000 239 : 349; 400,000 of 12
-// packets 56.4 : 71.2; but a mean of 17 packets 131,072 flows 82.9 : 69.3, 400,000 181 : 169, of 25 267 : 213; 400,000 of 24 packets 100.7 : 88.9;
-// 262,144 of 64 packets, window 64, 387 : 287; 300,000 of 50, windows 20 and 50, 565 : 358.
-bool long_lanes_pay(uint32_t per_unit, uint32_t n_flows, uint64_t n_pkts) { return per_unit >= 2u * 4u * kWave && n_pkts <= 16ull * n_flows; }
+// The same for windows deeper than 32 packets: lanes where most waves have no long flow and the batch is large enough that one
+// wave's chain of latencies no longer counts, the later the longer the flows.  Lanes : parts, us.
+//   flows of one length (none longer than 32), from 192 flows a unit up to 12 packets (123,008 of 4, window 64, 10.7 : 16.9; 50,800 of 12 9.5 :
+//     11.0), from 320 up to 15 (121,512 of 13, windows 18 and 64, 24.4 : 31.5), from 768 of 16, from 1,536 above (1,170,295 of 24, windows 2, 16, 64, 293 : 401; 457,367 of 20, four windows, 164 : 201; but
+//     120,000 of 24 1.28 times as long), and from 320 where they fill 32 (wide loads; 1,199,700, window 64, 136 : 237);
+//   ragged ones by their mean: up to 2 packets 256 flows a unit, 8 384 (108,635 of 4.8, windows 3 and 42, 28.4 : 33.7), 12 512 (262,144 of 10, windows 8 and
+//     64, 79.5 : 92.8), 15 1,024, 18 2,048 (1,042,169 of 16.9, windows 8, 29, 64, 501 : 563); but a mean of 17, 131,072 flows, 82.9 : 69.3, 400,000
+//     181 : 169, of 25 267 : 213.
+// Flows longer than 32 packets go in parts: 262,144 of 64, window 64, 387 : 287; 300,000 of 50, windows 20 and 50, 565 : 358.
+bool long_lanes_pay(uint32_t per_unit, uint32_t n_flows, uint64_t n_pkts)
+{
+    const uint64_t len = n_pkts / n_flows;
+    if (n_pkts % n_flows == 0) return len <= 32 && per_unit >= (len <= 12 ? 192u : len <= 15 || len == 32 ? 320u : len == 16 ? 768u : 1536u);
+    const auto mean_to = [=](uint32_t m) { return n_pkts <= (uint64_t)m * n_flows; };
+    return mean_to(18) && per_unit >= (mean_to(2) ? 256u : mean_to(8) ? 384u : mean_to(12) ? 512u : mean_to(15) ? 1024u : 2048u);
+}
 
 } // namespace
 
