@@ -878,9 +878,14 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
             a.w_last = (const uint16_t*)mlp->w3;
             a.wo_last = (const uint4*)w3o;
             a.b_last = mlp->b3;
-            // (not where its weights lie in rows that are no whole 16-byte pieces: every tile would read them value by value.  74,148 rows through
-            // 48-76-1636-30: its own launch 156 us, along with the second hidden layer 191)
-            a.n_last = mlp->n_classes <= 32u && (w3o || ((mlp->n_h2 & 7u) == 0 && ((uintptr_t)mlp->w3 & 15u) == 0)) ? mlp->n_classes : 0u;
+            // Not where its weights lie in rows that are no whole 16-byte pieces: every tile would read them value by value (74,148 rows
+            // through 48-76-1636-30: its own launch 156 us, along with the second hidden layer 191).  And not where the first layer does most
+            // of the work, eight times the second's: such a pass runs at the clock that the power allows, and the launch saved is paid back
+            // at a lower one, by every kernel (a million flows of 10 x 480 header bits through 1024-512, whole passes 1,875 : 1,940, where the
+            // launches of the two layers alone take 229 : 205; 100,000 rows of 20 x 480 1,743 : 1,766; a first layer of 4.7 times the second's
+            // work, 210,000 rows of 5 x 480, 1,095 : 1,073; of twice, 648 : 612).
+            const bool read_whole = w3o || ((mlp->n_h2 & 7u) == 0 && ((uintptr_t)mlp->w3 & 15u) == 0);
+            a.n_last = mlp->n_classes <= 32u && read_whole && mlp->n_in < 8u * mlp->n_h2 ? mlp->n_classes : 0u;
             a.logits = logits;
             {
                 const int rc = sf::wide_layer(ctx, A_BF16, a, w2o, R);
