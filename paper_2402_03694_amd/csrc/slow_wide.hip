@@ -423,7 +423,7 @@ __device__ __forceinline__ void wide_tiles(const LayerArgs& a, const uint4* __re
 // order of K, as in the tiles: the same bits.  Tiles of 128 x 512 : these, whole call in us: one
 // row through 64-1024-1024-10 40.7 : 20.2, 500 46.8 : 24.5, 2,000 47.8 : 32.3, 500 through 96-300-900-20 46.8 : 22.9.
 template <int AMODE, int FORM>
-__device__ __forceinline__ void wide_few(const LayerArgs& a, const uint4* __restrict__ ws, uint32_t rows, uint32_t total, unsigned char* smem)
+__device__ __forceinline__ void wide_few(const LayerArgs& a, const uint4* __restrict__ ws, uint32_t rows, unsigned char* smem)
 {
     uint16_t* A = reinterpret_cast<uint16_t*>(smem); // [2][32][FLD]
     uint32_t* s_flow = reinterpret_cast<uint32_t*>(smem + (size_t)2 * kFewTileRows * FLD * 2);
@@ -541,7 +541,7 @@ __device__ __forceinline__ void wide_any(const LayerArgs& a, const uint4* __rest
     if (a.row_begin >= total) return;
     const uint32_t left = total - a.row_begin, rows = left < a.rows_cap ? left : a.rows_cap;
     if (wide_few_tiles(rows, a.ldh) <= gridDim.x)
-        wide_few<AMODE, FORM>(a, ws, rows, total, smem);
+        wide_few<AMODE, FORM>(a, ws, rows, smem);
     else if (LAST && wide_takes_last(rows, a.ldh, gridDim.x, RESIDENT))
         wide_tiles<AMODE, RESIDENT, FORM, LAST>(a, ws, n_cb, smem);
     else
