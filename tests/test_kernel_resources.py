@@ -84,3 +84,36 @@ def test_no_spills(kernels, name):
     ("featurize_forest<128, 8, 0, 0, 16, true>", 16), ("featurize_forest<128, 8, 0, 0, 16, false>", 16)])  # the feature phase of 16 packets
 def test_few_spills(kernels, name, most):
     assert kernels[name]["spilled"] <= most, kernels[name]
+
+
+SHORT_FORMS = ["featurize_forest_few<%s, 16, %s>" % (t, r) for t in ("128, 8, 0, 0", "128, 4, 5, 2", "64, 8, 3, 1") for r in ("true", "false")] + [
+    "mlp_few<%d, %d, %d, sfsmall::%s>" % (k, n1, n2, g) for k in (4, 8) for n1 in (1, 2) for n2 in (1, 2) for g in ("GateRows", "NoGate")] + [
+    "featurize_long<2>", "mlp_wide_last<true>", "mlp_wide_last<false>", "mlp_last_layer<1>", "mlp_last_layer<2>", "f32_mlp<sfsmall::GateRows>",
+    "f32_mlp<sfsmall::NoGate>"]
+
+
+@pytest.mark.parametrize("name", SHORT_FORMS)
+def test_no_spills_short_forms(kernels, name):
+    """The forms for few rows, small batches and the wide models' last layer, which hold rings of operands in registers."""
+    assert kernels[name]["spilled"] == 0, kernels[name]
+
+
+def test_few_spills_long_flows(kernels):
+    """Four blocks a unit: 128 registers."""
+    assert kernels["featurize_long<4>"]["spilled"] <= 14, kernels["featurize_long<4>"]
+
+
+def test_slow_model_has_no_arrays_in_memory():
+    """Bytes a lane of memory that are no spills: an array the compiler did not keep in registers."""
+    held = {}
+    for code in _code_objects(hip_build.build(force=False)):
+        with tempfile.NamedTemporaryFile(suffix=".o") as f:
+            f.write(code)
+            f.flush()
+            for block in _run(LLVM + "llvm-readelf", "--notes", f.name).split("\n  - "):
+                name = re.search(r"\.symbol: +'?(\w+)\.kd", block)
+                if name and ("mlp_" in name.group(1)):
+                    count = lambda what: int(re.search(r"\.%s: +(\d+)" % what, block).group(1))
+                    held[name.group(1)] = count("private_segment_fixed_size"), count("vgpr_spill_count")
+    assert len(held) > 40
+    assert not {n: v for n, v in held.items() if v[0] and not v[1]}
