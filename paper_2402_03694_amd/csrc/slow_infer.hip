@@ -503,7 +503,7 @@ __device__ __forceinline__ void f32_rows(const F32Args& a, const F32Model& m, ui
         l.wide = (l.K & 3u) == 0 && (reinterpret_cast<uintptr_t>(l.w) & 15u) == 0;
         return l;
     };
-    if (block * R >= total) return; // (nothing to request weights for: no rows of 16,850, 75-204-59-53, 9.7 us with the requests, 7.7 without)
+    if (block * R >= total) return; // (nothing to request weights for: no rows of 16,850, 75-204-59-53, whole call 9.7 us with the requests, 5.3 without)
     // the first weights of a layer are requested ahead of what the layer waits for
     F32Weights<R> w;
     f32_first_weights<R>(layer_at(0), wave, lane, w);

@@ -90,8 +90,8 @@ __device__ __forceinline__ void wave_sync()
 // FORM: how header bits lie (A_RAW).
 // LAST: the last layer goes along (a block holds all columns of a row, wide_takes_last): a wave multiplies the 64 columns it has
 // staged with their weights, the eight waves' sums meet in shared memory, and the activations are neither written nor read back: 60,000
-// rows through 1024-1024-16 a whole call 204 -> 181 us, 200,000 through 1024-512-16 419 -> 376, the large workload's pass 14.5 -> 13.3-13.8 ms,
-// header bits 1,975 -> 1,930 us (sum of the launches).  A logit is its bias plus the sums of 64 columns each, in order, as in mlp_last_layer: the same bits.
+// rows through 1024-1024-16 a whole call 168 -> 156 us, 200,000 through 1024-512-16 372 -> 333, the large workload's pass 14.1 -> 13.4 ms; which models at
+// run_slow.  A logit is its bias plus the sums of 64 columns each, in order, as in mlp_last_layer: the same bits.
 template <int AMODE, bool RESIDENT, int FORM, bool LAST>
 __device__ __forceinline__ void wide_tiles(const LayerArgs& a, const uint4* __restrict__ ws, uint32_t n_cb, unsigned char* smem)
 {
@@ -421,7 +421,7 @@ __device__ __forceinline__ void wide_tiles(const LayerArgs& a, const uint4* __re
 // through one unit's path to the cache (half a megabyte for K = 1,024), so the weights are requested first, 16 k-steps ahead, and the
 // rows' values come to shared memory 1,024 at a time, so that waves meet once in as many k-steps.  A sum starts at its bias and runs in
 // order of K, as in the tiles: the same bits.  Tiles of 128 x 512 : these, whole call in us: one
-// row through 64-1024-1024-10 40.7 : 20.2, 500 46.8 : 24.5, 2,000 47.8 : 32.3, 500 through 96-300-900-20 46.8 : 22.9.
+// row through 64-1024-1024-10 41.9 : 18.0, 500 46.5 : 22.6, 2,000 46.9 : 27.5, 500 through 96-300-900-20 44.8 : 20.3.
 template <int AMODE, int FORM>
 __device__ __forceinline__ void wide_few(const LayerArgs& a, const uint4* __restrict__ ws, uint32_t rows, unsigned char* smem)
 {
