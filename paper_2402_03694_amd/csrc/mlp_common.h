@@ -4,11 +4,13 @@
 #pragma once
 
 #include "common.h"
+#include "slow_label.h"
 
 namespace sfmlp {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4; // (an array of uint4 the compiler may keep in memory)
 
 constexpr int BM = 128; // rows per block
 
@@ -45,9 +47,8 @@ struct LayerArgs {
     float* logits;   // [esc_cap][classes] or NULL
     uint16_t* labels;
     const uint16_t* pred; // labels = pred for all n_labels flows first, by the first hidden layer's launch; NULL = they stay
-    // The second hidden layer may take the last one along (wide_takes_last): its weights [n_last][N], biases and classes (0: it may not)
-    const uint16_t* w_last;
-    const uint4* wo_last; // operand-ordered copy, or NULL
+    // The second hidden layer may take the last one along (wide_takes_last): its operand-ordered weights (or NULL), biases and classes (0: it may not)
+    const uint4* wo_last;
     const float* b_last;
     uint32_t n_last;
     // ... and for the last layer's own launch: blocks of the second hidden layer's (0: that one took nothing along) and its K
@@ -76,12 +77,37 @@ static __device__ __forceinline__ uint4 weight_chunk(const uint16_t* w, uint32_t
     return make_uint4(pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7]));
 }
 
-// the last layer's operand of one k-step (32 classes from 32 j on): from the ordered copy, which a wave reads as it lies, if there is one
-// (up to 32 classes; 200,000 rows through 2048-32, rows of weights one by one: as long again in the address path)
-static __device__ __forceinline__ uint4 last_weights(const LayerArgs& a, uint32_t N, uint32_t K, uint32_t j, uint32_t ks, uint32_t lane)
+// The end of the last layer for 32 rows, a row's classes in lanes l and l ^ 32: sum[j][v] of class 32 j + 8 * (v / 4) + 4 * half + v % 4,
+// weights first in the multiplication.  s_bias: shared memory, zeros behind the last class; row: among the logits.
+template <int NI>
+static __device__ __forceinline__ void last_rows(const LayerArgs& a, const f32x16 (&sum)[NI], const float* s_bias, uint32_t classes, uint32_t half, bool there,
+                                                 uint32_t row, uint32_t dst)
 {
-    if (a.wo_last) return a.wo_last[ks * 64u + lane];
-    return weight_chunk(a.w_last, N, K, j * 32u + (lane & 31u), ks * 16u + 8u * (lane >> 5));
+    // class 0 first, then every class that is strictly larger than all before it (label_start, label_of)
+    uint32_t best = 4u * half;
+    float bv = 0.f;
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const uint32_t c0 = j * 32u + 8u * g + 4u * half; // ascending in j and g
+            const float4 b = *reinterpret_cast<const float4*>(s_bias + c0);
+            const float y[4] = {sum[j][4 * g] + b.x, sum[j][4 * g + 1] + b.y, sum[j][4 * g + 2] + b.z, sum[j][4 * g + 3] + b.w};
+            if (j == 0 && g == 0) bv = label_start(half, y[0]);
+#pragma unroll
+            for (uint32_t e = 0; e < 4u; ++e) {
+                const uint32_t c = c0 + e;
+                if (c < classes) {
+                    if (a.logits && there) a.logits[(size_t)row * classes + c] = y[e];
+                    if (y[e] > bv) {
+                        bv = y[e];
+                        best = c;
+                    }
+                }
+            }
+        }
+    best = label_of(best, bv);
+    if (half == 0 && there && dst < a.n_labels) a.labels[dst] = (uint16_t)best;
 }
 
 // How a hidden layer's tiles of 128 rows x 512 columns are dealt out to `units` blocks: a row block with all its n_cb column blocks
@@ -97,11 +123,15 @@ static __host__ __device__ __forceinline__ uint64_t wide_few_tiles(uint32_t rows
 {
     return (uint64_t)((rows + kFewTileRows - 1u) / kFewTileRows) * ((ldh + kFewTileCols - 1u) / kFewTileCols);
 }
-// A block that holds all columns of a row takes the last layer along.
+// A block that holds all columns of a row takes the last layer along: two of its eight waves multiply, so it pays where the activations it
+// keeps from memory are many (more than one column block, 5 to 15 % of a whole call; more than 256 columns and more than a tile a block, 1 to 3),
+// or where its own launch would be one block's latency (up to a tile a block, up to 256 columns, 2 to 4; with more columns 2 % the other way,
+// as with fewer columns and more tiles: 41,385 rows through 6-640-192-25 71.2 us along, 67.1 in its own launch).
 static __device__ __forceinline__ bool wide_takes_last(uint32_t rows, uint32_t ldh, uint32_t units, bool resident)
 {
     const uint32_t n_cb = (ldh + 511u) / 512u;
-    return wide_few_tiles(rows, ldh) > units && (n_cb == 1u || wide_walks((rows + BM - 1u) / BM, n_cb, units, resident));
+    const uint32_t row_blocks = (rows + BM - 1u) / BM;
+    return wide_few_tiles(rows, ldh) > units && (n_cb == 1u ? (row_blocks <= units) == (ldh <= 256u) : wide_walks(row_blocks, n_cb, units, resident));
 }
 constexpr uint32_t kWideSlab = 64, kWideSlabs = 3; // K values of a slab, slabs that stay
 

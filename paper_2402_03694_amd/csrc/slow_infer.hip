@@ -37,26 +37,27 @@ namespace {
 using namespace sfmlp;
 
 // The last layer of a wide model: logits = A * W3^T + b3 on bfloat16 activations (at most 64 classes), then the arg-max per row
-// and the scatter of the label.  K is cut into pieces of 64, and a logit is its bias plus the pieces' sums in order, whatever form
-// makes them: mlp_wide_last (slow_wide.hip), which takes this layer along where it can, or one of the two here.
-//   - Long lists: 256 rows a block (128 with more than 32 classes), a wave 32 of them, K walked by all waves together through shared memory in steps of two pieces,
-//     the next step requested ahead of the MFMAs.  What bounds it is HBM (200,000 rows of 2,048 values 216 us, 3.8 TB/s; straight
+// and the scatter of the label.  A logit is one chain of products in order of K, from zero on, and its bias at the end, whatever form
+// makes it: mlp_wide_last (slow_wide.hip), which takes this layer along where it can, or one of the two here.
+//   - Long lists: 256 rows a block (128 with more than 32 classes), a wave 32 of them, K walked by all waves together through shared memory in steps of two pieces
+//     of 64, the next step requested ahead of the MFMAs.  What bounds it is HBM (200,000 rows of 2,048 values 216 us, 3.8 TB/s; straight
 //     from the cache into registers, a row's operands are 32 lines to the address path, 270).
-//   - Short ones: the waves of a block split the pieces of 32 rows, whose operands are all requested before the first MFMA; the
-//     pieces' sums meet in shared memory.  What bounds it is the chain of latencies: 500 rows of 1,024 values 11.4 -> 6.2 us, 19,600 14.
-//     Lists of up to four such blocks a unit go this way, two and a half where the weights lie in rows (a block then gathers them line by
+//   - Short ones: all waves of a block request the operands of 32 rows, a piece each and a round ahead, and put them into shared memory;
+//     one wave multiplies.  What bounds it is the chain of latencies, and past a few blocks a unit that chain of MFMAs.
+//     Lists of up to three such blocks a unit go this way, two where the weights lie in rows (a block then gathers them line by
 //     line), one with more than 32 classes; a block counts once for every 16 pieces (8 with more than 32 classes).  Short : long, whole call in
-//     us: 22,611 rows through 64-64-1536-10 41.5 : 48.2, rows of weights 13,663 through 32-256-1792-10 48.4 : 55.5; 34,672 through 128-448-576-10,
-//     4.2 blocks, 82.8 : 76.5, rows of weights 22,378 through 96-176-1042-16, 5.5, 76.7 : 66.1; 49 classes, 8,730 rows of 63 values, 46.8 : 37.7.
+//     us: 12,546 rows through 32-256-1536-10 46.4 : 53.0, rows of weights 8,513 through 32-320-1536-4 44.4 : 48.7; 34,672 through 128-448-576-10,
+//     4.2 blocks, 88.1 : 81.5, rows of weights 22,378 through 96-176-1042-16, 5.5, 79.2 : 69.4; 49 classes, 8,730 rows of 63 values, 42.2 : 38.2.
 constexpr int LROWS = 32, LWAVES = 8, LPIECE = 64;
 constexpr int LSTEP = 2 * LPIECE, LLDT = LSTEP + 8; // long lists: K of a step, row stride in shared memory
 template <int NI> // 32-class blocks
 struct LastShape {
-    static constexpr int kTile = LWAVES * 32 / NI;     // long lists: rows of a block (33 to 64 classes: half the waves only load)
-    static constexpr int kLd = NI * 32 + 4;            // row stride of a piece's sums (16-byte writes of 8 rows on distinct banks)
-    static constexpr int kHeld = LWAVES * (NI == 1 ? 2 : 1); // pieces whose sums are held at a time
-    static constexpr size_t kShort = (size_t)(kHeld + 1) * LROWS * kLd * 4, kLong = (size_t)(kTile + NI * 32) * LLDT * 2;
-    static constexpr size_t kLds = kShort > kLong ? kShort : kLong;
+    static constexpr int kTile = LWAVES * 32 / NI;  // long lists: rows of a block (33 to 64 classes: half the waves only load)
+    static constexpr int kHeld = LWAVES / NI;       // short lists: pieces in shared memory at a time, a wave loads a piece's weights of 32 classes
+    static constexpr int kRows = 4 / NI;            // ... and as many of the rows' four operands
+    static constexpr size_t kShort = (size_t)kHeld * 4 * (1 + NI) * 1024, kLong = (size_t)(kTile + NI * 32) * LLDT * 2;
+    static constexpr size_t kBias = kShort > kLong ? kShort : kLong; // the biases stand behind either
+    static constexpr size_t kLds = kBias + NI * 32 * 4;
 };
 
 // The hidden layer before writes 128 rows a block, and blocks go to the eight dies in turn, each with a cache of its own.  A row is read
@@ -71,7 +72,7 @@ __device__ __forceinline__ uint32_t long_rows(uint32_t i) { return (NI == 1 ? i 
 
 // A tile of a long list (from r0 on, long_rows) by the whole block, K in steps of two pieces
 template <int NI>
-__device__ __forceinline__ void last_tile(const LayerArgs& a, uint32_t r0, uint32_t rows, unsigned char* smem, uint32_t tid, uint32_t lane, uint32_t wave)
+__device__ __forceinline__ void last_tile(const LayerArgs& a, uint32_t r0, uint32_t rows, unsigned char* smem, const float* s_bias, uint32_t tid, uint32_t lane, uint32_t wave)
 {
     constexpr int LTILE = LastShape<NI>::kTile;
     static_assert(LTILE == (NI == 1 ? 2 : 1) * BM, "as long_rows has it");
@@ -81,14 +82,11 @@ __device__ __forceinline__ void last_tile(const LayerArgs& a, uint32_t r0, uint3
     const bool idle = NI > 1 && wave * 32u >= (uint32_t)LTILE; // (uniform)
     const uint32_t half = lane >> 5, r = (idle ? 0u : wave * 32u) + (lane & 31u); // this lane's row of the tile
     const uint32_t my_row = row_of(r), row = my_row < rows ? my_row : rows - 1u, dst = (a.scatter ? a.scatter : a.esc_idx)[a.row_begin + row];
-    float y[NI][16]; // class 32 j + 8 * (v / 4) + 4 * half + v % 4
+    f32x16 y[NI]; // class 32 j + 8 * (v / 4) + 4 * half + v % 4
 #pragma unroll
     for (int j = 0; j < NI; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const uint32_t c = j * 32u + 8u * (v >> 2) + 4u * half + (v & 3);
-            y[j][v] = c < a.N ? a.bias[c] : 0.f;
-        }
+        for (int v = 0; v < 16; ++v) y[j][v] = 0.f;
     uint4 ra[kA], rb[kB];
     const uint32_t ck = tid % (LSTEP / 8) * 8u, cr = tid / (LSTEP / 8); // (rows of As: every 32nd from cr on)
     auto fetch = [&](uint32_t k0) {
@@ -110,54 +108,27 @@ __device__ __forceinline__ void last_tile(const LayerArgs& a, uint32_t r0, uint3
         __syncthreads();
         if (k0 + LSTEP < a.K) fetch(k0 + LSTEP);
         __builtin_amdgcn_sched_barrier(0); // keep the requests ahead of the MFMAs
+        if (idle) continue;
 #pragma unroll
-        for (int p = 0; p < LSTEP / LPIECE; ++p) {
-            if (idle || k0 + p * LPIECE >= a.K) continue;
+        for (int s = 0; s < LSTEP / 16; ++s) {
+            const uint32_t at = s * 16u + 8u * half;
 #pragma unroll
-            for (int j = 0; j < NI; ++j) {
-                f32x16 c3;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) c3[v] = 0.f;
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const uint32_t at = p * LPIECE + s * 16u + 8u * half;
-                    c3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*reinterpret_cast<const uint4*>(Bs + (j * 32u + (lane & 31u)) * LLDT + at)),
-                                                                 as_bf16x8(*reinterpret_cast<const uint4*>(As + r * LLDT + at)), c3, 0, 0, 0);
-                }
-#pragma unroll
-                for (int v = 0; v < 16; ++v) y[j][v] += c3[v];
-            }
+            for (int j = 0; j < NI; ++j)
+                y[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*reinterpret_cast<const uint4*>(Bs + (j * 32u + (lane & 31u)) * LLDT + at)),
+                                                               as_bf16x8(*reinterpret_cast<const uint4*>(As + r * LLDT + at)), y[j], 0, 0, 0);
         }
     }
-    if (idle) return; // (the next tile's first barrier stands before anything this one wrote is used)
-    // class 0 first, then every class that is strictly larger than all before it (label_start, label_of)
-    uint32_t best = 4u * half;
-    float bv = label_start(half, y[0][0]);
-#pragma unroll
-    for (int j = 0; j < NI; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const uint32_t c = j * 32u + 8u * (v >> 2) + 4u * half + (v & 3); // ascending in v
-            if (c < a.N) {
-                if (a.logits && my_row < rows) a.logits[(size_t)(a.row_begin + my_row) * a.N + c] = y[j][v];
-                if (y[j][v] > bv) {
-                    bv = y[j][v];
-                    best = c;
-                }
-            }
-        }
-    best = label_of(best, bv);
-    if (half == 0 && my_row < rows && dst < a.n_labels) a.labels[dst] = (uint16_t)best;
+    if (!idle) last_rows<NI>(a, y, s_bias, a.N, half, my_row < rows, a.row_begin + my_row, dst);
+    // (the next tile's first barrier stands before anything this one reads is written)
 }
 
 template <int NI>
 __global__ __launch_bounds__(LWAVES * 64, 4) void mlp_last_layer(LayerArgs a, uint32_t short_tiles)
 {
     typedef LastShape<NI> S;
-    constexpr int kMine = S::kHeld / LWAVES;               // pieces a wave has at a time
-    constexpr int kOut = LROWS * NI * 32 / (LWAVES * 64);  // logits of a thread
-    extern __shared__ __attribute__((aligned(16))) float sums[]; // [kHeld][32][kLd]
-    float* s_logits = sums + S::kHeld * LROWS * S::kLd;          // [32][kLd]
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    uint4 *s_a = reinterpret_cast<uint4*>(smem), *s_w = s_a + S::kHeld * 256; // [kHeld][4][64], [kHeld][4][NI][64]
+    float* s_bias = reinterpret_cast<float*>(smem + S::kBias);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint32_t total = *a.esc_count;
     total = total < a.esc_cap ? total : a.esc_cap;
@@ -166,33 +137,30 @@ __global__ __launch_bounds__(LWAVES * 64, 4) void mlp_last_layer(LayerArgs a, ui
     if (a.units_before && wide_takes_last(rows, a.lda, a.units_before, a.k_before <= kWideSlab * kWideSlabs))
         return; // the layer before has taken this one along
     const uint32_t pieces = (a.K + LPIECE - 1u) / LPIECE, tiles = (rows + LROWS - 1u) / LROWS;
-    if (tiles * ((pieces + S::kHeld - 1u) / S::kHeld) > short_tiles) {
-        for (uint32_t i = blockIdx.x; long_rows<NI>(i) < rows; i += gridDim.x)
-            last_tile<NI>(a, long_rows<NI>(i), rows, reinterpret_cast<unsigned char*>(sums), tid, lane, wave);
+    if (tid < NI * 32u) s_bias[tid] = tid < a.N ? a.bias[tid] : 0.f; // (read several barriers on)
+    constexpr uint32_t kOnce = NI == 1 ? 16 : 8; // pieces for which a block counts once
+    if (tiles * ((pieces + kOnce - 1u) / kOnce) > short_tiles) {
+        for (uint32_t i = blockIdx.x; long_rows<NI>(i) < rows; i += gridDim.x) last_tile<NI>(a, long_rows<NI>(i), rows, smem, s_bias, tid, lane, wave);
         return;
     }
-    uint4 fa[kMine][4], fw[kMine][4][NI];
-    // operands of this wave's pieces from p0 on for the rows from r0 on (a row, piece or class past the last one: that one again)
-    auto request = [&](uint32_t r0, uint32_t p0) {
-        const uint32_t r = r0 + (lane & 31u);
-        const uint16_t* arow = a.a_bf16 + (size_t)(r < rows ? r : rows - 1u) * a.lda; // (lda: whole pieces, zeros behind K)
-        auto each = [&](auto ordered) {
+    const uint32_t m = wave % S::kHeld, jw = wave / S::kHeld; // this wave's piece of a round and its classes
+    u32x4 fa[S::kRows], fw[4];
+    // this wave's share of the round from piece p0 on for the rows from r0 on (a row, piece or class past the last one: that one again)
+    auto request = [&](uint32_t r0, uint32_t p0) __attribute__((always_inline)) {
+        const uint32_t r = r0 + (lane & 31u), ks = (p0 + m < pieces ? p0 + m : pieces - 1u) * (LPIECE / 16u);
+        const uint16_t* arow = a.a_bf16 + (size_t)(r < rows ? r : rows - 1u) * a.lda + 8u * (lane >> 5); // (lda: whole pieces, zeros behind K)
 #pragma unroll
-            for (int m = 0; m < kMine; ++m) {
-                const uint32_t p = p0 + wave + LWAVES * m, ks = (p < pieces ? p : pieces - 1u) * (LPIECE / 16u);
+        for (int s = 0; s < S::kRows; ++s) fa[s] = *reinterpret_cast<const u32x4*>(arow + (ks + jw * S::kRows + s) * 16u);
+        if (NI == 1 && a.wo_last) {
 #pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    fa[m][s] = *reinterpret_cast<const uint4*>(arow + (ks + s) * 16u + 8u * (lane >> 5));
+            for (int s = 0; s < 4; ++s) fw[s] = *reinterpret_cast<const u32x4*>(a.wo_last + (ks + s) * 64u + lane);
+        } else {
 #pragma unroll
-                    for (int j = 0; j < NI; ++j)
-                        fw[m][s][j] = decltype(ordered)::value ? a.wo_last[(ks + s) * 64u + lane] : last_weights(a, a.N, a.K, j, ks + s, lane);
-                }
+            for (int s = 0; s < 4; ++s) {
+                const uint4 w = weight_chunk(a.w, a.N, a.K, jw * 32u + (lane & 31u), (ks + s) * 16u + 8u * (lane >> 5));
+                fw[s] = u32x4{w.x, w.y, w.z, w.w};
             }
-        };
-        if (NI == 1 && a.wo_last)
-            each(std::true_type{});
-        else
-            each(std::false_type{});
+        }
     };
     const uint32_t blocks = (tiles + kDies * 4u - 1u) / (kDies * 4u) * (kDies * 4u); // (some of the last 32 have no rows)
     auto from = [&](uint32_t i) { // the next block from i on that has
@@ -203,68 +171,51 @@ __global__ __launch_bounds__(LWAVES * 64, 4) void mlp_last_layer(LayerArgs a, ui
     if (i >= blocks) return;
     request(short_rows(i), 0);
     for (uint32_t next; i < blocks; i = next) {
-        const uint32_t r0 = short_rows(i);
+        const uint32_t r0 = short_rows(i), row = r0 + (lane & 31u);
         next = from(i + gridDim.x);
         uint32_t dst = 0;
-        if (tid < LROWS && r0 + tid < rows) dst = (a.scatter ? a.scatter : a.esc_idx)[a.row_begin + r0 + tid];
-        float y[kOut];
+        if (wave == 0) dst = (a.scatter ? a.scatter : a.esc_idx)[a.row_begin + (row < rows ? row : rows - 1u)];
+        f32x16 y[NI]; // (of the first wave)
 #pragma unroll
-        for (int q = 0; q < kOut; ++q) {
-            const uint32_t c = (tid + q * LWAVES * 64u) % (NI * 32u);
-            y[q] = c < a.N ? a.bias[c] : 0.f;
-        }
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) y[j][v] = 0.f;
         for (uint32_t p0 = 0; p0 < pieces; p0 += S::kHeld) {
+            // what was requested goes to shared memory, the next round is requested, the first wave multiplies
 #pragma unroll
-            for (int m = 0; m < kMine; ++m) {
-                if (p0 + wave + LWAVES * m >= pieces) continue;
+            for (int s = 0; s < S::kRows; ++s) *reinterpret_cast<u32x4*>(s_a + (m * 4u + jw * S::kRows + s) * 64u + lane) = fa[s];
 #pragma unroll
-                for (int j = 0; j < NI; ++j) {
-                    f32x16 c3;
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) c3[v] = 0.f;
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) c3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fw[m][s][j]), as_bf16x8(fa[m][s]), c3, 0, 0, 0);
-                    // the weights first: element v of lane l is row l % 32, class 8 * (v / 4) + 4 * (l / 32) + v % 4
-                    float* to = sums + ((size_t)(wave + LWAVES * m) * LROWS + (lane & 31u)) * S::kLd + j * 32u + 4u * (lane >> 5);
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        *reinterpret_cast<float4*>(to + 8 * g) = make_float4(c3[4 * g], c3[4 * g + 1], c3[4 * g + 2], c3[4 * g + 3]);
-                }
-            }
-            // the next operands are on their way while the sums meet
+            for (int s = 0; s < 4; ++s) *reinterpret_cast<u32x4*>(s_w + ((m * 4u + s) * NI + jw) * 64u + lane) = fw[s];
+            __syncthreads();
             const bool more = p0 + S::kHeld < pieces;
             if (more || next < blocks) request(more ? r0 : short_rows(next), more ? p0 + S::kHeld : 0u);
-            __syncthreads();
-            const uint32_t held = pieces - p0 < (uint32_t)S::kHeld ? pieces - p0 : S::kHeld;
-            for (uint32_t p = 0; p < held; ++p)
+            __builtin_amdgcn_sched_barrier(0);
+            if (wave == 0) {
+                constexpr int kRing = NI == 1 ? 4 : 2; // steps whose operands are on their way out of shared memory
+                const uint32_t steps = (pieces - p0 < (uint32_t)S::kHeld ? pieces - p0 : S::kHeld) * 4u;
+                u32x4 ca[kRing], cw[kRing][NI];
+                auto read = [&](int s, uint32_t t) __attribute__((always_inline)) {
+                    ca[s] = *reinterpret_cast<const u32x4*>(s_a + t * 64u + lane);
 #pragma unroll
-                for (int q = 0; q < kOut; ++q) {
-                    const uint32_t e = tid + q * LWAVES * 64u;
-                    y[q] += sums[((size_t)p * LROWS + e / (NI * 32u)) * S::kLd + e % (NI * 32u)];
-                }
-            __syncthreads(); // the sums have been read
-        }
+                    for (int j = 0; j < NI; ++j) cw[s][j] = *reinterpret_cast<const u32x4*>(s_w + (t * NI + j) * 64u + lane);
+                };
 #pragma unroll
-        for (int q = 0; q < kOut; ++q) {
-            const uint32_t e = tid + q * LWAVES * 64u, row = e / (NI * 32u), c = e % (NI * 32u);
-            s_logits[row * S::kLd + c] = y[q];
-            if (a.logits && c < a.N && r0 + row < rows) a.logits[(size_t)(a.row_begin + r0 + row) * a.N + c] = y[q];
-        }
-        __syncthreads();
-        if (tid < LROWS && r0 + tid < rows) {
-            const float* lr = s_logits + tid * S::kLd;
-            uint32_t best = 0;
-            float bv = lr[0];
-#pragma unroll 8
-            for (uint32_t c = 1; c < a.N; ++c) {
-                const float v = lr[c];
-                if (v > bv) {
-                    bv = v;
-                    best = c;
+                for (int s = 0; s < kRing; ++s) read(s, s);
+                for (uint32_t t = 0; t < steps; t += kRing) {
+                    const uint32_t after = t + kRing < steps ? t + kRing : t;
+#pragma unroll
+                    for (int s = 0; s < kRing; ++s) {
+#pragma unroll
+                        for (int j = 0; j < NI; ++j)
+                            y[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, cw[s][j]), __builtin_bit_cast(bf16x8, ca[s]), y[j], 0, 0, 0);
+                        read(s, after + s);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
             }
-            if (dst < a.n_labels) a.labels[dst] = (uint16_t)best;
-        } // (the next rows' logits are written two barriers on)
+            __syncthreads(); // the round has been read
+        }
+        if (wave == 0) last_rows<NI>(a, y, s_bias, a.N, lane >> 5, row < rows, a.row_begin + row, dst);
     }
 }
 
@@ -692,7 +643,7 @@ int launch_last(sf_ctx* ctx, const LayerArgs& a, uint32_t rows_cap)
 {
     SF_ALLOW_LDS(ctx, sf::kLdsLast + NI - 1, mlp_last_layer<NI>);
     const uint32_t tiles = (rows_cap + LROWS * 4u * kDies - 1u) / (LROWS * 4u * kDies) * (4u * kDies), most = 4u * (uint32_t)ctx->n_cu; // (rows that exist are dealt out in the kernel)
-    mlp_last_layer<NI><<<tiles < most ? tiles : most, LWAVES * 64, LastShape<NI>::kLds, ctx->stream>>>(a, (NI > 1 ? 2u : a.wo_last ? 8u : 5u) * (uint32_t)ctx->n_cu / 2u);
+    mlp_last_layer<NI><<<tiles < most ? tiles : most, LWAVES * 64, LastShape<NI>::kLds, ctx->stream>>>(a, (NI > 1 ? 1u : a.wo_last ? 3u : 2u) * (uint32_t)ctx->n_cu);
     SF_LAUNCH_CHECK(ctx, "mlp_last_layer");
     return SF_OK;
 }
@@ -875,17 +826,15 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
             a.K = mlp->n_h1;
             a.h_out = h2;
             a.ldh = ld2;
-            a.w_last = (const uint16_t*)mlp->w3;
             a.wo_last = (const uint4*)w3o;
             a.b_last = mlp->b3;
-            // Not where its weights lie in rows that are no whole 16-byte pieces: every tile would read them value by value (74,148 rows
-            // through 48-76-1636-30: its own launch 156 us, along with the second hidden layer 191).  And not where the first layer does most
+            // Only with operand-ordered weights: each tile's two multiplying waves would gather the others line by line (70,077 rows through
+            // 64-9-1032-10: its own launch 87 us, along with the second hidden layer 127).  And not where the first layer does most
             // of the work, eight times the second's: such a pass runs at the clock that the power allows, and the launch saved is paid back
             // at a lower one, by every kernel (a million flows of 10 x 480 header bits through 1024-512, whole passes 1,875 : 1,940, where the
             // launches of the two layers alone take 229 : 205; 100,000 rows of 20 x 480 1,743 : 1,766; a first layer of 4.7 times the second's
             // work, 210,000 rows of 5 x 480, 1,095 : 1,073; of twice, 648 : 612).
-            const bool read_whole = w3o || ((mlp->n_h2 & 7u) == 0 && ((uintptr_t)mlp->w3 & 15u) == 0);
-            a.n_last = mlp->n_classes <= 32u && read_whole && mlp->n_in < 8u * mlp->n_h2 ? mlp->n_classes : 0u;
+            a.n_last = w3o && mlp->n_in < 8u * mlp->n_h2 ? mlp->n_classes : 0u;
             a.logits = logits;
             {
                 const int rc = sf::wide_layer(ctx, A_BF16, a, w2o, R);

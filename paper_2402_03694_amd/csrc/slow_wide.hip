@@ -52,9 +52,8 @@ constexpr int WSTAGE = WBM / 2;   // rows of a wave's output staged at a time
 constexpr size_t kSlabBytes = (size_t)WBUF * WBM * WLDS * 2;
 constexpr size_t kStageBytes = (size_t)WSTAGE * WLDO * 2 + WCOLS * 4; // a wave's staged output rows and bias
 constexpr size_t kWideLds = kSlabBytes + WWAVES * kStageBytes + WBM * 4; // slabs, waves' own space, flow ids
-constexpr int WLDP = 36;          // row stride of the last layer's sums (floats): a wave's 64 rows of them take the place of its staged output
-static_assert(WLDP * 4 == WLDO * 2, "the sums in the staged rows' place");
-constexpr size_t kLastLds = (size_t)WBM * WLDP * 4; // a tile's logits, between column blocks
+constexpr size_t kLastLds = (size_t)WBM * 32 * 4 + 32 * 4; // the last layer: a tile's sums between column blocks, biases
+constexpr int LRING = 8;          // its weights in flight, k-steps
 static_assert(WBN == 512 && WSLAB == kWideSlab && WBUF == kWideSlabs, "as the last layer's launch assumes");
 constexpr int FCHUNK = 1024, FLD = FCHUNK + 8, FRING = 16; // few rows: K values in shared memory at a time, their row stride, k-steps of weights in flight
 constexpr size_t kFewLds = (size_t)2 * kFewTileRows * FLD * 2 + kFewTileRows * 4;
@@ -88,10 +87,10 @@ __device__ __forceinline__ void wave_sync()
 
 // RESIDENT: every slab of a row block has a buffer of its own (K up to WBUF slabs).
 // FORM: how header bits lie (A_RAW).
-// LAST: the last layer goes along (a block holds all columns of a row, wide_takes_last): a wave multiplies the 64 columns it has
-// staged with their weights, the eight waves' sums meet in shared memory, and the activations are neither written nor read back: 60,000
-// rows through 1024-1024-16 a whole call 168 -> 156 us, 200,000 through 1024-512-16 372 -> 333, the large workload's pass 14.1 -> 13.4 ms; which models at
-// run_slow.  A logit is its bias plus the sums of 64 columns each, in order, as in mlp_last_layer: the same bits.
+// LAST: the last layer goes along (a block holds all columns of a row, wide_takes_last): when the waves have staged 64 rows of their
+// columns, two of them multiply 32 rows each with the last layer's weights, all columns in order of K, and the activations are neither
+// written nor read back: FIGURES; which models at
+// run_slow.  A logit is one chain over K, and its bias at the end, as in mlp_last_layer: the same bits.
 template <int AMODE, bool RESIDENT, int FORM, bool LAST>
 __device__ __forceinline__ void wide_tiles(const LayerArgs& a, const uint4* __restrict__ ws, uint32_t n_cb, unsigned char* smem)
 {
@@ -114,7 +113,9 @@ __device__ __forceinline__ void wide_tiles(const LayerArgs& a, const uint4* __re
     const uint32_t rows = total - a.row_begin < a.rows_cap ? total - a.row_begin : a.rows_cap; // of this chunk
     const uint32_t units = gridDim.x;
     const bool walk = wide_walks(rb_count, n_cb, units, RESIDENT);
-    float* s_logits = reinterpret_cast<float*>(smem + kWideLds); // [128][WLDP]
+    float4* s_sums = reinterpret_cast<float4*>(smem + kWideLds); // [row block of 32][4][64]
+    float* s_b3 = reinterpret_cast<float*>(smem + kWideLds + (size_t)WBM * 32 * 4);
+    if (LAST && threadIdx.x < 32u) s_b3[threadIdx.x] = threadIdx.x < a.n_last ? a.b_last[threadIdx.x] : 0.f; // (read several barriers on)
     const uint32_t n_items = walk ? rb_count : rb_count * n_cb;
     const uint32_t cb_per_item = walk ? n_cb : 1u;
 
@@ -321,6 +322,17 @@ __device__ __forceinline__ void wide_tiles(const LayerArgs& a, const uint4* __re
             const uint32_t ln = again(lane);
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
+                // LAST: the wave that multiplies a row block of 32 requests the weights ahead of the rows (steps past the last one: that one again)
+                const uint32_t steps = LAST ? ((a.ldh - cb * WBN < (uint32_t)WBN ? a.ldh - cb * WBN : (uint32_t)WBN) / 16u) : 0u;
+                const bool mine = LAST && wave / 2u == (uint32_t)half;
+                u32x4 lw[LAST ? LRING : 1];
+                auto weights = [&](uint32_t t) __attribute__((always_inline)) {
+                    return *reinterpret_cast<const u32x4*>(a.wo_last + (cb * (WBN / 16u) + (t < steps ? t : steps - 1u)) * 64u + ln);
+                };
+                if (mine) {
+#pragma unroll
+                    for (int t = 0; t < LRING; ++t) lw[LAST ? t : 0] = weights(t);
+                }
                 if (col0 < a.ldh) { // (ldh is a multiple of the wave's 64 columns)
 #pragma unroll
                     for (int j = 0; j < WNI; ++j) {
@@ -339,31 +351,8 @@ __device__ __forceinline__ void wide_tiles(const LayerArgs& a, const uint4* __re
                             }
                         }
                     }
-                    wave_sync();
-                    if (LAST) {
-                        // this wave's piece of the logits of 64 rows: operands from the staged rows, the sums then in their place
-                        uint4 fw[4], fh[2][4];
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            fw[k] = last_weights(a, a.n_last, a.N, 0, col0 / 16u + k, ln);
-#pragma unroll
-                            for (int i = 0; i < 2; ++i)
-                                fh[i][k] = *reinterpret_cast<const uint4*>(stage + (i * 32u + (ln & 31u)) * WLDO + k * 16u + 8u * (ln >> 5));
-                        }
+                    if (!LAST) {
                         wave_sync();
-#pragma unroll
-                        for (int i = 0; i < 2; ++i) {
-                            f32x16 c3;
-#pragma unroll
-                            for (int v = 0; v < 16; ++v) c3[v] = 0.f;
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) c3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fw[k]), as_bf16x8(fh[i][k]), c3, 0, 0, 0);
-                            float* to = reinterpret_cast<float*>(stage) + (i * 32u + (ln & 31u)) * WLDP + 4u * (ln >> 5);
-#pragma unroll
-                            for (int g = 0; g < 4; ++g)
-                                *reinterpret_cast<float4*>(to + 8 * g) = make_float4(c3[4 * g], c3[4 * g + 1], c3[4 * g + 2], c3[4 * g + 3]);
-                        }
-                    } else {
 #pragma unroll
                         for (int q = 0; q < WSTAGE / 8; ++q) {
                             const uint32_t rh = q * 8u + (ln >> 3), k = (ln & 7u) * 8u;
@@ -371,47 +360,59 @@ __device__ __forceinline__ void wide_tiles(const LayerArgs& a, const uint4* __re
                             const uint4 v = *reinterpret_cast<const uint4*>(stage + rh * WLDO + k);
                             if (row0 + r < total) *reinterpret_cast<uint4*>(a.h_out + (size_t)(rb * WBM + r) * a.ldh + col0 + k) = v;
                         }
+                        wave_sync(); // the staged rows are out: the space may be written again
                     }
-                    wave_sync(); // the staged rows are out: the space may be written again
                 }
                 if (LAST) {
-                    // (every wave comes here: what is added to a row's logits, the waves with columns have written)
-                    __syncthreads();
-                    const uint32_t pieces = (a.ldh - cb * WBN + WCOLS - 1u) / WCOLS, held = pieces < (uint32_t)WWAVES ? pieces : WWAVES;
-                    const uint32_t t = again(tid);
+                    __syncthreads(); // all columns are staged
+                    if (mine) {
+                        const uint32_t blk = wave, in = (wave & 1u) * 32u + (ln & 31u); // row block of the tile, row inside the staged half
+                        const unsigned char* arow = smem + kSlabBytes + ((size_t)in * WLDO + 8u * (ln >> 5)) * 2;
+                        u32x4 ca[4];
+                        auto rows_of = [&](uint32_t t) __attribute__((always_inline)) { // four steps: one wave's columns
+                            const uint32_t w = t < steps ? t / 4u : steps / 4u - 1u;
 #pragma unroll
-                    for (int q = 0; q < WSTAGE * 32 / (WWAVES * 64); ++q) {
-                        const uint32_t e = t + q * WWAVES * 64u, r = e / 32u, cls = e % 32u;
-                        float y = cb == 0u ? (cls < a.n_last ? a.b_last[cls] : 0.f) : s_logits[(half * WSTAGE + r) * WLDP + cls];
-                        for (uint32_t w = 0; w < held; ++w)
-                            y += reinterpret_cast<const float*>(smem + kSlabBytes + w * kStageBytes)[r * WLDP + cls];
-                        s_logits[(half * WSTAGE + r) * WLDP + cls] = y;
-                    }
-                    __syncthreads();
-                }
-            }
-            if (LAST && last_cb) {
-                const uint32_t t = again(tid);
-                if (t < WBM && row0 + t < total) {
-                    const uint32_t dst = (a.scatter ? a.scatter : a.esc_idx)[row0 + t];
-                    const float* lr = s_logits + t * WLDP;
-                    uint32_t best = 0;
-                    float bv = lr[0];
-                    for (uint32_t k = 1; k < a.n_last; ++k) {
-                        const float v = lr[k];
-                        if (v > bv) {
-                            bv = v;
-                            best = k;
+                            for (int q = 0; q < 4; ++q) ca[q] = *reinterpret_cast<const u32x4*>(arow + w * kStageBytes + q * 32);
+                        };
+                        f32x16 sum[1];
+                        if (cb == 0u) {
+#pragma unroll
+                            for (int v = 0; v < 16; ++v) sum[0][v] = 0.f;
+                        } else {
+#pragma unroll
+                            for (int g = 0; g < 4; ++g) {
+                                const float4 v = s_sums[(blk * 4u + g) * 64u + ln];
+                                sum[0][4 * g] = v.x, sum[0][4 * g + 1] = v.y, sum[0][4 * g + 2] = v.z, sum[0][4 * g + 3] = v.w;
+                            }
+                        }
+                        rows_of(0);
+                        for (uint32_t t0 = 0; t0 < steps; t0 += LRING) {
+#pragma unroll
+                            for (int s = 0; s < LRING; s += 4) {
+                                if (t0 + s < steps) { // (steps is a multiple of 4)
+#pragma unroll
+                                    for (int q = 0; q < 4; ++q)
+                                        sum[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, lw[LAST ? s + q : 0]), __builtin_bit_cast(bf16x8, ca[q]), sum[0], 0, 0, 0);
+                                    rows_of(t0 + s + 4);
+                                }
+                                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                                for (int q = 0; q < 4; ++q) lw[LAST ? s + q : 0] = weights(t0 + s + q + LRING);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                        }
+                        if (last_cb) {
+                            const uint32_t row = row0 + blk * 32u + (ln & 31u);
+                            const bool there = row < total;
+                            last_rows<1>(a, sum, s_b3, a.n_last, ln >> 5, there, row, there ? (a.scatter ? a.scatter : a.esc_idx)[row] : 0u);
+                        } else {
+#pragma unroll
+                            for (int g = 0; g < 4; ++g) s_sums[(blk * 4u + g) * 64u + ln] = make_float4(sum[0][4 * g], sum[0][4 * g + 1], sum[0][4 * g + 2], sum[0][4 * g + 3]);
                         }
                     }
-                    if (dst < a.n_labels) a.labels[dst] = (uint16_t)best;
+                    __syncthreads(); // the staged rows have been read
                 }
-                if (a.logits)
-                    for (uint32_t e = t; e < WBM * a.n_last; e += WWAVES * 64u) {
-                        const uint32_t r = e / a.n_last;
-                        if (row0 + r < total) a.logits[(size_t)row0 * a.n_last + e] = s_logits[r * WLDP + (e - r * a.n_last)];
-                    }
-            } // (the next row block's first sums are two barriers away)
+            }
             wave_sync();
         }
     }

@@ -88,7 +88,7 @@ def test_few_spills(kernels, name, most):
 
 SHORT_FORMS = ["featurize_forest_few<%s, 16, %s>" % (t, r) for t in ("128, 8, 0, 0", "128, 4, 5, 2", "64, 8, 3, 1") for r in ("true", "false")] + [
     "mlp_few<%d, %d, %d, sfsmall::%s>" % (k, n1, n2, g) for k in (4, 8) for n1 in (1, 2) for n2 in (1, 2) for g in ("GateRows", "NoGate")] + [
-    "featurize_long<2>", "mlp_wide_last<true>", "mlp_wide_last<false>", "mlp_last_layer<1>", "mlp_last_layer<2>", "f32_mlp<sfsmall::GateRows>",
+    "featurize_long<2>", "mlp_wide_last<true>", "mlp_last_layer<1>", "mlp_last_layer<2>", "f32_mlp<sfsmall::GateRows>",
     "f32_mlp<sfsmall::NoGate>"]
 
 
@@ -98,9 +98,10 @@ def test_no_spills_short_forms(kernels, name):
     assert kernels[name]["spilled"] == 0, kernels[name]
 
 
-def test_few_spills_long_flows(kernels):
-    """Four blocks a unit: 128 registers."""
-    assert kernels["featurize_long<4>"]["spilled"] <= 14, kernels["featurize_long<4>"]
+@pytest.mark.parametrize("name,most", [("featurize_long<4>", 14),   # four blocks a unit: 128 registers
+                                       ("mlp_wide_last<false>", 8)])  # once a tile, around the last layer
+def test_few_spills_short_forms(kernels, name, most):
+    assert kernels[name]["spilled"] <= most, kernels[name]
 
 
 def test_slow_model_has_no_arrays_in_memory():
