@@ -896,7 +896,10 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
         const size_t lds = f32_fused_lds(mlp->n_in, mlp->n_h1, mlp->n_h2, mlp->n_classes);
         const bool whole = (mlp->n_h1 & 3u) == 0 && ((uintptr_t)mlp->w2 & 15u) == 0;
         const uint32_t few = (whole ? 2u : 1u) * kF32FewRows * (uint32_t)ctx->n_cu;
-        const uint32_t tiles = (esc_cap + kF32FewRows - 1u) / kF32FewRows, most = 4u * (uint32_t)ctx->n_cu;
+        const uint32_t tiles = (esc_cap + kF32FewRows - 1u) / kF32FewRows;
+        // Two blocks a unit are resident; with four, long lists even out (253,066 rows through 64-200-48-7 595 : 566), up to 65,536 rows the
+        // other blocks are launches for nothing: 16,682 rows through 32-8-18-13 14.1 : 15.2, 18,369 through 32-56-8-37 18.6 : 20.8.
+        const uint32_t most = (esc_cap > 65536u ? 4u : 2u) * (uint32_t)ctx->n_cu;
         const uint32_t grid = (tiles < most ? tiles : most) + m.n_copy;
         if (gate) {
             SF_ALLOW_LDS(ctx, sf::kLdsF32 + 1, f32_mlp<sfsmall::GateRows>);
