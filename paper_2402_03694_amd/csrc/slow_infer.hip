@@ -43,7 +43,8 @@ using namespace sfmlp;
 //     of 64, the next step requested ahead of the MFMAs.  What bounds it is HBM (200,000 rows of 2,048 values 216 us, 3.8 TB/s; straight
 //     from the cache into registers, a row's operands are 32 lines to the address path, 270).
 //   - Short ones: all waves of a block request the operands of 32 rows, a piece each and a round ahead, and put them into shared memory;
-//     one wave multiplies.  What bounds it is the chain of latencies, and past a few blocks a unit that chain of MFMAs.
+//     one wave multiplies.  What bounds it is the chain of latencies, and past a few blocks a unit that chain of MFMAs: 500 rows of 1,024 values
+//     11.2 -> 6.1 us, 19,600 12.9 : 13.3.
 //     Lists of up to three such blocks a unit go this way, two where the weights lie in rows (a block then gathers them line by
 //     line), one with more than 32 classes; a block counts once for every 16 pieces (8 with more than 32 classes).  Short : long, whole call in
 //     us: 12,546 rows through 32-256-1536-10 46.4 : 53.0, rows of weights 8,513 through 32-320-1536-4 44.4 : 48.7; 34,672 through 128-448-576-10,
@@ -831,9 +832,9 @@ int run_slow(sf_ctx* ctx, const float* feat, uint32_t feat_ld, uint32_t n_rows, 
             // Only with operand-ordered weights: each tile's two multiplying waves would gather the others line by line (70,077 rows through
             // 64-9-1032-10: its own launch 87 us, along with the second hidden layer 127).  And not where the first layer does most
             // of the work, eight times the second's: such a pass runs at the clock that the power allows, and the launch saved is paid back
-            // at a lower one, by every kernel (a million flows of 10 x 480 header bits through 1024-512, whole passes 1,875 : 1,940, where the
-            // launches of the two layers alone take 229 : 205; 100,000 rows of 20 x 480 1,743 : 1,766; a first layer of 4.7 times the second's
-            // work, 210,000 rows of 5 x 480, 1,095 : 1,073; of twice, 648 : 612).
+            // at a lower one, by every kernel (a million flows of 10 x 480 header bits through 1024-512, whole passes of three processes each
+            // 1,857-1,862 : 1,869-1,913, though the launches of the two layers are shorter; 100,000 rows of 20 x 480 1,694 : 1,707; a first layer
+            // of 4.7 times the second's work, 210,000 rows of 5 x 480, 1,101 : 1,061; of twice, 647 : 606).
             a.n_last = w3o && mlp->n_in < 8u * mlp->n_h2 ? mlp->n_classes : 0u;
             a.logits = logits;
             {

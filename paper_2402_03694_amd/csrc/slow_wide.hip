@@ -89,8 +89,8 @@ __device__ __forceinline__ void wave_sync()
 // FORM: how header bits lie (A_RAW).
 // LAST: the last layer goes along (a block holds all columns of a row, wide_takes_last): when the waves have staged 64 rows of their
 // columns, two of them multiply 32 rows each with the last layer's weights, all columns in order of K, and the activations are neither
-// written nor read back: FIGURES; which models at
-// run_slow.  A logit is one chain over K, and its bias at the end, as in mlp_last_layer: the same bits.
+// written nor read back: 60,000 rows through 1024-1024-16 a whole call 169 -> 152 us, 200,000 through 1024-512-16 373 -> 330, the large
+// workload's pass 14.1 -> 13.3 ms; which models and lists at run_slow and wide_takes_last.  A logit is one chain over K, and its bias at the end, as in mlp_last_layer: the same bits.
 template <int AMODE, bool RESIDENT, int FORM, bool LAST>
 __device__ __forceinline__ void wide_tiles(const LayerArgs& a, const uint4* __restrict__ ws, uint32_t n_cb, unsigned char* smem)
 {
@@ -422,7 +422,7 @@ __device__ __forceinline__ void wide_tiles(const LayerArgs& a, const uint4* __re
 // through one unit's path to the cache (half a megabyte for K = 1,024), so the weights are requested first, 16 k-steps ahead, and the
 // rows' values come to shared memory 1,024 at a time, so that waves meet once in as many k-steps.  A sum starts at its bias and runs in
 // order of K, as in the tiles: the same bits.  Tiles of 128 x 512 : these, whole call in us: one
-// row through 64-1024-1024-10 41.9 : 18.0, 500 46.5 : 22.6, 2,000 46.9 : 27.5, 500 through 96-300-900-20 44.8 : 20.3.
+// row through 64-1024-1024-10 42.0 : 18.5, 500 46.5 : 22.6, 2,000 46.6 : 27.4, 500 through 96-300-900-20 45.0 : 20.3.
 template <int AMODE, int FORM>
 __device__ __forceinline__ void wide_few(const LayerArgs& a, const uint4* __restrict__ ws, uint32_t rows, unsigned char* smem)
 {

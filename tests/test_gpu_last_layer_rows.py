@@ -37,3 +37,29 @@ def test_last_layer(dims):
         got, labels = run(rows)
         assert torch.equal(got.view(torch.int32), want[:rows].view(torch.int32)), rows
         assert torch.equal(labels, want_labels[:rows]), rows
+
+
+@pytest.mark.parametrize("dims", [(8, 40, 1100, 3), (8, 520, 500, 7), (8, 520, 200, 32), (8, 520, 1030, 40)])
+def test_one_chain(dims):
+    """A logit is one binary32 chain in order of K: behind 2^26 each step's 16 products of 1/4 are half a unit in the last place and go
+    (halves round to the even 2^26), 64 of them summed apart would not.  Hidden units are all one."""
+    import torch
+    import paper_2402_03694_amd as sf
+    most = 70000
+    w3 = torch.full((dims[3], dims[2]), 0.25)
+    w3[:, :16] = 2.0 ** 22
+    zero = lambda o, k: torch.zeros((o, k), dtype=torch.bfloat16, device=DEV)
+    par = (zero(dims[1], dims[0]), torch.ones(dims[1], device=DEV), zero(dims[2], dims[1]), torch.ones(dims[2], device=DEV), w3.to(torch.bfloat16).to(DEV),
+           torch.zeros(dims[3], device=DEV))
+    feat = torch.zeros((most, dims[0]), device=DEV)
+    idx = torch.arange(most, dtype=torch.int32, device=DEV)
+    ctx = sf.ServeFlow(sf.sf_workspace_bytes(most, 0, 0, *dims[:3]))
+    for ordered in (False, True):
+        mlp = sf.DeviceMlp(dims, sf.SF_BF16, *par)
+        if ordered and dims[3] <= 32:
+            ctx.sf_mlp_order(mlp)
+        for rows in (1, 500, 5000, 16384, 32769, most):
+            logits = torch.zeros((most, dims[3]), device=DEV)
+            labels = torch.full((most,), -1, dtype=torch.int16, device=DEV)
+            ctx.sf_slow_infer(mlp, idx, torch.tensor([rows], dtype=torch.int32, device=DEV), labels, feat=feat, logits=logits)
+            assert (logits[:rows] == 2.0 ** 26).all() and (labels[:rows] == 0).all(), (ordered, rows)
