@@ -56,7 +56,7 @@ constexpr size_t kLastLds = (size_t)WBM * 32 * 4 + 32 * 4; // the last layer: a 
 constexpr int LRING = 8;          // its weights in flight, k-steps
 static_assert(WBN == 512 && WSLAB == kWideSlab && WBUF == kWideSlabs, "as the last layer's launch assumes");
 constexpr int FCHUNK = 1024, FLD = FCHUNK + 8, FRING = 16; // few rows: K values in shared memory at a time, their row stride, k-steps of weights in flight
-constexpr size_t kFewLds = (size_t)2 * kFewTileRows * FLD * 2 + kFewTileRows * 4;
+constexpr size_t kFewLds = (size_t)2 * kFewTileRows * FLD * 2;
 
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {
@@ -427,7 +427,6 @@ template <int AMODE, int FORM>
 __device__ __forceinline__ void wide_few(const LayerArgs& a, const uint4* __restrict__ ws, uint32_t rows, unsigned char* smem)
 {
     uint16_t* A = reinterpret_cast<uint16_t*>(smem); // [2][32][FLD]
-    uint32_t* s_flow = reinterpret_cast<uint32_t*>(smem + (size_t)2 * kFewTileRows * FLD * 2);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t n_cb = (a.ldh + kFewTileCols - 1u) / kFewTileCols, cb = blockIdx.x % n_cb, row0 = blockIdx.x / n_cb * kFewTileRows;
     if (row0 >= rows) return;
